@@ -309,60 +309,108 @@ __device__ __forceinline__ int block_exclusive_count(bool flag, int *scratch, in
     return base + before;
 }
 
-// One workgroup per image: 4 passes of an 8-bit radix select find the key of
-// the K-th largest score, then one ordered compaction pass writes every index
-// with a larger key plus the lowest-index ties, in ascending index order.
+// inclusive prefix sum over the lanes of a wave
+template <typename T>
+__device__ __forceinline__ T wave_inclusive_sum(T v)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T up = __shfl_up(v, o, 64);
+        if (lane >= o) v += up;
+    }
+    return v;
+}
+
+// One workgroup per image: three passes of a radix select (11, 11 and 10 bits) find the key of the K-th largest score,
+// then one scan over the workgroup places every index with a larger key and the lowest-index ties in ascending index
+// order.  One CU works alone here, so what counts is the length of the serial chain: the keys are read once and kept in
+// registers (ITEMS consecutive ones per thread; 16-byte loads), a pass is a histogram in LDS and a scan of its bins by
+// all threads (4096 scores: 32 -> 7.5 us; 16384: 63 -> 15; 65536: 160 -> 60; four 8-bit passes over memory with a serial
+// walk of the bins and two barriers for every 1024 scores of the compaction before).
+constexpr int SEL_BINS = 2048;
+template <int ITEMS>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int N, int K)
 {
-    __shared__ int hist[256];
-    __shared__ int scratch[SEL_THREADS / 64];
+    __shared__ int hist[SEL_BINS];
+    __shared__ unsigned long long scratch[SEL_THREADS / 64];
     __shared__ uint32_t sh_prefix;
     __shared__ int sh_remaining;
     const float *s = scores + (long)blockIdx.x * N;
     int32_t *out = keep + (long)blockIdx.x * K;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int first = tid * ITEMS;
+
+    uint32_t key[ITEMS];                        // past N: 0, below the key of every score
+    if (first + ITEMS <= N && (reinterpret_cast<uintptr_t>(s) & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; i += 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(s + first + i);
+            key[i] = score_key(v.x); key[i + 1] = score_key(v.y); key[i + 2] = score_key(v.z); key[i + 3] = score_key(v.w);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) key[i] = first + i < N ? score_key(s[first + i]) : 0u;
+    }
 
     uint32_t prefix = 0, prefix_mask = 0;
     int remaining = K;   // how many of the keys matching the prefix are still to be taken
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < 256; i += SEL_THREADS) hist[i] = 0;
+    constexpr int SHIFT[3] = { 21, 10, 0 }, BITS[3] = { 11, 11, 10 };
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+        const uint32_t mask = (1u << BITS[pass]) - 1u;
+        for (int i = tid; i < SEL_BINS; i += SEL_THREADS) hist[i] = 0;
         __syncthreads();
-        for (int i = threadIdx.x; i < N; i += SEL_THREADS) {
-            uint32_t key = score_key(s[i]);
-            if ((key & prefix_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-        }
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (first + i < N && (key[i] & prefix_mask) == prefix) atomicAdd(&hist[(key[i] >> SHIFT[pass]) & mask], 1);
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int rem = remaining, bucket = 255;
-            for (; bucket > 0; --bucket) {
-                int c = hist[bucket];
-                if (c >= rem) break;
-                rem -= c;
-            }
-            sh_prefix = prefix | ((uint32_t)bucket << shift);
-            sh_remaining = rem;
+        // thread t holds bins 2t and 2t + 1 counted from the top: the bin in which the running count reaches `remaining`
+        const int b0 = SEL_BINS - 1 - 2 * tid, b1 = b0 - 1;
+        const int c0 = hist[b0], c1 = hist[b1];
+        const int incl = wave_inclusive_sum(c0 + c1);
+        if (lane == 63) scratch[wave] = (unsigned)incl;
+        __syncthreads();
+        int above = incl - (c0 + c1);
+#pragma unroll
+        for (int w = 0; w < SEL_THREADS / 64; ++w) above += w < wave ? (int)scratch[w] : 0;
+        const bool in0 = above < remaining && above + c0 >= remaining, in1 = above + c0 < remaining && above + c0 + c1 >= remaining;
+        if (in0 || in1) {                       // exactly one thread
+            sh_prefix = prefix | ((uint32_t)(in0 ? b0 : b1) << SHIFT[pass]);
+            sh_remaining = remaining - above - (in0 ? 0 : c0);
         }
         __syncthreads();
         prefix = sh_prefix;
         remaining = sh_remaining;
-        prefix_mask |= 255u << shift;
-        __syncthreads();
+        prefix_mask |= mask << SHIFT[pass];
     }
     // prefix = key of the K-th largest element; `remaining` ties are taken, lowest index first
     const uint32_t threshold = prefix;
-    int taken = 0, ties_seen = 0;
-    for (int base = 0; base < N; base += SEL_THREADS) {
-        int i = base + threadIdx.x;
-        uint32_t key = (i < N) ? score_key(s[i]) : 0u;
-        bool gt = (i < N) && key > threshold;
-        bool eq = (i < N) && key == threshold;
-        int eq_total, sel_total;
-        int eq_rank = ties_seen + block_exclusive_count(eq, scratch, eq_total);
-        bool sel = gt || (eq && eq_rank < remaining);
-        int pos = taken + block_exclusive_count(sel, scratch, sel_total);
-        if (sel && pos < K) out[pos] = i;
-        ties_seen += eq_total;
-        taken += sel_total;
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        gt += first + i < N && key[i] > threshold;
+        eq += first + i < N && key[i] == threshold;
+    }
+    const unsigned long long mine = ((unsigned long long)gt << 32) | eq;
+    const unsigned long long incl = wave_inclusive_sum(mine);
+    __syncthreads();                            // the last pass has read scratch
+    if (lane == 63) scratch[wave] = incl;
+    __syncthreads();
+    unsigned long long before = incl - mine;
+#pragma unroll
+    for (int w = 0; w < SEL_THREADS / 64; ++w) before += w < wave ? scratch[w] : 0ull;
+    int ties = (int)(before & 0xffffffffu);
+    int pos = (int)(before >> 32) + min(ties, remaining);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool tie = key[i] == threshold;
+        if (first + i < N && (key[i] > threshold || (tie && ties < remaining))) {
+            if (pos < K) out[pos] = first + i;
+            ++pos;
+        }
+        ties += first + i < N && tie;
     }
 }
 
@@ -443,9 +491,71 @@ fill_bias_rows_kernel(bf16 *__restrict__ C, long ldc, const float *__restrict__ 
 }
 
 // ---------------------------------------------------------------- content-aware order
-// One workgroup per (image, window): the window's cells are ranked by (score descending, cell index
-// ascending; padding cells last) with a bitonic sort of 64-bit keys in LDS, then the stripe interleave
-// sigma[g*(S/G)+t] = pi[t*G+g] (Sec. 4.1) places rank t*G+g at scan position g*(S/G)+t.
+// The cells of an attention group are ranked by (score descending, cell index ascending; padding cells last), then the
+// stripe interleave sigma[g*(S/G)+t] = pi[t*G+g] (Sec. 4.1) places rank t*G+g at scan position g*(S/G)+t.
+// Sort key of cell i of the group at (wr, wc): ascending keys are descending scores.
+__device__ __forceinline__ uint32_t content_key(const float *sc, int g, int w, int wr, int wc, int i)
+{
+    const int row = wr * w + i / w, col = wc * w + i % w;
+    return ~score_key(row < g && col < g ? sc[row * g + col] : -INFINITY);
+}
+
+__device__ __forceinline__ void content_place(int cell, int rank, int g, int w, int wr, int wc, int G, long base,
+                                              int32_t *__restrict__ gather_table, int32_t *__restrict__ sigma)
+{
+    const int S = w * w, pos = (rank % G) * (S / G) + rank / G;
+    const int row = wr * w + cell / w, col = wc * w + cell % w;
+    sigma[base + pos] = cell;
+    gather_table[base + pos] = (row < g && col < g) ? row * g + col : -1;
+}
+
+// Rank by counting: a cell's rank is the number of cells of its group that come before it.  Quadratic in the group, but
+// every cell is independent of the others: RANK_LANES neighbouring lanes share one cell, each against its part of the keys
+// (all keys of the group in LDS, 32 bits each), and a group spreads over as many workgroups as it has runs of blockDim /
+// RANK_LANES cells; the sort below has one workgroup per group and a chain of log^2 barriers (64 x 64 grid: 40 -> 7.6 us).  Equal keys are told apart by their
+// index: a key before the cell counts if it is <= the cell's, i.e. < mine + 1 (no key is the largest 32-bit number), a key
+// behind it if it is < mine.  The four cells of a wave lie in one aligned run of four keys, so which of the two holds is
+// the same for the whole wave except in the step that contains that run.
+constexpr int RANK_LANES = 16, RANK_STEP = 4 * RANK_LANES;
+__device__ __forceinline__ int count_below(const uint4 &k, uint32_t t) { return (k.x < t) + (k.y < t) + (k.z < t) + (k.w < t); }
+
+__global__ void __launch_bounds__(1024)
+content_rank_kernel(const float *__restrict__ scores, int g, int w, int nws, int G, int runs,
+                    int32_t *__restrict__ gather_table, int32_t *__restrict__ sigma)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint32_t *keys = reinterpret_cast<uint32_t *>(smem);
+    const int S = w * w, nW = nws * nws;
+    const int group = blockIdx.x / runs, run = blockIdx.x - group * runs;
+    const int b = group / nW, win = group - b * nW, wr = win / nws, wc = win - wr * nws;
+    const float *sc = scores + (long)b * g * g;
+    const int padded = (S + RANK_STEP - 1) / RANK_STEP * RANK_STEP;      // past S: the largest number, counted by nobody
+    if (w == g) {
+        for (int i = threadIdx.x; i < padded; i += blockDim.x) keys[i] = i < S ? ~score_key(sc[i]) : ~0u;
+    } else {
+        for (int i = threadIdx.x; i < padded; i += blockDim.x) keys[i] = i < S ? content_key(sc, g, w, wr, wc, i) : ~0u;
+    }
+    __syncthreads();
+    const int cell = run * (blockDim.x / RANK_LANES) + threadIdx.x / RANK_LANES, part = threadIdx.x % RANK_LANES;
+    const int four = __builtin_amdgcn_readfirstlane(cell & ~3), step = four / RANK_STEP * RANK_STEP;
+    const uint32_t mine = keys[min(cell, S - 1)];
+    const uint4 *kp = reinterpret_cast<const uint4 *>(keys) + part;
+    int before = 0;
+#pragma unroll 4
+    for (int j = 0; j < step; j += RANK_STEP) before += count_below(kp[j / 4], mine + 1);
+    if (step < padded) {
+        const uint4 k = kp[step / 4];
+        const int j = step + part * 4;
+        before += (k.x < mine + (j < cell)) + (k.y < mine + (j + 1 < cell)) + (k.z < mine + (j + 2 < cell)) + (k.w < mine + (j + 3 < cell));
+    }
+#pragma unroll 4
+    for (int j = step + RANK_STEP; j < padded; j += RANK_STEP) before += count_below(kp[j / 4], mine);
+#pragma unroll
+    for (int o = RANK_LANES / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if (part == 0 && cell < S) content_place(cell, before, g, w, wr, wc, G, (long)group * S, gather_table, sigma);
+}
+
+// One workgroup per (image, window): a bitonic sort of 64-bit (key, cell) pairs in LDS.
 // P = the power of two >= S that is sorted; entries S..P-1 carry the largest key.
 __global__ void __launch_bounds__(1024)
 content_tables_kernel(const float *__restrict__ scores, int g, int w, int nws, int G, int P,
@@ -457,15 +567,8 @@ content_tables_kernel(const float *__restrict__ scores, int g, int w, int nws, i
     const int b = blockIdx.x / nW, win = blockIdx.x % nW;
     const int wr = win / nws, wc = win % nws;
     const float *sc = scores + (long)b * g * g;
-    for (int i = threadIdx.x; i < P; i += blockDim.x) {
-        unsigned long long key = ~0ull;
-        if (i < S) {
-            const int row = wr * w + i / w, col = wc * w + i % w;
-            const float m = (row < g && col < g) ? sc[row * g + col] : -INFINITY;
-            key = ((unsigned long long)(~score_key(m)) << 32) | (unsigned)i;
-        }
-        keys[i] = key;
-    }
+    for (int i = threadIdx.x; i < P; i += blockDim.x)
+        keys[i] = i < S ? ((unsigned long long)content_key(sc, g, w, wr, wc, i) << 32) | (unsigned)i : ~0ull;
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -478,15 +581,8 @@ content_tables_kernel(const float *__restrict__ scores, int g, int w, int nws, i
             }
             __syncthreads();
         }
-    const int rows = S / G;
-    for (int rk = threadIdx.x; rk < S; rk += blockDim.x) {
-        const int cell = (int)(keys[rk] & 0xffffffffu);
-        const int pos = (rk % G) * rows + rk / G;
-        const int row = wr * w + cell / w, col = wc * w + cell % w;
-        const long o = ((long)b * nW + win) * S + pos;
-        sigma[o] = cell;
-        gather_table[o] = (row < g && col < g) ? row * g + col : -1;
-    }
+    for (int rk = threadIdx.x; rk < S; rk += blockDim.x)
+        content_place((int)(keys[rk] & 0xffffffffu), rk, g, w, wr, wc, G, (long)blockIdx.x * S, gather_table, sigma);
 }
 
 extern "C" int ssam_permute(const void *x, const int32_t *idx, void *y, int B, int Nin, int Nout, int D, void *stream)
@@ -606,9 +702,24 @@ extern "C" int ssam_select_tokens(const float *scores, int32_t *keep_idx, int B,
 {
     if (!scores || !keep_idx || B <= 0 || N <= 0 || K <= 0 || K > N) return SSAM_EINVAL;
     if (N > 65536) return SSAM_EUNSUPPORTED;
-    hipLaunchKernelGGL(select_kernel, dim3(B), dim3(SEL_THREADS), 0, (hipStream_t)stream, scores, keep_idx, N, K);
+    const hipStream_t st = (hipStream_t)stream;
+    if (N <= 4 * SEL_THREADS) hipLaunchKernelGGL(select_kernel<4>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
+    else if (N <= 16 * SEL_THREADS) hipLaunchKernelGGL(select_kernel<16>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
+    else hipLaunchKernelGGL(select_kernel<64>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
+}
+
+// Whether counting beats the sort, from their measured times.  Counting takes 5 us and 80 us for every 2^30 pairs of cells
+// (64 x 64 grids: 7.6 us for one, 14 for 8, 25 for 16, 44 for 32; windows of 8 images: 7 us).  The sort has one CU per group
+// and takes 0.2 us for every step of its network and 1024 exchanges (64 x 64: 40 us whether one grid or 100; windows: 9.5 us;
+// 128 x 128: 163 us against 27 for one grid by counting and 257 for 16).
+static bool rank_by_counting(long groups, long S, int P)
+{
+    int lg = 0;
+    while ((1 << lg) < P) ++lg;
+    const double sort_us = 0.2 * (lg * (lg + 1) / 2) * (P > 2048 ? P / 2048 : 1) * (double)((groups + 511) / 512);
+    return 5.0 + (double)groups * S * S * (80.0 / 1073741824.0) < sort_us;
 }
 
 extern "C" int ssam_build_content_tables(const float *scores, int B, int g, int ws, int G,
@@ -619,8 +730,17 @@ extern "C" int ssam_build_content_tables(const float *scores, int B, int g, int 
     if (w > 128) return SSAM_EUNSUPPORTED;
     const int S = w * w, nws = (g + w - 1) / w;
     if (S % G != 0) return SSAM_EINVAL;
+    const long groups = (long)B * nws * nws;
     int P = 2;
     while (P < S) P <<= 1;
+    if (rank_by_counting(groups, S, P)) {
+        const int threads = S > 8192 ? 1024 : 512, runs = ssam_div_up(S, threads / RANK_LANES);
+        const size_t lds = (size_t)ssam_div_up(S, RANK_STEP) * RANK_STEP * sizeof(uint32_t);       // <= 64 KiB (w <= 128)
+        hipLaunchKernelGGL(content_rank_kernel, dim3((unsigned)(groups * runs)), dim3(threads), lds, (hipStream_t)stream,
+                           scores, g, w, nws, G, runs, gather_table, sigma);
+        SSAM_CHECK_LAUNCH();
+        return SSAM_OK;
+    }
     const int threads = P / 2 < 1024 ? (P / 2 < 64 ? 64 : P / 2) : 1024;
     const size_t lds = (size_t)P * sizeof(unsigned long long);
     if (lds > 64 * 1024 &&

@@ -1,0 +1,56 @@
+"""Keep-set and content-aware tables where their kernels change form: 4 / 16 / 64 keys per thread in the selection, ranking
+by counting or by sorting for the tables."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import announce
+from paper_2605_17633_amd import binding as B
+from paper_2605_17633_amd import inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("n,K", [(1, 1), (3, 2), (4095, 1000), (4096, 4096), (4097, 1), (16384, 9000), (16385, 16385), (65533, 30000), (65536, 1)])
+@pytest.mark.parametrize("kind", ["spread", "ties", "extremes"])
+def test_select_sizes(n, K, kind):
+    announce("select", n, K, kind)
+    rng = np.random.default_rng(n + K)
+    if kind == "spread":
+        s = rng.normal(size=(2, n))
+    elif kind == "ties":                       # a handful of values, zeros of both signs among them
+        s = rng.choice([-1.0, -0.0, 0.0, 0.5, 2.0], size=(2, n))
+    else:
+        s = rng.choice([np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-42, -1e-42, 0.0], size=(2, n))
+    s = s.astype(np.float32)
+    keep = B.ssam_select_tokens(torch.from_numpy(s).to(DEV), K).cpu().numpy()
+    for b in range(2):
+        assert np.array_equal(keep[b], oracle.select_tokens(s[b], K))
+
+
+@pytest.mark.parametrize("Bn,g,ws,levels", [(1, 14, 14, 0), (2, 30, 14, 3), (1, 5, 2, 0), (1, 50, 0, 4), (9, 128, 0, 50)])
+def test_content_tables_forms(Bn, g, ws, levels):
+    """levels > 0: only that many different scores, so that most pairs are decided by the cell index.  The last case is past
+    the point where the tables are sorted instead of counted."""
+    announce("content tables", Bn, g, ws, levels)
+    rng = np.random.default_rng(g + ws)
+    s = rng.integers(0, levels, size=(Bn, g * g)).astype(np.float32) if levels else inputs.lognormal_scores(rng, Bn, g * g)
+    if not levels:
+        s[0, :3] = [np.nan, -np.inf, -0.0]
+    table, sigma = B.ssam_build_content_tables(torch.from_numpy(s).to(DEV), g, ws, 4)
+    table, sigma = table.cpu().numpy(), sigma.cpu().numpy()
+    w = ws or g
+    nws, S = -(-g // w), w * w
+    for b in range(Bn):
+        for win in range(nws * nws):
+            row, col = (win // nws) * w + np.arange(S) // w, (win % nws) * w + np.arange(S) % w
+            inside = (row < g) & (col < g)
+            v = np.where(inside, s[b, np.where(inside, row * g + col, 0)], -np.inf)
+            v = np.where(np.isnan(v), -np.inf, v) + 0.0
+            pi = np.lexsort((np.arange(S), -v))
+            order = pi.reshape(S // 4, 4).T.reshape(-1)
+            assert np.array_equal(sigma[b * nws * nws + win], order), (b, win)
+            cell = np.where(inside, row * g + col, -1)[order]
+            assert np.array_equal(table[b, win * S:(win + 1) * S], cell), (b, win)
