@@ -1,5 +1,5 @@
 // Dispatcher of the bf16 NT GEMM (qkv / proj / fc1 / fc2 of the SAM block).
-#include "gemm_kernel.h"
+#include "gemm_ring.h"
 
 namespace {
 
@@ -145,6 +145,8 @@ int launch_tile(int tile, const bf16 *A, const bf16 *W, const float *bias, bf16 
     }
 }
 
+double large_tile_us(double rounds_us, bool packed) { return packed ? 5.0 + 0.72 * rounds_us : 3.0 + rounds_us; }
+
 // Pick the tile by a time model in microseconds, fitted on MI355X to the ViT-H layer shapes: a round of
 // workgroups costs nk * t_slab + t_epi.  The 256x256 tile (eight waves, one workgroup per CU) and the 128x256
 // tile (four waves in a row, two workgroups per CU) give a wave the same 128x64 piece and move the same data
@@ -152,7 +154,7 @@ int launch_tile(int tile, const bf16 *A, const bf16 *W, const float *bias, bf16 
 // 5 us a round behind the GELU epilogue and 1-2.5 us behind the others.  The 128x128 tile (two per CU) moves
 // more data per flop and is for small problems.  The left-over launch costs a lone workgroup's walk over its
 // K range, latency bound, plus the reduce.
-int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed)
+int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed, double &launch_us)
 {
     struct Cand { int id, bm, bn, tm, tn, slots; double t_slab, t_epi[4]; };   // t_epi: bias, +GELU, scatter-add, scatter
     const Cand cands[4] = { { 1, 256, 256, 128, 128, 256, 1.73, { 5.1, 13.6, 13.5, 6.0 } },
@@ -176,9 +178,78 @@ int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed)
             const int n_sub = plan.rem * subs;
             t += plan.parts > 1 ? ssam_div_up(nk, plan.parts) * 0.9 + 11.0 : (nk * 0.75 + 5.0) * (1.0 + n_sub / 1024.0);
         }
-        if (t < best_time) { best_time = t; best = c.id; }
+        if (t >= best_time) continue;
+        best_time = t;
+        best = c.id;
+        // What such a launch was measured to take on those shapes (see ring_tiles):
+        // the time above leaves the launch out and is pessimistic with packed weights (11 % standard error); a problem
+        // that is all left-over with K cut pays for its ranges and for writing and reading its partial tiles (5 %).
+        const int n_all = total * subs;
+        launch_us = plan.rem == total && plan.parts > 1
+                        ? 6.6 + ssam_div_up(nk, plan.parts) * (packed ? 0.90 : 1.21) + 0.41e-6 * n_all * plan.parts * c.tm * c.tn * 4
+                        : large_tile_us(t, packed);
     }
     return best;
+}
+
+// The ring's tiles (gemm_ring.h) for a problem that they hold in one round of workgroups.  A launch takes t0 plus
+// t_slab[k - 1] per slab of 64 when its busiest CU has k workgroups: fitted to 290 shapes (M 196 to 8192, the layers
+// of widths 576 to 1280, both weight layouts) with weights that no cache holds, as in a deep stack; 8-10 % standard error.
+struct RingTile { int bm, bn, slots; double t0, t_slab[3]; };
+constexpr RingTile ring_tiles[3] = { { 128, 128, 2, 4.9, { 0.66, 0.95, 0. } },
+                                     { 128, 64, 3, 3.5, { 0.56, 0.67, 0.95 } },
+                                     { 64, 64, 3, 3.2, { 0.28, 0.40, 0.61 } } };
+
+// Index of the ring tile that is faster than the large tiles (launch_us), or -1.  On the 290 shapes the choice is 1-2 % on
+// average from the faster of the two (the large tiles alone: 20 % with packed, 32 % with row-major weights), and the ring is
+// taken where it is slower on 7, by up to 7 %.
+int pick_ring(int M, int N, int K, double launch_us)
+{
+    const int nk = ssam_div_up(K, GEMM_BK);
+    int best = -1;
+    double best_us = launch_us;
+    for (int i = 0; i < 3; ++i) {
+        const RingTile &t = ring_tiles[i];
+        const long tiles = (long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn);
+        if (tiles > 256L * t.slots) continue;
+        const double us = t.t0 + nk * t.t_slab[ssam_div_up(tiles, 256) - 1];
+        if (us < best_us) { best_us = us; best = i; }
+    }
+    return best;
+}
+
+template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF>
+int launch_ring_tile(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
+                     const GemmLd &ld, const GemmRowMap &rm, const GemmFold &fold, hipStream_t st)
+{
+    constexpr size_t lds = gemm_ring_lds_bytes<BM, BN, GEMM_BK, STAGES>();
+    static_assert(lds <= 64 * 1024, "default LDS limit");
+    GemmTileRange tr = { ssam_div_up(M, BM), ssam_div_up(N, BN), 0, 0 };
+    tr.tile_count = tr.tiles_m * tr.tiles_n;
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, GEMM_BK, STAGES, EPI, WPACK, LNF>), dim3(ssam_div_up(tr.tile_count, 8) * 8), dim3(256), lds, st,
+                       A, W, bias, C, M, N, K, ld, tr, rm, fold);
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
+}
+
+template <int EPI, bool WPACK, bool LNF = false>
+int launch_ring(int ring, const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
+                const GemmLd &ld, const GemmRowMap &rm, const GemmFold &fold, hipStream_t st)
+{
+    switch (ring) {
+    case 0: return launch_ring_tile<128, 128, 2, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, rm, fold, st);
+    case 1: return launch_ring_tile<128, 64, 2, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, rm, fold, st);
+    default: return launch_ring_tile<64, 64, 3, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, rm, fold, st);
+    }
+}
+
+template <int EPI, bool WPACK>
+int launch_any(int tile, int ring, const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
+               const GemmLd &ld, const GemmRowMap &rm, const SplitWs &ws, hipStream_t st)
+{
+    if (ring >= 0) return launch_ring<EPI, WPACK>(ring, A, W, bias, C, M, N, K, ld, rm, no_fold, st);
+    if constexpr (WPACK) return launch_tile_packed<EPI>(tile, A, W, bias, C, M, N, K, ld, rm, ws, st);
+    else return launch_tile<EPI>(tile, A, W, bias, C, M, N, K, ld, rm, ws, st);
 }
 
 }  // namespace
@@ -190,21 +261,26 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
     const SplitWs ws = { split_ws, split_ws_bytes };
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
     bf16 *c = (bf16 *)C;
-    if (tile == 0) tile = pick_tile(M, N, K, epilogue, ws, packed);
+    int ring = -1;
+    if (tile == 0) {
+        double us;
+        tile = pick_tile(M, N, K, epilogue, ws, packed, us);
+        ring = pick_ring(M, N, K, us);
+    }
     if (packed) {
         switch (epilogue) {
-        case SSAM_EPI_BIAS: return launch_tile_packed<SSAM_EPI_BIAS>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-        case SSAM_EPI_BIAS_GELU: return launch_tile_packed<SSAM_EPI_BIAS_GELU>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-        case SSAM_EPI_BIAS_SCATTER_ADD: return launch_tile_packed<SSAM_EPI_BIAS_SCATTER_ADD>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-        case SSAM_EPI_BIAS_SCATTER: return launch_tile_packed<SSAM_EPI_BIAS_SCATTER>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
+        case SSAM_EPI_BIAS: return launch_any<SSAM_EPI_BIAS, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+        case SSAM_EPI_BIAS_GELU: return launch_any<SSAM_EPI_BIAS_GELU, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+        case SSAM_EPI_BIAS_SCATTER_ADD: return launch_any<SSAM_EPI_BIAS_SCATTER_ADD, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+        case SSAM_EPI_BIAS_SCATTER: return launch_any<SSAM_EPI_BIAS_SCATTER, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
         default: return SSAM_EINVAL;
         }
     }
     switch (epilogue) {
-    case SSAM_EPI_BIAS: return launch_tile<SSAM_EPI_BIAS>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-    case SSAM_EPI_BIAS_GELU: return launch_tile<SSAM_EPI_BIAS_GELU>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-    case SSAM_EPI_BIAS_SCATTER_ADD: return launch_tile<SSAM_EPI_BIAS_SCATTER_ADD>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
-    case SSAM_EPI_BIAS_SCATTER: return launch_tile<SSAM_EPI_BIAS_SCATTER>(tile, a, w, bias, c, M, N, K, ld, rm, ws, st);
+    case SSAM_EPI_BIAS: return launch_any<SSAM_EPI_BIAS, false>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+    case SSAM_EPI_BIAS_GELU: return launch_any<SSAM_EPI_BIAS_GELU, false>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+    case SSAM_EPI_BIAS_SCATTER_ADD: return launch_any<SSAM_EPI_BIAS_SCATTER_ADD, false>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
+    case SSAM_EPI_BIAS_SCATTER: return launch_any<SSAM_EPI_BIAS_SCATTER, false>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
     default: return SSAM_EINVAL;
     }
 }
@@ -218,7 +294,10 @@ int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *s
     const SplitWs ws = { split_ws, split_ws_bytes };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src };
     const GemmRowMap none = { nullptr, 1, 0, 1 };
-    const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true);
+    double us;
+    const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
+    if (const int ring = pick_ring(M, N, K, us); ring >= 0)
+        return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
     return launch_tile_packed<SSAM_EPI_BIAS_GELU, true>(tile, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld,
                                                         none, ws, st, fold);
 }
@@ -232,6 +311,12 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr };
+    // 512 workgroups a round, a last round of at most half of them at 0.62 of a round's time (as in pick_tile)
+    const double round = (K / GEMM_BK) * 1.71 + 5.5;
+    const int last = tr.tile_count % 512;
+    const double us = large_tile_us((tr.tile_count / 512) * round + (last == 0 ? 0.0 : last <= 256 ? 0.62 * round : round), true);
+    if (const int ring = pick_ring(M, N, K, us); ring >= 0)
+        return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
     const int per_xcd = ssam_div_up(tr.tile_count, 8);
     hipLaunchKernelGGL((gemm_bf16_nt_lnf_kernel<128, 256, SSAM_EPI_BIAS_SCATTER, 1, 4>), dim3(per_xcd * 8), dim3(256), lds, st,
                        (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, tr, rm, fold);
