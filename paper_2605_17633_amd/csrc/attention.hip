@@ -102,7 +102,7 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 //   tq[q*tstr + (p&1)*hw + (p>>1)]            = q . rel_h[row(q)-p+w-1] / scale      (p = key row)
 //   tq[q*tstr + 2*hw + (p&1)*hw + (p>>1)]     = q . rel_w[col(q)-p+w-1] / scale      (p = key column)
 // hw = ceil(w/2): even and odd rows (columns) are stored apart, so that rows two apart are neighbours: the 32-key
-// blocks of the position-only Stripe-Sort order are 4 x 8 patches of stride 2 (see attn_scores_patch), whose 4 row
+// blocks of the position-only Stripe-Sort order are 4 x 8 patches of stride 2 (see attn_patch_body), whose 4 row
 // and 8 column entries are then contiguous.  tstr = 4*hw + 4: the 8 bytes of padding put the 32 lanes of a look-up
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
 __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; }
@@ -340,7 +340,7 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
     attn_softmax_pv<D, NB, FULL, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
 }
 
-// Scores of a chunk whose 32-key blocks are 4 x 8 patches of stride 2 in the grid: key k of a block (bits c0 r1'.. in
+// Patches: scores of 32-key blocks that are 4 x 8 patches of stride 2 in the grid: key k of a block (bits c0 r1'.. in
 // scan order: bit 0 and bits 2, 4 count columns, bits 1 and 3 rows, i.e. a Z-order walk) sits 2*rr(k) rows and 2*cc(k)
 // columns from the block's first key.  That is how the position-only Stripe-Sort order (Sec. 4.1: Z-order, then the
 // stripe interleave with G = 4, which collects the cells of one row and column parity) lays out a power-of-two grid.
@@ -348,46 +348,7 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
 // picks a key's row entry (f = rr) and column entry (f = 4 + cc) and T the 4 row and 8 column entries of every
 // query, which are contiguous in the query's table row (build_bias_rows).  So the bias is ONE more MFMA (fp16
 // operands, the same fp32 accumulator, issued first) and the vector unit does no look-ups and no additions.
-//   efrag:  the lane's part of E (operand a; the same for every block)
-//   blkoff: LDS, per block of the tile the table offsets of its first key (as in krc)
-//   tq_lane: this lane's query row of the table
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-template <int D, int NB>
-__device__ __forceinline__ void attn_chunk_step_patch(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
-                                                      const uint32_t *blkoff, const int (&blk)[NB], const f16x8 &efrag,
-                                                      const unsigned char *tq_lane, float scale_log2e)
-{
-    using C = AttnCfg<D>;
-    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    f32x16 s[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        // operand b of the bias product: f = 8*half + e; f 0..3 the block's rows, 4..11 its columns, 12..15 meet zeros
-        // of E (whatever finite values the second read of the upper half-wave returns)
-        const uint32_t bo = blkoff[blk[b]];
-        const f16x4 t1 = *reinterpret_cast<const f16x4 *>(tq_lane + (half ? (bo >> 16) + 8 : (bo & 0xffffu)));
-        const f16x4 t2 = *reinterpret_cast<const f16x4 *>(tq_lane + (bo >> 16));
-        const f16x8 tf = { t1[0], t1[1], t1[2], t1[3], t2[0], t2[1], t2[2], t2[3] };
-        const f32x16 zero = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
-        s[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(efrag, tf, zero, 0, 0, 0);
-        const bf16 *kblk = Ks + blk[b] * 32 * C::KSTR + l32 * C::KSTR + half * 8;
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 a = *reinterpret_cast<const bf16x8 *>(kblk + ks * 16);
-            s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[b], 0, 0, 0);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    float mx = -INFINITY;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[b][r]);
-    attn_softmax_pv<D, NB, true, true>(st, s, mx, Vs, blk, NB, scale_log2e);
-}
-
 // row and column steps (in units of 2 cells) of key k of a patch block from the block's first key
 __device__ __forceinline__ int patch_rr(int k) { return ((k >> 1) & 1) | ((k >> 2) & 2); }
 __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2) | ((k >> 2) & 4); }
@@ -709,10 +670,394 @@ size_t global_lds_bytes(int w)
     return (size_t)2 * GLB_TILE * AttnCfg<D>::KSTR * 2 + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w)) + (size_t)GLB_TILE * 4;
 }
 
-// Everything a workgroup of the global kernel does once it knows which way its scores are formed.
-// PATCHED: every block of every tile this workgroup visits is a patch (attn_chunk_step_patch: bias by MFMA);
-// otherwise the general path (per-key table look-ups, any order).
-template <int D, bool PATCHED>
+// ---- patch path
+// One workgroup = one 128-query tile, four waves of 32 queries, as in the general path, but a pipeline of 32-key blocks.
+// Scores, softmax and P V of a block depend on each other, and with a tile of 128 keys at a time between two barriers the matrix,
+// vector and LDS pipes were all 35-50 % busy.  So
+//   * a wave works on three blocks at once: while the vector unit takes the exponentials of block b, one MFMA behind every
+//     few of those instructions forms the scores of block b + 1 and adds P V of block b - 1;
+//   * K and V blocks go from memory straight into two rings of three blocks in LDS, two blocks ahead (no registers, no LDS
+//     writes, one barrier per block).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
+//     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
+//   * the exponent reference moves by whole powers of two, so that the rare rescaling is exact and can also be applied to
+//     the probabilities of block b - 1 that still wait for their P V.
+constexpr int PATCH_RING = 3;
+
+template <int D>
+struct PatchPipe {
+    using C = AttnCfg<D>;
+    static constexpr int SLOT = 32 * D * 2;                       // bytes of a block of K or V
+    static constexpr int NQ = 1 + C::KS, NP = 2 * C::DT;          // MFMAs of a block's scores (bias first) and of its P V
+    static_assert(NQ == NP || NQ == NP + 1, "scores and P V alternate");
+    static constexpr int LOADS_HI = (C::CH + 3) / 4;              // 1 KB requests of K and V of a block: CH over four waves
+    static constexpr int AHEAD = 3, FR = 4;                       // operand fragments are read three MFMAs ahead
+
+    // chunk c of row `row` sits at chunk position c ^ swz(row): 16 rows at one chunk then touch 16 distinct 16-byte banks
+    static __device__ __forceinline__ int swz(int row)
+    {
+        return C::CH == 8 ? (row >> 1) & 7 : C::CH == 4 ? (row >> 2) & 3 : (row >> 3) & 1;
+    }
+
+    WaveState<D> &st;
+    const bf16x8 *qf;
+    const unsigned char *lds, *tq_lane;
+    float scale_log2e;
+    int half;
+    bool ones_lane;                  // D = 16 mod 32: this lane's columns of the last O tile are the ones columns
+    f16x8 efrag;
+    int ka[C::KS], va[2], ones_at;   // byte offsets: this lane's K chunks in a block, its V reads (rows +0 and +8), the ones
+    uint32_t bo;                     // table offsets of the first key of the block whose scores are formed next
+    f32x16 s[2];
+    bf16x8 p[2][2], frag[FR];
+
+    // operand I of the interleaved sequence of a step with scores (HQ) and / or P V (HP): even places scores, odd P V
+    template <bool HQ, bool HP> static constexpr bool is_q(int k) { return HQ && (!HP || k % 2 == 0); }
+    template <bool HQ, bool HP> static constexpr int idx(int k) { return HQ && HP ? k / 2 : k; }
+
+    template <bool HQ, bool HP, int K>
+    __device__ __forceinline__ void load(int k_slot, int v_slot)
+    {
+        if constexpr (K < (HQ ? NQ : 0) + (HP ? NP : 0)) {
+            constexpr int i = idx<HQ, HP>(K);
+            bf16x8 &f = frag[K % FR];
+            if constexpr (!is_q<HQ, HP>(K)) {
+                constexpr int t = i / C::DT, dt = i % C::DT;
+                bf16x4 v[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    // column tile dt: four chunks on, under the swizzle of 8-chunk rows the other half of the row
+                    const int col = C::CH == 8 ? ((dt ^ u) - u) * 64 : dt * 64;
+                    int at = va[u] + v_slot + t * 16 * D * 2 + col;
+                    if (C::ONES && dt == C::DT - 1) at = ones_lane ? ones_at : at;
+                    v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(lds + at));
+                }
+                f = bf16x8{ v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3] };
+            } else if constexpr (i == 0) {
+                // operand b of the bias product: f = 8*half + e; f 0..3 the block's rows, 4..11 its columns, 12..15 meet
+                // zeros of E (whatever finite values the second read of the upper half-wave returns)
+                const f16x4 t1 = *reinterpret_cast<const f16x4 *>(tq_lane + (half ? (bo >> 16) + 8 : (bo & 0xffffu)));
+                const f16x4 t2 = *reinterpret_cast<const f16x4 *>(tq_lane + (bo >> 16));
+                f = __builtin_bit_cast(bf16x8, f16x8{ t1[0], t1[1], t1[2], t1[3], t2[0], t2[1], t2[2], t2[3] });
+            } else {
+                f = *reinterpret_cast<const bf16x8 *>(lds + k_slot + ka[i - 1]);
+            }
+        }
+    }
+
+    // PAR: parity of the block whose softmax this step is (the scores formed are the other parity's, so is the P V)
+    template <bool HQ, bool HP, int PAR, int K>
+    __device__ __forceinline__ void mfma()
+    {
+        constexpr int i = idx<HQ, HP>(K);
+        const bf16x8 &f = frag[K % FR];
+        if constexpr (!is_q<HQ, HP>(K)) {
+            st.o[i % C::DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, p[PAR ^ 1][i / C::DT], st.o[i % C::DT], 0, 0, 0);
+        } else if constexpr (i == 0) {
+            const f32x16 zero = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
+            s[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(efrag, __builtin_bit_cast(f16x8, f), zero, 0, 0, 0);
+        } else {
+            s[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[i - 1], s[PAR ^ 1], 0, 0, 0);
+        }
+    }
+
+    template <int PAR, int J, int J1>
+    __device__ __forceinline__ void exp_pairs(float mref)         // probabilities 2*J .. 2*J1 - 1
+    {
+        if constexpr (J < J1) {
+            const float e0 = __builtin_amdgcn_exp2f(fmaf(s[PAR][2 * J], scale_log2e, -mref));
+            const float e1 = __builtin_amdgcn_exp2f(fmaf(s[PAR][2 * J + 1], scale_log2e, -mref));
+            if constexpr (!C::ONES) st.l += e0 + e1;
+            u32x4 w = __builtin_bit_cast(u32x4, p[PAR][J / 4]);
+            w[J % 4] = pack_bf16x2(e0, e1);
+            p[PAR][J / 4] = __builtin_bit_cast(bf16x8, w);
+            exp_pairs<PAR, J + 1, J1>(mref);
+        }
+    }
+
+    template <bool HQ, bool HP, int PAR, bool SM, int K>
+    __device__ __forceinline__ void steps(int k_slot, int v_slot, float mref)
+    {
+        constexpr int n = (HQ ? NQ : 0) + (HP ? NP : 0);
+        if constexpr (K < n) {
+            load<HQ, HP, K + AHEAD>(k_slot, v_slot);
+            mfma<HQ, HP, PAR, K>();
+            if constexpr (SM) exp_pairs<PAR, 8 * K / n, 8 * (K + 1) / n>(mref);       // spread evenly behind the MFMAs
+            __builtin_amdgcn_sched_barrier(0);
+            steps<HQ, HP, PAR, SM, K + 1>(k_slot, v_slot, mref);
+        }
+    }
+
+    // softmax of block b (parity PAR) with, behind it, the scores of b + 1 (HQ) and P V of b - 1 (HP)
+    template <bool HQ, bool HP, int PAR>
+    __device__ __forceinline__ void block(int k_slot, int v_slot)
+    {
+        load<HQ, HP, 0>(k_slot, v_slot);
+        load<HQ, HP, 1>(k_slot, v_slot);
+        load<HQ, HP, 2>(k_slot, v_slot);
+        float mx = fmaxf(s[PAR][0], s[PAR][1]);
+#pragma unroll
+        for (int r = 2; r < 16; ++r) mx = fmaxf(mx, s[PAR][r]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
+        const bool move = mx > st.m + ATTN_LAG;         // see attn_softmax_pv
+        if (__builtin_amdgcn_ballot_w64(move) != 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");      // earlier P V MFMAs may be in flight (as in finish_and_store)
+            __builtin_amdgcn_sched_barrier(0);
+            const float mnew = move ? ceilf(mx) : st.m;
+            const int e = move ? (int)fmaxf(st.m - mnew, -1000.f) : 0;
+            st.m = mnew;
+            if constexpr (!C::ONES) st.l = ldexpf(st.l, e);
+#pragma unroll
+            for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) st.o[dt][r] = ldexpf(st.o[dt][r], e);
+            if constexpr (HP) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) p[PAR ^ 1][t][i] = (bf16)ldexpf((float)p[PAR ^ 1][t][i], e);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // ahead of the other workgroup's requests, maxima and barriers (1 % at batch 16, 5 % when a launch is one round)
+        __builtin_amdgcn_s_setprio(1);
+        steps<HQ, HP, PAR, true, 0>(k_slot, v_slot, st.m);
+        __builtin_amdgcn_s_setprio(0);
+    }
+};
+
+// LDS of the patch path: K ring, V ring (below 64 KB: the reach of M0 as LDS address), 32 bytes of ones, the waves' check
+// results, table offsets of every block, the waves' bias tables
+inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_blocks * 4 + 15) & ~15; }
+template <int D>
+inline __host__ __device__ size_t patch_lds_bytes(int w, int n_blocks)
+{
+    return (size_t)2 * PATCH_RING * PatchPipe<D>::SLOT + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
+}
+
+// The bias table (layout of build_bias_rows) of a wave whose 32 queries are a patch: rows qr0 .. qr0 + 6 and columns
+// qc0 .. qc0 + 14 in steps of two, so that only w + 6 and w + 14 relative positions occur, and away from both ends every one of
+// them is an entry of every query: one conversion and one store per entry (the general form spends
+// nine vector instructions on one; at 64 x 64 the tables took 107 us of 850, now 65).
+template <int D>
+__device__ __forceinline__ void build_bias_rows_patch(const bf16x8 *qf, const bf16 *rel_h, const bf16 *rel_w, int w, int lgw, int qrow, int qcol,
+                                                      int qr0, int qc0, GlbTab *tq_lane, float inv_scale)
+{
+    constexpr int KS = AttnCfg<D>::KS;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int nrel = 2 * w - 1, hw = w >> 1;
+    bf16x8 cur[2][KS], nxt[2][KS];
+    auto load_slab = [&](bf16x8 (&a)[2][KS], int mt) {
+#pragma unroll
+        for (int tab = 0; tab < 2; ++tab) {
+            const bf16 *src = (tab ? rel_w : rel_h) + min((tab ? qc0 : qr0) + mt * 32 + l32, nrel - 1) * D + half * 8;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) a[tab][ks] = *reinterpret_cast<const bf16x8 *>(src + ks * 16);
+        }
+    };
+    load_slab(cur, 0);
+    for (int mt = 0; mt * 32 < w + 14; ++mt) {
+        load_slab(nxt, mt + 1);
+#pragma unroll
+        for (int tab = 0; tab < 2; ++tab) {
+            f32x16 u;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) u[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur[tab][ks], qf[ks], u, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // MFMA passes done before u is read under branches
+            __builtin_amdgcn_sched_barrier(0);
+            // entry r of the lane is relative position q0 + mt*32 + 8*(r>>2) + 4*half + (r&3), i.e. key row p = p0 - 8*(r>>2) - (r&3)
+            const int spread = tab ? 14 : 6, p0 = (tab ? qcol - qc0 : qrow - qr0) + w - 1 - mt * 32 - 4 * half;
+            GlbTab *row = tq_lane + (tab ? 2 * hw : 0);
+            GlbTab *ev = row + ((p0 & 1) << (lgw - 1)) + (p0 >> 1);              // where p0 lies; p0 - 2 is one entry in front of it
+            GlbTab *od = row + (((p0 - 1) & 1) << (lgw - 1)) + ((p0 - 1) >> 1);  // where p0 - 1 lies
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int d0 = mt * 32 + 8 * g;                                  // the group's first relative position less q0
+                if (d0 > w - 1 + spread) continue;                               // no query has these (wave-uniform, as below)
+                if (d0 >= spread && d0 + 7 < w) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ((e & 1) ? od : ev)[-4 * g - (e >> 1)] = (GlbTab)(u[4 * g + e] * inv_scale);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if ((unsigned)(p0 - 8 * g - e) < (unsigned)w) ((e & 1) ? od : ev)[-4 * g - (e >> 1)] = (GlbTab)(u[4 * g + e] * inv_scale);
+                }
+            }
+        }
+#pragma unroll
+        for (int tab = 0; tab < 2; ++tab)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) cur[tab][ks] = nxt[tab][ks];
+    }
+}
+
+// The patch path of a workgroup.  Any table is legal input, so the cells of every key it will visit (its own queries among
+// them) are looked at first, under the latency of the first K, V and Q requests: false = some block is not a patch, nothing has
+// been stored, and the caller takes the general path.  w is a power of two, 16 or more: S is a multiple of the tile.
+template <int D>
+__device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int grp, int head, float inv_scale, unsigned char *smem)
+{
+    using C = AttnCfg<D>;
+    using Pipe = PatchPipe<D>;
+    constexpr int SLOT = Pipe::SLOT, V0 = PATCH_RING * SLOT, ONES0 = 2 * PATCH_RING * SLOT;
+    static_assert(ONES0 <= 64 * 1024, "the rings are filled through M0");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+    const int lgw = 31 - __builtin_clz(P.w), nact = P.n_pre + (qt >= P.n_pre ? 1 : 0), nblk = nact * (GLB_TILE / 32);
+    int *ok_words = reinterpret_cast<int *>(smem + ONES0 + 32);
+    uint32_t *bo_tab = reinterpret_cast<uint32_t *>(smem + ONES0 + 64);
+    const int tstr = glb_tstr(P.w);
+    unsigned char *Tb = smem + ONES0 + 64 + patch_blocks_bytes(nblk);
+    GlbTab *tq = reinterpret_cast<GlbTab *>(Tb + wave * wave_scratch_bytes<D>(tstr));
+
+    const long base = (long)grp * P.S * P.row_stride + (long)head * D;
+    const uint32_t rs2 = (uint32_t)P.row_stride * 2u;
+    const unsigned char *kbase = reinterpret_cast<const unsigned char *>(P.k + base), *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
+    // request j of a block (K: j < CH/2, then V) is wave j % 4's: lane l brings the chunk that belongs at 16-byte place
+    // 64*(j % (CH/2)) + l of the block
+    uint32_t src_off[Pipe::LOADS_HI];
+#pragma unroll
+    for (int i = 0; i < Pipe::LOADS_HI; ++i) {
+        const int j = wave + 4 * i, place = (j % (C::CH / 2)) * 64 + lane, row = place / C::CH, pos = place % C::CH;
+        src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row)) * 16u;
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
+    auto key0_of = [&](int blk) {
+        blk = max(min(blk, nblk - 1), 0);        // past the end: the last block again, so that every wait below can count
+        const int a = blk >> 2;
+        return (a < P.n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32;
+    };
+    auto request = [&](int kblk, int k_slot, int vblk, int v_slot) {       // slots in bytes; a negative block: not requested
+        const unsigned char *kb = kbase + (size_t)key0_of(kblk) * rs2, *vb = vbase + (size_t)key0_of(vblk) * rs2;
+#pragma unroll
+        for (int i = 0; i < Pipe::LOADS_HI; ++i) {
+            const int j = wave + 4 * i;                                    // wave-uniform
+            const bool is_k = j < C::CH / 2;
+            if (j >= C::CH || (is_k ? kblk : vblk) < 0) continue;
+            const uint32_t at = lds0 + (is_k ? k_slot + j * 1024 : V0 + v_slot + (j - C::CH / 2) * 1024);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(at), "v"(src_off[i]), "s"(is_k ? kb : vb) : "m0", "memory");
+        }
+    };
+    request(0, 0, -1, 0);
+    request(1, SLOT, -1, 0);
+    request(2, 2 * SLOT, 0, 0);
+
+    const int qpos = qt * GLB_TILE + wave * 32 + l32;
+    bf16x8 qf[C::KS];
+    load_q_frags<D>(qf, P.q + base + (long)qpos * P.row_stride);
+    const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
+    const int qcell = sg[qpos];
+    long my_row = (long)grp * P.S + qpos;         // output row of this lane's query
+    if (P.out_rows) my_row = P.out_rows[my_row];
+
+    // A key passes if it sits where the patch anchored at its block's first key puts it (inside the grid) and, for a block's
+    // first key, the block's 4 row and 8 column entries start at 8- and 16-byte boundaries of a table row.
+    bool ok = true;
+    constexpr int BATCH = 8;                                            // cells per thread per pass: 16 tiles a pass
+    for (int a = 0; a < nact; a += 2 * BATCH) {
+        int cell[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {                               // the loads of a pass are in flight together
+            const int a1 = min(a + 2 * j + (tid >> 7), nact - 1);       // this thread's tile (past the end: the last one again)
+            cell[j] = sg[(a1 < P.n_pre ? a1 : qt) * GLB_TILE + (tid & 127)];
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int a1 = min(a + 2 * j + (tid >> 7), nact - 1);
+            const int c0 = __shfl(cell[j], lane & 32, 64);              // cell of the block's first key
+            const int k = tid & 31, r0 = c0 >> lgw, cl0 = c0 & (P.w - 1);
+            ok = ok && c0 >= 0 && r0 + 6 < P.w && cl0 + 14 < P.w && cell[j] == c0 + ((2 * patch_rr(k)) << lgw) + 2 * patch_cc(k);
+            if (k == 0) {
+                const uint32_t hw = (uint32_t)P.w >> 1, esz = sizeof(GlbTab);
+                const uint32_t off = (esz * ((r0 & 1) * hw + (r0 >> 1))) | ((esz * (2 * hw + (cl0 & 1) * hw + (cl0 >> 1))) << 16);
+                ok = ok && (off & 7u) == 0 && ((off >> 16) & 15u) == 0;
+                bo_tab[a1 * (GLB_TILE / 32) + ((tid & 127) >> 5)] = off;
+            }
+        }
+    }
+    const bool wave_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
+    if (lane == 0) ok_words[wave] = wave_ok;
+    if (C::ONES && tid < 8) reinterpret_cast<uint32_t *>(smem + ONES0)[tid] = 0x3f803f80u;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the first blocks have landed
+    __syncthreads();
+    if ((ok_words[0] & ok_words[1] & ok_words[2] & ok_words[3]) == 0) {
+        __syncthreads();                          // the words are part of another region from here on
+        return false;
+    }
+
+    const int qrow = qcell >> lgw, qcol = qcell & (P.w - 1);
+    GlbTab *tq_lane = tq + l32 * tstr;            // this lane's query row of the wave's bias table
+    build_bias_rows_patch<D>(qf, P.rel_h, P.rel_w, P.w, lgw, qrow, qcol, __builtin_amdgcn_readfirstlane(qrow), __builtin_amdgcn_readfirstlane(qcol),
+                             tq_lane, inv_scale);
+    WaveState<D> st;
+    init_state<D>(st);
+
+    const int li = lane & 15, fblk = (lane >> 4) & 1;
+    Pipe pipe{ st, qf, smem, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e, half, C::ONES && fblk != 0 };
+    pipe.ones_at = ONES0;
+    // operand a of the bias product: lane (key l32, half) holds E[l32][8*half + e]
+    const int rr = patch_rr(l32), cc = patch_cc(l32);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int f = 8 * half + e;
+        pipe.efrag[e] = (_Float16)((f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? 1.f : 0.f);
+    }
+#pragma unroll
+    for (int ks = 0; ks < C::KS; ++ks) pipe.ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ Pipe::swz(l32)) * 16;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        // transposing read: lane li of a 16-lane group points at row (li >> 2) of its 4 keys, column chunk (li & 3) of 4
+        // features of its 16; feature columns past D are the ones columns (their lanes read elsewhere, see load)
+        const int row = 8 * u + 4 * half + (li >> 2), f0 = (C::ONES && D == 16 ? 0 : 16 * fblk) + 4 * (li & 3);
+        pipe.va[u] = V0 + row * D * 2 + (((f0 >> 3) ^ Pipe::swz(row)) << 4) + (f0 & 7) * 2;
+    }
+
+    // Block b: everything of block b - 1 has been read, so the scores of b (slot of K(b)) and V(b - 2) make room for K(b + 3) and
+    // V(b + 1); K(b + 1) and V(b - 1) were requested two blocks ago, and only the requests of one block are younger.
+    int s0 = 0, s1 = SLOT, s2 = 2 * SLOT;        // slots of block index b, b + 1, b + 2 modulo the ring
+    auto enter = [&](int b) {
+        if (C::CH % 4 == 0 || wave < C::CH % 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((C::CH + 3) / 4) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::CH / 4) : "memory");
+        LDS_BARRIER();
+        request(b + 3, s0, b + 1, s1);
+        pipe.bo = bo_tab[min(b + 1, nblk - 1)];
+    };
+    auto rotate = [&]() { const int t = s0; s0 = s1; s1 = s2; s2 = t; };
+    pipe.bo = bo_tab[0];
+    pipe.template load<true, false, 0>(s0, 0);
+    pipe.template load<true, false, 1>(s0, 0);
+    pipe.template load<true, false, 2>(s0, 0);
+    pipe.template steps<true, false, 1, false, 0>(s0, 0, 0.f);       // scores of block 0
+    enter(0);
+    pipe.template block<true, false, 0>(s1, s2);
+    rotate();
+    for (int b = 1; b < nblk - 1; b += 2) {      // nblk is a multiple of four
+        enter(b);
+        pipe.template block<true, true, 1>(s1, s2);
+        rotate();
+        enter(b + 1);
+        pipe.template block<true, true, 0>(s1, s2);
+        rotate();
+    }
+    enter(nblk - 1);
+    pipe.template block<false, true, 1>(s1, s2);
+    // V of the last block was requested in front of the block before it
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    LDS_BARRIER();
+    pipe.template load<false, true, 0>(s1, s0);
+    pipe.template load<false, true, 1>(s1, s0);
+    pipe.template load<false, true, 2>(s1, s0);
+    pipe.template steps<false, true, 0, false, 0>(s1, s0, 0.f);      // P V of the last block (parity 1)
+    finish_and_store<D>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
+    return true;
+}
+
+// The general path of a workgroup: per-key table look-ups, any order, any S.
+template <int D>
 __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, int grp, int head, float inv_scale, unsigned char *smem)
 {
     using C = AttnCfg<D>;
@@ -723,9 +1068,9 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
     bf16 *Vs = Ks + GLB_TILE * C::KSTR;
     unsigned char *Tb = reinterpret_cast<unsigned char *>(Vs + GLB_TILE * C::KSTR);
     const int wsb = wave_scratch_bytes<D>(tstr);
-    uint32_t *krc = reinterpret_cast<uint32_t *>(Tb + 4 * wsb);    // [128] per key (general) or [4] per block (patches)
+    uint32_t *krc = reinterpret_cast<uint32_t *>(Tb + 4 * wsb);    // [128] per key
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31;
     const int S = P.S;
     const long base = (long)grp * S * P.row_stride + (long)head * D;
 
@@ -752,20 +1097,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
     const unsigned char *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
     const uint32_t rs2 = (uint32_t)P.row_stride * 2u;
 
-    // operand a of the bias product of patch blocks: lane (key l32, half) holds E[l32][8*half + e]
-    f16x8 efrag;
-    if constexpr (PATCHED) {
-        const int rr = patch_rr(l32), cc = patch_cc(l32);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int f = 8 * half + e;
-            efrag[e] = (_Float16)((f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? 1.f : 0.f);
-        }
-    }
-
     // WHAT: 1 = K and the keys' cells, 2 = V; the two halves are requested at different points of the
-    // current tile's work so that the waves do not queue up behind each other's loads.  With patches only the
-    // first key of each block is looked up.
+    // current tile's work so that the waves do not queue up behind each other's loads.
 #define ATTN_LOAD_TILE(kt_, WHAT)                                                                       \
     {                                                                                                   \
         __builtin_amdgcn_sched_barrier(0);                                                              \
@@ -778,8 +1111,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
             if ((WHAT) & 1) rk[i] = *reinterpret_cast<const u32x4 *>(kbase + off_);                     \
             if ((WHAT) & 2) rv[i] = *reinterpret_cast<const u32x4 *>(vbase + off_);                     \
         }                                                                                               \
-        if (((WHAT) & 1) && tid < (PATCHED ? GLB_TILE / 32 : GLB_TILE))                                 \
-            rcell = sg[min(key0_ + (PATCHED ? 32 * tid : tid), S - 1)]; /* used at the LDS store, not before */ \
+        if (((WHAT) & 1) && tid < GLB_TILE)                                                             \
+            rcell = sg[min(key0_ + tid, S - 1)]; /* used at the LDS store, not before */                \
         __builtin_amdgcn_sched_barrier(0);                                                              \
     }
 #define ATTN_STORE_TILE()                                                                               \
@@ -790,7 +1123,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
             *reinterpret_cast<u32x4 *>(Ks + key * C::KSTR + c * 8) = rk[i];                             \
             *reinterpret_cast<u32x4 *>(Vs + key * C::KSTR + c * 8) = rv[i];                             \
         }                                                                                               \
-        if (tid < (PATCHED ? GLB_TILE / 32 : GLB_TILE)) krc[tid] = cell_bias_offsets(rcell, P.w);      \
+        if (tid < GLB_TILE) krc[tid] = cell_bias_offsets(rcell, P.w);                                   \
     }
 
     ATTN_LOAD_TILE(0 < P.n_pre ? 0 : qt, 3)       // in flight while the bias rows are formed
@@ -808,31 +1141,20 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
         if (a + 1 < nact) ATTN_LOAD_TILE(kt_next, NB < GLB_TILE / 32 ? 1 : 3)     // one step per tile: nothing to put V between
         // the softmax / MFMA phase goes ahead of the other workgroup's tile traffic (loads, LDS stores, barriers)
         __builtin_amdgcn_s_setprio(1);
-        if constexpr (PATCHED) {
+        const int nblk = min(GLB_TILE / 32, (S - kt * GLB_TILE + 31) / 32);     // blocks wholly past the end are skipped
 #pragma unroll
-            for (int c0 = 0; c0 < GLB_TILE / 32; c0 += NB) {
-                int blk[NB];
+        for (int c0 = 0; c0 < GLB_TILE / 32; c0 += NB) {
+            if (c0 >= nblk) break;
+            int blk[NB], key0[NB];
 #pragma unroll
-                for (int b = 0; b < NB; ++b) blk[b] = c0 + b;
-                attn_chunk_step_patch<D, NB>(st, qf, Ks, Vs, krc, blk, efrag, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e);
-                if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
-            }
-        } else {
-            const int nblk = min(GLB_TILE / 32, (S - kt * GLB_TILE + 31) / 32);     // blocks wholly past the end are skipped
-#pragma unroll
-            for (int c0 = 0; c0 < GLB_TILE / 32; c0 += NB) {
-                if (c0 >= nblk) break;
-                int blk[NB], key0[NB];
-#pragma unroll
-                for (int b = 0; b < NB; ++b) { blk[b] = c0 + b; key0[b] = kt * GLB_TILE + 32 * (c0 + b); }
-                const int nb = min(NB, nblk - c0);
-                const bool ragged = key0[NB - 1] + 32 > S;
-                if (ragged)
-                    attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
-                else
-                    attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
-                if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
-            }
+            for (int b = 0; b < NB; ++b) { blk[b] = c0 + b; key0[b] = kt * GLB_TILE + 32 * (c0 + b); }
+            const int nb = min(NB, nblk - c0);
+            const bool ragged = key0[NB - 1] + 32 > S;
+            if (ragged)
+                attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+            else
+                attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+            if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
         }
         __builtin_amdgcn_s_setprio(0);
     }
@@ -841,9 +1163,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 #undef ATTN_STORE_TILE
 }
 
-// TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid.  The workgroup first looks at
-// the cells of every key it will visit: if every 32-key block is a patch (see attn_chunk_step_patch) it forms the bias
-// with the matrix core, otherwise (any table is legal) it takes the general path.  !TRY_PATCH: the general path only.
+// TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid (attn_patch_body, and the general
+// path where a block is not a patch).  !TRY_PATCH: the general path only.
 template <int D, bool TRY_PATCH>
 __global__ void __launch_bounds__(256, 2)
 attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
@@ -854,50 +1175,9 @@ attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
     const int qt = (blockIdx.x >> 3) % T, gh = ((blockIdx.x >> 3) / T) * 8 + (blockIdx.x & 7);
     if (gh >= n_gh) return;
     const int grp = gh / P.h, head = gh % P.h;
-    if constexpr (TRY_PATCH) {
-        // A key passes if it lies inside S, sits where the patch anchored at its block's first key puts it (inside the
-        // grid), and, for a block's first key, the block's 4 row and 8 column entries start at 8- and 16-byte
-        // boundaries of a table row.  256 consecutive keys a pass, the cells of a pass requested together.
-        const int tid = threadIdx.x, lane = tid & 63;
-        const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
-        const int nact = P.n_pre + (qt >= P.n_pre ? 1 : 0);
-        int *flag = reinterpret_cast<int *>(smem);
-        if (tid == 0) *flag = 1;
-        bool ok = true;
-        constexpr int BATCH = 8;                                            // cells per thread per pass: 16 tiles a pass
-        for (int a = 0; a < nact; a += 2 * BATCH) {
-            int cell[BATCH], key[BATCH];
-#pragma unroll
-            for (int j = 0; j < BATCH; ++j) {                               // the loads of a pass are in flight together
-                const int a1 = min(a + 2 * j + (tid >> 7), nact - 1);       // this thread's tile (past the end: the last one again)
-                const int kt = a1 < P.n_pre ? a1 : qt;
-                key[j] = kt * GLB_TILE + (tid & 127);
-                cell[j] = sg[min(key[j], P.S - 1)];
-            }
-#pragma unroll
-            for (int j = 0; j < BATCH; ++j) {
-                const int c0 = __shfl(cell[j], lane & 32, 64);              // cell of the block's first key
-                const int k = tid & 31, r0 = c0 / P.w, cl0 = c0 - r0 * P.w;
-                bool good = key[j] < P.S && c0 >= 0 && r0 + 6 < P.w && cl0 + 14 < P.w &&
-                            cell[j] == c0 + 2 * P.w * patch_rr(k) + 2 * patch_cc(k);
-                if (k == 0) {
-                    const uint32_t off = cell_bias_offsets(cell[j], P.w);
-                    good = good && (off & 7u) == 0 && ((off >> 16) & 15u) == 0;
-                }
-                ok = ok && good;
-            }
-        }
-        __syncthreads();
-        if (!ok) *flag = 0;
-        __syncthreads();
-        const bool patched = *flag != 0;
-        __syncthreads();                        // the flag's word is part of the K tile from here on
-        if (patched) {
-            attn_global_body<D, true>(P, qt, grp, head, inv_scale, smem);
-            return;
-        }
-    }
-    attn_global_body<D, false>(P, qt, grp, head, inv_scale, smem);
+    if constexpr (TRY_PATCH)
+        if (attn_patch_body<D>(P, qt, grp, head, inv_scale, smem)) return;
+    attn_global_body<D>(P, qt, grp, head, inv_scale, smem);
 }
 
 // CU count and LDS bytes per CU of the current device, asked once per device (host-side queries, no allocation)
@@ -946,10 +1226,14 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, float inv_
     } else {
         int T = ssam_div_up(P.S, GLB_TILE);
         size_t lds = global_lds_bytes<D>(P.w);
-        if (lds > ds.lds) return SSAM_EUNSUPPORTED;
         // a shared table on a power-of-two grid of 16 x 16 or more can be the position-only order whose blocks are
         // patches; the kernel checks every tile, so any table is still handled correctly
         const bool patch = P.sigma_stride == 0 && P.w >= 16 && (P.w & (P.w - 1)) == 0;
+        if (patch) {
+            const size_t need = patch_lds_bytes<D>(P.w, (P.n_pre < T ? P.n_pre + 1 : T) * (GLB_TILE / 32));
+            lds = need > lds ? need : lds;
+        }
+        if (lds > ds.lds) return SSAM_EUNSUPPORTED;
         auto kern = patch ? attn_global_kernel<D, true> : attn_global_kernel<D, false>;
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)

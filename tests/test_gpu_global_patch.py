@@ -1,0 +1,42 @@
+"""Global attention on power-of-two grids in the position-only order (pipelined path): the shortest and longest lists of key
+blocks, every head size, and logits that grow along the scan order, so that the exponent reference moves again and again
+while probabilities are still waiting for their product."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import announce, assert_close
+from paper_2605_17633_amd import binding as B
+from paper_2605_17633_amd import inputs
+from test_gpu_block import dev_bf16, dev_i32, run_attention_case, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("w,h,d,r", [(16, 2, 16, 0.3), (16, 1, 64, 0.6), (32, 3, 16, 0.1), (32, 1, 80, 0.1), (32, 1, 32, 1.0),
+                                     (32, 9, 64, 0.5), (64, 1, 80, 0.02), (128, 1, 16, 0.01), (128, 1, 80, 0.01)])
+def test_block_lists(w, h, d, r):
+    announce("global patch", w, h, d, r)
+    got, ref = run_attention_case(1, w, h, d, 128, r)
+    assert_close(got, ref, f"global attention w={w} d={d} r={r}")
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 80])
+@pytest.mark.parametrize("grow", [40.0, -40.0])
+def test_growing_logits(d, grow):
+    announce("global patch, growing logits", d, grow)
+    w, h, r = 32, 2, 0.5
+    S, rng = w * w, np.random.default_rng(d)
+    sigma, _ = oracle.grid_sigma(w, 4)
+    ramp = np.linspace(0.0, 1.0, S) if grow > 0 else np.linspace(1.0, 0.0, S)
+    q = np.abs(rng.normal(size=(S, h, d))) * 0.3 + 0.7
+    k = rng.normal(size=(S, h, d)) * 0.05 + (abs(grow) / np.sqrt(d)) * ramp[:, None, None]     # logits 0 .. about 40
+    v = rng.normal(size=(S, h, d))
+    scan = inputs.bf16_round(np.stack([q, k, v], 1).astype(np.float32))                         # [S,3,h,d], scan order
+    rel = [inputs.bf16_round(rng.normal(0, 0.1, size=(2 * w - 1, d)).astype(np.float32)) for _ in range(2)]
+    got = to_np(B.ssam_sparse_attention(dev_bf16(scan[None]), dev_bf16(rel[0]), dev_bf16(rel[1]), dev_i32(B.ssam_build_perm(w, w, 4)[0]),
+                                        w, 128, r)).reshape(S, h, d)
+    spatial = np.empty_like(scan)
+    spatial[sigma] = scan
+    o = oracle.attention(*(np.ascontiguousarray(spatial[:, i].transpose(1, 0, 2)) for i in range(3)), *rel, w, 4, 128, r)
+    assert_close(got, o.transpose(1, 0, 2)[sigma], f"growing logits d={d}")
