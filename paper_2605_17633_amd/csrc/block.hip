@@ -11,8 +11,8 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 
 int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int Nout, int N,
                        int32_t *real_slot, int32_t *real_spatial, int32_t *slot_row, int32_t *pad_slot, hipStream_t st);
-int ssam_fill_bias_rows(void *C, long ldc, const float *bias, int n_cols, const int32_t *pad_slot, int npad,
-                        int rows_per_batch, int B, hipStream_t st);
+int ssam_ln_gather_impl(const void *x, const int32_t *idx, int idx_batch_stride, const float *gamma, const float *beta, float eps, void *y,
+                        int B, int Nin, int Nout, int D, const PadFill &fill, void *stream);
 int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int Nout, int N, int32_t *inv, hipStream_t st);
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
                         void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st);
@@ -21,7 +21,7 @@ int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *s
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
                                void *split_ws, size_t split_ws_bytes, hipStream_t st);
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
-                       int Nin, int Nout, int32_t *src, hipStream_t st);
+                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st);
 
 namespace {
 
@@ -86,7 +86,8 @@ size_t block_tables_bytes(int B, const BlockGeom &g) { return pad_tables_bytes(B
 
 int32_t *slot_of_table(unsigned char *tables, int B, const BlockGeom &g) { return (int32_t *)(tables + pad_tables_bytes(B, g)); }
 
-int build_block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int32_t *gather_table, unsigned char *tables, hipStream_t st)
+// slots: some block folds its LayerNorm into the qkv contraction and reads slot_of (a launch of its own, 3 us of a small block)
+int build_block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int32_t *gather_table, unsigned char *tables, bool slots, hipStream_t st)
 {
     const int per_image = cfg->content_order != 0;
     if (g.Nout != g.N) {
@@ -94,6 +95,7 @@ int build_block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int3
         int rc = ssam_compact_slots(gather_table, per_image ? g.Nout : 0, cfg->B, g.Nout, g.N, pt.real_slot, pt.real_spatial, pt.slot_row, pt.pad_slot, st);
         if (rc != SSAM_OK) return rc;
     }
+    if (!slots) return SSAM_OK;
     return ssam_invert_table(gather_table, per_image ? g.Nout : 0, per_image ? cfg->B : 1, g.Nout, g.N, slot_of_table(tables, cfg->B, g), st);
 }
 
@@ -129,7 +131,7 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
         // the region of the normalised rows holds only their statistics and the rows of x they are (8 + 4 bytes a row)
         float *stats = (float *)a2;
         int32_t *src = (int32_t *)(stats + 2 * (size_t)B * K);
-        rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, st);
+        rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st);
         if (rc != SSAM_OK) return rc;
         rc = ssam_linear_fold_gelu_impl(x, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st);
     } else {
@@ -229,15 +231,22 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     if (kv_shift && (!fold || !w->bproj_folded)) return SSAM_EINVAL;
     const float *bproj = kv_shift ? w->bproj_folded : w->bproj;
     if (!tables_ready) {
-        rc = build_block_tables(cfg, g, gather_table, tables, st);
+        rc = build_block_tables(cfg, g, gather_table, tables, fold, st);
         if (rc != SSAM_OK) return rc;
     }
+    // The padding slots hold the qkv of a zero row: the bias, or, with the key and value biases taken out of the contraction,
+    // zeros in the columns attention reads (k, v), which then need writing only when something else has used the memory
+    // since.  The LayerNorm's launch writes them.
+    PadFill fill = {};
+    if (padded && !(kv_shift && pad_rows_zero && *pad_rows_zero))
+        fill = { (bf16 *)qkv, 3L * D, kv_shift ? nullptr : w->bqkv, 3 * D, carve_pad_tables(tables, B, g).pad_slot, g.Nout - g.N, g.Nout, B * (g.Nout - g.N) };
+    if (pad_rows_zero) *pad_rows_zero = padded && kv_shift;         // (an unpadded block's qkv tensor lies over the windowed blocks' one)
     if (fold) {
         // LN1 folded into the qkv contraction: only the statistics of every token are taken here (parked at the
         // start of u, which nothing else uses before attention writes its output there); the contraction reads
         // the tokens where they lie and stores every row to its scan-order slot
         float *stats = (float *)u;
-        rc = ssam_ln_stats(x, stats, crows, D, cfg->eps, stream);
+        rc = ssam_ln_stats_impl(x, stats, crows, D, cfg->eps, nullptr, 0, 0, 0, nullptr, fill, st);
         if (rc != SSAM_OK) return rc;
         if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
         GemmRowMap to_slot = { slot_of_table(tables, B, g), g.N, per_image ? g.N : 0, g.Nout };
@@ -246,7 +255,6 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     }
 
     if (!padded) {
-        if (pad_rows_zero) *pad_rows_zero = false;              // this block's qkv tensor lies over the windowed blocks' one
         if (!fold) {
             rc = ssam_ln_gather(x, gather_table, per_image ? g.Nout : 0, w->ln1_g, w->ln1_b, cfg->eps, u, B, g.N, g.Nout, D, stream);
             if (rc != SSAM_OK) return rc;
@@ -266,28 +274,16 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
         // Windows with padding: the padding slots are zero rows after LN1, so their qkv rows are the bias and
         // their attention outputs are dropped.  LN1 gathers the N real tokens of every image into a compact
         // [B*N][D] matrix in scan order, the qkv contraction runs on those rows and scatters them to their
-        // slots, the padding slots are filled with the bias, attention writes only the real queries (compact
+        // slots (the padding slots were filled above), attention writes only the real queries (compact
         // again), and the proj contraction scatters them back to spatial order.
         const PadTables pt = carve_pad_tables(tables, B, g);
         if (!fold) {
-            rc = ssam_ln_gather(x, pt.real_spatial, g.N, w->ln1_g, w->ln1_b, cfg->eps, u, B, g.N, g.N, D, stream);
+            rc = ssam_ln_gather_impl(x, pt.real_spatial, g.N, w->ln1_g, w->ln1_b, cfg->eps, u, B, g.N, g.N, D, fill, stream);
             if (rc != SSAM_OK) return rc;
             if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
             GemmRowMap to_slot = { pt.real_slot, g.N, g.N, g.Nout };
             rc = ssam_linear_impl(u, w->wqkv, w->bqkv, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, packed, SSAM_EPI_BIAS_SCATTER, to_slot, 0, split, GEMM_SPLIT_WS_BYTES, st);
             if (rc != SSAM_OK) return rc;
-        }
-        // the padding slots hold the qkv of a zero row: the bias, or, with the key and value biases taken out of
-        // the contraction, zeros in the columns attention reads (k, v), which then need writing only when something
-        // else has used the memory since
-        if (!kv_shift) {
-            rc = ssam_fill_bias_rows(qkv, 3L * D, w->bqkv, 3 * D, pt.pad_slot, g.Nout - g.N, g.Nout, B, st);
-            if (rc != SSAM_OK) return rc;
-            if (pad_rows_zero) *pad_rows_zero = false;
-        } else if (!pad_rows_zero || !*pad_rows_zero) {
-            rc = ssam_fill_bias_rows(qkv, 3L * D, nullptr, 3 * D, pt.pad_slot, g.Nout - g.N, g.Nout, B, st);
-            if (rc != SSAM_OK) return rc;
-            if (pad_rows_zero) *pad_rows_zero = true;
         }
         if (qkv_events && qkv_events[1] && hipEventRecord((hipEvent_t)qkv_events[1], st) != hipSuccess) return SSAM_EHIP;
         rc = ssam_sparse_attention(qp, qp + D, qp + 2 * D, 3L * D, w->rel_h, w->rel_w, sigma, per_image ? g.S : 0, u, pt.slot_row,
@@ -337,8 +333,11 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
                                     void *workspace, size_t workspace_bytes, void **qkv_events, void *stream)
 {
     if (!x || !weights || !is_global || n_blocks <= 0 || !scores || !keep_idx || !workspace) return SSAM_EINVAL;
-    bool any_local = false, any_global = false;
-    for (int i = 0; i < n_blocks; ++i) (is_global[i] ? any_global : any_local) = true;
+    bool any_local = false, any_global = false, slots_local = false, slots_global = false;
+    for (int i = 0; i < n_blocks; ++i) {
+        (is_global[i] ? any_global : any_local) = true;
+        if (weights[i].fold_ln1 != 0) (is_global[i] ? slots_global : slots_local) = true;
+    }
     if ((any_local && (!cfg_local || !window_table || !sigma_window)) ||
         (any_global && (!cfg_global || !global_table || !sigma_global)))
         return SSAM_EINVAL;
@@ -383,11 +382,11 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
     unsigned char *tables_local = (unsigned char *)workspace + core;
     unsigned char *tables_global = tables_local + (any_local ? block_tables_bytes(cfg_local->B, gl) : 0);
     if (any_local) {
-        rc = build_block_tables(cfg_local, gl, window_table, tables_local, (hipStream_t)stream);
+        rc = build_block_tables(cfg_local, gl, window_table, tables_local, slots_local, (hipStream_t)stream);
         if (rc != SSAM_OK) return rc;
     }
     if (any_global) {
-        rc = build_block_tables(cfg_global, gg, global_table, tables_global, (hipStream_t)stream);
+        rc = build_block_tables(cfg_global, gg, global_table, tables_global, slots_global, (hipStream_t)stream);
         if (rc != SSAM_OK) return rc;
     }
     bool pad_rows_zero = false;                 // the padding slots of the windowed blocks' qkv tensor hold zeros

@@ -24,6 +24,17 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");       \
     } while (0)
 
+// Rows of a windowed block's qkv tensor that hold no token (padding slots): rows_per_batch * b + pad_slot[b][i] of C, i < npad,
+// become bf16(bias) (NULL: zeros).  They are written by extra workgroups of the block's LayerNorm launch.
+struct PadFill {
+    bf16 *C;
+    long ldc;
+    const float *bias;
+    int n_cols;
+    const int32_t *pad_slot;
+    int npad, rows_per_batch, total_rows;      // total_rows = B * npad; 0: none
+};
+
 #define SSAM_CHECK_LAUNCH()                                   \
     do {                                                      \
         if (hipGetLastError() != hipSuccess) return SSAM_EHIP; \

@@ -51,6 +51,25 @@ unpermute_kernel(const uint4 *__restrict__ y, const int32_t *__restrict__ idx, u
     }
 }
 
+// one padding row (see PadFill): a wave, 16 bytes per lane.  A launch of its own took 5 us of every unfolded block with padding
+// (ViT-B, 50 x 50 tokens, batch 2) and after every global block of a folded stack; behind the LayerNorm it is hidden.
+__device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
+{
+    if (r >= f.total_rows) return;
+    const int b = r / f.npad, i = r - b * f.npad, lane = threadIdx.x & 63;
+    bf16 *dst = f.C + ((long)b * f.rows_per_batch + f.pad_slot[(long)b * f.npad + i]) * f.ldc;
+    for (int c = lane * 8; c < f.n_cols; c += 64 * 8) {
+        if (f.bias == nullptr) {
+            *reinterpret_cast<uint4 *>(dst + c) = make_uint4(0, 0, 0, 0);
+            continue;
+        }
+        const float4 *b4 = reinterpret_cast<const float4 *>(f.bias + c);
+        float4 x0 = b4[0], x1 = b4[1];
+        float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
+        *reinterpret_cast<uint4 *>(dst + c) = pack_bf16x8(v);
+    }
+}
+
 // ---------------------------------------------------------------- LN + gather
 // One wave per output row; the row lives in registers (MAXC 16-byte chunks per
 // lane), two-pass statistics in fp32.
@@ -58,10 +77,14 @@ template <int MAXC>
 __global__ void __launch_bounds__(256)
 ln_gather_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx, int idx_batch_stride,
                  const float *__restrict__ gamma, const float *__restrict__ beta, float eps,
-                 uint4 *__restrict__ y, int B, int Nin, int Nout, int chunks)
+                 uint4 *__restrict__ y, int B, int Nin, int Nout, int chunks, PadFill fill, int ln_blocks)
 {
     int lane = threadIdx.x & 63;
     long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if ((int)blockIdx.x >= ln_blocks) {
+        fill_pad_row(fill, ((int)blockIdx.x - ln_blocks) * 4 + (threadIdx.x >> 6));
+        return;
+    }
     if (row >= (long)B * Nout) return;
     int p = (int)(row % Nout), b = (int)(row / Nout);
     int src = idx[(long)b * idx_batch_stride + p];
@@ -134,10 +157,15 @@ ln_gather_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx, i
 template <int MAXC>
 __global__ void __launch_bounds__(256)
 ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long rows, int chunks, float eps,
-                const int32_t *__restrict__ idx, int idx_batch_stride, int Nin, int Nout, int32_t *__restrict__ src)
+                const int32_t *__restrict__ idx, int idx_batch_stride, int Nin, int Nout, int32_t *__restrict__ src,
+                PadFill fill, int ln_blocks)
 {
     int lane = threadIdx.x & 63;
     long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if ((int)blockIdx.x >= ln_blocks) {
+        fill_pad_row(fill, ((int)blockIdx.x - ln_blocks) * 4 + (threadIdx.x >> 6));
+        return;
+    }
     if (row >= rows) return;
     long xr = row;
     if (idx) {
@@ -469,27 +497,6 @@ compact_slots_kernel(const int32_t *__restrict__ table, int table_batch_stride, 
     }
 }
 
-// rows[b*rows_per_batch + pad_slot[b][i]] = bf16(bias) (bias == nullptr: zeros): one wave per row, 16 bytes per lane
-__global__ void __launch_bounds__(256)
-fill_bias_rows_kernel(bf16 *__restrict__ C, long ldc, const float *__restrict__ bias, int n_cols,
-                      const int32_t *__restrict__ pad_slot, int npad, int rows_per_batch, int total_rows)
-{
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (r >= total_rows) return;
-    const int b = r / npad, i = r - b * npad;
-    bf16 *dst = C + ((long)b * rows_per_batch + pad_slot[(long)b * npad + i]) * ldc;
-    for (int c = lane * 8; c < n_cols; c += 64 * 8) {
-        if (bias == nullptr) {
-            *reinterpret_cast<uint4 *>(dst + c) = make_uint4(0, 0, 0, 0);
-            continue;
-        }
-        const float4 *b4 = reinterpret_cast<const float4 *>(bias + c);
-        float4 x0 = b4[0], x1 = b4[1];
-        float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
-        *reinterpret_cast<uint4 *>(dst + c) = pack_bf16x8(v);
-    }
-}
-
 // ---------------------------------------------------------------- content-aware order
 // The cells of an attention group are ranked by (score descending, cell index ascending; padding cells last), then the
 // stripe interleave sigma[g*(S/G)+t] = pi[t*G+g] (Sec. 4.1) places rank t*G+g at scan position g*(S/G)+t.
@@ -607,28 +614,37 @@ extern "C" int ssam_unpermute(const void *y, const int32_t *idx, void *x, const 
     return SSAM_OK;
 }
 
-extern "C" int ssam_ln_gather(const void *x, const int32_t *idx, int idx_batch_stride,
+// fill: padding rows written by the same launch
+int ssam_ln_gather_impl(const void *x, const int32_t *idx, int idx_batch_stride,
                               const float *gamma, const float *beta, float eps, void *y,
-                              int B, int Nin, int Nout, int D, void *stream)
+                              int B, int Nin, int Nout, int D, const PadFill &fill, void *stream)
 {
     if (!movers_args_ok(x, idx, y, B, Nin, Nout, D) || !gamma || !beta || idx_batch_stride < 0) return SSAM_EINVAL;
     if (!ssam_aligned16(gamma) || !ssam_aligned16(beta)) return SSAM_EINVAL;
     if (D > 2048) return SSAM_EUNSUPPORTED;
     int chunks = D / 8;
     long rows = (long)B * Nout;
-    dim3 grid(ssam_div_up(rows, 4)), block(256);
+    const int ln_blocks = ssam_div_up(rows, 4);
+    dim3 grid(ln_blocks + ssam_div_up(fill.total_rows, 4)), block(256);
     hipStream_t st = (hipStream_t)stream;
     if (chunks <= 128)
         hipLaunchKernelGGL(ln_gather_kernel<2>, grid, block, 0, st, (const uint4 *)x, idx, idx_batch_stride,
-                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks);
+                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks, fill, ln_blocks);
     else if (chunks <= 192)
         hipLaunchKernelGGL(ln_gather_kernel<3>, grid, block, 0, st, (const uint4 *)x, idx, idx_batch_stride,
-                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks);
+                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks, fill, ln_blocks);
     else
         hipLaunchKernelGGL(ln_gather_kernel<4>, grid, block, 0, st, (const uint4 *)x, idx, idx_batch_stride,
-                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks);
+                           gamma, beta, eps, (uint4 *)y, B, Nin, Nout, chunks, fill, ln_blocks);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
+}
+
+extern "C" int ssam_ln_gather(const void *x, const int32_t *idx, int idx_batch_stride,
+                              const float *gamma, const float *beta, float eps, void *y,
+                              int B, int Nin, int Nout, int D, void *stream)
+{
+    return ssam_ln_gather_impl(x, idx, idx_batch_stride, gamma, beta, eps, y, B, Nin, Nout, D, PadFill{}, stream);
 }
 
 extern "C" size_t ssam_score_tokens_workspace_bytes(int B, int gh, int gw)
@@ -752,7 +768,7 @@ extern "C" int ssam_build_content_tables(const float *scores, int B, int g, int 
     return SSAM_OK;
 }
 
-// internal (block composition): see compact_slots_kernel / fill_bias_rows_kernel
+// internal (block composition): see compact_slots_kernel
 int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int Nout, int N,
                        int32_t *real_slot, int32_t *real_spatial, int32_t *slot_row, int32_t *pad_slot, hipStream_t st)
 {
@@ -762,40 +778,30 @@ int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int 
     return SSAM_OK;
 }
 
-int ssam_fill_bias_rows(void *C, long ldc, const float *bias, int n_cols, const int32_t *pad_slot, int npad,
-                        int rows_per_batch, int B, hipStream_t st)
-{
-    const int total = B * npad;
-    if (total <= 0) return SSAM_OK;
-    hipLaunchKernelGGL(fill_bias_rows_kernel, dim3(ssam_div_up(total, 4)), dim3(256), 0, st, (bf16 *)C, ldc, bias, n_cols,
-                       pad_slot, npad, rows_per_batch, total);
-    SSAM_CHECK_LAUNCH();
-    return SSAM_OK;
-}
-
 // statistics of rows idx[b][p] of image b (idx == NULL: of every row in order), see ln_stats_kernel
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
-                       int Nin, int Nout, int32_t *src, hipStream_t st)
+                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st)
 {
     if (!x || !stats || rows <= 0 || D <= 0 || D % 8 != 0) return SSAM_EINVAL;
     if (!ssam_aligned16(x) || ((uintptr_t)stats & 7)) return SSAM_EINVAL;
     if (idx && (!src || Nin <= 0 || Nout <= 0 || (long)(rows / Nout) * Nin > 0x7fffffffL)) return SSAM_EINVAL;
     if (D > 2048) return SSAM_EUNSUPPORTED;
     int chunks = D / 8;
-    dim3 grid((unsigned)ssam_div_up(rows, 4)), block(256);
+    const int ln_blocks = ssam_div_up(rows, 4);
+    dim3 grid((unsigned)(ln_blocks + ssam_div_up(fill.total_rows, 4))), block(256);
     if (chunks <= 128)
-        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src);
+        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
     else if (chunks <= 192)
-        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src);
+        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
     else
-        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src);
+        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
 
 extern "C" int ssam_ln_stats(const void *x, float *stats, long rows, int D, float eps, void *stream)
 {
-    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, (hipStream_t)stream);
+    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, PadFill{}, (hipStream_t)stream);
 }
 
 extern "C" int ssam_fold_ln_weight(const void *W, int ldw, const float *bias, const float *gamma, const float *beta,
