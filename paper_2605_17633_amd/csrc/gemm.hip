@@ -1,4 +1,5 @@
 // Dispatcher of the bf16 NT GEMM (qkv / proj / fc1 / fc2 of the SAM block).
+#include "gemm_direct.h"
 #include "gemm_ring.h"
 
 namespace {
@@ -200,10 +201,12 @@ constexpr RingTile ring_tiles[3] = { { 128, 128, 2, 4.9, { 0.66, 0.95, 0. } },
                                      { 128, 64, 3, 3.5, { 0.56, 0.67, 0.95 } },
                                      { 64, 64, 3, 3.2, { 0.28, 0.40, 0.61 } } };
 
-// Index of the ring tile that is faster than the large tiles (launch_us), or -1.  On the 290 shapes the choice is 1-2 % on
+constexpr int RING_DIRECT = 3;
+
+// Index of the ring tile (or RING_DIRECT) that is faster than the large tiles (launch_us), or -1.  On the 290 shapes the choice is 1-2 % on
 // average from the faster of the two (the large tiles alone: 20 % with packed, 32 % with row-major weights), and the ring is
 // taken where it is slower on 7, by up to 7 %.
-int pick_ring(int M, int N, int K, double launch_us)
+int pick_ring(int M, int N, int K, bool packed, double launch_us)
 {
     const int nk = ssam_div_up(K, GEMM_BK);
     int best = -1;
@@ -215,6 +218,8 @@ int pick_ring(int M, int N, int K, double launch_us)
         const double us = t.t0 + nk * t.t_slab[ssam_div_up(tiles, 256) - 1];
         if (us < best_us) { best_us = us; best = i; }
     }
+    // gemm_direct.h: at most one tile per CU; fitted to K 768 to 5120 as the rings
+    if (packed && (long)ssam_div_up(M, 32) * (N / 32) <= 256 && 3.3 + nk * 0.16 < best_us) best = RING_DIRECT;
     return best;
 }
 
@@ -236,6 +241,13 @@ template <int EPI, bool WPACK, bool LNF = false>
 int launch_ring(int ring, const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
                 const GemmLd &ld, const GemmRowMap &rm, const GemmFold &fold, hipStream_t st)
 {
+    if constexpr (WPACK) if (ring == RING_DIRECT) {
+        GemmTileRange tr = { ssam_div_up(M, 32), N / 32, 0, 0 };
+        tr.tile_count = tr.tiles_m * tr.tiles_n;
+        hipLaunchKernelGGL((gemm_direct_kernel<EPI, LNF>), dim3(ssam_div_up(tr.tile_count, 8) * 8), dim3(256), 0, st, A, W, bias, C, M, N, K, ld, tr, rm, fold);
+        SSAM_CHECK_LAUNCH();
+        return SSAM_OK;
+    }
     switch (ring) {
     case 0: return launch_ring_tile<128, 128, 2, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, rm, fold, st);
     case 1: return launch_ring_tile<128, 64, 2, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, rm, fold, st);
@@ -265,7 +277,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
     if (tile == 0) {
         double us;
         tile = pick_tile(M, N, K, epilogue, ws, packed, us);
-        ring = pick_ring(M, N, K, us);
+        ring = pick_ring(M, N, K, packed, us);
     }
     if (packed) {
         switch (epilogue) {
@@ -296,7 +308,7 @@ int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *s
     const GemmRowMap none = { nullptr, 1, 0, 1 };
     double us;
     const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
-    if (const int ring = pick_ring(M, N, K, us); ring >= 0)
+    if (const int ring = pick_ring(M, N, K, true, us); ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
     return launch_tile_packed<SSAM_EPI_BIAS_GELU, true>(tile, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld,
                                                         none, ws, st, fold);
@@ -315,7 +327,7 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     const double round = (K / GEMM_BK) * 1.71 + 5.5;
     const int last = tr.tile_count % 512;
     const double us = large_tile_us((tr.tile_count / 512) * round + (last == 0 ? 0.0 : last <= 256 ? 0.62 * round : round), true);
-    if (const int ring = pick_ring(M, N, K, us); ring >= 0)
+    if (const int ring = pick_ring(M, N, K, true, us); ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
     const int per_xcd = ssam_div_up(tr.tile_count, 8);
     hipLaunchKernelGGL((gemm_bf16_nt_lnf_kernel<128, 256, SSAM_EPI_BIAS_SCATTER, 1, 4>), dim3(per_xcd * 8), dim3(256), lds, st,

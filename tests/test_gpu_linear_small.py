@@ -1,5 +1,5 @@
-"""The contraction on problems of at most one round of small workgroups (tile chosen by the library): edges of the 64x64, 128x64
-and 128x128 tiles, one to three slabs of K and ragged ones, every epilogue, both weight layouts, the folded LayerNorm."""
+"""The contraction on problems of at most one round of small workgroups (tile chosen by the library): edges of the 32x32, 64x64,
+128x64 and 128x128 tiles, one to three slabs of K and ragged ones, every epilogue, both weight layouts, the folded LayerNorm."""
 import numpy as np
 import pytest
 import torch
@@ -21,7 +21,8 @@ def _operands(M, N, K):
 
 @pytest.mark.parametrize("epi", [0, 1, 2, 3])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (64, 64, 64), (65, 72, 136), (63, 56, 200), (129, 200, 192), (784, 768, 768),
-                                   (1640, 776, 328), (1638, 1536, 384), (3001, 1544, 128), (2500, 3064, 136), (2433, 3072, 128)])
+                                   (1640, 776, 328), (1638, 1536, 384), (3001, 1544, 128), (2500, 3064, 136), (2433, 3072, 128),
+                                   (31, 128, 64), (33, 256, 128), (313, 768, 1536), (97, 2048, 192)])
 @pytest.mark.parametrize("packed", [False, True])
 def test_small_problems(M, N, K, epi, packed):
     """Element-wise within one bf16 rounding of the result and the fp32 summation error of a dot product of unit-variance terms."""
