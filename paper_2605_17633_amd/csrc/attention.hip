@@ -98,14 +98,24 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 }
 
 // Bias table of the wave's 32 queries in the global kernel, query-major, fp16 (see GlbTab), divided by the softmax
-// scale so that (score + row entry + column entry) * scale * log2e is the logit in log2 units:
-//   tq[q*tstr + (p&1)*hw + (p>>1)]            = q . rel_h[row(q)-p+w-1] / scale      (p = key row)
-//   tq[q*tstr + 2*hw + (p&1)*hw + (p>>1)]     = q . rel_w[col(q)-p+w-1] / scale      (p = key column)
-// hw = ceil(w/2): even and odd rows (columns) are stored apart, so that rows two apart are neighbours: the 32-key
+// scale so that (score + row entry + column entry) * scale * log2e is the logit in log2 units.  General path:
+//   tq[q*tstr + p]                            = q . rel_h[row(q)-p+w-1] / scale      (p = key row)
+//   tq[q*tstr + wk + p]                       = q . rel_w[col(q)-p+w-1] / scale      (p = key column)
+// Up to w = 64 wk is w rounded up to whole 16-entry operands (32 or 64), the entries past w zero, and tstr = 2*wk + 8: the 16 bytes
+// of padding put the operand reads of 16 lanes on distinct banks.  Above, where entries are looked up one by one, wk is w
+// rounded up to even and tstr = 2*wk + 4: 8 bytes of padding put the 32 lanes of a look-up (one entry, 32 queries) on
+// distinct banks.  Patch path (w a power of two):
+//   tq[q*tstr + (p&1)*hw + (p>>1)]            row entries,    tq[q*tstr + 2*hw + (p&1)*hw + (p>>1)]   column entries
+// hw = w/2: even and odd rows (columns) are stored apart, so that rows two apart are neighbours: the 32-key
 // blocks of the position-only Stripe-Sort order are 4 x 8 patches of stride 2 (see attn_patch_body), whose 4 row
 // and 8 column entries are then contiguous.  tstr = 4*hw + 4: the 8 bytes of padding put the 32 lanes of a look-up
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
 __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; }
+// Entries per table of the operand form, 0: look-ups.  Two images of 50 x 50, d = 80: 111 us by look-up, 88 by operand; of
+// 72 x 72, where the operand form takes 96 or 128 entries and its table a second workgroup's LDS: d = 64 264 against 434, d = 80 428 against 500.
+__host__ __device__ inline int glb_operand(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 0; }
+__host__ __device__ inline int glb_wk(int w) { return glb_operand(w) ? glb_operand(w) : (w + 1) & ~1; }
+__host__ __device__ inline int glb_general_tstr(int w) { return 2 * glb_wk(w) + (glb_operand(w) ? 8 : 4); }
 
 template <int D, typename TabT>
 __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *rel_h, const bf16 *rel_w, int rstr,
@@ -113,7 +123,8 @@ __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *re
 {
     constexpr int KS = AttnCfg<D>::KS;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    const int nrel = 2 * w - 1, hw = (w + 1) >> 1;
+    const int nrel = 2 * w - 1, wk = glb_wk(w);
+    for (int p = w + half; p < wk; p += 2) tq_lane[p] = tq_lane[wk + p] = (TabT)0.f;      // (the two half-waves share a query)
     // operand a of slab mt: rows mt*32 + l32 of both tables; rows past the table re-read its last row (their
     // products are never stored), so every load is unconditional and a slab's 2*KS loads are in flight together
     bf16x8 cur[2][KS], nxt[2][KS];
@@ -140,13 +151,13 @@ __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *re
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // MFMA passes done before u is read under predicates
             __builtin_amdgcn_sched_barrier(0);
-            TabT *dst = tq_lane + (tab ? 2 * hw : 0);
-            const int qpos = tab ? qcol : qrow;
+            // entry of relative position m = mt*32 + 8*(r>>2) + 4*half + (r&3); positions past the table (m > 2w-2) would be negative ones
+            const int p0 = (tab ? qcol : qrow) + (w - 1) - mt * 32 - 4 * half;
+            TabT *dst = tq_lane + (tab ? wk : 0) + p0;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                int m = mt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                int p = qpos + (w - 1) - m;
-                if (p >= 0 && p < w && m < nrel) dst[(p & 1) * hw + (p >> 1)] = (TabT)(u[r] * inv_scale);
+                const int d = 8 * (r >> 2) + (r & 3);
+                if ((unsigned)(p0 - d) < (unsigned)w) dst[-d] = (TabT)(u[r] * inv_scale);
             }
         }
 #pragma unroll
@@ -353,6 +364,65 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ int patch_rr(int k) { return ((k >> 1) & 1) | ((k >> 2) & 2); }
 __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2) | ((k >> 2) & 4); }
 
+// Scores of a chunk in any order, with the decomposed bias as a product too: B[k][q] = sum_p E[k][p] T[p][q], where E has a one at
+// the key's row and a one at its column and T is the query's table row, WK entries each: 2 * WK / 16 more MFMAs per block
+// (fp16 operands, the same fp32 accumulator, issued first).  A lane makes its part of E from its key's row and column in
+// registers.  Two look-ups per score instead cost 32 LDS reads and 80 vector instructions per block.  One launch of 2
+// images, 50 x 50, 12 heads, d = 64, r = 0.5: 78 -> 63 us.
+template <int D, int NB, bool RAGGED, int WK>
+__device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
+                                                       const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB],
+                                                       int S, float scale_log2e, const _Float16 *tq_lane)
+{
+    using C = AttnCfg<D>;
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    f32x16 s[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        // the table operands are the same for every block: read again all the same (kept in registers they spill at d = 80)
+        uint32_t fresh = 0;
+        asm volatile("" : "+v"(fresh));
+        const uint32_t rc = krc[blk[b] * 32 + l32];               // row | column << 16
+        s[b] = f32x16{ 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
+#pragma unroll
+        for (int tab = 0; tab < 2; ++tab) {
+            // the one's place among 8 consecutive entries (two per register), and which such group it is in
+            const uint32_t at = tab ? rc >> 16 : rc & 0xffffu, one = (at & 1u) ? 0x3c000000u : 0x3c00u;
+            u32x4 e;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[j] = ((at >> 1) & 3u) == (uint32_t)j ? one : 0u;
+#pragma unroll
+            for (int ks = 0; ks < WK / 16; ++ks) {
+                const bool here = (at >> 3) == (uint32_t)(2 * ks + half);
+                u32x4 a;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j] = here ? e[j] : 0u;
+                const f16x8 t = *reinterpret_cast<const f16x8 *>(tq_lane + fresh + tab * WK + ks * 16 + half * 8);
+                s[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), t, s[b], 0, 0, 0);
+            }
+        }
+        const bf16 *kblk = Ks + blk[b] * 32 * C::KSTR + l32 * C::KSTR + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks) {
+            bf16x8 a = *reinterpret_cast<const bf16x8 *>(kblk + ks * 16);
+            s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[b], 0, 0, 0);
+        }
+        if constexpr (D > 64) __builtin_amdgcn_sched_barrier(0);       // one block's operands at a time: both at once spill
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // MFMA passes done before the scores are read (as in attn_chunk_step)
+    __builtin_amdgcn_sched_barrier(0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (RAGGED) s[b][r] = key0[b] + 8 * (r >> 2) + 4 * half + (r & 3) < S ? s[b][r] : -INFINITY;
+            mx = fmaxf(mx, s[b][r]);
+        }
+    attn_softmax_pv<D, NB, true, true>(st, s, mx, Vs, blk, NB, scale_log2e);
+}
+
 template <int D, int NB, typename TabT>
 __device__ __forceinline__ void attn_chunk(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
                                            const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB], int nb,
@@ -431,15 +501,6 @@ __device__ __forceinline__ uint32_t cell_row_col(int cell, int w)
 __device__ __forceinline__ uint32_t key_row_col(const int32_t *sigma, int p, int S, int w)
 {
     return cell_row_col(sigma[p < S ? p : S - 1], w);
-}
-
-// byte offsets of a cell's two entries within a query's row of the global kernel's bias table (row part in the low
-// half, column part in the high half; see build_bias_rows)
-__device__ __forceinline__ uint32_t cell_bias_offsets(int cell, int w)
-{
-    const uint32_t rc = cell_row_col(cell, w), esz = sizeof(_Float16);
-    const uint32_t hw = (uint32_t)(w + 1) >> 1, row = rc & 0xffffu, col = rc >> 16;
-    return (esz * ((row & 1) * hw + (row >> 1))) | ((esz * (2 * hw + (col & 1) * hw + (col >> 1))) << 16);
 }
 
 // window kernel: byte offsets of the key's entries within a query's two table rows, less the query's own part
@@ -655,9 +716,6 @@ attn_window_kernel(AttnParams P, int n_groups)
 
 // ------------------------------------------------------------------ global kernel
 constexpr int GLB_TILE = 128;
-// key blocks per softmax chunk: the register budget of two waves per SIMD allows 2 at d = 80 and 4 up to d = 64
-// (the chunk step specialised for full chunks spills in this kernel at either size)
-template <int D> constexpr int glb_nb() { return D <= 64 ? 4 : 2; }
 // Bias rows of the global kernel are held as fp16 (11 significant bits on log2e * q.r, below the bf16
 // rounding of the probabilities that feed the second product): at w = 64 that brings a workgroup to
 // 78 KB of LDS, so two workgroups share a CU and one hides the other's LDS, MFMA and barrier latency.
@@ -667,7 +725,7 @@ template <int D>
 size_t global_lds_bytes(int w)
 {
     // K and V tile, the four waves' bias tables, per key (or per block) table offsets
-    return (size_t)2 * GLB_TILE * AttnCfg<D>::KSTR * 2 + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w)) + (size_t)GLB_TILE * 4;
+    return (size_t)2 * GLB_TILE * AttnCfg<D>::KSTR * 2 + (size_t)4 * wave_scratch_bytes<D>(glb_general_tstr(w)) + (size_t)GLB_TILE * 4;
 }
 
 // ---- patch path
@@ -1056,14 +1114,15 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     return true;
 }
 
-// The general path of a workgroup: per-key table look-ups, any order, any S.
-template <int D>
+// The general path of a workgroup: any order, any S (attn_chunk_step_onehot).  WK: see build_bias_rows' table; NB: key
+// blocks per softmax chunk, as many as the register budget of two waves per SIMD allows.
+template <int D, int WK, int NB>
 __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, int grp, int head, float inv_scale, unsigned char *smem)
 {
     using C = AttnCfg<D>;
     constexpr int LOADS = GLB_TILE * C::CH / 256;       // 16-byte chunks per thread per operand
     static_assert(GLB_TILE * C::CH % 256 == 0, "tile chunks must divide over the workgroup");
-    const int tstr = glb_tstr(P.w);
+    const int wk = WK ? WK : glb_wk(P.w), tstr = 2 * wk + (WK ? 8 : 4);
     bf16 *Ks = reinterpret_cast<bf16 *>(smem);
     bf16 *Vs = Ks + GLB_TILE * C::KSTR;
     unsigned char *Tb = reinterpret_cast<unsigned char *>(Vs + GLB_TILE * C::KSTR);
@@ -1080,15 +1139,9 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
     load_q_frags<D>(qf, P.q + base + (long)qclamp * P.row_stride);
     const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
     const uint32_t qrc = key_row_col(sg, qclamp, S, P.w);
-    long my_row = -1;                             // output row of this lane's query
-    if (qpos < S) {
-        my_row = (long)grp * S + qpos;
-        if (P.out_rows) my_row = P.out_rows[my_row];
-    }
     GlbTab *tq = reinterpret_cast<GlbTab *>(Tb + wave * wsb);
     GlbTab *tq_lane = tq + l32 * tstr;            // this lane's query row of the wave's bias table
 
-    constexpr int NB = glb_nb<D>();
     const int nact = P.n_pre + (qt >= P.n_pre ? 1 : 0);
     u32x4 rk[LOADS], rv[LOADS];
     int rcell = 0;
@@ -1123,7 +1176,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
             *reinterpret_cast<u32x4 *>(Ks + key * C::KSTR + c * 8) = rk[i];                             \
             *reinterpret_cast<u32x4 *>(Vs + key * C::KSTR + c * 8) = rv[i];                             \
         }                                                                                               \
-        if (tid < GLB_TILE) krc[tid] = cell_bias_offsets(rcell, P.w);                                   \
+        if (tid < GLB_TILE) krc[tid] = WK ? cell_row_col(rcell, P.w) : 2 * cell_row_col(rcell, P.w) + ((uint32_t)wk << 17); \
     }
 
     ATTN_LOAD_TILE(0 < P.n_pre ? 0 : qt, 3)       // in flight while the bias rows are formed
@@ -1141,22 +1194,30 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
         if (a + 1 < nact) ATTN_LOAD_TILE(kt_next, NB < GLB_TILE / 32 ? 1 : 3)     // one step per tile: nothing to put V between
         // the softmax / MFMA phase goes ahead of the other workgroup's tile traffic (loads, LDS stores, barriers)
         __builtin_amdgcn_s_setprio(1);
-        const int nblk = min(GLB_TILE / 32, (S - kt * GLB_TILE + 31) / 32);     // blocks wholly past the end are skipped
+        const int nblk = min(GLB_TILE / 32, (S - kt * GLB_TILE + 31) / 32);     // blocks wholly past the end are skipped ...
 #pragma unroll
         for (int c0 = 0; c0 < GLB_TILE / 32; c0 += NB) {
             if (c0 >= nblk) break;
             int blk[NB], key0[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b) { blk[b] = c0 + b; key0[b] = kt * GLB_TILE + 32 * (c0 + b); }
-            const int nb = min(NB, nblk - c0);
-            const bool ragged = key0[NB - 1] + 32 > S;
-            if (ragged)
-                attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
-            else
-                attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+            const bool ragged = key0[NB - 1] + 32 > S;                          // ... but for one in a chunk with a block that is not: masked
+            if constexpr (WK != 0) {
+                if (ragged) attn_chunk_step_onehot<D, NB, true, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane);
+                else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane);
+            } else {
+                const int nb = min(NB, nblk - c0);
+                if (ragged) attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+                else attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+            }
             if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
         }
         __builtin_amdgcn_s_setprio(0);
+    }
+    long my_row = -1;                             // output row of this lane's query (not looked up before: no registers)
+    if (qpos < S) {
+        my_row = (long)grp * S + qpos;
+        if (P.out_rows) my_row = P.out_rows[my_row];
     }
     finish_and_store<D>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
 #undef ATTN_LOAD_TILE
@@ -1165,7 +1226,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 
 // TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid (attn_patch_body, and the general
 // path where a block is not a patch).  !TRY_PATCH: the general path only.
-template <int D, bool TRY_PATCH>
+template <int D, bool TRY_PATCH, int WK>
 __global__ void __launch_bounds__(256, 2)
 attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
 {
@@ -1177,7 +1238,7 @@ attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
     const int grp = gh / P.h, head = gh % P.h;
     if constexpr (TRY_PATCH)
         if (attn_patch_body<D>(P, qt, grp, head, inv_scale, smem)) return;
-    attn_global_body<D>(P, qt, grp, head, inv_scale, smem);
+    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : WK != 0 && TRY_PATCH && D > 64 ? 1 : 2)>(P, qt, grp, head, inv_scale, smem);
 }
 
 // CU count and LDS bytes per CU of the current device, asked once per device (host-side queries, no allocation)
@@ -1234,7 +1295,10 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, float inv_
             lds = need > lds ? need : lds;
         }
         if (lds > ds.lds) return SSAM_EUNSUPPORTED;
-        auto kern = patch ? attn_global_kernel<D, true> : attn_global_kernel<D, false>;
+        const int wk = glb_operand(P.w);
+        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, 32> : attn_global_kernel<D, false, 32>)
+                  : wk == 64 ? (patch ? attn_global_kernel<D, true, 64> : attn_global_kernel<D, false, 64>)
+                             : (patch ? attn_global_kernel<D, true, 0> : attn_global_kernel<D, false, 0>);
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return SSAM_EHIP;

@@ -21,6 +21,15 @@ def test_block_lists(w, h, d, r):
     assert_close(got, ref, f"global attention w={w} d={d} r={r}")
 
 
+@pytest.mark.parametrize("w,h,d,r", [(17, 1, 80, 0.5), (31, 1, 64, 0.2), (33, 2, 80, 0.3), (63, 1, 16, 0.1), (63, 1, 80, 0.02), (65, 1, 64, 0.05),
+                                     (72, 1, 80, 0.03), (127, 1, 16, 0.01)])
+def test_any_grid(w, h, d, r):
+    """Sides around 32 and 64, where the bias table changes from 32 to 64 entries and to look-ups, ragged last tiles."""
+    announce("global general", w, h, d, r)
+    got, ref = run_attention_case(1, w, h, d, 128, r, G=1)
+    assert_close(got, ref, f"global attention w={w} d={d} r={r}")
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 80])
 @pytest.mark.parametrize("grow", [40.0, -40.0])
 def test_growing_logits(d, grow):
