@@ -368,7 +368,7 @@ __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2)
 // the key's row and a one at its column and T is the query's table row, WK entries each: 2 * WK / 16 more MFMAs per block
 // (fp16 operands, the same fp32 accumulator, issued first).  A lane makes its part of E from its key's row and column in
 // registers.  Two look-ups per score instead cost 32 LDS reads and 80 vector instructions per block.  One launch of 2
-// images, 50 x 50, 12 heads, d = 64, r = 0.5: 78 -> 63 us.
+// images, 50 x 50, 12 heads, d = 64, r = 0.5: 78 -> 67 us.
 template <int D, int NB, bool RAGGED, int WK>
 __device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
                                                        const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB],
