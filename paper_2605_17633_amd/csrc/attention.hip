@@ -54,6 +54,8 @@ struct AttnParams {
     const int32_t *out_rows;   // NULL: query p of group g goes to output row g*S+p; else to out_rows[g*S+p] (-1: dropped)
     int S, w, h, n_pre;
     float scale_log2e;
+    uint32_t half_one;      // global kernel's products with the bias table (see bias_shift): their one in fp16,
+    float table_inv;        // and what turns a bias into an entry
 };
 
 template <int D>
@@ -110,6 +112,22 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 // blocks of the position-only Stripe-Sort order are 4 x 8 patches of stride 2 (see attn_patch_body), whose 4 row
 // and 8 column entries are then contiguous.  tstr = 4*hw + 4: the 8 bytes of padding put the 32 lanes of a look-up
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
+//
+// Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_chunk_step_onehot, PatchPipe) every entry
+// meets every key, most of them as a zero, and an infinity would make NaNs of the query's whole row.  So there
+//   * entries past the range of fp16 become +-65504 (clamp_fp16), which as a logit is 65504 * scale, and
+//   * with a small scale the table is 2^shift times smaller and the ones of that matrix are 2^shift: shift is the least that
+//     puts 65504 * 2^shift * scale past 128 (bias_shift), since exp(-128) is the "no weight" that such a bias asks for.
+// Look-ups take infinities as they are: -inf gives the keys it belongs to no weight and leaves the others alone.
+inline int bias_shift(float scale)
+{
+    int n = 0;
+    while (n < 15 && ldexpf(65504.f * scale, n) < 128.f) ++n;
+    return n;
+}
+// bit 23 of the mode register: fp16 results past the range are clamped instead of rounded to infinity
+__device__ __forceinline__ void clamp_fp16(bool on) { __builtin_amdgcn_s_setreg(1 | 23 << 6 | (1 - 1) << 11, on); }
+
 __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; }
 // Entries per table of the operand form, 0: look-ups.  Two images of 50 x 50, d = 80: 111 us by look-up, 88 by operand; of
 // 72 x 72, where the operand form takes 96 or 128 entries and its table a second workgroup's LDS: d = 64 264 against 434, d = 80 428 against 500.
@@ -219,7 +237,8 @@ constexpr float ATTN_LAG = 8.f;
 
 // Second half of a chunk step, the same for every way of forming the scores: s holds the chunk's logits (RAW: before
 // the multiplication by scale_log2e), mx their maximum over this lane's keys, in the same units.
-template <int D, int NB, bool FULL, bool RAW>
+// MASKED: all logits of a chunk may be -inf: a query that has met no other key yet takes 0 as its reference.
+template <int D, int NB, bool FULL, bool RAW, bool MASKED = false>
 __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB], float mx, const bf16 *Vs,
                                                 const int (&blk)[NB], int nb_, float scale_log2e)
 {
@@ -235,7 +254,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
     const bool move = mx > st.m + ATTN_LAG;
     if (__builtin_amdgcn_ballot_w64(move) != 0) {
         const float mnew = move ? mx : st.m;
-        const float alpha = __builtin_amdgcn_exp2f(st.m - mnew);
+        const float alpha = MASKED && !move ? 1.f : __builtin_amdgcn_exp2f(st.m - mnew);
         st.m = mnew;
         if constexpr (!C::ONES) st.l *= alpha;
 #pragma unroll
@@ -243,7 +262,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.o[dt][r] *= alpha;
     }
-    const float mref = st.m;
+    const float mref = MASKED && st.m == -INFINITY ? 0.f : st.m;
     float psum = 0.f;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -348,7 +367,7 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
             }
         }
     }
-    attn_softmax_pv<D, NB, FULL, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
+    attn_softmax_pv<D, NB, FULL, RAW, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
 }
 
 // Patches: scores of 32-key blocks that are 4 x 8 patches of stride 2 in the grid: key k of a block (bits c0 r1'.. in
@@ -372,7 +391,7 @@ __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2)
 template <int D, int NB, bool RAGGED, int WK>
 __device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
                                                        const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB],
-                                                       int S, float scale_log2e, const _Float16 *tq_lane)
+                                                       int S, float scale_log2e, const _Float16 *tq_lane, uint32_t half_one)
 {
     using C = AttnCfg<D>;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
@@ -387,7 +406,7 @@ __device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const b
 #pragma unroll
         for (int tab = 0; tab < 2; ++tab) {
             // the one's place among 8 consecutive entries (two per register), and which such group it is in
-            const uint32_t at = tab ? rc >> 16 : rc & 0xffffu, one = (at & 1u) ? 0x3c000000u : 0x3c00u;
+            const uint32_t at = tab ? rc >> 16 : rc & 0xffffu, one = half_one << ((at << 4) & 31u);
             u32x4 e;
 #pragma unroll
             for (int j = 0; j < 4; ++j) e[j] = ((at >> 1) & 3u) == (uint32_t)j ? one : 0u;
@@ -1050,7 +1069,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     const int qrow = qcell >> lgw, qcol = qcell & (P.w - 1);
     GlbTab *tq_lane = tq + l32 * tstr;            // this lane's query row of the wave's bias table
     build_bias_rows_patch<D>(qf, P.rel_h, P.rel_w, P.w, lgw, qrow, qcol, __builtin_amdgcn_readfirstlane(qrow), __builtin_amdgcn_readfirstlane(qcol),
-                             tq_lane, inv_scale);
+                             tq_lane, P.table_inv);
     WaveState<D> st;
     init_state<D>(st);
 
@@ -1059,10 +1078,11 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     pipe.ones_at = ONES0;
     // operand a of the bias product: lane (key l32, half) holds E[l32][8*half + e]
     const int rr = patch_rr(l32), cc = patch_cc(l32);
+    const _Float16 one = __builtin_bit_cast(_Float16, (uint16_t)P.half_one);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int f = 8 * half + e;
-        pipe.efrag[e] = (_Float16)((f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? 1.f : 0.f);
+        pipe.efrag[e] = (f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? one : (_Float16)0.f;
     }
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) pipe.ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ Pipe::swz(l32)) * 16;
@@ -1181,7 +1201,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 
     ATTN_LOAD_TILE(0 < P.n_pre ? 0 : qt, 3)       // in flight while the bias rows are formed
     set_ones_columns<D>(Vs, GLB_TILE, tid, 256);
-    build_bias_rows<D, GlbTab>(qf, P.rel_h, P.rel_w, D, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq_lane, inv_scale);
+    build_bias_rows<D, GlbTab>(qf, P.rel_h, P.rel_w, D, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq_lane, WK ? P.table_inv : inv_scale);
 
     WaveState<D> st;
     init_state<D>(st);
@@ -1203,8 +1223,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
             for (int b = 0; b < NB; ++b) { blk[b] = c0 + b; key0[b] = kt * GLB_TILE + 32 * (c0 + b); }
             const bool ragged = key0[NB - 1] + 32 > S;                          // ... but for one in a chunk with a block that is not: masked
             if constexpr (WK != 0) {
-                if (ragged) attn_chunk_step_onehot<D, NB, true, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane);
-                else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane);
+                if (ragged) attn_chunk_step_onehot<D, NB, true, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+                else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
             } else {
                 const int nb = min(NB, nblk - c0);
                 if (ragged) attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
@@ -1236,8 +1256,10 @@ attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
     const int qt = (blockIdx.x >> 3) % T, gh = ((blockIdx.x >> 3) / T) * 8 + (blockIdx.x & 7);
     if (gh >= n_gh) return;
     const int grp = gh / P.h, head = gh % P.h;
+    if constexpr (TRY_PATCH || WK != 0) clamp_fp16(true);      // (here and not at the table: nothing moves across it)
     if constexpr (TRY_PATCH)
         if (attn_patch_body<D>(P, qt, grp, head, inv_scale, smem)) return;
+    if constexpr (TRY_PATCH && WK == 0) clamp_fp16(false);
     attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : WK != 0 && TRY_PATCH && D > 64 ? 1 : 2)>(P, qt, grp, head, inv_scale, smem);
 }
 
@@ -1345,6 +1367,9 @@ extern "C" int ssam_sparse_attention(const void *q, const void *k, const void *v
     P.scale_log2e = scale * LOG2E;
     if (!(scale > 0.f)) return SSAM_EINVAL;      // the global kernel's bias table holds bias / scale
     const float inv_scale = 1.0f / scale;
+    const int shift = bias_shift(scale);
+    P.half_one = 0x3c00u + ((uint32_t)shift << 10);
+    P.table_inv = ldexpf(inv_scale, -shift);
     hipStream_t st = (hipStream_t)stream;
     switch (d) {
     case 64: return launch_attention<64>(P, groups, mask_block, inv_scale, st);

@@ -49,3 +49,31 @@ def test_growing_logits(d, grow):
     spatial[sigma] = scan
     o = oracle.attention(*(np.ascontiguousarray(spatial[:, i].transpose(1, 0, 2)) for i in range(3)), *rel, w, 4, 128, r)
     assert_close(got, o.transpose(1, 0, 2)[sigma], f"growing logits d={d}")
+
+
+@pytest.mark.parametrize("w,d,order,scale", [(20, 64, "row", 1e-3), (31, 16, "row", 1e-5), (32, 80, "row", 1e-3), (50, 64, "row", 0.125), (50, 80, "position", 1e-3),
+                                             (64, 32, "row", 1e-3), (64, 80, "row", 1e-5), (72, 64, "position", 1e-3), (72, 80, "row", 1e-3),
+                                             (16, 64, "position", 0.125), (32, 16, "position", 1e-5), (64, 80, "position", 1e-3), (64, 32, "position", 1e-3)])
+def test_bias_past_fp16(w, d, order, scale):
+    """Bias / scale, what the kernel's tables hold, past the range of fp16: a bias of -120 at scales of 1e-3 and 1e-5, of -16384 at
+    1/8.  The keys concerned get no weight (exp(-120) of what the others have at most), the query's other keys what they
+    would have without.  Some queries meet nothing else in their first 64 keys."""
+    announce("bias past fp16", w, d, order, scale)
+    S, rng, r = w * w, np.random.default_rng(w + d), 0.4
+    sigma = np.arange(S, dtype=np.int32) if order == "row" else np.ascontiguousarray(B.ssam_build_perm(w, w, 4 if w % 2 == 0 else 1)[0])
+    qkv = rng.normal(size=(1, S, 3, 1, d)).astype(np.float32)                                   # scan order
+    qkv[:, :, 0, :, 0] = 4.0
+    qkv = inputs.bf16_round(qkv)
+    rel = [inputs.bf16_round(rng.normal(0, 0.02, size=(2 * w - 1, d)).astype(np.float32)) for _ in range(2)]
+    far = np.r_[w + 2, w - 1 + w // 2:2 * w - 1]                                              # three rows, and half the grid or more, above the query
+    rel[0][far], rel[0][far, 0] = 0.0, -30.0 if scale < 0.1 else -4096.0
+    got = to_np(B.ssam_sparse_attention(dev_bf16(qkv), dev_bf16(rel[0]), dev_bf16(rel[1]), dev_i32(sigma), w, 128, r, scale=scale))[0]
+    q, k, v = (qkv[0, :, i, 0].astype(np.float64) for i in range(3))
+    row, col = sigma // w, sigma % w
+    logit = scale * (q @ k.T)
+    for t, c in zip(rel, (row, col)):
+        logit += np.take_along_axis(q @ t.T.astype(np.float64), c[:, None] - c[None, :] + w - 1, axis=1)
+    tile = np.arange(S) // 128
+    logit[~((tile[None, :] < int(r * (tile[-1] + 1) + 1e-6)) | (tile[None, :] == tile[:, None]))] = -np.inf
+    p = np.exp(logit - logit.max(1, keepdims=True))
+    assert_close(got, p @ v / p.sum(1, keepdims=True), f"bias past fp16 w={w} d={d} {order} scale={scale}")
