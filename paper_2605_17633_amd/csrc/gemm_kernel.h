@@ -98,169 +98,6 @@ __device__ __forceinline__ void gemm_tile_origin(const GemmTileRange &tr, int t,
     n0 = (tn * sub_n + sub % sub_n) * bn;
 }
 
-// Epilogue of a workgroup's BM x BN tile (WGM x WGN waves, each with its MT16 x NT16 accumulator tiles): shared by the
-// two main loops (gemm_bf16_nt_body below and the ring of gemm_ring.h).
-template <int BM, int BN, int EPI, int WGM, int WGN, bool LNF, int MT16, int NT16>
-__device__ __forceinline__ void
-gemm_epilogue(f32x4 (&acc)[MT16][NT16], const float *__restrict__ bias, bf16 *C, int M, int N, const GemmLd &ld,
-              const GemmRowMap &rm, const GemmSplit &sp, const GemmFold &fold, unsigned char *smem, int m0, int n0, int slot, int kpart)
-{
-    // a K range of a folded product only gathers its rows: the normalisation is finished where the ranges are added
-    constexpr bool FOLD_EPI = LNF && EPI != GEMM_EPI_PARTIAL;
-    constexpr int WM = BM / WGM, WN = BN / WGN, MT = WM / 32;       // MT: 32-row slices
-    static_assert(MT16 == WM / 16 && NT16 == WN / 16, "accumulators of the wave tile");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
-    const int l16 = lane & 15, quad = lane >> 4;
-    const int parts = EPI == GEMM_EPI_PARTIAL ? sp.parts : 1;
-    // 32-row slices through a per-wave fp32 LDS region
-    constexpr int EPS = WN + 4;                 // floats per staged row (16-byte multiple, odd in 16-byte units)
-    constexpr int LPR = WN / 8;                 // lanes per row when each lane owns 8 columns
-    constexpr int RPP = 64 / LPR;               // rows per pass
-    float *stage = reinterpret_cast<float *>(smem) + wave * 32 * EPS;
-    const int cl = lane % LPR, rl = lane / LPR;
-    const int ncol = n0 + wn + cl * 8;
-    float bv[8];
-    if (EPI == GEMM_EPI_PARTIAL) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bv[e] = 0.f;
-    } else {
-        const float4 *b4 = reinterpret_cast<const float4 *>(bias + (ncol < N ? ncol : 0));
-        float4 x0 = b4[0], x1 = b4[1];
-        bv[0] = x0.x; bv[1] = x0.y; bv[2] = x0.z; bv[3] = x0.w;
-        bv[4] = x1.x; bv[5] = x1.y; bv[6] = x1.z; bv[7] = x1.w;
-    }
-    const bool col_ok = ncol < N;               // N % 8 == 0: a lane's 8 columns are all inside or all outside
-    constexpr int PASSES = 32 / RPP;
-    float sv[FOLD_EPI ? 8 : 1];
-    if constexpr (FOLD_EPI) {
-        const float4 *c4 = reinterpret_cast<const float4 *>(fold.colsum + (ncol < N ? ncol : 0));
-        float4 x0 = c4[0], x1 = c4[1];
-        sv[0] = x0.x; sv[1] = x0.y; sv[2] = x0.z; sv[3] = x0.w;
-        sv[4] = x1.x; sv[5] = x1.y; sv[6] = x1.z; sv[7] = x1.w;
-    }
-    // The scatter epilogue is a read-modify-write of rows of the residual stream.  Its destination rows
-    // are looked up once per tile (one row per thread, parked in LDS behind the staging regions) and the
-    // old values of a whole 32-row slice are requested before the slice is staged, so that the slice pays
-    // one memory round trip instead of one per pass.
-    int *dst_row = reinterpret_cast<int *>(reinterpret_cast<float *>(smem) + WGM * WGN * 32 * EPS);   // [BM], -1 = skip
-    constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER;
-    float2 *row_stats = reinterpret_cast<float2 *>(dst_row + BM);    // [BM] { rstd, -rstd*mean } (LNF), parked like dst_row
-    if (MAPPED || FOLD_EPI) {
-        int mine = -1;
-        float2 mine_stats = { 0.f, 0.f };
-        if (tid < BM && m0 + tid < M) {
-            int m = m0 + tid;
-            if constexpr (FOLD_EPI) mine_stats = fold.stats[m];
-            if (MAPPED) {
-                int b = m / rm.rows_per_batch, p = m - b * rm.rows_per_batch;
-                int idx = rm.map[(long)b * rm.map_batch_stride + p];
-                if (idx >= 0 && idx < rm.dst_rows_per_batch) mine = b * rm.dst_rows_per_batch + idx;
-            }
-        }
-        __syncthreads();                        // every wave is done with the pipeline buffers
-        if (tid < BM) {
-            if (MAPPED) dst_row[tid] = mine;
-            if constexpr (FOLD_EPI) row_stats[tid] = mine_stats;
-        }
-    }
-    __syncthreads();                            // pipeline buffers free for staging; dst_row visible
-    // The bias values must have landed before the first store pass: a pass that first touched them behind its
-    // row predicate would wait with a full drain of the memory counter, which on this hardware also counts the
-    // stores of the passes before it, and every pass would then wait for the previous pass's store to complete.
-#pragma unroll
-    for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(bv[e]));
-    if constexpr (FOLD_EPI) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(sv[e]));
-    }
-    // From here on a wave touches only its own staging region: LDS operations of one wave execute in
-    // order, so the slices need no workgroup barrier (which would also wait for the previous slice's
-    // global stores); wavefront fences keep the compiler from reordering the LDS accesses.
-    // Destination rows and old values of a 32-row slice.  The loads are unconditional (a skipped row or column
-    // reads row 0 / column 0 and drops the value: loads behind a predicate would each be waited for on their own)
-    // and a slice's loads are issued before the stores of the slice before it, so the wait for them (a count
-    // of younger operations still allowed in flight) does not wait for those stores to complete.
-    uint4 old[PASSES], old_next[PASSES];
-    int drow[PASSES], drow_next[PASSES];
-    auto preload_slice = [&](int i, uint4 (&o)[PASSES], int (&d)[PASSES]) {
-#pragma unroll
-        for (int pass = 0; pass < PASSES; ++pass) {
-            d[pass] = dst_row[wm + i * 32 + pass * RPP + rl];
-            if (EPI == SSAM_EPI_BIAS_SCATTER_ADD)
-                o[pass] = *reinterpret_cast<const uint4 *>(C + (long)max(d[pass], 0) * ld.c + (col_ok ? ncol : 0));
-        }
-    };
-    if (MAPPED) preload_slice(0, old, drow);
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)             // the slice's two 16-row tiles: lane (l16, quad) holds rows 4*quad + r
-#pragma unroll
-            for (int j = 0; j < NT16; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    stage[(t * 16 + 4 * quad + r) * EPS + j * 16 + l16] = acc[2 * i + t][j][r];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (MAPPED && i + 1 < MT) preload_slice(i + 1, old_next, drow_next);
-        if (EPI == SSAM_EPI_BIAS_SCATTER_ADD) {   // this slice's old values, waited for once (see the bias values above)
-#pragma unroll
-            for (int pass = 0; pass < PASSES; ++pass)
-                asm volatile("" : "+v"(old[pass].x), "+v"(old[pass].y), "+v"(old[pass].z), "+v"(old[pass].w));
-        }
-#pragma unroll
-        for (int pass = 0; pass < PASSES; ++pass) {
-            const int row = pass * RPP + rl;
-            const int m = m0 + wm + i * 32 + row;
-            if (m >= M || (EPI != GEMM_EPI_PARTIAL && !col_ok)) continue;
-            const float4 *s4 = reinterpret_cast<const float4 *>(stage + row * EPS + cl * 8);
-            float4 y0 = s4[0], y1 = s4[1];
-            if (EPI == GEMM_EPI_PARTIAL) {
-                float4 *dst = reinterpret_cast<float4 *>(sp.partial + (((long)slot * parts + kpart) * BM + (wm + i * 32 + row)) * BN + wn + cl * 8);
-                dst[0] = y0;
-                dst[1] = y1;
-                continue;
-            }
-            float v[8] = { y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w };
-            if constexpr (FOLD_EPI) {
-                const float2 t = row_stats[wm + i * 32 + row];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] * t.x + (t.y * sv[e] + bv[e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += bv[e];
-            }
-            if (EPI == SSAM_EPI_BIAS_GELU) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
-            }
-            if (EPI == SSAM_EPI_BIAS_SCATTER_ADD) {
-                if (drow[pass] < 0) continue;
-                float o[8];
-                unpack_bf16x8(old[pass], o);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += o[e];
-                *reinterpret_cast<uint4 *>(C + (long)drow[pass] * ld.c + ncol) = pack_bf16x8(v);
-            } else if (EPI == SSAM_EPI_BIAS_SCATTER) {
-                // (a mapped store is the qkv tensor: written once, read once by the attention kernel that follows; the
-                // non-temporal hint keeps it from displacing what the later kernels of the block want cached)
-                if (drow[pass] >= 0) {
-                    const uint4 pk_ = pack_bf16x8(v);
-                    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, pk_), reinterpret_cast<u32x4 *>(C + (long)drow[pass] * ld.c + ncol));
-                }
-            } else {
-                *reinterpret_cast<uint4 *>(C + (long)m * ld.c + ncol) = pack_bf16x8(v);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // the slice is read before the next one is staged
-        if (MAPPED && i + 1 < MT) {
-#pragma unroll
-            for (int pass = 0; pass < PASSES; ++pass) { old[pass] = old_next[pass]; drow[pass] = drow_next[pass]; }
-        }
-    }
-}
-
 // The workgroup's work, as a function of its index `bid` in the launch (the kernels below pass blockIdx.x, or
 // blockIdx.x less the workgroups of another kind that share the launch).
 template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
@@ -270,8 +107,10 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
                   const GemmSplit &sp, int bid, const GemmFold &fold = GemmFold{ nullptr, nullptr, nullptr })
 {
     static_assert(!LNF || WPACK, "the folded forms exist for packed weights");
+    // a K range of a folded product only gathers its rows: the normalisation is finished where the ranges are added
+    constexpr bool FOLD_EPI = LNF && EPI != GEMM_EPI_PARTIAL;
     constexpr int THREADS = 64 * WGM * WGN, RSTEP = THREADS / 8;   // waves in a WGM x WGN grid; rows staged per pass
-    constexpr int WM = BM / WGM, WN = BN / WGN;
+    constexpr int WM = BM / WGM, WN = BN / WGN, MT = WM / 32;       // MT: 32-row slices of the epilogue
     constexpr int MT16 = WM / 16, NT16 = WN / 16;                  // the wave's accumulator tiles (16x16)
     // A slab of 64 holds two MFMA k-steps of 32.  A k-step is issued in HP phases of AF row tiles each, so that only
     // AF operand-a fragments are live per register slot: phase p = (k-step p / HP, row tiles (p % HP)*AF ...).
@@ -500,7 +339,152 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 
-    gemm_epilogue<BM, BN, EPI, WGM, WGN, LNF>(acc, bias, C, M, N, ld, rm, sp, fold, smem, m0, n0, slot, kpart);
+    // ---- epilogue: 32-row slices through a per-wave fp32 LDS region
+    constexpr int EPS = WN + 4;                 // floats per staged row (16-byte multiple, odd in 16-byte units)
+    constexpr int LPR = WN / 8;                 // lanes per row when each lane owns 8 columns
+    constexpr int RPP = 64 / LPR;               // rows per pass
+    float *stage = reinterpret_cast<float *>(smem) + wave * 32 * EPS;
+    const int cl = lane % LPR, rl = lane / LPR;
+    const int ncol = n0 + wn + cl * 8;
+    float bv[8];
+    if (EPI == GEMM_EPI_PARTIAL) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[e] = 0.f;
+    } else {
+        const float4 *b4 = reinterpret_cast<const float4 *>(bias + (ncol < N ? ncol : 0));
+        float4 x0 = b4[0], x1 = b4[1];
+        bv[0] = x0.x; bv[1] = x0.y; bv[2] = x0.z; bv[3] = x0.w;
+        bv[4] = x1.x; bv[5] = x1.y; bv[6] = x1.z; bv[7] = x1.w;
+    }
+    const bool col_ok = ncol < N;               // N % 8 == 0: a lane's 8 columns are all inside or all outside
+    constexpr int PASSES = 32 / RPP;
+    float sv[FOLD_EPI ? 8 : 1];
+    if constexpr (FOLD_EPI) {
+        const float4 *c4 = reinterpret_cast<const float4 *>(fold.colsum + (ncol < N ? ncol : 0));
+        float4 x0 = c4[0], x1 = c4[1];
+        sv[0] = x0.x; sv[1] = x0.y; sv[2] = x0.z; sv[3] = x0.w;
+        sv[4] = x1.x; sv[5] = x1.y; sv[6] = x1.z; sv[7] = x1.w;
+    }
+    // The scatter epilogue is a read-modify-write of rows of the residual stream.  Its destination rows
+    // are looked up once per tile (one row per thread, parked in LDS behind the staging regions) and the
+    // old values of a whole 32-row slice are requested before the slice is staged, so that the slice pays
+    // one memory round trip instead of one per pass.
+    int *dst_row = reinterpret_cast<int *>(reinterpret_cast<float *>(smem) + WGM * WGN * 32 * EPS);   // [BM], -1 = skip
+    constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER;
+    float2 *row_stats = reinterpret_cast<float2 *>(dst_row + BM);    // [BM] { rstd, -rstd*mean } (LNF), parked like dst_row
+    if (MAPPED || FOLD_EPI) {
+        int mine = -1;
+        float2 mine_stats = { 0.f, 0.f };
+        if (tid < BM && m0 + tid < M) {
+            int m = m0 + tid;
+            if constexpr (FOLD_EPI) mine_stats = fold.stats[m];
+            if (MAPPED) {
+                int b = m / rm.rows_per_batch, p = m - b * rm.rows_per_batch;
+                int idx = rm.map[(long)b * rm.map_batch_stride + p];
+                if (idx >= 0 && idx < rm.dst_rows_per_batch) mine = b * rm.dst_rows_per_batch + idx;
+            }
+        }
+        __syncthreads();                        // every wave is done with the pipeline buffers
+        if (tid < BM) {
+            if (MAPPED) dst_row[tid] = mine;
+            if constexpr (FOLD_EPI) row_stats[tid] = mine_stats;
+        }
+    }
+    __syncthreads();                            // pipeline buffers free for staging; dst_row visible
+    // The bias values must have landed before the first store pass: a pass that first touched them behind its
+    // row predicate would wait with a full drain of the memory counter, which on this hardware also counts the
+    // stores of the passes before it, and every pass would then wait for the previous pass's store to complete.
+#pragma unroll
+    for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(bv[e]));
+    if constexpr (FOLD_EPI) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(sv[e]));
+    }
+    // From here on a wave touches only its own staging region: LDS operations of one wave execute in
+    // order, so the slices need no workgroup barrier (which would also wait for the previous slice's
+    // global stores); wavefront fences keep the compiler from reordering the LDS accesses.
+    // Destination rows and old values of a 32-row slice.  The loads are unconditional (a skipped row or column
+    // reads row 0 / column 0 and drops the value: loads behind a predicate would each be waited for on their own)
+    // and a slice's loads are issued before the stores of the slice before it, so the wait for them (a count
+    // of younger operations still allowed in flight) does not wait for those stores to complete.
+    uint4 old[PASSES], old_next[PASSES];
+    int drow[PASSES], drow_next[PASSES];
+    auto preload_slice = [&](int i, uint4 (&o)[PASSES], int (&d)[PASSES]) {
+#pragma unroll
+        for (int pass = 0; pass < PASSES; ++pass) {
+            d[pass] = dst_row[wm + i * 32 + pass * RPP + rl];
+            if (EPI == SSAM_EPI_BIAS_SCATTER_ADD)
+                o[pass] = *reinterpret_cast<const uint4 *>(C + (long)max(d[pass], 0) * ld.c + (col_ok ? ncol : 0));
+        }
+    };
+    if (MAPPED) preload_slice(0, old, drow);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)             // the slice's two 16-row tiles: lane (l16, quad) holds rows 4*quad + r
+#pragma unroll
+            for (int j = 0; j < NT16; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    stage[(t * 16 + 4 * quad + r) * EPS + j * 16 + l16] = acc[2 * i + t][j][r];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (MAPPED && i + 1 < MT) preload_slice(i + 1, old_next, drow_next);
+        if (EPI == SSAM_EPI_BIAS_SCATTER_ADD) {   // this slice's old values, waited for once (see the bias values above)
+#pragma unroll
+            for (int pass = 0; pass < PASSES; ++pass)
+                asm volatile("" : "+v"(old[pass].x), "+v"(old[pass].y), "+v"(old[pass].z), "+v"(old[pass].w));
+        }
+#pragma unroll
+        for (int pass = 0; pass < PASSES; ++pass) {
+            const int row = pass * RPP + rl;
+            const int m = m0 + wm + i * 32 + row;
+            if (m >= M || (EPI != GEMM_EPI_PARTIAL && !col_ok)) continue;
+            const float4 *s4 = reinterpret_cast<const float4 *>(stage + row * EPS + cl * 8);
+            float4 y0 = s4[0], y1 = s4[1];
+            if (EPI == GEMM_EPI_PARTIAL) {
+                float4 *dst = reinterpret_cast<float4 *>(sp.partial + (((long)slot * parts + kpart) * BM + (wm + i * 32 + row)) * BN + wn + cl * 8);
+                dst[0] = y0;
+                dst[1] = y1;
+                continue;
+            }
+            float v[8] = { y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w };
+            if constexpr (FOLD_EPI) {
+                const float2 t = row_stats[wm + i * 32 + row];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = v[e] * t.x + (t.y * sv[e] + bv[e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += bv[e];
+            }
+            if (EPI == SSAM_EPI_BIAS_GELU) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
+            }
+            if (EPI == SSAM_EPI_BIAS_SCATTER_ADD) {
+                if (drow[pass] < 0) continue;
+                float o[8];
+                unpack_bf16x8(old[pass], o);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += o[e];
+                *reinterpret_cast<uint4 *>(C + (long)drow[pass] * ld.c + ncol) = pack_bf16x8(v);
+            } else if (EPI == SSAM_EPI_BIAS_SCATTER) {
+                // (a mapped store is the qkv tensor: written once, read once by the attention kernel that follows; the
+                // non-temporal hint keeps it from displacing what the later kernels of the block want cached)
+                if (drow[pass] >= 0) {
+                    const uint4 pk_ = pack_bf16x8(v);
+                    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, pk_), reinterpret_cast<u32x4 *>(C + (long)drow[pass] * ld.c + ncol));
+                }
+            } else {
+                *reinterpret_cast<uint4 *>(C + (long)m * ld.c + ncol) = pack_bf16x8(v);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // the slice is read before the next one is staged
+        if (MAPPED && i + 1 < MT) {
+#pragma unroll
+            for (int pass = 0; pass < PASSES; ++pass) { old[pass] = old_next[pass]; drow[pass] = drow_next[pass]; }
+        }
+    }
 }
 
 template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
