@@ -5,8 +5,10 @@
 // is 32x32; its four waves cut K between them (wave w takes the k-steps w, w + 4, ...) and load their MFMA fragments straight
 // into registers, DIRECT_DEPTH steps ahead, with no LDS and no barrier until the four partial tiles are added there, in wave
 // order.  Packed weights only: with rows in both operands the half cache lines of the fragments cost what the width gains.
-// Measured (us, before = 64x64 ring): 313 x 768 x 3072 15.0 -> 11.0, 196 x 1024 x 4096 23 -> 13.5, 313 x 768 x 768 6.1 -> 5.7; with two
-// tiles per CU the ring is ahead again (313 x 2304 x 768 6.2 against 8.7).  Pairs of adjacent k-steps per wave: no faster.
+// Measured (us, weights that no cache holds, before = 64x64 ring): 313 x 768 x 3072 18.6 -> 10.6, 196 x 1024 x 4096 23.8 -> 12.8, 313 x 768 x 768
+// 6.1 -> 4.9, 64 x 1280 x 1280 8.3 -> 7.0; with two tiles per CU the two are level (253 x 1152 x 1152 9.2 against 9.5).  Pairs of adjacent
+// k-steps per wave: no faster.  Loads chosen between the operand and a chunk of zeros became FLAT loads that the compiler
+// moved next to their use and waited for one by one: 313 x 768 x 3072 14.8 with the bias epilogue, 12.0 mapped.
 #pragma once
 
 #include "gemm_kernel.h"
@@ -35,17 +37,23 @@ gemm_direct_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const
         pa[i] = A + arow * ld.a + quad * 8;
         pw[i] = W + (long)((n0 >> 4) + i) * nsteps * 512 + lane * 8;         // N is a multiple of 32
     }
-    const bf16 *zchunk = reinterpret_cast<const bf16 *>(gemm_zero_chunk);
     bf16x8 fa[DEPTH][2], fw[DEPTH][2];
-    // k-step wave + 4*i into register set s; zeros past the end of K
+    // k-step wave + 4*i into register set s; past the end of K the last step again, which is not multiplied: the loads carry
+    // no predicate and stay where they are written (sched_barrier), so that each wait leaves the steps behind it in flight
     auto load = [&](int i, int s) {
-        const int k = (wave + 4 * i) * 32;
-        const bool in = k < K;
+        const int k = min(wave + 4 * i, nsteps - 1) * 32;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            fa[s][j] = *reinterpret_cast<const bf16x8 *>(in ? pa[j] + k : zchunk);
-            fw[s][j] = *reinterpret_cast<const bf16x8 *>(in ? pw[j] + (long)k * 16 : zchunk);
+            fa[s][j] = *reinterpret_cast<const bf16x8 *>(pa[j] + k);
+            fw[s][j] = *reinterpret_cast<const bf16x8 *>(pw[j] + (long)k * 16);
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mul = [&](f32x4 (&acc)[2][2], int s) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][x], fw[s][y], acc[x][y], 0, 0, 0);
     };
     f32x4 acc[2][2];
 #pragma unroll
@@ -54,17 +62,17 @@ gemm_direct_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{ 0.f, 0.f, 0.f, 0.f };
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) load(s, s);
-    // whole turns of the register ring; the steps that a last turn has too many are zeros
-    for (int i = 0; i < n; i += DEPTH) {
+    int i = 0;
+    for (; i + DEPTH < n; i += DEPTH) {          // turns of the register ring with steps behind them
 #pragma unroll
         for (int s = 0; s < DEPTH; ++s) {
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][x], fw[s][y], acc[x][y], 0, 0, 0);
+            mul(acc, s);
             load(i + s + DEPTH, s);
         }
     }
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s)              // the last turn, all of it requested
+        if (i + s < n) mul(acc, s);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");       // see gemm_bf16_nt_body
     __builtin_amdgcn_sched_barrier(0);
