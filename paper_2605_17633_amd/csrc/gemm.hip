@@ -146,7 +146,21 @@ int launch_tile(int tile, const bf16 *A, const bf16 *W, const float *bias, bf16 
     }
 }
 
-double large_tile_us(double rounds_us, bool packed) { return packed ? 5.0 + 0.72 * rounds_us : 3.0 + rounds_us; }
+// What launches of the large tiles take (see pick_ring), from the time that pick_tile orders them by.
+double large_tile_us(int tile, double rounds_us, bool packed)
+{
+    if (tile == 3) return 0.2 + 1.18 * rounds_us;
+    return packed ? 3.7 + 0.76 * rounds_us : 0.5 + rounds_us;
+}
+
+// The same for a problem that is all left-over with K cut (tm x tn tiles): its ranges, and its partial tiles, of which only rows
+// that exist are written and read.
+double all_split_us(int M, int N, int nk, int parts, int bn, int tm, int tn, bool packed)
+{
+    const double tiles = (double)ssam_div_up(M, tm) * ssam_div_up(N, bn) * (bn / tn);
+    const double mb = tiles * parts * (M < tm ? M : tm) * tn * 4e-6;
+    return (packed ? 6.7 : 7.0) + ssam_div_up(nk, parts) * (packed ? 0.84 : 1.10) + 0.37 * mb;
+}
 
 // Pick the tile by a time model in microseconds, fitted on MI355X to the ViT-H layer shapes: a round of
 // workgroups costs nk * t_slab + t_epi.  The 256x256 tile (eight waves, one workgroup per CU) and the 128x256
@@ -182,31 +196,31 @@ int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed,
         if (t >= best_time) continue;
         best_time = t;
         best = c.id;
-        // What such a launch was measured to take on those shapes (see ring_tiles):
-        // the time above leaves the launch out and is pessimistic with packed weights (11 % standard error); a problem
-        // that is all left-over with K cut pays for its ranges and for writing and reading its partial tiles (5 %).
-        const int n_all = total * subs;
-        launch_us = plan.rem == total && plan.parts > 1
-                        ? 6.6 + ssam_div_up(nk, plan.parts) * (packed ? 0.90 : 1.21) + 0.41e-6 * n_all * plan.parts * c.tm * c.tn * 4
-                        : large_tile_us(t, packed);
+        // t leaves the launch out and serves to order the tiles; what the launch takes:
+        launch_us = plan.rem == total && plan.parts > 1 ? all_split_us(M, N, nk, plan.parts, c.bn, c.tm, c.tn, packed)
+                                                        : large_tile_us(c.id, t, packed);
     }
     return best;
 }
 
-// The ring's tiles (gemm_ring.h) for a problem that they hold in one round of workgroups.  A launch takes t0 plus
-// t_slab[k - 1] per slab of 64 when its busiest CU has k workgroups: fitted to 290 shapes (M 196 to 8192, the layers
-// of widths 576 to 1280, both weight layouts) with weights that no cache holds, as in a deep stack; 8-10 % standard error.
-struct RingTile { int bm, bn, slots; double t0, t_slab[3]; };
-constexpr RingTile ring_tiles[3] = { { 128, 128, 2, 4.9, { 0.66, 0.95, 0. } },
-                                     { 128, 64, 3, 3.5, { 0.56, 0.67, 0.95 } },
-                                     { 64, 64, 3, 3.2, { 0.28, 0.40, 0.61 } } };
+// The ring's tiles (gemm_ring.h) for a problem that they hold in one round of workgroups.  A launch takes t0 plus t_slab[k - 1] per
+// slab of 64 when its busiest CU has k workgroups, with row-major and with packed weights.
+struct RingTile { int bm, bn, slots; struct { double t0, t_slab; } us[2][3]; };
+constexpr RingTile ring_tiles[3] = { { 128, 128, 2, { { { 3.6, 0.82 }, { 7.4, 0.79 }, {} }, { { 3.7, 0.73 }, { 6.9, 0.80 }, {} } } },
+                                     { 128, 64, 3, { { { 2.6, 0.70 }, { 4.7, 0.70 }, { 6.2, 0.85 } }, { { 2.65, 0.65 }, { 4.3, 0.645 }, { 6.0, 0.78 } } } },
+                                     { 64, 64, 3, { { { 2.7, 0.335 }, { 3.9, 0.385 }, { 4.5, 0.58 } }, { { 2.7, 0.31 }, { 3.7, 0.355 }, { 4.0, 0.565 } } } } };
 
 constexpr int RING_DIRECT = 3;
 
-// Index of the ring tile (or RING_DIRECT) that is faster than the large tiles (launch_us), or -1.  On the 290 shapes the choice is 1-2 % on
-// average from the faster of the two (the large tiles alone: 20 % with packed, 32 % with row-major weights), and the ring is
-// taken where it is slower on 7, by up to 7 %.
-int pick_ring(int M, int N, int K, bool packed, double launch_us)
+// Index of the ring tile (or RING_DIRECT: gemm_direct.h) that is faster than the large tiles (launch_us), or -1.  whole_lines: the rows
+// of row-major operands begin at multiples of 128 bytes; where they do not, a slab's 128-byte pieces of a row take two
+// lines each and a CU with two or three workgroups 1.35 times as long (427 x 3824 x 4560: 54 us, large tiles 44).
+// The estimates are fitted to 1200 shapes (M 8 to 8192, N 8 to 6144, K 8 to 6144: the layers of widths 576 to 1280, any sizes, few
+// rows against a long K) with weights that no cache holds, as in a deep stack: those cost every form 0.2 us a megabyte on top
+// of its estimate, the direct kernel 0.1, hence its credit.  Standard errors are 7-12 %.  What is taken is 0.9 % on
+// average from the fastest form, and on 9 of the shapes slower than the large tiles by more than 3 %, 7 % at most; with it they
+// are 25 % (row-major) and 31 % (packed) faster on average than with the large tiles alone.
+int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double launch_us)
 {
     const int nk = ssam_div_up(K, GEMM_BK);
     int best = -1;
@@ -215,11 +229,12 @@ int pick_ring(int M, int N, int K, bool packed, double launch_us)
         const RingTile &t = ring_tiles[i];
         const long tiles = (long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn);
         if (tiles > 256L * t.slots) continue;
-        const double us = t.t0 + nk * t.t_slab[ssam_div_up(tiles, 256) - 1];
+        const auto &u = t.us[packed][ssam_div_up(tiles, 256) - 1];
+        const double us = u.t0 + nk * u.t_slab * (!whole_lines && !packed && tiles > 256 ? 1.35 : 1.0);
         if (us < best_us) { best_us = us; best = i; }
     }
-    // gemm_direct.h: at most one tile per CU; fitted to K 768 to 5120 as the rings
-    if (packed && (long)ssam_div_up(M, 32) * (N / 32) <= 256 && 3.3 + nk * 0.16 < best_us) best = RING_DIRECT;
+    // at most one tile per CU
+    if (packed && (long)ssam_div_up(M, 32) * (N / 32) <= 256 && 3.2 + nk * 0.14 - 0.2e-6 * N * K < best_us) best = RING_DIRECT;
     return best;
 }
 
@@ -277,7 +292,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
     if (tile == 0) {
         double us;
         tile = pick_tile(M, N, K, epilogue, ws, packed, us);
-        ring = pick_ring(M, N, K, packed, us);
+        ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
     }
     if (packed) {
         switch (epilogue) {
@@ -308,10 +323,18 @@ int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *s
     const GemmRowMap none = { nullptr, 1, 0, 1 };
     double us;
     const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
-    if (const int ring = pick_ring(M, N, K, true, us); ring >= 0)
+    if (const int ring = pick_ring(M, N, K, true, true, us); ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
     return launch_tile_packed<SSAM_EPI_BIAS_GELU, true>(tile, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld,
                                                         none, ws, st, fold);
+}
+
+// Time of its large tiles: 512 workgroups a round, a last round of at most half of them at 0.62 of a round's time (as in pick_tile).
+static double folded_ln_us(int tiles, int K)
+{
+    const double round = (K / GEMM_BK) * 1.71 + 5.5;
+    const int last = tiles % 512;
+    return large_tile_us(4, (tiles / 512) * round + (last == 0 ? 0.0 : last <= 256 ? 0.62 * round : round), true);
 }
 
 // The contraction with the LayerNorm of its A rows folded in (see GemmFold): 128x256 tiles, packed weights,
@@ -323,11 +346,7 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr };
-    // 512 workgroups a round, a last round of at most half of them at 0.62 of a round's time (as in pick_tile)
-    const double round = (K / GEMM_BK) * 1.71 + 5.5;
-    const int last = tr.tile_count % 512;
-    const double us = large_tile_us((tr.tile_count / 512) * round + (last == 0 ? 0.0 : last <= 256 ? 0.62 * round : round), true);
-    if (const int ring = pick_ring(M, N, K, true, us); ring >= 0)
+    if (const int ring = pick_ring(M, N, K, true, true, folded_ln_us(tr.tile_count, K)); ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
     const int per_xcd = ssam_div_up(tr.tile_count, 8);
     hipLaunchKernelGGL((gemm_bf16_nt_lnf_kernel<128, 256, SSAM_EPI_BIAS_SCATTER, 1, 4>), dim3(per_xcd * 8), dim3(256), lds, st,
@@ -349,6 +368,21 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     if (M % 128 != 0 || N % 256 != 0 || K % GEMM_BK != 0) return SSAM_EUNSUPPORTED;
     const GemmRowMap rm = { row_map, rows_per_batch, map_batch_stride, dst_rows_per_batch };
     return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream);
+}
+
+// Which kernel a contraction takes (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
+// 17: 128x64, 18: 64x64, 19: the direct one).  Host only, for tests; not part of the interface.
+extern "C" int ssam_linear_form(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > SSAM_EPI_BIAS_SCATTER) return SSAM_EINVAL;
+    double us = folded_ln_us((M / 128) * (N / 256), K);
+    int tile = 4;
+    if (!folded) {
+        alignas(16) unsigned char some;
+        tile = pick_tile(M, N, K, epilogue, SplitWs{ workspace_bytes ? &some : nullptr, workspace_bytes }, packed != 0, us);
+    }
+    const int ring = pick_ring(M, N, K, packed != 0 || folded != 0, K % GEMM_BK == 0, us);
+    return ring >= 0 ? 16 + ring : tile;
 }
 
 extern "C" size_t ssam_linear_workspace_bytes(void) { return GEMM_SPLIT_WS_BYTES; }
