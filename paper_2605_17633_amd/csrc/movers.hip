@@ -726,17 +726,28 @@ extern "C" int ssam_select_tokens(const float *scores, int32_t *keep_idx, int B,
     return SSAM_OK;
 }
 
-// Whether counting beats the sort, from their measured times.  Counting takes 5 us and 80 us for every 2^30 pairs of cells
-// (64 x 64 grids: 7.6 us for one, 14 for 8, 25 for 16, 44 for 32; windows of 8 images: 7 us).  The sort has one CU per group
-// and takes 0.2 us for every step of its network and 1024 exchanges (64 x 64: 40 us whether one grid or 100; windows: 9.5 us;
-// 128 x 128: 163 us against 27 for one grid by counting and 257 for 16).
-static bool rank_by_counting(long groups, long S, int P)
+// Threads of a counting workgroup: no more waves than the group has cells for.
+static int rank_threads(int S) { return S > 8192 ? 1024 : S >= 512 / RANK_LANES ? 512 : ssam_div_up(S, 64 / RANK_LANES) * 64; }
+
+// Whether counting beats the sort, from their measured times (us, 233 pairs of a side w and a number of groups; chosen wrongly by
+// more than 7 % only where both take 2.5 to 5 us).  The sort takes a latency that grows with its network, the same for up to 256
+// groups, and then the chip's throughput; counting takes 3 us, 2.2 for every 1000 workgroups of 512 threads (its keys, loaded by
+// each of a group's `runs` workgroups) and 75 for every 2^30 pairs of cells:
+//   groups of 14 x 14: 25 3.6 by counting, 9.4 sorted; 200 7.1, 9.4; 400 10.9, 10.3; 1600 34, 12; 12800 235, 48
+//   of 8 x 8: 25 3.3, 6.1; 800 6.4, 6.3; 12800 57, 17       of 64 x 64: 1 7.5, 40; 16 30, 41; 25 45, 41; 200 289, 41
+static bool rank_by_counting(long groups, int S)
 {
-    int lg = 0;
-    while ((1 << lg) < P) ++lg;
-    const double sort_us = 0.2 * (lg * (lg + 1) / 2) * (P > 2048 ? P / 2048 : 1) * (double)((groups + 511) / 512);
-    return 5.0 + (double)groups * S * S * (80.0 / 1073741824.0) < sort_us;
+    int lg = 1;
+    while ((1 << lg) < S) ++lg;
+    const double P = 1 << lg, steps = lg * (lg + 1) / 2;
+    const double sort_us = 2.3 + steps * (0.17 + 8e-5 * P) + (groups > 256 ? (groups - 256) * (2.5e-4 + 3.8e-7 * P * steps) : 0.0);
+    const int threads = rank_threads(S), runs = ssam_div_up(S, threads / RANK_LANES);
+    const double count_us = 3.0 + 4e-4 * S + groups * (4.4e-6 * runs * threads + 7e-8 * S * S);
+    return count_us < sort_us;
 }
+
+// 1 if the tables of `groups` groups of w x w cells are made by counting, 0 if by the sort.  For tests; not part of the interface.
+extern "C" int ssam_content_tables_form(long groups, int w) { return rank_by_counting(groups, w * w); }
 
 extern "C" int ssam_build_content_tables(const float *scores, int B, int g, int ws, int G,
                                          int32_t *gather_table, int32_t *sigma, void *stream)
@@ -749,8 +760,8 @@ extern "C" int ssam_build_content_tables(const float *scores, int B, int g, int 
     const long groups = (long)B * nws * nws;
     int P = 2;
     while (P < S) P <<= 1;
-    if (rank_by_counting(groups, S, P)) {
-        const int threads = S > 8192 ? 1024 : 512, runs = ssam_div_up(S, threads / RANK_LANES);
+    if (rank_by_counting(groups, S)) {
+        const int threads = rank_threads(S), runs = ssam_div_up(S, threads / RANK_LANES);
         const size_t lds = (size_t)ssam_div_up(S, RANK_STEP) * RANK_STEP * sizeof(uint32_t);       // <= 64 KiB (w <= 128)
         hipLaunchKernelGGL(content_rank_kernel, dim3((unsigned)(groups * runs)), dim3(threads), lds, (hipStream_t)stream,
                            scores, g, w, nws, G, runs, gather_table, sigma);

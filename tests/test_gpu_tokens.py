@@ -30,10 +30,11 @@ def test_select_sizes(n, K, kind):
         assert np.array_equal(keep[b], oracle.select_tokens(s[b], K))
 
 
-@pytest.mark.parametrize("Bn,g,ws,levels", [(1, 14, 14, 0), (2, 30, 14, 3), (1, 5, 2, 0), (1, 50, 0, 4), (9, 128, 0, 50)])
+@pytest.mark.parametrize("Bn,g,ws,levels", [(1, 14, 14, 0), (2, 30, 14, 3), (1, 5, 2, 0), (1, 50, 0, 4), (9, 128, 0, 50),
+                                            (1, 6, 2, 0), (3, 12, 6, 2), (2, 90, 2, 3), (1, 230, 8, 5), (20, 70, 14, 0), (40, 70, 14, 7)])
 def test_content_tables_forms(Bn, g, ws, levels):
-    """levels > 0: only that many different scores, so that most pairs are decided by the cell index.  The last case is past
-    the point where the tables are sorted instead of counted."""
+    """levels > 0: only that many different scores, so that most pairs are decided by the cell index.  Windows of 2 x 2 and 64
+    cells or more in few and in many groups, on both sides of the point where the tables are sorted instead of counted."""
     announce("content tables", Bn, g, ws, levels)
     rng = np.random.default_rng(g + ws)
     s = rng.integers(0, levels, size=(Bn, g * g)).astype(np.float32) if levels else inputs.lognormal_scores(rng, Bn, g * g)
@@ -54,3 +55,12 @@ def test_content_tables_forms(Bn, g, ws, levels):
             assert np.array_equal(sigma[b * nws * nws + win], order), (b, win)
             cell = np.where(inside, row * g + col, -1)[order]
             assert np.array_equal(table[b, win * S:(win + 1) * S], cell), (b, win)
+
+
+def test_content_tables_of_millions_of_windows():
+    """Windows of one cell: the tables name the cells in window order."""
+    announce("content tables, one cell a window")
+    g = 2900
+    s = torch.randn(1, g * g, device=DEV)
+    table, sigma = B.ssam_build_content_tables(s, g, 1, 1)
+    assert torch.equal(table.reshape(-1), torch.arange(g * g, dtype=torch.int32, device=DEV)) and not sigma.any()
