@@ -1253,14 +1253,17 @@ attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // the query tiles of one (image, head) run on one XCD (workgroup b sits on XCD b & 7), whose L2 then
     // serves the re-reads of that problem's K and V tiles
-    const int qt = (blockIdx.x >> 3) % T, gh = ((blockIdx.x >> 3) / T) * 8 + (blockIdx.x & 7);
+    int qt = (blockIdx.x >> 3) % T;
+    const int gh = ((blockIdx.x >> 3) / T) * 8 + (blockIdx.x & 7);
     if (gh >= n_gh) return;
     const int grp = gh / P.h, head = gh % P.h;
     if constexpr (TRY_PATCH || WK != 0) clamp_fp16(true);      // (here and not at the table: nothing moves across it)
-    if constexpr (TRY_PATCH)
+    if constexpr (TRY_PATCH) {
         if (attn_patch_body<D>(P, qt, grp, head, inv_scale, smem)) return;
+        asm volatile("" : "+s"(qt));                            // nothing of what follows is computed in front of the patch path
+    }
     if constexpr (TRY_PATCH && WK == 0) clamp_fp16(false);
-    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : WK != 0 && TRY_PATCH && D > 64 ? 1 : 2)>(P, qt, grp, head, inv_scale, smem);
+    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : 2)>(P, qt, grp, head, inv_scale, smem);
 }
 
 // CU count and LDS bytes per CU of the current device, asked once per device (host-side queries, no allocation)
@@ -1317,9 +1320,12 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, float inv_
             lds = need > lds ? need : lds;
         }
         if (lds > ds.lds) return SSAM_EUNSUPPORTED;
-        const int wk = glb_operand(P.w);
-        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, 32> : attn_global_kernel<D, false, 32>)
-                  : wk == 64 ? (patch ? attn_global_kernel<D, true, 64> : attn_global_kernel<D, false, 64>)
+        // beside the patch path the operand form has registers for one block at a time at d = 80, and is no better than look-ups up to
+        // 32 x 32 and worse at 64 x 64 (16 images row-major, r = 0.4: 1260 us against 1190; 2 images, dense: 370 against 350)
+        constexpr bool PATCH_OPERAND = D <= 64;
+        const int wk = patch && !PATCH_OPERAND ? 0 : glb_operand(P.w);
+        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, PATCH_OPERAND ? 32 : 0> : attn_global_kernel<D, false, 32>)
+                  : wk == 64 ? (patch ? attn_global_kernel<D, true, PATCH_OPERAND ? 64 : 0> : attn_global_kernel<D, false, 64>)
                              : (patch ? attn_global_kernel<D, true, 0> : attn_global_kernel<D, false, 0>);
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
