@@ -54,8 +54,9 @@ struct AttnParams {
     const int32_t *out_rows;   // NULL: query p of group g goes to output row g*S+p; else to out_rows[g*S+p] (-1: dropped)
     int S, w, h, n_pre;
     float scale_log2e;
-    uint32_t half_one;      // global kernel's products with the bias table (see bias_shift): their one in fp16,
-    float table_inv;        // and what turns a bias into an entry
+    uint32_t half_one;      // global kernel, see bias_shift: 2^shift in fp16
+    float table_one;        // and in fp32
+    float table_inv;        // what turns a bias into an entry: 1 / (scale * 2^shift)
 };
 
 template <int D>
@@ -114,11 +115,11 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
 //
 // Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_chunk_step_onehot, PatchPipe) every entry
-// meets every key, most of them as a zero, and an infinity would make NaNs of the query's whole row.  So there
+// meets every key, most of them as a zero, and an infinity would make NaNs of the query's whole row.  So
 //   * entries past the range of fp16 become +-65504 (clamp_fp16), which as a logit is 65504 * scale, and
-//   * with a small scale the table is 2^shift times smaller and the ones of that matrix are 2^shift: shift is the least that
-//     puts 65504 * 2^shift * scale past 128 (bias_shift), since exp(-128) is the "no weight" that such a bias asks for.
-// Look-ups take infinities as they are: -inf gives the keys it belongs to no weight and leaves the others alone.
+//   * with a small scale the table is 2^shift times smaller and the ones of that matrix, or what a looked-up entry is multiplied
+//     by, are 2^shift: shift is the least that puts 65504 * 2^shift * scale past 128 (bias_shift), since exp(-128) is the "no
+//     weight" that such a bias asks for.
 inline int bias_shift(float scale)
 {
     int n = 0;
@@ -126,7 +127,7 @@ inline int bias_shift(float scale)
     return n;
 }
 // bit 23 of the mode register: fp16 results past the range are clamped instead of rounded to infinity
-__device__ __forceinline__ void clamp_fp16(bool on) { __builtin_amdgcn_s_setreg(1 | 23 << 6 | (1 - 1) << 11, on); }
+__device__ __forceinline__ void clamp_fp16() { __builtin_amdgcn_s_setreg(1 | 23 << 6 | (1 - 1) << 11, 1); }
 
 __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; }
 // Entries per table of the operand form, 0: look-ups.  Two images of 50 x 50, d = 80: 111 us by look-up, 88 by operand; of
@@ -231,14 +232,13 @@ __device__ __forceinline__ void build_bias_rows_window(const bf16x8 *qf, const b
 //   FULL:   the chunk has all NB blocks (nb is not looked at: no per-block branches, no dummy scores)
 //   MIXADD: the column part of the bias is added by one mixed-precision fma (fp16 operand widened inside the
 //           instruction) instead of convert + add
-//   RAW:    the tables hold bias / scale and the scores stay unscaled: logit = (s + bh + bw) * scale_log2e
+//   RAW:    the tables hold bias / (scale * one) and the scores stay unscaled: logit = (s + (bh + bw) * one) * scale_log2e
 //           (global kernel); otherwise the tables hold bias * log2e and logit = s * scale_log2e + bh + bw
 constexpr float ATTN_LAG = 8.f;
 
 // Second half of a chunk step, the same for every way of forming the scores: s holds the chunk's logits (RAW: before
 // the multiplication by scale_log2e), mx their maximum over this lane's keys, in the same units.
-// MASKED: all logits of a chunk may be -inf: a query that has met no other key yet takes 0 as its reference.
-template <int D, int NB, bool FULL, bool RAW, bool MASKED = false>
+template <int D, int NB, bool FULL, bool RAW>
 __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB], float mx, const bf16 *Vs,
                                                 const int (&blk)[NB], int nb_, float scale_log2e)
 {
@@ -254,7 +254,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
     const bool move = mx > st.m + ATTN_LAG;
     if (__builtin_amdgcn_ballot_w64(move) != 0) {
         const float mnew = move ? mx : st.m;
-        const float alpha = MASKED && !move ? 1.f : __builtin_amdgcn_exp2f(st.m - mnew);
+        const float alpha = __builtin_amdgcn_exp2f(st.m - mnew);
         st.m = mnew;
         if constexpr (!C::ONES) st.l *= alpha;
 #pragma unroll
@@ -262,7 +262,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.o[dt][r] *= alpha;
     }
-    const float mref = MASKED && st.m == -INFINITY ? 0.f : st.m;
+    const float mref = st.m;
     float psum = 0.f;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -308,7 +308,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
 template <int D, int NB, bool RAGGED, bool FULL, typename TabT, bool MIXADD = false, bool RAW = false>
 __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
                                                 const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB], int nb_,
-                                                int S, float scale_log2e, const TabT *tq_h, const TabT *tq_w)
+                                                int S, float scale_log2e, const TabT *tq_h, const TabT *tq_w, float one = 1.f)
 {
     using C = AttnCfg<D>;
     const int nb = FULL ? NB : nb_;
@@ -354,11 +354,12 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
                     if constexpr (MIXADD) {
                         static_assert(sizeof(TabT) == 2, "bias tables are fp16");
                         const uint32_t bw16 = *reinterpret_cast<const uint16_t *>(tqw + (c >> 16));
-                        val = RAW ? s[b][r] + bh : s[b][r] * scale_log2e + bh;   // the compiler forms this mixed op by itself
-                        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val));
+                        val = RAW ? fmaf(bh, one, s[b][r]) : s[b][r] * scale_log2e + bh;   // the compiler forms these mixed ops by itself
+                        if constexpr (RAW) asm("v_fma_mix_f32 %0, %1, %3, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val), "s"(one));
+                        else asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val));
                     } else {
                         const float bw = (float)*reinterpret_cast<const TabT *>(tqw + (c >> 16));
-                        val = RAW ? s[b][r] + bh + bw : s[b][r] * scale_log2e + bh + bw;
+                        val = RAW ? fmaf(bw, one, fmaf(bh, one, s[b][r])) : s[b][r] * scale_log2e + bh + bw;
                     }
                     if (RAGGED) val = (key0[b] + 8 * g + 4 * half + e < S) ? val : -INFINITY;
                     s[b][r] = val;
@@ -367,7 +368,7 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
             }
         }
     }
-    attn_softmax_pv<D, NB, FULL, RAW, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
+    attn_softmax_pv<D, NB, FULL, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
 }
 
 // Patches: scores of 32-key blocks that are 4 x 8 patches of stride 2 in the grid: key k of a block (bits c0 r1'.. in
@@ -976,7 +977,7 @@ __device__ __forceinline__ void build_bias_rows_patch(const bf16x8 *qf, const bf
 // them) are looked at first, under the latency of the first K, V and Q requests: false = some block is not a patch, nothing has
 // been stored, and the caller takes the general path.  w is a power of two, 16 or more: S is a multiple of the tile.
 template <int D>
-__device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int grp, int head, float inv_scale, unsigned char *smem)
+__device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
 {
     using C = AttnCfg<D>;
     using Pipe = PatchPipe<D>;
@@ -1137,7 +1138,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
 // The general path of a workgroup: any order, any S (attn_chunk_step_onehot).  WK: see build_bias_rows' table; NB: key
 // blocks per softmax chunk, as many as the register budget of two waves per SIMD allows.
 template <int D, int WK, int NB>
-__device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, int grp, int head, float inv_scale, unsigned char *smem)
+__device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
 {
     using C = AttnCfg<D>;
     constexpr int LOADS = GLB_TILE * C::CH / 256;       // 16-byte chunks per thread per operand
@@ -1201,7 +1202,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 
     ATTN_LOAD_TILE(0 < P.n_pre ? 0 : qt, 3)       // in flight while the bias rows are formed
     set_ones_columns<D>(Vs, GLB_TILE, tid, 256);
-    build_bias_rows<D, GlbTab>(qf, P.rel_h, P.rel_w, D, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq_lane, WK ? P.table_inv : inv_scale);
+    build_bias_rows<D, GlbTab>(qf, P.rel_h, P.rel_w, D, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq_lane, P.table_inv);
 
     WaveState<D> st;
     init_state<D>(st);
@@ -1227,8 +1228,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
                 else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
             } else {
                 const int nb = min(NB, nblk - c0);
-                if (ragged) attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
-                else attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane);
+                if (ragged) attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
+                else attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
             }
             if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
         }
@@ -1248,7 +1249,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 // path where a block is not a patch).  !TRY_PATCH: the general path only.
 template <int D, bool TRY_PATCH, int WK>
 __global__ void __launch_bounds__(256, 2)
-attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
+attn_global_kernel(AttnParams P, int T, int n_gh)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // the query tiles of one (image, head) run on one XCD (workgroup b sits on XCD b & 7), whose L2 then
@@ -1257,13 +1258,12 @@ attn_global_kernel(AttnParams P, int T, int n_gh, float inv_scale)
     const int gh = ((blockIdx.x >> 3) / T) * 8 + (blockIdx.x & 7);
     if (gh >= n_gh) return;
     const int grp = gh / P.h, head = gh % P.h;
-    if constexpr (TRY_PATCH || WK != 0) clamp_fp16(true);      // (here and not at the table: nothing moves across it)
+    clamp_fp16();                                               // (here and not at the table: nothing moves across it)
     if constexpr (TRY_PATCH) {
-        if (attn_patch_body<D>(P, qt, grp, head, inv_scale, smem)) return;
+        if (attn_patch_body<D>(P, qt, grp, head, smem)) return;
         asm volatile("" : "+s"(qt));                            // nothing of what follows is computed in front of the patch path
     }
-    if constexpr (TRY_PATCH && WK == 0) clamp_fp16(false);
-    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : 2)>(P, qt, grp, head, inv_scale, smem);
+    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : 2)>(P, qt, grp, head, smem);
 }
 
 // CU count and LDS bytes per CU of the current device, asked once per device (host-side queries, no allocation)
@@ -1285,7 +1285,7 @@ inline int device_shape(DeviceShape &out)
 }
 
 template <int D>
-int launch_attention(const AttnParams &P, int groups, int mask_block, float inv_scale, hipStream_t st)
+int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_t st)
 {
     DeviceShape ds;
     if (int rc = device_shape(ds); rc != SSAM_OK) return rc;
@@ -1330,7 +1330,7 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, float inv_
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return SSAM_EHIP;
-        hipLaunchKernelGGL(kern, dim3((unsigned)((long)T * ssam_div_up(groups * P.h, 8) * 8)), dim3(256), lds, st, P, T, groups * P.h, inv_scale);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((long)T * ssam_div_up(groups * P.h, 8) * 8)), dim3(256), lds, st, P, T, groups * P.h);
     }
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
@@ -1372,16 +1372,16 @@ extern "C" int ssam_sparse_attention(const void *q, const void *k, const void *v
     P.n_pre = ssam_prefix_tiles(ssam_div_up(S, mask_block), r);
     P.scale_log2e = scale * LOG2E;
     if (!(scale > 0.f)) return SSAM_EINVAL;      // the global kernel's bias table holds bias / scale
-    const float inv_scale = 1.0f / scale;
     const int shift = bias_shift(scale);
     P.half_one = 0x3c00u + ((uint32_t)shift << 10);
-    P.table_inv = ldexpf(inv_scale, -shift);
+    P.table_one = ldexpf(1.f, shift);
+    P.table_inv = ldexpf(1.f / scale, -shift);
     hipStream_t st = (hipStream_t)stream;
     switch (d) {
-    case 64: return launch_attention<64>(P, groups, mask_block, inv_scale, st);
-    case 80: return launch_attention<80>(P, groups, mask_block, inv_scale, st);
-    case 32: return launch_attention<32>(P, groups, mask_block, inv_scale, st);
-    case 16: return launch_attention<16>(P, groups, mask_block, inv_scale, st);
+    case 64: return launch_attention<64>(P, groups, mask_block, st);
+    case 80: return launch_attention<80>(P, groups, mask_block, st);
+    case 32: return launch_attention<32>(P, groups, mask_block, st);
+    case 16: return launch_attention<16>(P, groups, mask_block, st);
     default: return SSAM_EUNSUPPORTED;
     }
 }

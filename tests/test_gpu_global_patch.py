@@ -52,7 +52,7 @@ def test_growing_logits(d, grow):
 
 
 @pytest.mark.parametrize("w,d,order,scale", [(20, 64, "row", 1e-3), (31, 16, "row", 1e-5), (32, 80, "row", 1e-3), (50, 64, "row", 0.125), (50, 80, "position", 1e-3),
-                                             (64, 32, "row", 1e-3), (64, 80, "row", 1e-5), (72, 64, "position", 1e-3), (72, 80, "row", 1e-3),
+                                             (64, 32, "row", 1e-3), (64, 80, "row", 1e-5), (72, 64, "position", 1e-3), (72, 80, "row", 1e-5),
                                              (16, 64, "position", 0.125), (32, 16, "position", 1e-5), (64, 80, "position", 1e-3), (64, 32, "position", 1e-3)])
 def test_bias_past_fp16(w, d, order, scale):
     """Bias / scale, what the kernel's tables hold, past the range of fp16: a bias of -120 at scales of 1e-3 and 1e-5, of -16384 at
