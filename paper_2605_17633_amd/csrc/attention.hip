@@ -757,6 +757,8 @@ size_t global_lds_bytes(int w)
 //   * K and V blocks go from memory straight into two rings of three blocks in LDS, two blocks ahead (no registers, no LDS
 //     writes, one barrier per block).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
 //     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
+//     With d = 16 and 32 a block is two thirds and less of the work between two barriers, so they come by twos (UNIT): r = 1,
+//     2 images of 64 x 64, d = 32 158 -> 139 us, d = 16 135 -> 127, below what a tile of 128 keys at a time takes (153, 126);
 //   * the exponent reference moves by whole powers of two, so that the rare rescaling is exact and can also be applied to
 //     the probabilities of block b - 1 that still wait for their P V.
 constexpr int PATCH_RING = 3;
@@ -765,9 +767,12 @@ template <int D>
 struct PatchPipe {
     using C = AttnCfg<D>;
     static constexpr int SLOT = 32 * D * 2;                       // bytes of a block of K or V
+    static constexpr int UNIT = D <= 32 ? 2 : 1;                  // blocks requested together, between two barriers
+    static constexpr int RING = PATCH_RING * UNIT * SLOT;         // bytes of a ring
     static constexpr int NQ = 1 + C::KS, NP = 2 * C::DT;          // MFMAs of a block's scores (bias first) and of its P V
     static_assert(NQ == NP || NQ == NP + 1, "scores and P V alternate");
-    static constexpr int LOADS_HI = (C::CH + 3) / 4;              // 1 KB requests of K and V of a block: CH over four waves
+    static constexpr int LOADS = UNIT * C::CH;                    // 1 KB requests of K and V of a unit, over four waves
+    static constexpr int LOADS_HI = (LOADS + 3) / 4;
     static constexpr int AHEAD = 3, FR = 4;                       // operand fragments are read three MFMAs ahead
 
     // chunk c of row `row` sits at chunk position c ^ swz(row): 16 rows at one chunk then touch 16 distinct 16-byte banks
@@ -911,7 +916,7 @@ inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_bloc
 template <int D>
 inline __host__ __device__ size_t patch_lds_bytes(int w, int n_blocks)
 {
-    return (size_t)2 * PATCH_RING * PatchPipe<D>::SLOT + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
+    return (size_t)2 * PatchPipe<D>::RING + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
 }
 
 // The bias table (layout of build_bias_rows) of a wave whose 32 queries are a patch: rows qr0 .. qr0 + 6 and columns
@@ -981,7 +986,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
 {
     using C = AttnCfg<D>;
     using Pipe = PatchPipe<D>;
-    constexpr int SLOT = Pipe::SLOT, V0 = PATCH_RING * SLOT, ONES0 = 2 * PATCH_RING * SLOT;
+    constexpr int SLOT = Pipe::SLOT, UNIT = Pipe::UNIT, V0 = Pipe::RING, ONES0 = 2 * Pipe::RING;
     static_assert(ONES0 <= 64 * 1024, "the rings are filled through M0");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
     const int lgw = 31 - __builtin_clz(P.w), nact = P.n_pre + (qt >= P.n_pre ? 1 : 0), nblk = nact * (GLB_TILE / 32);
@@ -994,35 +999,34 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     const long base = (long)grp * P.S * P.row_stride + (long)head * D;
     const uint32_t rs2 = (uint32_t)P.row_stride * 2u;
     const unsigned char *kbase = reinterpret_cast<const unsigned char *>(P.k + base), *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
-    // request j of a block (K: j < CH/2, then V) is wave j % 4's: lane l brings the chunk that belongs at 16-byte place
-    // 64*(j % (CH/2)) + l of the block
+    // request j of a unit (K: j < LOADS/2, then V) is wave j % 4's: lane l brings the chunk that belongs at 16-byte place
+    // 64*(j % (LOADS/2)) + l of the unit
     uint32_t src_off[Pipe::LOADS_HI];
 #pragma unroll
     for (int i = 0; i < Pipe::LOADS_HI; ++i) {
-        const int j = wave + 4 * i, place = (j % (C::CH / 2)) * 64 + lane, row = place / C::CH, pos = place % C::CH;
+        const int j = wave + 4 * i, place = (j % (Pipe::LOADS / 2)) * 64 + lane, row = place / C::CH, pos = place % C::CH;
         src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row)) * 16u;
     }
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
-    auto key0_of = [&](int blk) {
-        blk = max(min(blk, nblk - 1), 0);        // past the end: the last block again, so that every wait below can count
-        const int a = blk >> 2;
+    auto key0_of = [&](int unit) {
+        const int blk = max(min(unit * UNIT, nblk - UNIT), 0), a = blk >> 2;   // past the end: the last unit again, so that every wait below can count
         return (a < P.n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32;
     };
-    auto request = [&](int kblk, int k_slot, int vblk, int v_slot) {       // slots in bytes; a negative block: not requested
-        const unsigned char *kb = kbase + (size_t)key0_of(kblk) * rs2, *vb = vbase + (size_t)key0_of(vblk) * rs2;
+    auto request = [&](int kunit, int k_slot, int vunit, int v_slot) {     // slots in bytes; a negative unit: not requested
+        const unsigned char *kb = kbase + (size_t)key0_of(kunit) * rs2, *vb = vbase + (size_t)key0_of(vunit) * rs2;
 #pragma unroll
         for (int i = 0; i < Pipe::LOADS_HI; ++i) {
             const int j = wave + 4 * i;                                    // wave-uniform
-            const bool is_k = j < C::CH / 2;
-            if (j >= C::CH || (is_k ? kblk : vblk) < 0) continue;
-            const uint32_t at = lds0 + (is_k ? k_slot + j * 1024 : V0 + v_slot + (j - C::CH / 2) * 1024);
+            const bool is_k = j < Pipe::LOADS / 2;
+            if (j >= Pipe::LOADS || (is_k ? kunit : vunit) < 0) continue;
+            const uint32_t at = lds0 + (is_k ? k_slot + j * 1024 : V0 + v_slot + (j - Pipe::LOADS / 2) * 1024);
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                          :: "s"(at), "v"(src_off[i]), "s"(is_k ? kb : vb) : "m0", "memory");
         }
     };
     request(0, 0, -1, 0);
-    request(1, SLOT, -1, 0);
-    request(2, 2 * SLOT, 0, 0);
+    request(1, UNIT * SLOT, UNIT == 1 ? -1 : 0, 0);
+    if constexpr (UNIT == 1) request(2, 2 * SLOT, 0, 0);
 
     const int qpos = qt * GLB_TILE + wave * 32 + l32;
     bf16x8 qf[C::KS];
@@ -1095,42 +1099,73 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
         pipe.va[u] = V0 + row * D * 2 + (((f0 >> 3) ^ Pipe::swz(row)) << 4) + (f0 & 7) * 2;
     }
 
-    // Block b: everything of block b - 1 has been read, so the scores of b (slot of K(b)) and V(b - 2) make room for K(b + 3) and
-    // V(b + 1); K(b + 1) and V(b - 1) were requested two blocks ago, and only the requests of one block are younger.
-    int s0 = 0, s1 = SLOT, s2 = 2 * SLOT;        // slots of block index b, b + 1, b + 2 modulo the ring
-    auto enter = [&](int b) {
-        if (C::CH % 4 == 0 || wave < C::CH % 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((C::CH + 3) / 4) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::CH / 4) : "memory");
-        LDS_BARRIER();
-        request(b + 3, s0, b + 1, s1);
-        pipe.bo = bo_tab[min(b + 1, nblk - 1)];
-    };
+    int s0 = 0, s1 = UNIT * SLOT, s2 = 2 * UNIT * SLOT;      // slots of unit u, u + 1, u + 2 modulo the ring
     auto rotate = [&]() { const int t = s0; s0 = s1; s1 = s2; s2 = t; };
     pipe.bo = bo_tab[0];
     pipe.template load<true, false, 0>(s0, 0);
     pipe.template load<true, false, 1>(s0, 0);
     pipe.template load<true, false, 2>(s0, 0);
     pipe.template steps<true, false, 1, false, 0>(s0, 0, 0.f);       // scores of block 0
-    enter(0);
-    pipe.template block<true, false, 0>(s1, s2);
-    rotate();
-    for (int b = 1; b < nblk - 1; b += 2) {      // nblk is a multiple of four
-        enter(b);
-        pipe.template block<true, true, 1>(s1, s2);
+    int last_v;                                  // where V of the last block is
+    if constexpr (UNIT == 1) {
+        // Block b: everything of block b - 1 has been read, so the scores of b (slot of K(b)) and V(b - 2) make room for K(b + 3) and
+        // V(b + 1); K(b + 1) and V(b - 1) were requested two blocks ago, and only the requests of one block are younger.
+        auto enter = [&](int b) {
+            if (Pipe::LOADS % 4 == 0 || wave < Pipe::LOADS % 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((Pipe::LOADS + 3) / 4) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(Pipe::LOADS / 4) : "memory");
+            LDS_BARRIER();
+            request(b + 3, s0, b + 1, s1);
+            pipe.bo = bo_tab[min(b + 1, nblk - 1)];
+        };
+        enter(0);
+        pipe.template block<true, false, 0>(s1, s2);
         rotate();
-        enter(b + 1);
-        pipe.template block<true, true, 0>(s1, s2);
+        for (int b = 1; b < nblk - 1; b += 2) {      // nblk is a multiple of four
+            enter(b);
+            pipe.template block<true, true, 1>(s1, s2);
+            rotate();
+            enter(b + 1);
+            pipe.template block<true, true, 0>(s1, s2);
+            rotate();
+        }
+        enter(nblk - 1);
+        pipe.template block<false, true, 1>(s1, s2);
+        // V of the last block was requested in front of the block before it
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        LDS_BARRIER();
+        last_v = s0;
+    } else {
+        // Unit u = blocks 2u and 2u + 1, whose scores, like those of block 2u + 2, need K of units u and u + 1, and whose P V, of blocks
+        // 2u - 1 and 2u, needs V of units u - 1 and u.  So K(u - 1) and V(u - 2) make room for K(u + 2) and V(u + 1), and what was
+        // requested a unit ago has to be there.
+        auto enter = [&](int u) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            LDS_BARRIER();
+            const int units = nblk / 2;
+            request(u + 2 < units ? u + 2 : -1, s2, u + 1 < units ? u + 1 : -1, s1);
+            pipe.bo = bo_tab[2 * u + 1];
+        };
+        enter(0);
+        pipe.template block<true, false, 0>(s0 + SLOT, 0);
+        pipe.bo = bo_tab[2];
+        pipe.template block<true, true, 1>(s1, s0);
         rotate();
+        for (int u = 1; u < nblk / 2 - 1; ++u) {
+            enter(u);
+            pipe.template block<true, true, 0>(s0 + SLOT, s2 + SLOT);
+            pipe.bo = bo_tab[2 * u + 2];
+            pipe.template block<true, true, 1>(s1, s0);
+            rotate();
+        }
+        enter(nblk / 2 - 1);
+        pipe.template block<true, true, 0>(s0 + SLOT, s2 + SLOT);
+        pipe.template block<false, true, 1>(0, s0);
+        last_v = s0 + SLOT;
     }
-    enter(nblk - 1);
-    pipe.template block<false, true, 1>(s1, s2);
-    // V of the last block was requested in front of the block before it
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    LDS_BARRIER();
-    pipe.template load<false, true, 0>(s1, s0);
-    pipe.template load<false, true, 1>(s1, s0);
-    pipe.template load<false, true, 2>(s1, s0);
-    pipe.template steps<false, true, 0, false, 0>(s1, s0, 0.f);      // P V of the last block (parity 1)
+    pipe.template load<false, true, 0>(0, last_v);
+    pipe.template load<false, true, 1>(0, last_v);
+    pipe.template load<false, true, 2>(0, last_v);
+    pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
     finish_and_store<D>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
     return true;
 }
