@@ -49,6 +49,15 @@ def _resources(stderr: str):
     return kernels
 
 
+HOT = ("gemm_bf16_nt_", "gemm_ring_kernel", "gemm_direct_kernel", "attn_")     # kernels that are written to a register budget
+
+
+def spilled(kernels):
+    """Messages for the kernels of HOT that spill."""
+    return [f"{k['name']}: {k['VGPRs Spill']} VGPRs spilled" for k in kernels
+            if k.get("VGPRs Spill", 0) > 0 and any(h in k["name"] for h in HOT)]
+
+
 def _compile(src: str, obj: str):
     cmd = [_hipcc(), *FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj]
     p = subprocess.run(cmd, capture_output=True, text=True)
@@ -85,19 +94,16 @@ def build_library(force: bool = True, jobs: int = 6) -> str:
     objs = [os.path.join(bdir, s.replace(".hip", ".o")) for s in SOURCES]
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         per_source = list(ex.map(_compile, SOURCES, objs))
-    # The GEMM and attention kernels are written to a register budget (two waves per SIMD): a variant that spills
+    # The GEMM and attention kernels are written to a register budget (two waves per SIMD or three): a variant that spills
     # runs at a fraction of its speed and would otherwise go unnoticed.  The figures are kept beside the objects.
-    spilled = []
     with open(os.path.join(bdir, "kernel_resources.txt"), "w") as f:
         for src, kernels in zip(SOURCES, per_source):
             for k in kernels:
                 f.write(f"{src} {k['name']} vgprs={k.get('VGPRs', -1)} agprs={k.get('AGPRs', -1)} "
                         f"scratch={k.get('ScratchSize', -1)} spill={k.get('VGPRs Spill', -1)} "
                         f"occupancy={k.get('Occupancy', -1)} lds={k.get('LDS Size', -1)}\n")
-                if k.get("VGPRs Spill", 0) > 0 and ("gemm_bf16_nt_" in k["name"] or "attn_" in k["name"]):
-                    spilled.append(f"{k['name']}: {k['VGPRs Spill']} VGPRs spilled")
-    if spilled:
-        raise RuntimeError("hot kernels spill registers:\n" + "\n".join(spilled))
+    if bad := spilled(k for kernels in per_source for k in kernels):
+        raise RuntimeError("hot kernels spill registers:\n" + "\n".join(bad))
     p = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)
     if p.returncode != 0:

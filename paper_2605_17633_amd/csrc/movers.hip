@@ -354,8 +354,9 @@ __device__ __forceinline__ T wave_inclusive_sum(T v)
 // then one scan over the workgroup places every index with a larger key and the lowest-index ties in ascending index
 // order.  One CU works alone here, so what counts is the length of the serial chain: the keys are read once and kept in
 // registers (ITEMS consecutive ones per thread; 16-byte loads), a pass is a histogram in LDS and a scan of its bins by
-// all threads (4096 scores: 32 -> 7.5 us; 16384: 63 -> 15; 65536: 160 -> 60; four 8-bit passes over memory with a serial
-// walk of the bins and two barriers for every 1024 scores of the compaction before).
+// all threads (4096 scores: 32 -> 7.5 us; 16384: 45 -> 13; 65536: 151 -> 50; four 8-bit passes over memory with a serial
+// walk of the bins and two barriers for every 1024 scores of the compaction before).  With ITEMS = 64 (more than 16384 scores) a
+// thread's 128 registers do not hold its keys and all the rest: 42 of them go through scratch (16400 scores: 34 us).
 constexpr int SEL_BINS = 2048;
 template <int ITEMS>
 __global__ void __launch_bounds__(SEL_THREADS)
