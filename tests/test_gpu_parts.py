@@ -292,8 +292,9 @@ def _sweep_case(M, N, K):
                                         (3, 4200, 2048, 256), (3, 4200, 2048, 1024), (3, 4150, 2048, 1024),
                                         (4, 8400, 2048, 256), (4, 8400, 2048, 1024), (4, 8350, 2048, 1024)])
 def test_linear_every_instantiation(tile, M, N, K, epi, packed):
-    """Every kernel instantiation the dispatcher can reach: large tile, its left-over launch (plain at K = 256,
-    cut along K at K = 1024 with a workspace), each epilogue, row-major and packed weights, ragged last rows."""
+    """Every kernel instantiation of the large tiles: large tile, its left-over launch (plain at K = 256, cut along K
+    at K = 1024 with a workspace), each epilogue, row-major and packed weights, ragged last rows (the kernels for small
+    problems: test_gpu_linear_small.py)."""
     if packed and tile == 2:
         pytest.skip("the 256x128 tile has no packed-weight form")
     announce("linear instantiation", tile, M, N, K, epi, packed)

@@ -4,6 +4,7 @@ import ctypes as C
 import pytest
 
 from paper_2605_17633_amd import binding as B
+from test_gpu_linear_small import FOLDED, FORM_CASES, MLP
 
 WS = 32 << 20
 
@@ -36,3 +37,12 @@ def test_large_problems_take_the_large_tiles():
         for N, K in ((2304, 768), (3840, 1280), (5120, 1280), (1280, 5120)):
             assert form(M, N, K, 0, True) < 16 and form(M, N, K, 0, False) < 16
     assert form(32768, 3840, 1280, 3, True, folded=True) == 4
+
+
+def test_the_gpu_tests_reach_every_small_kernel():
+    for f, packed, epi, M, N, K in FORM_CASES:
+        assert form(M, N, K, epi, packed, ws=0) == f, (f, packed, epi, M, N, K)
+    for f, M, N, K in FOLDED:
+        assert form(M, N, K, 3, True, folded=True) == f, (f, M, N, K)
+    for f, rows, Dm, D in MLP:
+        assert form(rows, Dm, D, 1, True) == f, (f, rows, Dm, D)
