@@ -16,14 +16,16 @@
 // the transposing LDS read of gfx950 (ds_read_b64_tr_b16: a 16-lane group reads
 // 4 rows x 16 columns and every lane receives one column), so V is staged
 // exactly like K and never transposed in memory.
-// Key blocks are processed in chunks of two (64 keys; the register budget of two
-// waves per SIMD): all score MFMAs of the chunk first, one max / one rescale of
-// the running output per chunk, then all P V MFMAs.
-// Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept
-// in LDS as fp16, pre-multiplied by log2 e; the inner loop adds two table
-// look-ups per score through per-key byte offsets.  Global kernel: scattered into
-// entry-major rows B^H[key_row][q], B^W[key_col][q]; window kernel: stored as the
-// MFMA tile comes out, U[q][m], a key being entry q_row - key_row + w - 1.
+// Key blocks (32 keys) are processed in chunks of one (window kernel, patch path) or as many as the register budget of
+// two waves per SIMD allows (two to four): all score MFMAs of the chunk first, one max and, where the reference moves,
+// one rescale of the running output per chunk, then all P V MFMAs; the patch path interleaves three blocks instead.
+// Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept in LDS as fp16, query-major.  How a
+// score gets its two entries:
+//   window kernel: two look-ups at per-key byte offsets, the entries stored as the MFMA tile comes out, U[q][m], a key
+//                  being entry q_row - key_row + w - 1, times log2 e;
+//   global kernel: as a product with the table in the scores' accumulator: of one 16-entry operand on orders whose
+//                  blocks are patches (PatchPipe), of the whole row of up to 64 entries a table on others
+//                  (attn_chunk_step_onehot); above 64 x 64 by two look-ups.
 // Memory requests are spread over a problem's / a tile's phases (see the prefetch
 // macros): a wave whose loads do not fit the CU's request queues waits instead of
 // computing, and a wait placed behind a branch or on a value that is used at once
@@ -35,9 +37,10 @@
 //                  and V in LDS, the next problem's K and V prefetched into registers
 //                  and its Q straight into LDS, in three pieces, the rel-pos tables
 //                  resident in LDS;
-//   global kernel: one workgroup per (128-query mask tile, image, head), 4 waves, two
-//                  workgroups per CU, active 128-key tiles streamed through LDS with
-//                  register prefetch (K and V requested at different points).
+//   global kernel: one workgroup per (128-query mask tile, image, head), 4 waves, two or
+//                  more workgroups per CU; active key blocks go straight into rings in LDS (patch
+//                  path), or active 128-key tiles through registers into LDS (K and V requested
+//                  at different points).
 #include "common.h"
 
 namespace {
@@ -757,8 +760,8 @@ size_t global_lds_bytes(int w)
 //   * K and V blocks go from memory straight into two rings of three blocks in LDS, two blocks ahead (no registers, no LDS
 //     writes, one barrier per block).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
 //     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
-//     With d = 16 and 32 a block is two thirds and less of the work between two barriers, so they come by twos (UNIT): r = 1,
-//     2 images of 64 x 64, d = 32 158 -> 139 us, d = 16 135 -> 127, below what a tile of 128 keys at a time takes (153, 126);
+//     With d = 16 and 32 one block is little work between two barriers, so blocks come by twos there (UNIT): 2 images of 64 x 64,
+//     r = 1, d = 32 158 -> 139 us, d = 16 135 -> 127; a tile of 128 keys at a time takes 153 and 126;
 //   * the exponent reference moves by whole powers of two, so that the rare rescaling is exact and can also be applied to
 //     the probabilities of block b - 1 that still wait for their P V.
 constexpr int PATCH_RING = 3;

@@ -242,11 +242,11 @@ template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF>
 int launch_ring_tile(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
                      const GemmLd &ld, const GemmRowMap &rm, const GemmFold &fold, hipStream_t st)
 {
-    constexpr size_t lds = gemm_ring_lds_bytes<BM, BN, GEMM_BK, STAGES>();
+    constexpr size_t lds = gemm_ring_lds_bytes<BM, BN, STAGES>();
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { ssam_div_up(M, BM), ssam_div_up(N, BN), 0, 0 };
     tr.tile_count = tr.tiles_m * tr.tiles_n;
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, GEMM_BK, STAGES, EPI, WPACK, LNF>), dim3(ssam_div_up(tr.tile_count, 8) * 8), dim3(256), lds, st,
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, STAGES, EPI, WPACK, LNF>), dim3(ssam_div_up(tr.tile_count, 8) * 8), dim3(256), lds, st,
                        A, W, bias, C, M, N, K, ld, tr, rm, fold);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;

@@ -1,7 +1,7 @@
 // The contraction of gemm_kernel.h, packed weights, for problems of at most one 32x32 tile per CU (a 28 x 28 grid, batch 1: 313
 // kept rows x 768 columns): too few tiles for the rings of gemm_ring.h to give every CU a workgroup.
 //
-// What bounds such a problem is what one CU can pull from the L2, about 50 bytes a ns: all CUs have to pull.  A workgroup's tile
+// What bounds such a problem is what one CU can pull from the L2, 50 to 60 bytes a ns (8 KB in 0.14 us here): all CUs have to pull.  A workgroup's tile
 // is 32x32; its four waves cut K between them (wave w takes the k-steps w, w + 4, ...) and load their MFMA fragments straight
 // into registers, DIRECT_DEPTH steps ahead, with no LDS and no barrier until the four partial tiles are added there, in wave
 // order.  Packed weights only: with rows in both operands the half cache lines of the fragments cost what the width gains.

@@ -11,21 +11,23 @@
 //     Rows are swizzled on the memory side: a lane requests the 16-byte chunk that belongs at its place in LDS, so that
 //     the fragment reads are conflict-free; packed weights arrive as fragments already;
 //   * K is never cut: no partial tiles in memory and no second launch to add them (4 us and more in a chain of kernels).
-// Past one round of workgroups the traffic from the L2 bounds it (about 20 TB/s) and the larger tiles of
-// gemm_kernel.h are faster again.
-// Measured (us, packed weights | row-major; before = the loop of gemm_kernel.h with its K-split launch):
-//   784 x 2304 x 768 21 -> 7.7 | 22 -> 8.1; 1638 x 768 x 3072 25.9 -> 20.1 | 28 -> 20.8; 4096 x 768 x 768 14.4 -> 11.1 |
-//   17.8 -> 11.6; 1638 x 3072 x 768 + GELU 18.6 -> 16.2 | 22.1 -> 16.4; 8192 x 576 x 2304 - | 45 -> 32;
-//   8192 x 2304 x 768 32.3 (kept) | 44 -> 38.  Slabs of 32, four stages, wave priority and 256-row tiles gave nothing more.
+//   * what the epilogue reads is requested before the loop ends (gemm_bf16_nt_body's epilogue begins with it: there other
+//     workgroups' main loops cover it).
+// Past one round of workgroups the traffic from the L2 bounds it and the larger tiles of gemm_kernel.h are faster again: a slab of a
+// 64x64 tile is 16 KB, and takes 0.31 us with one workgroup to a CU and 0.565 with three, 22 TB/s over the chip.
+// Measured (us, weights that no cache holds, packed | row-major; before = the loop of gemm_kernel.h with its K-split launch):
+//   784 x 2304 x 768 21.6 -> 8.9 | 23 -> 9.3; 1638 x 768 x 3072 26.2 -> 20.9 | 28.5 -> 22.3; 4096 x 768 x 768 15 -> 11.8 | 18.1 -> 12.5;
+//   1638 x 3072 x 768 + GELU 20.4 -> 17.4 | 24.2 -> 18; 8192 x 576 x 2304 - | 48 -> 40.  Slabs of 32, four stages, wave priority, 256-row
+//   tiles and a non-temporal hint on the mapped store gave nothing more.
 // Blocks: ViT-B 28 x 28 windowed 88 -> 62 us; encoder ViT-B batch 1 1.57 -> 1.39 ms, row-major 800 x 800 batch 2 2.08 -> 1.80 ms.
 #pragma once
 
 #include "gemm_kernel.h"
 
-template <int BM, int BN, int BK, int STAGES>
+template <int BM, int BN, int STAGES>
 constexpr size_t gemm_ring_lds_bytes()
 {
-    size_t pipe = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16);
+    size_t pipe = (size_t)STAGES * (BM + BN) * GEMM_BK * sizeof(bf16);
     size_t epi = (size_t)4 * 32 * (BN / 2 + 4) * sizeof(float);
     return pipe > epi ? pipe : epi;
 }
@@ -37,18 +39,17 @@ __device__ __forceinline__ void gemm_load_lds16(uint32_t lds, const bf16 *src)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "m0", "memory");
 }
 
-template <int BM, int BN, int BK, int STAGES, int EPI, bool WPACK, bool LNF = false>
+template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF = false>
 __device__ __forceinline__ void
 gemm_ring_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                bf16 *C, int M, int N, int K, const GemmLd &ld, const GemmTileRange &tr, const GemmRowMap &rm,
                int bid, const GemmFold &fold)
 {
-    constexpr int WGM = 2, WGN = 2, WM = BM / WGM, WN = BN / WGN, MT16 = WM / 16, NT16 = WN / 16, KS = BK / 32;
+    constexpr int BK = GEMM_BK, WGM = 2, WGN = 2, WM = BM / WGM, WN = BN / WGN, MT16 = WM / 16, NT16 = WN / 16, KS = BK / 32;
     constexpr int CPR = BK / 8, RPI = 64 / CPR;                 // 16-byte chunks per row of a slab; rows per request
     constexpr int NA = BM * BK / 512 / 4, NW = BN * BK / 512 / 4, L = NA + NW;     // 1 KB requests per wave and slab
-    static_assert(BK == 32 || BK == 64, "swizzle");
     static_assert(NA >= 1 && NW >= 1 && (size_t)STAGES * (BM + BN) * BK * 2 <= 64 * 1024, "ring within the reach of M0");
-    static_assert(STAGES >= 2 && L * (STAGES - 2) < 64, "vmcnt is 6 bits");
+    static_assert((STAGES == 2 || STAGES == 3) && L < 64, "one wait per depth; vmcnt is 6 bits");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16 *ring = reinterpret_cast<bf16 *>(smem);
     constexpr int STAGE = (BM + BN) * BK;                      // elements of a stage: A rows, then W
@@ -65,7 +66,7 @@ gemm_ring_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const flo
     const int n = (K + BK - 1) / BK;
 
     const int rl = lane / CPR, cp = lane % CPR;
-    auto swz = [](int row) { return BK == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
+    auto swz = [](int row) { return (row >> 1) & 7; };
     const bf16 *ga[NA], *gw[NW];
     int ka[NA], kw[NW];                          // k of the lane's chunk inside a slab
 #pragma unroll
@@ -141,11 +142,8 @@ gemm_ring_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const flo
     float2 rst[LNF ? RR : 1];
     auto slab = [&](int it, int st) {
         // this wave's requests for slab `it` have landed when no more than those of the slabs behind it are out
-        const int behind = min(STAGES - 2, n - 1 - it);
-        if (STAGES == 2 || behind == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        else if (STAGES == 3 || behind == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * L) : "memory");
-        static_assert(STAGES <= 4, "one wait per depth");
+        if (STAGES == 2 || it == n - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L) : "memory");
         LDS_BARRIER();                           // every wave's have; and every wave is done reading the stage before
         if (it + STAGES - 1 < n) request(it + STAGES - 1, st == 0 ? STAGES - 1 : st - 1);
         const bf16 *as = ring + st * STAGE, *ws = as + BM * BK;
@@ -246,10 +244,10 @@ gemm_ring_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const flo
     }
 }
 
-template <int BM, int BN, int BK, int STAGES, int EPI, bool WPACK, bool LNF = false>
-__global__ void __launch_bounds__(256, (gemm_ring_lds_bytes<BM, BN, BK, STAGES>() <= 40 * 1024 ? 4 : gemm_ring_lds_bytes<BM, BN, BK, STAGES>() <= 53 * 1024 ? 3 : 2))
+template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF = false>
+__global__ void __launch_bounds__(256, (gemm_ring_lds_bytes<BM, BN, STAGES>() <= 53 * 1024 ? 3 : 2))
 gemm_ring_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                  bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
-    gemm_ring_body<BM, BN, BK, STAGES, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, (int)blockIdx.x, fold);
+    gemm_ring_body<BM, BN, STAGES, EPI, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, (int)blockIdx.x, fold);
 }
