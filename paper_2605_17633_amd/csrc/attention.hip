@@ -273,11 +273,11 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 s[b][r] = __builtin_amdgcn_exp2f(RAW ? fmaf(s[b][r], scale_log2e, -mref) : s[b][r] - mref);
-                if constexpr (!C::ONES) psum += s[b][r];
+                if constexpr (!C::ONES && !RAW) psum += s[b][r];
             }
         }
     }
-    if constexpr (!C::ONES) st.l += psum;
+    if constexpr (!C::ONES && !RAW) st.l += psum;
     // transposing read: lane li of a 16-lane group points at row (li >> 2), column chunk (li & 3) of a
     // 4-key x 16-feature block and receives the 4 keys of feature column li
     const int li = lane & 15, fblk = (lane >> 4) & 1;
@@ -290,6 +290,15 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
                 bf16x8 p;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) p[e] = (bf16)s[b][8 * t + e];
+                if constexpr (!C::ONES && RAW) {
+                    // the sum of what P V multiplies, the rounded probabilities, as with the ones columns: the rounding of a dominant
+                    // one cancels (with sums of the unrounded ones the error is 1-2 % larger where one key dominates)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        const bf16x2 pair = { p[e], p[e + 1] };
+                        st.l = __builtin_amdgcn_fdot2_f32_bf16(pair, bf16x2{ (bf16)1.f, (bf16)1.f }, st.l, false);
+                    }
+                }
 #pragma unroll
                 for (int dt = 0; dt < C::DT; ++dt) {
                     int col = dt * 32 + 16 * fblk + 4 * (li & 3);
@@ -762,8 +771,10 @@ size_t global_lds_bytes(int w)
 //     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
 //     With d = 16 and 32 one block is little work between two barriers, so blocks come by twos there (UNIT): 2 images of 64 x 64,
 //     r = 1, d = 32 158 -> 139 us, d = 16 135 -> 127; a tile of 128 keys at a time takes 153 and 126;
-//   * the exponent reference moves by whole powers of two, so that the rare rescaling is exact and can also be applied to
-//     the probabilities of block b - 1 that still wait for their P V.
+//   * where the exponent reference moves in block b, the output is rescaled in front of block b + 1, behind P V of block b - 1, whose probabilities are still
+//     in units of the reference before.  (Moving it by whole powers of two would allow rescaling those probabilities instead,
+//     but then a query's largest probability is no longer exactly 1 and is rounded to bf16 like the others: up to 19 % more
+//     error where one key dominates.)
 constexpr int PATCH_RING = 3;
 
 template <int D>
@@ -795,6 +806,8 @@ struct PatchPipe {
     uint32_t bo;                     // table offsets of the first key of the block whose scores are formed next
     f32x16 s[2];
     bf16x8 p[2][2], frag[FR];
+    float alpha;                     // the reference moved by this factor in the block before (moved, wave-uniform)
+    bool moved;
 
     // operand I of the interleaved sequence of a step with scores (HQ) and / or P V (HP): even places scores, odd P V
     template <bool HQ, bool HP> static constexpr bool is_q(int k) { return HQ && (!HP || k % 2 == 0); }
@@ -852,9 +865,12 @@ struct PatchPipe {
         if constexpr (J < J1) {
             const float e0 = __builtin_amdgcn_exp2f(fmaf(s[PAR][2 * J], scale_log2e, -mref));
             const float e1 = __builtin_amdgcn_exp2f(fmaf(s[PAR][2 * J + 1], scale_log2e, -mref));
-            if constexpr (!C::ONES) st.l += e0 + e1;
             u32x4 w = __builtin_bit_cast(u32x4, p[PAR][J / 4]);
-            w[J % 4] = pack_bf16x2(e0, e1);
+            const uint32_t pair = pack_bf16x2(e0, e1);
+            w[J % 4] = pair;
+            // the sum of what P V multiplies, the rounded probabilities, as with the ones columns: one instruction, and the rounding of
+            // a dominant one cancels
+            if constexpr (!C::ONES) st.l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), bf16x2{ (bf16)1.f, (bf16)1.f }, st.l, false);
             p[PAR][J / 4] = __builtin_bit_cast(bf16x8, w);
             exp_pairs<PAR, J + 1, J1>(mref);
         }
@@ -873,6 +889,19 @@ struct PatchPipe {
         }
     }
 
+    // the output in units of the present reference, if that moved in the block before
+    __device__ __forceinline__ void rescale()
+    {
+        if (!moved) return;
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // P V MFMAs may be in flight (as in finish_and_store)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[dt][r] *= alpha;
+    }
+
     // softmax of block b (parity PAR) with, behind it, the scores of b + 1 (HQ) and P V of b - 1 (HP)
     template <bool HQ, bool HP, int PAR>
     __device__ __forceinline__ void block(int k_slot, int v_slot)
@@ -886,24 +915,16 @@ struct PatchPipe {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
         mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
         const bool move = mx > st.m + ATTN_LAG;         // see attn_softmax_pv
-        if (__builtin_amdgcn_ballot_w64(move) != 0) {
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");      // earlier P V MFMAs may be in flight (as in finish_and_store)
-            __builtin_amdgcn_sched_barrier(0);
-            const float mnew = move ? ceilf(mx) : st.m;
-            const int e = move ? (int)fmaxf(st.m - mnew, -1000.f) : 0;
-            st.m = mnew;
-            if constexpr (!C::ONES) st.l = ldexpf(st.l, e);
-#pragma unroll
-            for (int dt = 0; dt < C::DT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) st.o[dt][r] = ldexpf(st.o[dt][r], e);
-            if constexpr (HP) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) p[PAR ^ 1][t][i] = (bf16)ldexpf((float)p[PAR ^ 1][t][i], e);
+        const bool any = __builtin_amdgcn_ballot_w64(move) != 0;
+        if (__builtin_expect(any || moved, 0)) {
+            rescale();                                  // P V of the block before is in the output: what moved there
+            alpha = 1.f;
+            moved = any;
+            if (move) {
+                alpha = __builtin_amdgcn_exp2f(st.m - mx);
+                st.m = mx;
             }
+            if constexpr (!C::ONES) st.l *= alpha;
         }
         __builtin_amdgcn_sched_barrier(0);
         // ahead of the other workgroup's requests, maxima and barriers (1 % at batch 16, 5 % when a launch is one round)
@@ -1084,6 +1105,8 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     const int li = lane & 15, fblk = (lane >> 4) & 1;
     Pipe pipe{ st, qf, smem, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e, half, C::ONES && fblk != 0 };
     pipe.ones_at = ONES0;
+    pipe.moved = false;
+    pipe.alpha = 1.f;
     // operand a of the bias product: lane (key l32, half) holds E[l32][8*half + e]
     const int rr = patch_rr(l32), cc = patch_cc(l32);
     const _Float16 one = __builtin_bit_cast(_Float16, (uint16_t)P.half_one);
@@ -1165,6 +1188,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
         pipe.template block<false, true, 1>(0, s0);
         last_v = s0 + SLOT;
     }
+    pipe.rescale();
     pipe.template load<false, true, 0>(0, last_v);
     pipe.template load<false, true, 1>(0, last_v);
     pipe.template load<false, true, 2>(0, last_v);

@@ -7,6 +7,7 @@
 #include "ssam.h"
 
 typedef __bf16 bf16;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -68,7 +69,6 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4 &v, float *f)
 // two floats -> two bf16 (round to nearest even) packed low|high
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     bf16x2 v = { (__bf16)lo, (__bf16)hi };
     return __builtin_bit_cast(uint32_t, v);
 }

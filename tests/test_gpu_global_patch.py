@@ -77,3 +77,33 @@ def test_bias_past_fp16(w, d, order, scale):
     logit[~((tile[None, :] < int(r * (tile[-1] + 1) + 1e-6)) | (tile[None, :] == tile[:, None]))] = -np.inf
     p = np.exp(logit - logit.max(1, keepdims=True))
     assert_close(got, p @ v / p.sum(1, keepdims=True), f"bias past fp16 w={w} d={d} {order} scale={scale}")
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 80])
+@pytest.mark.parametrize("w,r,order", [(32, 0.2, "position"), (64, 0.4, "position"), (28, 0.4, "position"), (50, 0.5, "row")])
+def test_error_where_one_key_dominates(w, r, order, d):
+    """Rounding to bf16 alone: the output's (2^-9 of a value at most, 1.2e-3 of it in the root mean square) and the probabilities',
+    which is the same for each key and cancels as far as one dominates: together 1.2e-3 * sqrt(2) = 1.7e-3 and some.  A largest
+    probability that is not exactly 1, over a sum of unrounded ones, gives 2.35e-3."""
+    announce("peaky softmax", w, r, order, d)
+    S, rng = w * w, np.random.default_rng(w + d)
+    sigma = np.arange(S, dtype=np.int32) if order == "row" else np.ascontiguousarray(B.ssam_build_perm(w, w, 4)[0])
+    qkv = rng.normal(size=(1, S, 3, 2, d)).astype(np.float32)
+    qkv[:, :, :2] *= 2.0
+    qkv = inputs.bf16_round(qkv)
+    rel = [inputs.bf16_round(rng.normal(0, 0.1, size=(2 * w - 1, d)).astype(np.float32)) for _ in range(2)]
+    got = to_np(B.ssam_sparse_attention(dev_bf16(qkv), dev_bf16(rel[0]), dev_bf16(rel[1]), dev_i32(sigma), w, 128, r))[0].reshape(S, 2, d)
+    tile, row, col = np.arange(S) // 128, sigma // w, sigma % w
+    off = ~((tile[None, :] < int(r * (tile[-1] + 1) + 1e-6)) | (tile[None, :] == tile[:, None]))
+    want = np.empty((S, 2, d))
+    for h in range(2):
+        q, k, v = (qkv[0, :, i, h].astype(np.float64) for i in range(3))
+        logit = d ** -0.5 * (q @ k.T)
+        for t, c in zip(rel, (row, col)):
+            logit += np.take_along_axis(q @ t.T.astype(np.float64), c[:, None] - c[None, :] + w - 1, axis=1)
+        logit[off] = -np.inf
+        p = np.exp(logit - logit.max(1, keepdims=True))
+        want[:, h] = p @ v / p.sum(1, keepdims=True)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print("error", err)
+    assert err < 2.0e-3
