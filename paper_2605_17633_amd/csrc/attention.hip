@@ -770,7 +770,7 @@ size_t global_lds_bytes(int w)
 //     writes, one barrier per block).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
 //     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
 //     With d = 16 and 32 one block is little work between two barriers, so blocks come by twos there (UNIT): 2 images of 64 x 64,
-//     r = 1, d = 32 158 -> 139 us, d = 16 135 -> 127; a tile of 128 keys at a time takes 153 and 126;
+//     r = 1, d = 32 157 -> 136 us, d = 16 135 -> 130; a tile of 128 keys at a time takes 152 and 126;
 //   * where the exponent reference moves in block b, the output is rescaled in front of block b + 1, behind P V of block b - 1, whose probabilities are still
 //     in units of the reference before.  (Moving it by whole powers of two would allow rescaling those probabilities instead,
 //     but then a query's largest probability is no longer exactly 1 and is rounded to bf16 like the others: up to 19 % more
