@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libssam.so")
-SOURCES = ["tables.hip", "movers.hip", "gemm.hip", "attention.hip", "block.hip", "ends.hip", "probe.hip"]
+SOURCES = ["gemm.hip", "gemm_wide_folded.hip", "gemm_wide_add.hip", "gemm_wide_scatter.hip", "gemm_wide_gelu.hip", "gemm_wide_bias.hip",
+           "attention.hip", "movers.hip", "tables.hip", "block.hip", "ends.hip", "probe.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          "-Wno-inline-asm"]     # the window attention kernel names m0 in an asm clobber list (LDS-destination loads)
@@ -49,7 +50,7 @@ def _resources(stderr: str):
     return kernels
 
 
-HOT = ("gemm_bf16_nt_", "gemm_ring_kernel", "gemm_direct_kernel", "attn_")     # kernels that are written to a register budget
+HOT = ("gemm_bf16_nt_", "gemm_ring_kernel", "gemm_direct_kernel", "gemm_wide_kernel", "attn_")     # kernels that are written to a register budget
 
 
 def spilled(kernels):

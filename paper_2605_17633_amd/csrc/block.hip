@@ -17,7 +17,7 @@ int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int N
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
                         void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st);
 
-int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
+int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
                                void *split_ws, size_t split_ws_bytes, hipStream_t st);
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
@@ -133,7 +133,7 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
         int32_t *src = (int32_t *)(stats + 2 * (size_t)B * K);
         rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st);
         if (rc != SSAM_OK) return rc;
-        rc = ssam_linear_fold_gelu_impl(x, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st);
+        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st);
     } else {
         rc = ssam_ln_gather(x, keep_idx, K, ln_g, ln_b, eps, a2, B, N, K, D, stream);
         if (rc != SSAM_OK) return rc;

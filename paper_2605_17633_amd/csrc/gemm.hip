@@ -1,6 +1,14 @@
 // Dispatcher of the bf16 NT GEMM (qkv / proj / fc1 / fc2 of the SAM block).
 #include "gemm_direct.h"
 #include "gemm_ring.h"
+#include "gemm_wide_launch.h"
+
+int ssam_gemm_wide_bias(int tile, bool packed, const GemmWideArgs &a);
+int ssam_gemm_wide_gelu(int tile, bool packed, const GemmWideArgs &a);
+int ssam_gemm_wide_add(int tile, bool packed, const GemmWideArgs &a);
+int ssam_gemm_wide_scatter(int tile, bool packed, const GemmWideArgs &a);
+int ssam_gemm_wide_ln_scatter(int tile, const GemmWideArgs &a);
+int ssam_gemm_wide_ln_gelu(int tile, const GemmWideArgs &a);
 
 namespace {
 
@@ -212,7 +220,7 @@ constexpr RingTile ring_tiles[3] = { { 128, 128, 2, { { { 3.6, 0.82 }, { 7.4, 0.
 
 constexpr int RING_DIRECT = 3;
 
-// Index of the ring tile (or RING_DIRECT: gemm_direct.h) that is faster than the large tiles (launch_us), or -1.  whole_lines: the rows
+// Index of the ring tile (or RING_DIRECT: gemm_direct.h) that is faster than the large tiles (launch_us; what is taken, on return), or -1.  whole_lines: the rows
 // of row-major operands begin at multiples of 128 bytes; where they do not, a slab's 128-byte pieces of a row take two
 // lines each and a CU with two or three workgroups 1.35 times as long (427 x 3824 x 4560: 54 us, large tiles 44).
 // The estimates are fitted to 1200 shapes (M 8 to 8192, N 8 to 6144, K 8 to 6144: the layers of widths 576 to 1280, any sizes, few
@@ -220,7 +228,7 @@ constexpr int RING_DIRECT = 3;
 // of its estimate, the direct kernel 0.1, hence its credit.  Standard errors are 7-12 %.  What is taken is 0.9 % on
 // average from the fastest form, and on 9 of the shapes slower than the large tiles by more than 3 %, 7 % at most; with it they
 // are 25 % (row-major) and 31 % (packed) faster on average than with the large tiles alone.
-int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double launch_us)
+int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double &launch_us)
 {
     const int nk = ssam_div_up(K, GEMM_BK);
     int best = -1;
@@ -234,8 +242,61 @@ int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double launch_
         if (us < best_us) { best_us = us; best = i; }
     }
     // at most one tile per CU
-    if (packed && (long)ssam_div_up(M, 32) * (N / 32) <= 256 && 3.2 + nk * 0.14 - 0.2e-6 * N * K < best_us) best = RING_DIRECT;
+    if (packed && (long)ssam_div_up(M, 32) * (N / 32) <= 256 && 3.2 + nk * 0.14 - 0.2e-6 * N * K < best_us) {
+        best = RING_DIRECT;
+        best_us = 3.2 + nk * 0.14 - 0.2e-6 * N * K;
+    }
+    launch_us = best_us;
     return best;
+}
+
+// The wide kernel's tiles (gemm_wide.h).  A launch of r rounds (one workgroup per CU at a time) takes
+// t0 + r * (t_round + t_slab per slab of 64, t_gelu and t_add behind those epilogues) + t_mb per megabyte of C.
+struct WideTile { int bm, bn; double t0, t_round, t_slab, t_gelu, t_add, t_mb; };
+constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
+    { 64, 64, 3.7, 0, 0.16, 0.262, 0, 0.326 },          { 96, 64, 0, 4.18, 0.207, 0.375, 0.03, 0.246 },   { 96, 96, 0, 4.66, 0.251, 0.336, 0.504, 0.223 },
+    { 64, 128, 0, 4.27, 0.228, 0.614, 0.075, 0.354 },   { 128, 128, 1.14, 2.89, 0.382, 1.2, 0, 0.153 },   { 128, 192, 0.896, 4.09, 0.498, 1.31, 0, 0.205 },
+    { 192, 128, 0.478, 3.86, 0.505, 1.71, 0, 0.183 },   { 256, 128, 0.243, 4.64, 0.623, 2.1, 0, 0.2 },    { 192, 192, 0.697, 5.38, 0.668, 1.56, 0, 0.22 },
+    { 192, 256, 1.07, 4.83, 0.85, 3.16, 0, 0.197 },     { 256, 192, 0.964, 5, 0.838, 3.1, 0, 0.194 },     { 256, 256, 1.7, 4.96, 1.09, 4.28, 0, 0.207 } };
+
+// Index of the wide kernel's tile that is faster than the others' launch_us, or -1.  rows_a: rows of A where its rows are
+// gathered.  The tiles below 128x128 add K in two chains instead of one, and are taken where that is faster than the others with either
+// layout of the weights (both_us), so that packing a program's weights does not change its bits.
+// The kernel takes whole slabs; below five of them its prologue is not earned back, and up to 32 rows packed weights have a kernel
+// with tiles of 32 (31 x 3840 x 3648: 12.9 us, the direct kernel 10.9).  Its requests address memory by 32-bit offsets from the tile's
+// first row, or from A's where rows are gathered.
+// Fitted to 1339 shapes (M 8 to 24576, N 128 to 5120, K 128 to 5376, all epilogues, both layouts, weights that no cache holds: hence
+// 0.4e-6 * N * K on top of the others' estimates).  What is taken is 0.9 % on average from the fastest form, 10 % faster on average
+// than without this kernel, and on 20 of the shapes slower than that by more than 3 %, on 6 by more than 6 % (9 % at most; shapes of 5
+// to 8 us).  More than four rounds are left to the large tiles, two workgroups to a CU: there the epilogues of packed problems
+// that last several rounds run under other workgroups' main loops (32768 x 3840 x 1280: 264 us against 269 and more).
+int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us)
+{
+    const int nk = K / GEMM_BK;
+    if (K % GEMM_BK != 0 || nk < 5 || (packed && M <= 32)) return -1;
+    if ((long)256 * ld.a * 2 >= 1L << 31 || (rows_a + 1) * ld.a * 2 >= 1L << 32 || (long)256 * (packed ? K : ld.w) * 2 >= 1L << 31) return -1;
+    int best = -1;
+    double best_us = 1e30;
+    for (int i = 0; i < GEMM_WIDE_COUNT; ++i) {
+        const WideTile &t = wide_tiles[i];
+        const int rounds = ssam_div_up(ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 8), 32);      // (see the kernel's XCDs)
+        if (rounds > 4) continue;
+        const double us = t.t0 + rounds * (t.t_round + nk * t.t_slab + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
+                          + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
+        if (us < best_us) { best_us = us; best = i; }
+    }
+    if (best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128) launch_us = both_us < launch_us ? both_us : launch_us;
+    return best_us < 0.96 * (launch_us + 0.4e-6 * N * K) ? best : -1;
+}
+
+// What the others take with the other layout of the weights (1e30: there is none).
+double other_layout_us(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed, bool whole_lines)
+{
+    if (!packed && N % 128 != 0) return 1e30;
+    double us;
+    pick_tile(M, N, K, epilogue, ws, !packed, us);
+    pick_ring(M, N, K, !packed, whole_lines, us);
+    return us;
 }
 
 template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF>
@@ -293,6 +354,16 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
         double us;
         tile = pick_tile(M, N, K, epilogue, ws, packed, us);
         ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
+        if (const int wide = pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, true)); wide >= 0) {
+            const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, no_fold, st };
+            switch (epilogue) {
+            case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
+            case SSAM_EPI_BIAS_GELU: return ssam_gemm_wide_gelu(wide, packed, args);
+            case SSAM_EPI_BIAS_SCATTER_ADD: return ssam_gemm_wide_add(wide, packed, args);
+            case SSAM_EPI_BIAS_SCATTER: return ssam_gemm_wide_scatter(wide, packed, args);
+            default: return SSAM_EINVAL;
+            }
+        }
     }
     if (packed) {
         switch (epilogue) {
@@ -313,8 +384,8 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 }
 
 // fc1 of the routed MLP with gather and LN2 folded in (see GemmFold): rows src[m] of A, packed folded weights,
-// GELU epilogue, any M; the tile is picked as for the plain contraction of the same shape.
-int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
+// GELU epilogue, any M; the kernel is picked as for the plain contraction of the same shape.  rows_a: rows of A.
+int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
                                void *split_ws, size_t split_ws_bytes, hipStream_t st)
 {
@@ -322,8 +393,10 @@ int ssam_linear_fold_gelu_impl(const void *A, const int32_t *src, const float *s
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src };
     const GemmRowMap none = { nullptr, 1, 0, 1 };
     double us;
-    const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
-    if (const int ring = pick_ring(M, N, K, true, true, us); ring >= 0)
+    const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us), ring = pick_ring(M, N, K, true, true, us);
+    if (const int wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us); wide >= 0)
+        return ssam_gemm_wide_ln_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
+    if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
     return launch_tile_packed<SSAM_EPI_BIAS_GELU, true>(tile, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld,
                                                         none, ws, st, fold);
@@ -346,7 +419,11 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr };
-    if (const int ring = pick_ring(M, N, K, true, true, folded_ln_us(tr.tile_count, K)); ring >= 0)
+    double us = folded_ln_us(tr.tile_count, K);
+    const int ring = pick_ring(M, N, K, true, true, us);
+    if (const int wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, us, us); wide >= 0)
+        return ssam_gemm_wide_ln_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });
+    if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
     const int per_xcd = ssam_div_up(tr.tile_count, 8);
     hipLaunchKernelGGL((gemm_bf16_nt_lnf_kernel<128, 256, SSAM_EPI_BIAS_SCATTER, 1, 4>), dim3(per_xcd * 8), dim3(256), lds, st,
@@ -370,7 +447,7 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream);
 }
 
-// Which kernel a contraction takes (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
+// Which kernel a contraction takes where the wide kernel does not (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
 // 17: 128x64, 18: 64x64, 19: the direct one).  Host only, for tests; not part of the interface.
 extern "C" int ssam_linear_form(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes)
 {
@@ -383,6 +460,19 @@ extern "C" int ssam_linear_form(int M, int N, int K, int epilogue, int packed, i
     }
     const int ring = pick_ring(M, N, K, packed != 0 || folded != 0, K % GEMM_BK == 0, us);
     return ring >= 0 ? 16 + ring : tile;
+}
+
+// The wide kernel's tile that the same contraction takes instead (its index in wide_tiles), or -1.
+extern "C" int ssam_linear_wide_form(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > SSAM_EPI_BIAS_SCATTER) return -1;
+    double us = folded_ln_us((M / 128) * (N / 256), K);
+    alignas(16) unsigned char some;
+    const SplitWs ws = { workspace_bytes ? &some : nullptr, workspace_bytes };
+    if (!folded) pick_tile(M, N, K, epilogue, ws, packed != 0, us);
+    pick_ring(M, N, K, packed != 0 || folded != 0, K % GEMM_BK == 0, us);
+    return pick_wide(M, N, K, epilogue, GemmLd{ K, K, N }, packed != 0 || folded != 0, 0, us,
+                     folded ? us : other_layout_us(M, N, K, epilogue, ws, packed != 0, true));
 }
 
 extern "C" size_t ssam_linear_workspace_bytes(void) { return GEMM_SPLIT_WS_BYTES; }

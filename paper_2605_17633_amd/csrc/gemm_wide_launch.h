@@ -1,0 +1,48 @@
+// Launches of gemm_wide_kernel.  The kernels of one epilogue are one source file (gemm_wide_*.hip), compiled side by side.
+#pragma once
+
+#include "gemm_wide.h"
+
+struct GemmWideArgs {
+    const bf16 *A, *W;
+    const float *bias;
+    bf16 *C;
+    int M, N, K;
+    GemmLd ld;
+    GemmRowMap rm;
+    GemmFold fold;
+    hipStream_t st;
+};
+
+// Tiles, in the order of their index in the dispatcher's time model (gemm.hip).
+#define GEMM_WIDE_TILES(X)                                                                                     \
+    X(0, 64, 64, 2) X(1, 96, 64, 2) X(2, 96, 96, 2) X(3, 64, 128, 2) X(4, 128, 128, 1) X(5, 128, 192, 1)         \
+    X(6, 192, 128, 1) X(7, 256, 128, 1) X(8, 192, 192, 1) X(9, 192, 256, 1) X(10, 256, 192, 1) X(11, 256, 256, 1)
+constexpr int GEMM_WIDE_COUNT = 12;
+
+template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF>
+int gemm_wide_launch_tile(const GemmWideArgs &a)
+{
+    constexpr size_t lds = GemmWide<BM, BN, WGK>::lds_bytes;
+    auto kern = gemm_wide_kernel<BM, BN, WGK, EPI, WPACK, LNF>;
+    // more than 64 KiB of LDS per workgroup needs the per-kernel opt-in (idempotent, host-side only)
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return SSAM_EHIP;
+    GemmTileRange tr = { ssam_div_up(a.M, BM), ssam_div_up(a.N, BN), 0, 0 };
+    tr.tile_count = tr.tiles_m * tr.tiles_n;
+    hipLaunchKernelGGL(kern, dim3(ssam_div_up(tr.tile_count, 8) * 8), dim3(512), lds, a.st, a.A, a.W, a.bias, a.C, a.M, a.N, a.K, a.ld, tr, a.rm, a.fold);
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
+}
+
+template <int EPI, bool WPACK, bool LNF>
+int gemm_wide_launch(int tile, const GemmWideArgs &a)
+{
+    switch (tile) {
+#define X(id, bm, bn, wgk) case id: return gemm_wide_launch_tile<bm, bn, wgk, EPI, WPACK, LNF>(a);
+    GEMM_WIDE_TILES(X)
+#undef X
+    default: return SSAM_EINVAL;
+    }
+}
