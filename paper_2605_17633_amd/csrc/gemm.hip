@@ -265,11 +265,12 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 // The kernel takes whole slabs; below five of them its prologue is not earned back, and up to 32 rows packed weights have a kernel
 // with tiles of 32 (31 x 3840 x 3648: 12.9 us, the direct kernel 10.9).  Its requests address memory by 32-bit offsets from the tile's
 // first row, or from A's where rows are gathered.
-// Fitted to 1339 shapes (M 8 to 24576, N 128 to 5120, K 128 to 5376, all epilogues, both layouts, weights that no cache holds: hence
-// 0.4e-6 * N * K on top of the others' estimates).  What is taken is 0.9 % on average from the fastest form, 10 % faster on average
-// than without this kernel, and on 20 of the shapes slower than that by more than 3 %, on 6 by more than 6 % (9 % at most; shapes of 5
-// to 8 us).  More than four rounds are left to the large tiles, two workgroups to a CU: there the epilogues of packed problems
-// that last several rounds run under other workgroups' main loops (32768 x 3840 x 1280: 264 us against 269 and more).
+// Fitted to 1339 shapes (M 8 to 24576, N 128 to 5120, K 128 to 5376, all epilogues, both layouts, weights that no cache holds; those
+// cost the others 0.2 us a megabyte on top of their estimates, which is left out here: with warm weights 784 x 2304 x 768 takes the ring
+// 8.9 us and this kernel 9.5).  What is taken is 1 % on average from the fastest form, 10 % faster on average than
+// without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
+// are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
+// 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
 int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us)
 {
     const int nk = K / GEMM_BK;
@@ -280,13 +281,13 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
     for (int i = 0; i < GEMM_WIDE_COUNT; ++i) {
         const WideTile &t = wide_tiles[i];
         const int rounds = ssam_div_up(ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 8), 32);      // (see the kernel's XCDs)
-        if (rounds > 4) continue;
+        if (rounds > (packed ? 2 : 4)) continue;
         const double us = t.t0 + rounds * (t.t_round + nk * t.t_slab + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
                           + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
         if (us < best_us) { best_us = us; best = i; }
     }
     if (best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128) launch_us = both_us < launch_us ? both_us : launch_us;
-    return best_us < 0.96 * (launch_us + 0.4e-6 * N * K) ? best : -1;
+    return best_us < 0.99 * launch_us ? best : -1;
 }
 
 // What the others take with the other layout of the weights (1e30: there is none).
