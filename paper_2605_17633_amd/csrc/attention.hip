@@ -19,20 +19,19 @@
 // Key blocks (32 keys) are processed in chunks of one (window kernel, patch path) or as many as the register budget of
 // two waves per SIMD allows (two to four): all score MFMAs of the chunk first, one max and, where the reference moves,
 // one rescale of the running output per chunk, then all P V MFMAs; the patch path interleaves three blocks instead.
-// Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept in LDS as fp16, query-major.  How a
-// score gets its two entries:
-//   window kernel: two look-ups at per-key byte offsets, the entries stored as the MFMA tile comes out, U[q][m], a key
-//                  being entry q_row - key_row + w - 1, times log2 e;
-//   global kernel: as a product with the table in the scores' accumulator: of one 16-entry operand on orders whose
-//                  blocks are patches (PatchPipe), of the whole row of up to 64 entries a table on others
-//                  (attn_chunk_step_onehot); above 64 x 64 by two look-ups.
+// Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept in LDS as fp16, query-major.  A score gets
+// its two entries as a product with the table in the scores' accumulator: of one 16-entry operand on orders whose
+// blocks are patches (PatchPipe), of the whole row of up to 16 (windows) or 64 entries a table on others
+// (attn_chunk_step_onehot); above 64 x 64 by two look-ups.
 // Memory requests are spread over a problem's / a tile's phases (see the prefetch
 // macros): a wave whose loads do not fit the CU's request queues waits instead of
 // computing, and a wait placed behind a branch or on a value that is used at once
 // drains every load and store in flight.
 //
-// Two launch shapes:
-//   window kernel: persistent workgroups looping over (window, head) problems, one
+// Three launch shapes:
+//   window kernel, a wave to a query tile: one-wave workgroups, each walks the active key blocks of its tile by itself
+//                  (d <= 64, and few problems at d = 80);
+//   window kernel, persistent (d = 80): workgroups looping over (window, head) problems, one
 //                  wave per 32-query tile (= mask tile of 32), the window's whole K
 //                  and V in LDS, the next problem's K and V prefetched into registers
 //                  and its Q straight into LDS, in three pieces, the rel-pos tables
@@ -41,6 +40,8 @@
 //                  more workgroups per CU; active key blocks go straight into rings in LDS (patch
 //                  path), or active 128-key tiles through registers into LDS (K and V requested
 //                  at different points).
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -57,7 +58,7 @@ struct AttnParams {
     const int32_t *out_rows;   // NULL: query p of group g goes to output row g*S+p; else to out_rows[g*S+p] (-1: dropped)
     int S, w, h, n_pre;
     float scale_log2e;
-    uint32_t half_one;      // global kernel, see bias_shift: 2^shift in fp16
+    uint32_t half_one;      // see bias_shift: 2^shift in fp16
     float table_one;        // and in fp32
     float table_inv;        // what turns a bias into an entry: 1 / (scale * 2^shift)
 };
@@ -83,6 +84,14 @@ __device__ __forceinline__ void set_ones_columns(bf16 *Vs, int rows, int tid, in
         const u32x4 ones = { 0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u };
         for (int p = tid; p < rows; p += nthreads) *reinterpret_cast<u32x4 *>(Vs + p * AttnCfg<D>::KSTR + D) = ones;
     }
+}
+
+// LDS is in order per wave: this keeps the compiler from reordering what its lanes exchange through it
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Per-wave softmax/output state for 32 queries (one per lane pair l, l^32).
@@ -123,10 +132,12 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 //   * with a small scale the table is 2^shift times smaller and the ones of that matrix, or what a looked-up entry is multiplied
 //     by, are 2^shift: shift is the least that puts 65504 * 2^shift * scale past 128 (bias_shift), since exp(-128) is the "no
 //     weight" that such a bias asks for.
-inline int bias_shift(float scale)
+// The window kernels' shift is the least that puts a one past 1 / log2 e logits: their tables then have at least the range and the
+// small entries of logits in units of log 2, whatever the scale (from 2e-5).
+inline int bias_shift(float scale, bool window)
 {
     int n = 0;
-    while (n < 15 && ldexpf(65504.f * scale, n) < 128.f) ++n;
+    while (n < 15 && ldexpf(window ? scale * LOG2E : 65504.f / 128.f * scale, n) < 1.f) ++n;
     return n;
 }
 // bit 23 of the mode register: fp16 results past the range are clamped instead of rounded to infinity
@@ -189,59 +200,69 @@ __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *re
     }
 }
 
-// Window form of the bias tables.  A window has 2w-1 <= 32 relative positions, so rel x Q^T is one MFMA tile
-// per table and is stored the way it leaves the matrix core, query-major and without predicates:
-//   tq[q*WIN_TSTR + m]                 = log2e * q . rel_h[m]
-//   tq[(32 + q)*WIN_TSTR + m]          = log2e * q . rel_w[m]        (m = 0..31; rows past 2w-2 of rel are zero)
-// A key in row kr, column kc is then entry qrow - kr + w - 1 of the first and qcol - kc + w - 1 of the second
-// row of the lane's query.  Entries are fp16 (see GlbTab); the row stride keeps the 8-byte stores aligned.
 typedef _Float16 WinTab;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-constexpr int WIN_TSTR = 36;
-template <int D>
-__device__ __forceinline__ void build_bias_rows_window(const bf16x8 *qf, const bf16 *rel_h, const bf16 *rel_w, int rstr, WinTab *tq)
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+// Bias operands of the window kernels (attn_chunk_step_onehot): entry p of the lane's query (p = key row, or 16 + key column) at
+// tq[(l & 31) * WIN_OSTR + p], divided by the softmax scale (AttnParams::table_inv); those past w are zero.  A window has 2w-1 <= 32
+// relative positions, so rel x Q^T is one MFMA tile per table.  It is stored the way it leaves the matrix core, query-major, and
+// entry p read back as position q - p + w - 1: predicated stores of the entries to their places, as for larger grids, cost two to three times as much.
+// rel(tab, ks): fragment ks of the lane's row l & 31 of rel_h (tab 0) or rel_w (1), elements 16*ks + 8*(l >> 5) .. + 7.
+constexpr int WIN_TSTR = 36;             // row of a product: 8-byte stores aligned, and 32 lanes at one entry on distinct banks
+constexpr int WIN_OSTR = 40;             // row of operands: 2 * 16 entries; reads of 16 bytes aligned, and 16 lanes on distinct banks
+template <int D, typename Rel>
+__device__ __forceinline__ void build_bias_operands_window(const bf16x8 *qf, Rel rel, int w, int qrow, int qcol, WinTab *tq, float inv_scale)
 {
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    u32x4 keep, t[2];                    // this half-wave's entries 8*half .. + 7 that are below w
+#pragma unroll
+    for (int e = 0; e < 4; ++e) keep[e] = (8 * half + 2 * e < w ? 0xffffu : 0u) | (8 * half + 2 * e + 1 < w ? 0xffff0000u : 0u);
 #pragma unroll
     for (int tab = 0; tab < 2; ++tab) {
-        const bf16 *rel = (tab ? rel_w : rel_h) + l32 * rstr + half * 8;
         f32x16 u;
 #pragma unroll
         for (int r = 0; r < 16; ++r) u[r] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < AttnCfg<D>::KS; ++ks)
-            u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(rel + ks * 16), qf[ks], u, 0, 0, 0);
+            u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rel(tab, ks), qf[ks], u, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // MFMA passes done before u is read (as in build_bias_rows)
         __builtin_amdgcn_sched_barrier(0);
-        WinTab *dst = tq + (tab * 32 + l32) * WIN_TSTR + 4 * half;    // u[4g + e] is rel row 8g + 4*half + e of query l32
+        WinTab *row = tq + l32 * WIN_TSTR;                            // u[4g + e] is rel row 8g + 4*half + e of query l32
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            f16x4 hv = { (_Float16)(u[4 * g] * LOG2E), (_Float16)(u[4 * g + 1] * LOG2E),
-                         (_Float16)(u[4 * g + 2] * LOG2E), (_Float16)(u[4 * g + 3] * LOG2E) };
-            *reinterpret_cast<f16x4 *>(dst + 8 * g) = hv;
+            f16x4 hv = { (_Float16)(u[4 * g] * inv_scale), (_Float16)(u[4 * g + 1] * inv_scale),
+                         (_Float16)(u[4 * g + 2] * inv_scale), (_Float16)(u[4 * g + 3] * inv_scale) };
+            *reinterpret_cast<f16x4 *>(row + 4 * half + 8 * g) = hv;
         }
+        wave_lds_fence();
+        // up to 15 entries in front of the row for p past w: LDS of this workgroup, and not kept
+        const WinTab *at = row + ((tab ? qcol : qrow) + w - 1 - 8 * half);
+        f16x8 v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = at[-e];
+        t[tab] = __builtin_bit_cast(u32x4, v) & keep;
+        wave_lds_fence();
     }
+#pragma unroll
+    for (int tab = 0; tab < 2; ++tab) *reinterpret_cast<u32x4 *>(tq + l32 * WIN_OSTR + tab * 16 + half * 8) = t[tab];
+    wave_lds_fence();
 }
 
 // A chunk of nb (1..NB, wave-uniform) 32-key blocks against the wave's 32 queries.
 //   Ks, Vs: LDS, row-major rows ([keys][KSTR]); blk[b]: index of the chunk's b-th block in them
-//   krc:    LDS, per key two byte offsets into the bias tables, indexed like Ks: low half for the row part,
-//           high half for the column part (global kernel: within the query's table row, see build_bias_rows;
-//           window tables: the key's share of the entry index, see key_bias_offsets_window)
+//   krc:    LDS, per key two byte offsets into the query's table row, indexed like Ks: low half for the row part,
+//           high half for the column part (see build_bias_rows)
 //   key0[b]: scan position of the block's first key (for the S bound; RAGGED = the chunk crosses S)
 //   tq_h, tq_w: where this lane's query starts in the row-part and column-part bias tables; a key's two
 //           bias terms are read at tq_h + (low half of krc) and tq_w + (high half of krc), in bytes
-//   FULL:   the chunk has all NB blocks (nb is not looked at: no per-block branches, no dummy scores)
-//   MIXADD: the column part of the bias is added by one mixed-precision fma (fp16 operand widened inside the
-//           instruction) instead of convert + add
-//   RAW:    the tables hold bias / (scale * one) and the scores stay unscaled: logit = (s + (bh + bw) * one) * scale_log2e
-//           (global kernel); otherwise the tables hold bias * log2e and logit = s * scale_log2e + bh + bw
+// The tables hold bias / (scale * one) and the scores stay unscaled: logit = (s + (bh + bw) * one) * scale_log2e.
 constexpr float ATTN_LAG = 8.f;
 
-// Second half of a chunk step, the same for every way of forming the scores: s holds the chunk's logits (RAW: before
-// the multiplication by scale_log2e), mx their maximum over this lane's keys, in the same units.
-template <int D, int NB, bool FULL, bool RAW>
+// Second half of a chunk step, the same for every way of forming the scores: s holds the chunk's logits before
+// the multiplication by scale_log2e, mx their maximum over this lane's keys, in the same units.
+// FULL: the chunk has all NB blocks (nb is not looked at: no per-block branches, no dummy scores)
+template <int D, int NB, bool FULL>
 __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB], float mx, const bf16 *Vs,
                                                 const int (&blk)[NB], int nb_, float scale_log2e)
 {
@@ -249,7 +270,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
     const int nb = FULL ? NB : nb_;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    if constexpr (RAW) mx *= scale_log2e;
+    mx *= scale_log2e;
     // st.m is the exponent reference of the running sums, not the running maximum: it moves only when a chunk's
     // maximum exceeds it by more than 2^ATTN_LAG, so probabilities stay below 2^ATTN_LAG (all of a query's terms
     // carry the same power of two, which the final division removes) and the rescaling of the 32 x D accumulator
@@ -266,18 +287,13 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
             for (int r = 0; r < 16; ++r) st.o[dt][r] *= alpha;
     }
     const float mref = st.m;
-    float psum = 0.f;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (b < nb) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                s[b][r] = __builtin_amdgcn_exp2f(RAW ? fmaf(s[b][r], scale_log2e, -mref) : s[b][r] - mref);
-                if constexpr (!C::ONES && !RAW) psum += s[b][r];
-            }
+            for (int r = 0; r < 16; ++r) s[b][r] = __builtin_amdgcn_exp2f(fmaf(s[b][r], scale_log2e, -mref));
         }
     }
-    if constexpr (!C::ONES && !RAW) st.l += psum;
     // transposing read: lane li of a 16-lane group points at row (li >> 2), column chunk (li & 3) of a
     // 4-key x 16-feature block and receives the 4 keys of feature column li
     const int li = lane & 15, fblk = (lane >> 4) & 1;
@@ -290,7 +306,7 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
                 bf16x8 p;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) p[e] = (bf16)s[b][8 * t + e];
-                if constexpr (!C::ONES && RAW) {
+                if constexpr (!C::ONES) {
                     // the sum of what P V multiplies, the rounded probabilities, as with the ones columns: the rounding of a dominant
                     // one cancels (with sums of the unrounded ones the error is 1-2 % larger where one key dominates)
 #pragma unroll
@@ -317,13 +333,13 @@ __device__ __forceinline__ void attn_softmax_pv(WaveState<D> &st, f32x16 (&s)[NB
     }
 }
 
-template <int D, int NB, bool RAGGED, bool FULL, typename TabT, bool MIXADD = false, bool RAW = false>
+template <int D, int NB, bool RAGGED, typename TabT>
 __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
-                                                const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB], int nb_,
-                                                int S, float scale_log2e, const TabT *tq_h, const TabT *tq_w, float one = 1.f)
+                                                const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB], int nb,
+                                                int S, float scale_log2e, const TabT *tq_h, const TabT *tq_w, float one)
 {
     using C = AttnCfg<D>;
-    const int nb = FULL ? NB : nb_;
+    static_assert(sizeof(TabT) == 2, "bias tables are fp16");
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     f32x16 s[NB];
 #pragma unroll
@@ -362,17 +378,10 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
                     const int r = 4 * g + e;
                     const uint32_t c = rc[e];
                     const float bh = (float)*reinterpret_cast<const TabT *>(tqh + (c & 0xffffu));
-                    float val;
-                    if constexpr (MIXADD) {
-                        static_assert(sizeof(TabT) == 2, "bias tables are fp16");
-                        const uint32_t bw16 = *reinterpret_cast<const uint16_t *>(tqw + (c >> 16));
-                        val = RAW ? fmaf(bh, one, s[b][r]) : s[b][r] * scale_log2e + bh;   // the compiler forms these mixed ops by itself
-                        if constexpr (RAW) asm("v_fma_mix_f32 %0, %1, %3, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val), "s"(one));
-                        else asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val));
-                    } else {
-                        const float bw = (float)*reinterpret_cast<const TabT *>(tqw + (c >> 16));
-                        val = RAW ? fmaf(bw, one, fmaf(bh, one, s[b][r])) : s[b][r] * scale_log2e + bh + bw;
-                    }
+                    const uint32_t bw16 = *reinterpret_cast<const uint16_t *>(tqw + (c >> 16));
+                    // the column part in one mixed-precision fma (fp16 operand widened inside the instruction)
+                    float val = fmaf(bh, one, s[b][r]);
+                    asm("v_fma_mix_f32 %0, %1, %3, %2 op_sel_hi:[1,0,0]" : "=v"(val) : "v"(bw16), "v"(val), "s"(one));
                     if (RAGGED) val = (key0[b] + 8 * g + 4 * half + e < S) ? val : -INFINITY;
                     s[b][r] = val;
                     mx = fmaxf(mx, val);
@@ -380,7 +389,7 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
             }
         }
     }
-    attn_softmax_pv<D, NB, FULL, RAW>(st, s, mx, Vs, blk, nb_, scale_log2e);
+    attn_softmax_pv<D, NB, false>(st, s, mx, Vs, blk, nb, scale_log2e);
 }
 
 // Patches: scores of 32-key blocks that are 4 x 8 patches of stride 2 in the grid: key k of a block (bits c0 r1'.. in
@@ -391,7 +400,6 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
 // picks a key's row entry (f = rr) and column entry (f = 4 + cc) and T the 4 row and 8 column entries of every
 // query, which are contiguous in the query's table row (build_bias_rows).  So the bias is ONE more MFMA (fp16
 // operands, the same fp32 accumulator, issued first) and the vector unit does no look-ups and no additions.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // row and column steps (in units of 2 cells) of key k of a patch block from the block's first key
 __device__ __forceinline__ int patch_rr(int k) { return ((k >> 1) & 1) | ((k >> 2) & 2); }
 __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2) | ((k >> 2) & 4); }
@@ -452,21 +460,7 @@ __device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const b
             if (RAGGED) s[b][r] = key0[b] + 8 * (r >> 2) + 4 * half + (r & 3) < S ? s[b][r] : -INFINITY;
             mx = fmaxf(mx, s[b][r]);
         }
-    attn_softmax_pv<D, NB, true, true>(st, s, mx, Vs, blk, NB, scale_log2e);
-}
-
-template <int D, int NB, typename TabT>
-__device__ __forceinline__ void attn_chunk(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
-                                           const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB], int nb,
-                                           bool ragged, int S, float scale_log2e, const TabT *tq_h, const TabT *tq_w)
-{
-    if (nb == NB) {
-        if (ragged) attn_chunk_step<D, NB, true, true, TabT, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, scale_log2e, tq_h, tq_w);
-        else attn_chunk_step<D, NB, false, true, TabT, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, scale_log2e, tq_h, tq_w);
-    } else {
-        if (ragged) attn_chunk_step<D, NB, true, false, TabT, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, scale_log2e, tq_h, tq_w);
-        else attn_chunk_step<D, NB, false, false, TabT, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, scale_log2e, tq_h, tq_w);
-    }
+    attn_softmax_pv<D, NB, true>(st, s, mx, Vs, blk, NB, scale_log2e);
 }
 
 template <int D>
@@ -508,9 +502,7 @@ __device__ __forceinline__ void finish_and_store(WaveState<D> &st, bf16 *stage, 
                 *reinterpret_cast<uint2 *>(stage + l32 * STR + dd) = pk;
             }
         }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // LDS is in order per wave; keep the compiler from reordering
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     const int row_lo = (int)my_row, row_hi = (int)(my_row >> 32);
 #pragma unroll
     for (int i = 0; i < (32 * C::CH + 63) / 64; ++i) {
@@ -535,14 +527,6 @@ __device__ __forceinline__ uint32_t key_row_col(const int32_t *sigma, int p, int
     return cell_row_col(sigma[p < S ? p : S - 1], w);
 }
 
-// window kernel: byte offsets of the key's entries within a query's two table rows, less the query's own part
-__device__ __forceinline__ uint32_t key_bias_offsets_window(const int32_t *sigma, int p, int S, int w)
-{
-    uint32_t rc = key_row_col(sigma, p, S, w);
-    const uint32_t esz = sizeof(WinTab);
-    return (esz * (uint32_t)(w - 1 - (int)(rc & 0xffffu))) | ((esz * (uint32_t)(w - 1 - (int)(rc >> 16))) << 16);
-}
-
 // per-wave LDS scratch of the global kernel: the bias table of its 32 queries (rows of tstr fp16), later overlaid by
 // its output staging tile
 template <int D>
@@ -552,7 +536,9 @@ __host__ __device__ inline int wave_scratch_bytes(int tstr)
     return ((bias > stage ? bias : stage) + 15) & ~15;
 }
 
-// ------------------------------------------------------------------ window kernel
+// ------------------------------------------------------------------ window kernel, persistent
+// The bias as a product (two MFMAs a block, operands built once a tile) instead of 32 LDS look-ups and 80 vector instructions a block: 16 heads, d = 80,
+// 800 problems 34.2 -> 32.4 us at r = 0.4, 51.1 -> 45.7 dense; 3200: 99.6 -> 96.5 and 154.8 -> 137.3.
 inline int window_rel_rows(int w) { return ((2 * w - 1 + 31) / 32) * 32; }
 
 // per-wave LDS landing area of the next problem's queries: the KS operand-b fragments of the wave's 32 queries
@@ -568,7 +554,7 @@ constexpr long GFX950_LDS_BYTES = 160 * 1024;
 template <int D>
 __host__ __device__ constexpr int window_stage_stride()
 {
-    constexpr int KSTR = AttnCfg<D>::KSTR, bias = 2 * 32 * WIN_TSTR * (int)sizeof(WinTab), stage = 32 * KSTR * 2;
+    constexpr int KSTR = AttnCfg<D>::KSTR, bias = 32 * WIN_OSTR * (int)sizeof(WinTab), stage = 32 * KSTR * 2;
     constexpr long total = 7L * window_q_bytes<D>() + 2L * 224 * KSTR * 2 + 2L * 32 * KSTR * 2 +
                            7L * (bias > stage ? bias : stage) + 224 * 4;
     return total <= GFX950_LDS_BYTES ? KSTR : D;
@@ -577,7 +563,7 @@ __host__ __device__ constexpr int window_stage_stride()
 template <int D>
 __host__ __device__ inline int window_scratch_bytes()
 {
-    int bias = 2 * 32 * WIN_TSTR * (int)sizeof(WinTab), stage = 32 * window_stage_stride<D>() * 2;
+    int bias = 32 * WIN_OSTR * (int)sizeof(WinTab), stage = 32 * window_stage_stride<D>() * 2;
     return ((bias > stage ? bias : stage) + 15) & ~15;
 }
 
@@ -589,8 +575,6 @@ size_t window_lds_bytes(int nqb, int w)
            (size_t)2 * window_rel_rows(w) * AttnCfg<D>::KSTR * 2 + (size_t)nqb * window_scratch_bytes<D>() + (size_t)SP * 4;
 }
 
-constexpr int WIN_NB = 1;            // key blocks per softmax chunk in the window kernel: one (with two the kernel has no
-                                     // registers left for the ragged-block and mixed-add savings, and is no faster)
 constexpr int WIN_MAX_LOADS = 5;     // 16-byte K (and V) chunks per thread: 224 keys * 10 chunks / 448 threads
 
 template <int D>
@@ -614,9 +598,10 @@ attn_window_kernel(AttnParams P, int n_groups)
     const int S = P.S;
     const int nloads = (SP * C::CH + blockDim.x - 1) / blockDim.x;     // <= WIN_MAX_LOADS (checked on the host)
 
+    clamp_fp16();
     // problem-independent state: scan-order geometry and the rel-pos tables
     if (P.sigma_stride == 0)
-        for (int p = tid; p < SP; p += blockDim.x) krc[p] = key_bias_offsets_window(P.sigma, p, S, P.w);
+        for (int p = tid; p < SP; p += blockDim.x) krc[p] = key_row_col(P.sigma, p, S, P.w);
     for (int id = tid; id < 2 * rrows * C::CH; id += blockDim.x) {
         int tab = id / (rrows * C::CH), rem = id % (rrows * C::CH), row = rem / C::CH, c = rem % C::CH;
         u32x4 v = { 0, 0, 0, 0 };
@@ -704,7 +689,7 @@ attn_window_kernel(AttnParams P, int n_groups)
         }
         if (P.sigma_stride != 0) {                // per-group order: this window's own sigma
             const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
-            for (int p = tid; p < SP; p += blockDim.x) krc[p] = key_bias_offsets_window(sg, p, S, P.w);
+            for (int p = tid; p < SP; p += blockDim.x) krc[p] = key_row_col(sg, p, S, P.w);
             qrc = key_row_col(sg, qclamp, S, P.w);
         }
         // this problem's queries were sent to LDS during the previous problem (WIN_PREFETCH_Q): wait for every
@@ -715,35 +700,137 @@ attn_window_kernel(AttnParams P, int n_groups)
         for (int ks = 0; ks < C::KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(q_mine + ks * 512);
         const int next = local_problem(lp + nslots);
         if (next >= 0) WIN_PREFETCH(next, 1)
-        build_bias_rows_window<D>(qf, Rh, Rw, C::KSTR, tq);
-        const WinTab *tq_h = tq + l32 * WIN_TSTR + (int)(qrc & 0xffffu);            // this lane's query in the two tables
-        const WinTab *tq_w = tq + (32 + l32) * WIN_TSTR + (int)(qrc >> 16);
+        WinTab *tq_lane = tq + l32 * WIN_OSTR;
+        build_bias_operands_window<D>(qf, [&](int tab, int ks) {
+            return *reinterpret_cast<const bf16x8 *>((tab ? Rw : Rh) + l32 * C::KSTR + (lane >> 5) * 8 + ks * 16);
+        }, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq, P.table_inv);
         LDS_BARRIER();
         if (next >= 0) WIN_PREFETCH(next, 2)
 
         WaveState<D> st;
         init_state<D>(st);
-        // active key tiles of query tile `wave`: the dense prefix, then the diagonal; chunks of WIN_NB
-        for (int a0 = 0; a0 < nact; a0 += WIN_NB) {
-            int blk[WIN_NB], key0[WIN_NB];
-#pragma unroll
-            for (int b = 0; b < WIN_NB; ++b) {
-                int a = a0 + b;
-                blk[b] = a < P.n_pre ? a : wave;
-                key0[b] = blk[b] * 32;
-            }
+        // active key tiles of query tile `wave`: the dense prefix, then the diagonal
+        for (int a = 0; a < nact; ++a) {
+            const int blk[1] = { a < P.n_pre ? a : wave }, key0[1] = { blk[0] * 32 };
             // only the last 32-key tile of the window can cross S
-            bool ragged = false;
-#pragma unroll
-            for (int b = 0; b < WIN_NB; ++b) ragged |= (a0 + b < nact) && key0[b] + 32 > S;
-            attn_chunk<D, WIN_NB, WinTab>(st, qf, Ks, Vs, krc, blk, key0, min(WIN_NB, nact - a0), ragged, S, P.scale_log2e, tq_h, tq_w);
-            // after the second chunk (the only one, when the tile has one): early enough to cover the request's
-            // latency with the last chunk and the output stores on the tiles that have three, and not in the same
+            if (key0[0] + 32 > S) attn_chunk_step_onehot<D, 1, true, 16>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            else attn_chunk_step_onehot<D, 1, false, 16>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            // after the second tile (the only one, when there is one): early enough to cover the request's
+            // latency with the last tile and the output stores on the tiles that have three, and not in the same
             // burst as the K or the V requests
-            if (a0 == (nact > WIN_NB ? WIN_NB : 0) && next >= 0) WIN_PREFETCH_Q(next)
+            if (a == (nact > 1 ? 1 : 0) && next >= 0) WIN_PREFETCH_Q(next)
         }
         finish_and_store<D, window_stage_stride<D>()>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
     }
+}
+
+// ------------------------------------------------------------------ window kernel, a wave to a query tile
+// One workgroup = one wave = one 32-query tile: the active key blocks one after the other through LDS of its own, the next one
+// in registers, no barriers.  The persistent kernel above stages a problem's K and V once for its seven waves, but with one workgroup
+// to a CU it is bound by latency where there are few problems (set-up, tables, requests and seven waves' barriers in a chain, 15 us) and by its seven
+// tiles on four SIMDs and its nearly empty last round where there are more.  Here everything up to the first key block is requested
+// at once, twelve waves share a CU (eight at d = 80), and the tiles of a problem, which run next to each other on one XCD, find each other's K and V
+// in its L2.  us, persistent kernel with look-ups -> this one, cold inputs, 14 x 14, r = 0.4: d = 64, 48 problems 15.4 -> 7.7, 300 17.1 -> 12.5,
+// 800 30.2 -> 24.7, 1600 48.9 -> 42.9, 3200 86.3 -> 80.4 (5.6 TB/s of q, k, v and output, 3.9 bytes from the L2 for one of those); dense, 3200 140 -> 125; d = 32, 2400 54.6 -> 38.9; d = 16 49.2 -> 29.0.
+// Two blocks ahead, which leaves registers for two waves a SIMD, is slower (d = 64, 1600 problems 44.2 -> 47.8).
+template <int D, bool FAR>
+struct WinWave {
+    using C = AttnCfg<D>;
+    static constexpr int AHEAD = D <= 32 ? 2 : 1;         // key blocks requested ahead, in registers
+    static constexpr int LOADS = C::CH / 2;               // 16-byte chunks of a block's K (and V) per lane
+    static constexpr int KV = 32 * C::KSTR;               // elements of a block of K or V in LDS
+    static constexpr int WAVES = D <= 64 && !FAR ? 3 : 2; // per SIMD: the register budget
+    static size_t lds_bytes(int nact) { return (size_t)2 * KV * 2 + 32 * WIN_OSTR * sizeof(WinTab) + (size_t)nact * 32 * 4; }
+};
+
+// Problems (window, head) prob0 .. prob0 + n_problems - 1.  FAR: rows of a window need 64-bit byte offsets.
+template <int D, bool FAR>
+__global__ void __launch_bounds__(64, (WinWave<D, FAR>::WAVES))
+attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
+{
+    using C = AttnCfg<D>;
+    using G = WinWave<D, FAR>;
+    using Offset = std::conditional_t<FAR, uint64_t, uint32_t>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    bf16 *Ks = reinterpret_cast<bf16 *>(smem), *Vs = Ks + G::KV;          // one block of keys
+    WinTab *tq = reinterpret_cast<WinTab *>(Vs + G::KV);
+    uint32_t *krc = reinterpret_cast<uint32_t *>(tq + 32 * WIN_OSTR);      // cells of every active block, in the order of the list
+    // the tiles of a problem, and runs of problems, on one XCD (workgroup b sits on XCD b & 7)
+    const int per_xcd = (n_problems + 7) >> 3, slot = (int)(blockIdx.x >> 3), qt = slot % T;
+    int prob = (int)(blockIdx.x & 7) * per_xcd + slot / T;
+    if (prob >= n_problems) return;
+    prob += prob0;
+    const int grp = prob / P.h, head = prob % P.h;
+    clamp_fp16();
+    const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5, S = P.S;
+    const int nact = P.n_pre + (qt >= P.n_pre ? 1 : 0);
+    const int qpos = qt * 32 + l32, qclamp = min(qpos, S - 1);
+    const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
+    const long base = (long)grp * S * P.row_stride + (long)head * D;
+    const unsigned char *kbase = reinterpret_cast<const unsigned char *>(P.k + base), *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
+    const Offset rs2 = (Offset)P.row_stride * 2u;
+    auto block_at = [&](int a) { return a < P.n_pre ? a : qt; };
+
+    // everything up to the first key blocks is requested at once, in the order in which it is wanted
+    constexpr int PAIRS = 4;                       // pairs of active blocks: at most 7 blocks (S <= 224)
+    int32_t qcell = sg[qclamp], cell[PAIRS];
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i)
+        if (2 * i < nact) cell[i] = sg[min(block_at(min(2 * i + half, nact - 1)) * 32 + l32, S - 1)];
+    long my_row = -1;
+    if (qpos < S) my_row = P.out_rows ? (long)P.out_rows[(long)grp * S + qpos] : (long)grp * S + qpos;
+    bf16x8 qf[C::KS], rel[2][C::KS];
+    load_q_frags<D>(qf, P.q + base + (long)qclamp * P.row_stride);
+#pragma unroll
+    for (int tab = 0; tab < 2; ++tab)              // rows past the table repeat its last one: never looked up
+        load_q_frags<D>(rel[tab], (tab ? P.rel_w : P.rel_h) + min(l32, 2 * P.w - 2) * D);
+    u32x4 rk[G::AHEAD][G::LOADS], rv[G::AHEAD][G::LOADS];
+    auto load_block = [&](u32x4 (&k)[G::LOADS], u32x4 (&v)[G::LOADS], int a) {
+        const int key0 = block_at(a) * 32;
+#pragma unroll
+        for (int i = 0; i < G::LOADS; ++i) {
+            const int id = lane + 64 * i;          // pad keys repeat the last row: finite values, masked
+            const Offset at = (Offset)min(key0 + id / C::CH, S - 1) * rs2 + id % C::CH * 16;
+            k[i] = *reinterpret_cast<const u32x4 *>(kbase + at);
+            v[i] = *reinterpret_cast<const u32x4 *>(vbase + at);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < G::AHEAD; ++u)
+        if (u < nact) load_block(rk[u], rv[u], u);
+    __builtin_amdgcn_sched_barrier(0);
+
+    set_ones_columns<D>(Vs, 32, lane, 64);
+    const uint32_t qrc = cell_row_col(qcell, P.w);
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i)
+        if (2 * i + half < nact) krc[64 * i + lane] = cell_row_col(cell[i], P.w);
+    WinTab *tq_lane = tq + l32 * WIN_OSTR;
+    build_bias_operands_window<D>(qf, [&](int tab, int ks) { return rel[tab][ks]; }, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq, P.table_inv);
+
+    WaveState<D> st;
+    init_state<D>(st);
+    for (int a0 = 0; a0 < nact; a0 += G::AHEAD) {
+#pragma unroll
+        for (int u = 0; u < G::AHEAD; ++u) {
+            const int a = a0 + u;
+            if (a >= nact) break;
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < G::LOADS; ++i) {
+                const int id = lane + 64 * i, at = id / C::CH * C::KSTR + id % C::CH * 8;
+                *reinterpret_cast<u32x4 *>(Ks + at) = rk[u][i];
+                *reinterpret_cast<u32x4 *>(Vs + at) = rv[u][i];
+            }
+            wave_lds_fence();
+            if (a + G::AHEAD < nact) load_block(rk[u], rv[u], a + G::AHEAD);
+            const int blk[1] = { 0 }, key0[1] = { block_at(a) * 32 };
+            if (key0[0] + 32 > S) attn_chunk_step_onehot<D, 1, true, 16>(st, qf, Ks, Vs, krc + 32 * a, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            else attn_chunk_step_onehot<D, 1, false, 16>(st, qf, Ks, Vs, krc + 32 * a, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+        }
+    }
+    wave_lds_fence();
+    finish_and_store<D>(st, Ks, P.out + (long)head * D, (long)P.h * D, my_row);
 }
 
 // ------------------------------------------------------------------ global kernel
@@ -1290,8 +1377,8 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
                 else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
             } else {
                 const int nb = min(NB, nblk - c0);
-                if (ragged) attn_chunk_step<D, NB, true, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
-                else attn_chunk_step<D, NB, false, false, GlbTab, true, true>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
+                if (ragged) attn_chunk_step<D, NB, true, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
+                else attn_chunk_step<D, NB, false, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
             }
             if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
         }
@@ -1347,30 +1434,54 @@ inline int device_shape(DeviceShape &out)
 }
 
 template <int D>
+int launch_window_waves(const AttnParams &P, long n_problems, int nqb, hipStream_t st)
+{
+    const int nact = P.n_pre < nqb ? P.n_pre + 1 : nqb;
+    const bool far = (unsigned long)(P.S - 1) * P.row_stride * 2 + 2 * D > 0xffffffffUL;
+    auto kern = far ? attn_window_kernel_waves<D, true> : attn_window_kernel_waves<D, false>;
+    constexpr long MOST = 1L << 22;                       // a launch has fewer than 2^32 threads
+    for (long p0 = 0; p0 < n_problems; p0 += MOST) {
+        const int n = (int)(n_problems - p0 < MOST ? n_problems - p0 : MOST);
+        hipLaunchKernelGGL(kern, dim3(8 * ssam_div_up(n, 8) * nqb), dim3(64), (WinWave<D, false>::lds_bytes(nact)), st, P, (int)p0, n, nqb);
+    }
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
+}
+
+template <int D>
 int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_t st)
 {
     DeviceShape ds;
     if (int rc = device_shape(ds); rc != SSAM_OK) return rc;
     if (mask_block == 32) {
-        int nqb = ssam_div_up(P.S, 32);
-        size_t lds = window_lds_bytes<D>(nqb, P.w);
-        if (lds > ds.lds) return SSAM_EUNSUPPORTED;
-        // the queries of the next problem land in LDS through loads whose LDS address is a 16-bit immediate-free M0
-        // offset: their landing area is first in LDS and must end below 64 KB
-        if ((size_t)nqb * window_q_bytes<D>() > 64 * 1024) return SSAM_EUNSUPPORTED;
-        auto kern = attn_window_kernel<D>;
-        if (lds > 64 * 1024 &&
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return SSAM_EHIP;
-        if (ssam_div_up((long)nqb * 32 * AttnCfg<D>::CH, nqb * 64) > WIN_MAX_LOADS) return SSAM_EUNSUPPORTED;
-        if (2 * P.w - 1 > 32) return SSAM_EUNSUPPORTED;       // the window bias tables are one 32-row MFMA tile
-        int n_problems = groups * P.h;
-        // persistent workgroups: as many as fit on the device's CUs at once for this LDS footprint
-        int per_cu = (int)(ds.lds / lds);
-        if (per_cu < 1) per_cu = 1;
-        if (per_cu > 4) per_cu = 4;
-        int grid = n_problems < ds.cus * per_cu ? n_problems : ds.cus * per_cu;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(nqb * 64), lds, st, P, groups);
+        const int nqb = ssam_div_up(P.S, 32), n_problems = groups * P.h;
+        if (2 * P.w - 1 > 32) return SSAM_EUNSUPPORTED;       // a table is one 32-row MFMA tile, its entries one 16-entry operand
+        if constexpr (D <= 64) {
+            return launch_window_waves<D>(P, n_problems, nqb, st);
+        } else {
+            // About one and a half problems to a CU, where the persistent workgroups' second round would be half empty (r = 0.4, 400
+            // problems 19.5 us against 18.6, 464 19.9 against 21.5; dense, 352 26.4 against 26.2, 400 26.6 against 27.5; one window of 16 heads, which the
+            // persistent kernel keeps on one XCD, 52 against 8).  Above, staging a problem once wins at d = 80: K and V of three blocks
+            // ahead of eight waves no longer fit beside Q in what a CU can request (1600 problems 55 against 58.5, dense 77 against 90)
+            const int nact = P.n_pre < nqb ? P.n_pre + 1 : nqb;
+            if (n_problems <= (nact <= 5 ? 25 : 22) * ds.cus / 16) return launch_window_waves<D>(P, n_problems, nqb, st);
+            size_t lds = window_lds_bytes<D>(nqb, P.w);
+            if (lds > ds.lds) return SSAM_EUNSUPPORTED;
+            // the queries of the next problem land in LDS through loads whose LDS address is a 16-bit immediate-free M0
+            // offset: their landing area is first in LDS and must end below 64 KB
+            if ((size_t)nqb * window_q_bytes<D>() > 64 * 1024) return SSAM_EUNSUPPORTED;
+            auto kern = attn_window_kernel<D>;
+            if (lds > 64 * 1024 &&
+                hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                return SSAM_EHIP;
+            if (ssam_div_up((long)nqb * 32 * AttnCfg<D>::CH, nqb * 64) > WIN_MAX_LOADS) return SSAM_EUNSUPPORTED;
+            // persistent workgroups: as many as fit on the device's CUs at once for this LDS footprint
+            int per_cu = (int)(ds.lds / lds);
+            if (per_cu < 1) per_cu = 1;
+            if (per_cu > 4) per_cu = 4;
+            int grid = n_problems < ds.cus * per_cu ? n_problems : ds.cus * per_cu;
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(nqb * 64), lds, st, P, groups);
+        }
     } else {
         int T = ssam_div_up(P.S, GLB_TILE);
         size_t lds = global_lds_bytes<D>(P.w);
@@ -1434,7 +1545,7 @@ extern "C" int ssam_sparse_attention(const void *q, const void *k, const void *v
     P.n_pre = ssam_prefix_tiles(ssam_div_up(S, mask_block), r);
     P.scale_log2e = scale * LOG2E;
     if (!(scale > 0.f)) return SSAM_EINVAL;      // the global kernel's bias table holds bias / scale
-    const int shift = bias_shift(scale);
+    const int shift = bias_shift(scale, mask_block == 32);
     P.half_one = 0x3c00u + ((uint32_t)shift << 10);
     P.table_one = ldexpf(1.f, shift);
     P.table_inv = ldexpf(1.f / scale, -shift);
