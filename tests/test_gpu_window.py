@@ -34,14 +34,17 @@ def _case(groups, w, h, d, seed):
 
 @pytest.mark.parametrize("w", [8, 14])
 @pytest.mark.parametrize("r", [0.2, 0.4, 1.0])
-@pytest.mark.parametrize("groups", [26, 120])
-def test_both_kernels_of_d80(groups, r, w):
-    """26 and 120 windows of 16 heads loop over persistent workgroups, five of them run a wave to a tile: the same bits."""
-    announce("d = 80", groups, r, w)
+@pytest.mark.parametrize("groups,own", [(26, False), (120, False), (120, True)])
+def test_both_kernels_of_d80(groups, own, r, w):
+    """26 and 120 windows of 16 heads loop over persistent workgroups, five of them run a wave to a tile: the same bits, with an
+    order for all windows and with one for each."""
+    announce("d = 80", groups, own, r, w)
     qkv, rel, sigma = _case(groups, w, 16, 80, groups)
+    if own:
+        sigma = torch.stack([torch.randperm(w * w, generator=torch.Generator().manual_seed(g)) for g in range(groups)]).int().to(DEV)
     many = B.ssam_sparse_attention(qkv, *rel, sigma, w, 32, r)
     for g in range(0, groups, 5):
-        few = B.ssam_sparse_attention(qkv[g:g + 5].contiguous(), *rel, sigma, w, 32, r)
+        few = B.ssam_sparse_attention(qkv[g:g + 5].contiguous(), *rel, sigma[g:g + 5].contiguous() if own else sigma, w, 32, r)
         assert torch.equal(few, many[g:g + 5]), g
 
 
