@@ -730,8 +730,8 @@ attn_window_kernel(AttnParams P, int n_groups)
 // to a CU it is bound by latency where there are few problems (set-up, tables, requests and seven waves' barriers in a chain, 15 us) and by its seven
 // tiles on four SIMDs and its nearly empty last round where there are more.  Here everything up to the first key block is requested
 // at once, twelve waves share a CU (eight at d = 80), and the tiles of a problem, which run next to each other on one XCD, find each other's K and V
-// in its L2.  us, persistent kernel with look-ups -> this one, cold inputs, 14 x 14, r = 0.4: d = 64, 48 problems 15.4 -> 7.7, 300 17.1 -> 12.5,
-// 800 30.2 -> 24.7, 1600 48.9 -> 42.9, 3200 86.3 -> 80.4 (5.6 TB/s of q, k, v and output, 3.9 bytes from the L2 for one of those); dense, 3200 140 -> 125; d = 32, 2400 54.6 -> 38.9; d = 16 49.2 -> 29.0.
+// in its L2.  us, persistent kernel with look-ups -> this one, cold inputs, 14 x 14, r = 0.4: d = 64, 64 problems 15.9 -> 7.5, 400 18.1 -> 13.2,
+// 800 30.2 -> 24.0, 1600 48.9 -> 41.8, 3200 86.3 -> 79.5 (4.0 TB/s of q, k, v and output); dense, 3200 140 -> 125; d = 32, 2400 54.6 -> 38.9; d = 16 49.2 -> 29.0.
 // Two blocks ahead, which leaves registers for two waves a SIMD, is slower (d = 64, 1600 problems 44.2 -> 47.8).
 template <int D, bool FAR>
 struct WinWave {
@@ -775,10 +775,9 @@ attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
     constexpr int PAIRS = 4;                       // pairs of active blocks: at most 7 blocks (S <= 224)
     int32_t qcell = sg[qclamp], cell[PAIRS];
 #pragma unroll
-    for (int i = 0; i < PAIRS; ++i)
-        if (2 * i < nact) cell[i] = sg[min(block_at(min(2 * i + half, nact - 1)) * 32 + l32, S - 1)];
-    long my_row = -1;
-    if (qpos < S) my_row = P.out_rows ? (long)P.out_rows[(long)grp * S + qpos] : (long)grp * S + qpos;
+    for (int i = 0; i < PAIRS; ++i) cell[i] = sg[min(block_at(min(2 * i + half, nact - 1)) * 32 + l32, S - 1)];      // (behind a branch each would be waited for by itself)
+    const long row_at = (long)grp * S + qclamp;
+    const int32_t row_mapped = *(P.out_rows ? P.out_rows + row_at : sg + qclamp);      // without a map: read, not used
     bf16x8 qf[C::KS], rel[2][C::KS];
     load_q_frags<D>(qf, P.q + base + (long)qclamp * P.row_stride);
 #pragma unroll
@@ -797,8 +796,9 @@ attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
     };
 #pragma unroll
     for (int u = 0; u < G::AHEAD; ++u)
-        if (u < nact) load_block(rk[u], rv[u], u);
+        load_block(rk[u], rv[u], min(u, nact - 1));
     __builtin_amdgcn_sched_barrier(0);
+    const long my_row = qpos < S ? (P.out_rows ? (long)row_mapped : row_at) : -1;
 
     set_ones_columns<D>(Vs, 32, lane, 64);
     const uint32_t qrc = cell_row_col(qcell, P.w);
