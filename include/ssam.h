@@ -227,9 +227,10 @@ int ssam_linear_ln(const void *x, int ldx, const float *stats, const void *Wfp, 
  * {0..floor(r*T)-1} U {i}, tiles of mask_block tokens, T = ceil(S/mask_block).
  * B[p][p'] = q_p . rel_h[row(p)-row(p')+w-1] + q_p . rel_w[col(p)-col(p')+w-1]
  * (unscaled q), (row, col) = divmod(sigma[p], w): sigma maps scan position ->
- * spatial cell of the w x w grid, S = w*w.  The two terms of B are held as fp16:
- * windows, times log2 e (a term past +45400 is an infinity); global, over the scale and bounded to
- * +-128 or +-65504 * scale, whichever is more (a term past the lower bound gives its keys no weight).
+ * spatial cell of the w x w grid, S = w*w.  The two terms of B are held as fp16
+ * over the scale (and a power of two) and bounded.  Windows: to +-45400 or more at
+ * any scale.  Global: to +-128 or +-65504 * scale, whichever is more, from a scale of
+ * 6e-8 (a term past the lower bound gives its keys no weight).
  *   q, k, v  dev bf16; element (g, p, head, c) at ptr[(g*S+p)*row_stride + head*d + c]
  *            (a packed [groups][S][3][h][d] buffer: row_stride = 3*h*d, k = q + h*d, v = q + 2*h*d)
  *   rel_h, rel_w  dev bf16 [(2w-1)][d]

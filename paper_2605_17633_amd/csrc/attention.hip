@@ -61,6 +61,7 @@ struct AttnParams {
     uint32_t half_one;      // see bias_shift: 2^shift in fp16
     float table_one;        // and in fp32
     float table_inv;        // what turns a bias into an entry: 1 / (scale * 2^shift)
+    int q_exp;              // windows: the scores are formed with q * 2^q_exp (see window_scale); scale is that of these scores
 };
 
 template <int D>
@@ -132,13 +133,27 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 //   * with a small scale the table is 2^shift times smaller and the ones of that matrix, or what a looked-up entry is multiplied
 //     by, are 2^shift: shift is the least that puts 65504 * 2^shift * scale past 128 (bias_shift), since exp(-128) is the "no
 //     weight" that such a bias asks for.
-// The window kernels' shift is the least that puts a one past 1 / log2 e logits: their tables then have at least the range and the
-// small entries of logits in units of log 2, whatever the scale (from 2e-5).
-inline int bias_shift(float scale, bool window)
+inline int bias_shift(float scale)
 {
     int n = 0;
-    while (n < 15 && ldexpf(window ? scale * LOG2E : 65504.f / 128.f * scale, n) < 1.f) ++n;
+    while (n < 15 && ldexpf(65504.f / 128.f * scale, n) < 1.f) ++n;
     return n;
+}
+// Windows.  An entry of 1 is scale * 2^n * log2 e units of a logit in powers of two, by the choice of n at least 1 (the range of such
+// units: +-45400 as a logit) and below 512 (the spacing of the smallest entries is then 2^-15 of one; with n = 0 at a scale
+// of 1e6 a bias of 0.01 was 0), and n is 0 where it can be, from a scale of 0.7 to 350.  Ones of fp16 hold 2^-14 to 2^15; past those, below
+// a scale of 2e-5 and above 5e6, the rest goes into the queries, as a power of two that rounds nothing.
+struct WindowScale { int shift, q_exp; };
+inline WindowScale window_scale(float scale)
+{
+    const double unit = (double)scale * 1.4426950408889634;
+    int e, n = 0;
+    if (!(unit < HUGE_VAL)) return { 0, 0 };
+    frexp(unit, &e);                       // unit = 2^(e - 1) up to 2^e
+    if (e < 1) n = 1 - e;
+    else if (e > 9) n = 9 - e;
+    const int shift = n < -14 ? -14 : n > 15 ? 15 : n;
+    return { shift, shift - n };
 }
 // bit 23 of the mode register: fp16 results past the range are clamped instead of rounded to infinity
 __device__ __forceinline__ void clamp_fp16() { __builtin_amdgcn_s_setreg(1 | 23 << 6 | (1 - 1) << 11, 1); }
@@ -472,6 +487,20 @@ __device__ __forceinline__ void load_q_frags(bf16x8 *qf, const bf16 *qrow)
         qf[ks] = *reinterpret_cast<const bf16x8 *>(qrow + ks * 16 + half * 8);
 }
 
+// The wave's queries times 2^e (window_scale); what would overflow becomes the largest number, so that a zero key still gives 0.
+template <int D>
+__device__ __forceinline__ void scale_queries(bf16x8 *qf, int e)
+{
+    constexpr float MOST = 3.3895313892515355e38f;        // of bf16
+#pragma unroll
+    for (int ks = 0; ks < AttnCfg<D>::KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float x = (float)qf[ks][i], y = ldexpf(x, e);
+            if (fabsf(x) < INFINITY) qf[ks][i] = (bf16)fminf(fmaxf(y, -MOST), MOST);
+        }
+}
+
 // Normalise the wave's 32 x D output tile and write it out.  The accumulators hold O^T (lane = query,
 // registers = 4-feature groups); the tile goes through a per-wave LDS staging area ([32][STR] bf16) so
 // that the global stores are 16 bytes per lane and cover whole rows.  `stage` may overlay LDS that only
@@ -733,24 +762,25 @@ attn_window_kernel(AttnParams P, int n_groups)
 // in its L2.  us, persistent kernel with look-ups -> this one, cold inputs, 14 x 14, r = 0.4: d = 64, 64 problems 15.9 -> 7.5, 400 18.1 -> 13.2,
 // 800 30.2 -> 24.0, 1600 48.9 -> 41.8, 3200 86.3 -> 79.5 (4.0 TB/s of q, k, v and output); dense, 3200 140 -> 125; d = 32, 2400 54.6 -> 38.9; d = 16 49.2 -> 29.0.
 // Two blocks ahead, which leaves registers for two waves a SIMD, is slower (d = 64, 1600 problems 44.2 -> 47.8).
-template <int D, bool FAR>
+template <int D, bool ANY>
 struct WinWave {
     using C = AttnCfg<D>;
     static constexpr int AHEAD = D <= 32 ? 2 : 1;         // key blocks requested ahead, in registers
     static constexpr int LOADS = C::CH / 2;               // 16-byte chunks of a block's K (and V) per lane
     static constexpr int KV = 32 * C::KSTR;               // elements of a block of K or V in LDS
-    static constexpr int WAVES = D <= 64 && !FAR ? 3 : 2; // per SIMD: the register budget
+    static constexpr int WAVES = D <= 64 && !ANY ? 3 : 2; // per SIMD: the register budget
     static size_t lds_bytes(int nact) { return (size_t)2 * KV * 2 + 32 * WIN_OSTR * sizeof(WinTab) + (size_t)nact * 32 * 4; }
 };
 
-// Problems (window, head) prob0 .. prob0 + n_problems - 1.  FAR: rows of a window need 64-bit byte offsets.
-template <int D, bool FAR>
-__global__ void __launch_bounds__(64, (WinWave<D, FAR>::WAVES))
+// Problems (window, head) prob0 .. prob0 + n_problems - 1.  ANY: for rows of a window that need 64-bit byte offsets and for scales that the
+// queries take a part of.
+template <int D, bool ANY>
+__global__ void __launch_bounds__(64, (WinWave<D, ANY>::WAVES))
 attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
 {
     using C = AttnCfg<D>;
-    using G = WinWave<D, FAR>;
-    using Offset = std::conditional_t<FAR, uint64_t, uint32_t>;
+    using G = WinWave<D, ANY>;
+    using Offset = std::conditional_t<ANY, uint64_t, uint32_t>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16 *Ks = reinterpret_cast<bf16 *>(smem), *Vs = Ks + G::KV;          // one block of keys
     WinTab *tq = reinterpret_cast<WinTab *>(Vs + G::KV);
@@ -807,6 +837,7 @@ attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
         if (2 * i + half < nact) krc[64 * i + lane] = cell_row_col(cell[i], P.w);
     WinTab *tq_lane = tq + l32 * WIN_OSTR;
     build_bias_operands_window<D>(qf, [&](int tab, int ks) { return rel[tab][ks]; }, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq, P.table_inv);
+    if constexpr (ANY) if (P.q_exp != 0) scale_queries<D>(qf, P.q_exp);
 
     WaveState<D> st;
     init_state<D>(st);
@@ -1437,8 +1468,8 @@ template <int D>
 int launch_window_waves(const AttnParams &P, long n_problems, int nqb, hipStream_t st)
 {
     const int nact = P.n_pre < nqb ? P.n_pre + 1 : nqb;
-    const bool far = (unsigned long)(P.S - 1) * P.row_stride * 2 + 2 * D > 0xffffffffUL;
-    auto kern = far ? attn_window_kernel_waves<D, true> : attn_window_kernel_waves<D, false>;
+    const bool any = P.q_exp != 0 || (unsigned long)(P.S - 1) * P.row_stride * 2 + 2 * D > 0xffffffffUL;
+    auto kern = any ? attn_window_kernel_waves<D, true> : attn_window_kernel_waves<D, false>;
     constexpr long MOST = 1L << 22;                       // a launch has fewer than 2^32 threads
     for (long p0 = 0; p0 < n_problems; p0 += MOST) {
         const int n = (int)(n_problems - p0 < MOST ? n_problems - p0 : MOST);
@@ -1464,7 +1495,7 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_
             // persistent kernel keeps on one XCD, 52 against 8).  Above, staging a problem once wins at d = 80: K and V of three blocks
             // ahead of eight waves no longer fit beside Q in what a CU can request (1600 problems 55 against 58.5, dense 77 against 90)
             const int nact = P.n_pre < nqb ? P.n_pre + 1 : nqb;
-            if (n_problems <= (nact <= 5 ? 25 : 22) * ds.cus / 16) return launch_window_waves<D>(P, n_problems, nqb, st);
+            if (P.q_exp != 0 || n_problems <= (nact <= 5 ? 25 : 22) * ds.cus / 16) return launch_window_waves<D>(P, n_problems, nqb, st);
             size_t lds = window_lds_bytes<D>(nqb, P.w);
             if (lds > ds.lds) return SSAM_EUNSUPPORTED;
             // the queries of the next problem land in LDS through loads whose LDS address is a 16-bit immediate-free M0
@@ -1543,9 +1574,16 @@ extern "C" int ssam_sparse_attention(const void *q, const void *k, const void *v
     P.out_rows = out_rows;
     P.S = S; P.w = w; P.h = h;
     P.n_pre = ssam_prefix_tiles(ssam_div_up(S, mask_block), r);
+    if (!(scale > 0.f)) return SSAM_EINVAL;      // the bias tables hold bias / scale
+    int shift = bias_shift(scale);
+    P.q_exp = 0;
+    if (mask_block == 32) {
+        const WindowScale ws = window_scale(scale);
+        shift = ws.shift;
+        P.q_exp = ws.q_exp;
+        scale = ldexpf(scale, -ws.q_exp);
+    }
     P.scale_log2e = scale * LOG2E;
-    if (!(scale > 0.f)) return SSAM_EINVAL;      // the global kernel's bias table holds bias / scale
-    const int shift = bias_shift(scale, mask_block == 32);
     P.half_one = 0x3c00u + ((uint32_t)shift << 10);
     P.table_one = ldexpf(1.f, shift);
     P.table_inv = ldexpf(1.f / scale, -shift);

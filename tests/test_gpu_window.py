@@ -88,3 +88,58 @@ def test_bias_past_fp16(scale, bias, d, groups):
     p = np.exp(logit - logit.max(1, keepdims=True))
     assert np.array_equal(got, np.repeat(got[:1], groups, 0))
     assert_close(got[0], p @ v / p.sum(1, keepdims=True), f"window bias past fp16 d={d} scale={scale} bias={bias}")
+
+
+def _one_head(groups, d, seed, scale, mag):
+    """A window of 14 x 14 whose queries are of size `mag`, with biases of 18 to 30 on the keys some rows above a query, against 64 bits."""
+    w, S, rng = 14, 196, np.random.default_rng(seed)
+    sigma = np.ascontiguousarray(B.ssam_build_perm(w, w, 4)[0])
+    qkv = rng.normal(size=(1, S, 3, 1, d)).astype(np.float32)
+    qkv[:, :, 0, :, 0] = 4.0
+    qkv[:, :, 0] *= mag
+    qkv = inputs.bf16_round(qkv)
+    rel = [rng.normal(0, 0.2, size=(2 * w - 1, d)).astype(np.float32) for _ in range(2)]
+    rel[0][w + 2:], rel[0][w + 2:, 0] = 0.0, (18 + 4 * (np.arange(w - 3) % 4)) / 4
+    rel = [inputs.bf16_round((t / np.float32(mag)).astype(np.float32)) for t in rel]
+    got = B.ssam_sparse_attention(dev_bf16(np.repeat(qkv, groups, 0)), dev_bf16(rel[0]), dev_bf16(rel[1]), dev_i32(sigma), w, 32, 1.0, scale=scale)
+    q, k, v = (qkv[0, :, i, 0].astype(np.float64) for i in range(3))
+    logit = float(np.float32(scale)) * (q @ k.T)
+    for t, c in zip(rel, (sigma // w, sigma % w)):
+        logit += np.take_along_axis(q @ t.T.astype(np.float64), c[:, None] - c[None, :] + w - 1, axis=1)
+    p = np.exp(logit - logit.max(1, keepdims=True))
+    return got, p @ v / p.sum(1, keepdims=True)
+
+
+@pytest.mark.parametrize("groups", [1, 500])
+@pytest.mark.parametrize("d", [16, 64, 80])
+@pytest.mark.parametrize("scale", [1e-44, 1e-30, 1e-8, 1.9e-5, 2.3e-5, 0.6, 300.0, 400.0, 5e6, 7e6, 1e30])
+def test_any_scale(scale, d, groups):
+    """Queries of the size that gives logits of a few units at this scale: what the scale splits into (ones of fp16, the queries) is exact."""
+    announce("window scale", scale, d, groups)
+    mag = 2.0 ** np.clip(np.round(-np.log2(scale * d ** 0.5)), -116, 100)
+    got, want = _one_head(groups, d, 7, scale, mag)
+    assert bool((got == got[:1]).all())
+    assert_close(to_np(got)[0], want, f"window scale {scale} d={d}")
+
+
+@pytest.mark.parametrize("d", [16, 64, 80])
+@pytest.mark.parametrize("scale", [1e-44, 3e-39, 1e-30, 1e-8, 1e-6])
+def test_small_scale_keeps_the_bias(scale, d):
+    """Queries of size 1: the logits are the biases."""
+    announce("window bias alone", scale, d)
+    got, want = _one_head(3, d, 8, scale, 1.0)
+    assert_close(to_np(got)[0], want, f"window bias alone, scale {scale} d={d}")
+
+
+@pytest.mark.parametrize("groups", [1, 500])
+@pytest.mark.parametrize("d", [16, 64, 80])
+@pytest.mark.parametrize("e", [5, 16, 40, 100])
+def test_powers_of_two(e, d, groups):
+    """Queries 2^e times larger, tables and scale 2^e times smaller: the same bits."""
+    announce("window, powers of two", e, d, groups)
+    qkv, rel, sigma = _case(groups, 14, 1, d, 3)
+    want = B.ssam_sparse_attention(qkv, *rel, sigma, 14, 32, 0.6, scale=d ** -0.5)
+    far = qkv.clone()
+    far[:, :, 0] *= 2.0 ** e
+    got = B.ssam_sparse_attention(far, *[t * 2.0 ** -e for t in rel], sigma, 14, 32, 0.6, scale=d ** -0.5 * 2.0 ** -e)
+    assert torch.equal(got, want)
