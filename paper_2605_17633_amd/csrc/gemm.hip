@@ -265,10 +265,15 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 // The kernel takes whole slabs; below five of them its prologue is not earned back, and up to 32 rows packed weights have a kernel
 // with tiles of 32 (31 x 3840 x 3648: 12.9 us, the direct kernel 10.9).  Its requests address memory by 32-bit offsets from the tile's
 // first row, or from A's where rows are gathered.
+// Rows that do not begin on 128 bytes (torn: operands of such rows) take two lines for a slab's 128 bytes, and two chains over K pull
+// twice the bytes a flop of the large tiles: a slab takes 1.12 times as long for either operand and 1.36 for both in tiles below 128x128, 1.1 and 1.2
+// above.  Charged with more, since the others lose less there (a K-split 1.04 for both): of 639 row-major shapes with both operands torn 114 were
+// slower than without this kernel by more than 3 %, 84 % at most, with no such charge; 26, 13 % at most, with it, and 5 with one operand torn.
 // Fitted to 1339 shapes (M 8 to 24576, N 128 to 5120, K 128 to 5376, all epilogues, both layouts, weights that no cache holds; those
 // cost the others 0.2 us a megabyte on top of their estimates, which is left out here: with warm weights 784 x 2304 x 768 takes the ring
 // 8.9 us and this kernel 9.5).  What is taken is 1 % on average from the fastest form, 10 % faster on average than
-// without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
+// without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us); of 877 drawn later, down to
+// 8 rows, 15 % faster and slower on 21, the worst 60 x 2272 x 4416 row-major, 18.3 -> 23.8.  More than two rounds of packed problems
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
 int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us)
@@ -276,13 +281,15 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
     const int nk = K / GEMM_BK;
     if (K % GEMM_BK != 0 || nk < 5 || (packed && M <= 32)) return -1;
     if ((long)256 * ld.a * 2 >= 1L << 31 || (rows_a + 1) * ld.a * 2 >= 1L << 32 || (long)256 * (packed ? K : ld.w) * 2 >= 1L << 31) return -1;
+    const int torn = (ld.a % GEMM_BK != 0) + (!packed && ld.w % GEMM_BK != 0);
     int best = -1;
     double best_us = 1e30;
     for (int i = 0; i < GEMM_WIDE_COUNT; ++i) {
         const WideTile &t = wide_tiles[i];
+        const double slab = t.t_slab * (1.0 + torn * (t.bm * t.bn < 128 * 128 ? 0.3 : 0.15));
         const int rounds = ssam_div_up(ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 8), 32);      // (see the kernel's XCDs)
         if (rounds > (packed ? 2 : 4)) continue;
-        const double us = t.t0 + rounds * (t.t_round + nk * t.t_slab + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
+        const double us = t.t0 + rounds * (t.t_round + nk * slab + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
                           + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
         if (us < best_us) { best_us = us; best = i; }
     }
@@ -355,7 +362,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
         double us;
         tile = pick_tile(M, N, K, epilogue, ws, packed, us);
         ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
-        if (const int wide = pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, true)); wide >= 0) {
+        if (const int wide = pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0)); wide >= 0) {
             const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, no_fold, st };
             switch (epilogue) {
             case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
@@ -463,17 +470,23 @@ extern "C" int ssam_linear_form(int M, int N, int K, int epilogue, int packed, i
     return ring >= 0 ? 16 + ring : tile;
 }
 
-// The wide kernel's tile that the same contraction takes instead (its index in wide_tiles), or -1.
-extern "C" int ssam_linear_wide_form(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes)
+// The wide kernel's tile that the same contraction takes instead (its index in wide_tiles), or -1; _ld: with rows of lda and ldw elements.
+extern "C" int ssam_linear_wide_form_ld(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes, int lda, int ldw)
 {
-    if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > SSAM_EPI_BIAS_SCATTER) return -1;
+    if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > SSAM_EPI_BIAS_SCATTER || lda < K || ldw < K) return -1;
     double us = folded_ln_us((M / 128) * (N / 256), K);
     alignas(16) unsigned char some;
     const SplitWs ws = { workspace_bytes ? &some : nullptr, workspace_bytes };
+    const bool whole_lines = lda % GEMM_BK == 0 && ldw % GEMM_BK == 0;
     if (!folded) pick_tile(M, N, K, epilogue, ws, packed != 0, us);
-    pick_ring(M, N, K, packed != 0 || folded != 0, K % GEMM_BK == 0, us);
-    return pick_wide(M, N, K, epilogue, GemmLd{ K, K, N }, packed != 0 || folded != 0, 0, us,
-                     folded ? us : other_layout_us(M, N, K, epilogue, ws, packed != 0, true));
+    pick_ring(M, N, K, packed != 0 || folded != 0, folded != 0 || whole_lines, us);
+    return pick_wide(M, N, K, epilogue, GemmLd{ lda, ldw, N }, packed != 0 || folded != 0, 0, us,
+                     folded ? us : other_layout_us(M, N, K, epilogue, ws, packed != 0, lda % GEMM_BK == 0));
+}
+
+extern "C" int ssam_linear_wide_form(int M, int N, int K, int epilogue, int packed, int folded, size_t workspace_bytes)
+{
+    return ssam_linear_wide_form_ld(M, N, K, epilogue, packed, folded, workspace_bytes, K, K);
 }
 
 extern "C" size_t ssam_linear_workspace_bytes(void) { return GEMM_SPLIT_WS_BYTES; }

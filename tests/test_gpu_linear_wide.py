@@ -63,6 +63,32 @@ MLP = [(0, 131, 1664, 640), (1, 270, 3328, 640), (2, 513, 3712, 512), (3, 385, 3
        (5, 1734, 3328, 640), (6, 1161, 3328, 384), (7, 6540, 2432, 384), (8, 2326, 3456, 384), (9, 6438, 1792, 512),
        (10, 2314, 3712, 384), (11, 1567, 7552, 1792)]
 
+# (tile, packed, epilogue, M, N, K, elements past the end of a row of A, of W, of C)
+STRIDED = [(0, False, 2, 42, 304, 512, 64, 64, 8), (1, False, 2, 8326, 72, 448, 8, 8, 16), (2, False, 0, 6584, 264, 512, 8, 64, 24), (2, True, 2, 769, 2560, 1280, 8, 0, 8),
+           (3, False, 0, 4978, 264, 576, 8, 8, 16), (4, False, 3, 8333, 200, 320, 64, 64, 8), (4, True, 0, 782, 2560, 384, 8, 0, 8), (5, True, 2, 1946, 3072, 1280, 8, 0, 16),
+           (6, False, 0, 8260, 400, 384, 8, 8, 16), (7, False, 1, 6409, 2320, 320, 8, 8, 8), (10, False, 2, 7221, 1032, 320, 64, 64, 24), (11, True, 0, 8200, 2944, 448, 8, 0, 8)]
+
+
+@pytest.mark.parametrize("tile,packed,epi,M,N,K,pa,pw,pc", STRIDED)
+def test_row_strides(tile, packed, epi, M, N, K, pa, pw, pc):
+    """Rows of A, W and C with elements between them, which are not read and not written."""
+    announce("wide linear, row strides", tile, packed, epi, M, N, K, pa, pw, pc)
+    A, W, b, gen = _operands(M, N, K)
+    far = lambda t, pad: torch.cat([t, torch.full((t.shape[0], pad), 7.0, dtype=t.dtype, device=DEV)], 1)[:, :t.shape[1]]
+    to = {"row_map": torch.randperm(M, generator=gen, device=DEV).to(torch.int32), "rows_per_batch": M, "map_batch_stride": M, "dst_rows_per_batch": M} if epi >= 2 else {}
+    x = torch.randn(M, N, generator=gen, device=DEV).to(torch.bfloat16)
+    C = torch.full((M, N + pc), 3.0, dtype=torch.bfloat16, device=DEV)
+    C[:, :N] = x
+    B.ssam_linear_ld(far(A, pa), B.ssam_pack_weight(W) if packed else far(W, pw), b, C[:, :N], epilogue=epi, w_packed=packed, **to)
+    assert bool((C[:, N:] == 3.0).all())
+    want = A.double() @ W.double().t() + b.double()
+    want = torch.nn.functional.gelu(want) if epi == 1 else want
+    if epi >= 2:
+        back = to["row_map"].long().argsort()
+        want = want[back] + (x.double() if epi == 2 else 0.0)
+    err = (C[:, :N].double() - want).abs()
+    assert bool((err <= 2.0 ** -8 * want.abs() + 2e-5).all()), float((err / (want.abs() + 1e-2)).max())
+
 
 @pytest.mark.parametrize("tile,packed,epi,M,N,K", CASES)
 def test_every_tile(tile, packed, epi, M, N, K):

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2605_17633_amd import binding as B
 from test_gpu_linear_small import FOLDED as SMALL_FOLDED, FORM_CASES, MLP as SMALL_MLP
-from test_gpu_linear_wide import CASES, FOLDED, MLP
+from test_gpu_linear_wide import CASES, FOLDED, MLP, STRIDED
 
 
 def wide(M, N, K, epi=0, packed=False, folded=False, ws=32 << 20):
@@ -44,3 +44,21 @@ def test_two_chains_whatever_the_layout(epi):
         for N, K in ((768, 768), (768, 3072), (1280, 1280), (3072, 768), (256, 1024)):
             a, b = wide(M, N, K, epi, False), wide(M, N, K, epi, True)
             assert a == b or not (0 <= a < 4 or 0 <= b < 4), (M, N, K, a, b)
+
+
+def wide_ld(M, N, K, epi, packed, lda, ldw, ws=32 << 20):
+    return B.lib().ssam_linear_wide_form_ld(*(C.c_int(int(v)) for v in (M, N, K, epi, packed, False)), C.c_size_t(ws), C.c_int(lda), C.c_int(ldw))
+
+
+def test_row_strides_reach_the_kernel():
+    for tile, packed, epi, M, N, K, pa, pw, _ in STRIDED:
+        assert wide_ld(M, N, K, epi, packed, K + pa, K + pw, ws=0) == tile, (tile, packed, epi, M, N, K, pa, pw)
+    assert {t < 4 for t, *_ in STRIDED} == {True, False}
+
+
+@pytest.mark.parametrize("M,N,K,epi,us", [(30, 2488, 3648, 2, (18.1, 23.4)), (232, 368, 3776, 1, (16.5, 20.4)), (51, 272, 3648, 2, (14.5, 17.7)),
+                                          (136, 336, 3840, 1, (15.5, 20.4)), (327, 424, 3584, 1, (17.6, 19.5))])
+def test_rows_that_tear_lines_are_charged(M, N, K, epi, us):
+    """us: measured with rows of A and W that do not begin on 128 bytes, the others and this kernel."""
+    assert wide_ld(M, N, K, epi, False, K + 8, K + 8) == -1
+    assert wide_ld(M, N, K, epi, False, K + 64, K + 64) == wide(M, N, K, epi) >= 0
