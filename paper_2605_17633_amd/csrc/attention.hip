@@ -30,8 +30,8 @@
 //
 // Three launch shapes:
 //   window kernel, a wave to a query tile: one-wave workgroups, each walks the active key blocks of its tile by itself
-//                  (d <= 64, and few problems at d = 80);
-//   window kernel, persistent (d = 80): workgroups looping over (window, head) problems, one
+//                  (few problems or tiles at d = 80, nearly all below);
+//   window kernel, persistent (window_waves_most): workgroups looping over (window, head) problems, one
 //                  wave per 32-query tile (= mask tile of 32), the window's whole K
 //                  and V in LDS, the next problem's K and V prefetched into registers
 //                  and its Q straight into LDS, in three pieces, the rel-pos tables
@@ -1479,6 +1479,29 @@ int launch_window_waves(const AttnParams &P, long n_problems, int nqb, hipStream
     return SSAM_OK;
 }
 
+// The most problems that go to a wave a tile; above, staging a problem's K and V once for all of its tiles wins.  us, wave a tile | persistent.
+//   d = 80: K and V of three blocks ahead of eight waves no longer fit beside Q in what a CU can request (14 x 14, 1600 problems 58.5 | 55, dense 90 | 77); few
+//           problems leave the persistent workgroups' second round half empty (r = 0.4, 400 problems 18.6 | 19.5, 464 21.5 | 19.9; dense, 352 26.2 | 26.4,
+//           400 27.5 | 26.6; one window of 16 heads, which the persistent kernel keeps on one XCD, 8 | 52).  With fewer tiles a workgroup has
+//           fewer waves for the same requests, and wins later (r = 0.4: 12 x 12, 800 problems 24.5 | 30, 2400 62 | 65.5, dense, 4000 129 | 127.5; 10 x 10,
+//           1600 32 | 36, 4800 85 | 85, r = 1 104 | 114; 9 x 9, 800 15.6 | 17.1, 3200 42.6 | 40.2) or never (8 x 8, 3200 30 | 42)
+//   d = 64: four tiles, one to a SIMD, are the persistent kernel's best case; it wins where the tiles request K and V more than 2.5 times over (10 x 10, r = 0.4,
+//           2048 28.4 | 28, 3200 41.5 | 39, 6400 78 | 71; 11 x 11, r = 0.75, 6400 100 | 91.5; r = 0.4, twice over, 3200 43.4 | 44.5)
+//   below:  never (10 x 10, 6400 problems, r = 0.6, d = 32 58.7 | 75.6)
+template <int D>
+long window_waves_most(int nqb, int nact, int S, int cus)
+{
+    constexpr long ALL = 1L << 60;
+    if (D == 64) return nqb == 4 && 4 * 32 * nact > 2.5 * S ? 8L * cus : ALL;
+    switch (nqb) {
+    case 1: case 2: return ALL;
+    case 3: return 4L * cus;
+    case 4: return 16L * cus;
+    case 5: return 12L * cus;
+    default: return (nact <= 5 ? 25L : 22L) * cus / 16;
+    }
+}
+
 template <int D>
 int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_t st)
 {
@@ -1487,15 +1510,11 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_
     if (mask_block == 32) {
         const int nqb = ssam_div_up(P.S, 32), n_problems = groups * P.h;
         if (2 * P.w - 1 > 32) return SSAM_EUNSUPPORTED;       // a table is one 32-row MFMA tile, its entries one 16-entry operand
-        if constexpr (D <= 64) {
+        if constexpr (D < 64) {
             return launch_window_waves<D>(P, n_problems, nqb, st);
         } else {
-            // About one and a half problems to a CU, where the persistent workgroups' second round would be half empty (r = 0.4, 400
-            // problems 19.5 us against 18.6, 464 19.9 against 21.5; dense, 352 26.4 against 26.2, 400 26.6 against 27.5; one window of 16 heads, which the
-            // persistent kernel keeps on one XCD, 52 against 8).  Above, staging a problem once wins at d = 80: K and V of three blocks
-            // ahead of eight waves no longer fit beside Q in what a CU can request (1600 problems 55 against 58.5, dense 77 against 90)
             const int nact = P.n_pre < nqb ? P.n_pre + 1 : nqb;
-            if (P.q_exp != 0 || n_problems <= (nact <= 5 ? 25 : 22) * ds.cus / 16) return launch_window_waves<D>(P, n_problems, nqb, st);
+            if (P.q_exp != 0 || n_problems <= window_waves_most<D>(nqb, nact, P.S, ds.cus)) return launch_window_waves<D>(P, n_problems, nqb, st);
             size_t lds = window_lds_bytes<D>(nqb, P.w);
             if (lds > ds.lds) return SSAM_EUNSUPPORTED;
             // the queries of the next problem land in LDS through loads whose LDS address is a 16-bit immediate-free M0

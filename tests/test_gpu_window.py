@@ -1,5 +1,5 @@
 """Window attention at the edges of its kernels: every window side, a last tile of one to thirty-two keys, one to seven active blocks,
-both kernels of d = 80 on either side of the line between them, biases past the range of fp16, rows far apart."""
+both kernels on either side of the line between them, biases past the range of fp16, any softmax scale, rows far apart."""
 import ctypes as C
 
 import numpy as np
@@ -29,7 +29,7 @@ def _case(groups, w, h, d, seed):
     gen.manual_seed(seed)
     qkv = (torch.randn(groups, w * w, 3, h, d, generator=gen, device=DEV) * 0.7).bfloat16()
     rel = [(torch.randn(2 * w - 1, d, generator=gen, device=DEV) * 0.1).bfloat16() for _ in range(2)]
-    return qkv, rel, dev_i32(B.ssam_build_perm(w, w, 4)[0])
+    return qkv, rel, dev_i32(B.ssam_build_perm(w, w, 4 if w % 2 == 0 else 1)[0])
 
 
 @pytest.mark.parametrize("w", [8, 14])
@@ -44,6 +44,20 @@ def test_both_kernels_of_d80(groups, own, r, w):
         sigma = torch.stack([torch.randperm(w * w, generator=torch.Generator().manual_seed(g)) for g in range(groups)]).int().to(DEV)
     many = B.ssam_sparse_attention(qkv, *rel, sigma, w, 32, r)
     for g in range(0, groups, 5):
+        few = B.ssam_sparse_attention(qkv[g:g + 5].contiguous(), *rel, sigma[g:g + 5].contiguous() if own else sigma, w, 32, r)
+        assert torch.equal(few, many[g:g + 5]), g
+
+
+@pytest.mark.parametrize("own", [False, True])
+@pytest.mark.parametrize("d,w,r,groups", [(64, 10, 0.4, 132), (64, 11, 0.75, 132), (80, 9, 0.4, 66), (80, 10, 1.0, 260), (80, 12, 0.2, 196)])
+def test_both_kernels_by_side(d, w, r, groups, own):
+    """Windows of 16 heads, just enough for the persistent workgroups, and five of them a wave to a tile: the same bits."""
+    announce("window, both kernels", d, w, r, groups, own)
+    qkv, rel, sigma = _case(groups, w, 16, d, groups)
+    if own:
+        sigma = torch.stack([torch.randperm(w * w, generator=torch.Generator().manual_seed(g)) for g in range(groups)]).int().to(DEV)
+    many = B.ssam_sparse_attention(qkv, *rel, sigma, w, 32, r)
+    for g in range(0, groups - 4, 41):
         few = B.ssam_sparse_attention(qkv[g:g + 5].contiguous(), *rel, sigma[g:g + 5].contiguous() if own else sigma, w, 32, r)
         assert torch.equal(few, many[g:g + 5]), g
 
