@@ -140,7 +140,6 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             else gemm_wait_vm<L * s>();
         };
         if (rem >= MAX) out(integral_constant<int, MAX>{});
-        else if (MAX > 4 && rem >= 4) out(integral_constant<int, 4>{});
         else if (MAX > 2 && rem >= 2) out(integral_constant<int, 2>{});
         else if (MAX > 1 && rem >= 1) out(integral_constant<int, 1>{});
         else gemm_wait_vm<0>();
