@@ -50,8 +50,10 @@ def recorded():
 
 def test_hot_kernels_keep_their_register_budget():
     hot = [(n, r) for n, r in recorded() if any(h in n for h in build.HOT)]
-    # bf16_nt: tiles x epilogues x layouts; rings: 3 tiles x (4 epilogues x 2 layouts + 2 folded forms); direct: 4 epilogues + 2 folded forms
-    for family, count in (("gemm_bf16_nt_", 93), ("gemm_ring_kernel", 30), ("gemm_direct_kernel", 6), ("attn_global_kernel", 22), ("attn_window_kernel", 4)):
+    # bf16_nt: tiles x epilogues x layouts; rings: 3 tiles x (4 epilogues x 2 layouts + 2 folded forms); direct: 4 epilogues + 2 folded forms;
+    # wide: 12 tiles x (4 epilogues x 2 layouts + 2 folded forms); windows: d = 64 and 80 persistent, a wave to a tile at four d with any rows and near ones
+    for family, count in (("gemm_bf16_nt_", 93), ("gemm_ring_kernel", 30), ("gemm_direct_kernel", 6), ("gemm_wide_kernel", 120), ("attn_global_kernel", 22),
+                          ("attn_window_kernelI", 2), ("attn_window_kernel_wavesI", 8)):
         assert sum(family in n for n, _ in hot) >= count, f"expected every instantiation of {family} in the record"
     for name, r in hot:
         assert r["spill"] == 0 and r["scratch"] == 0, (name, r)
@@ -60,8 +62,9 @@ def test_hot_kernels_keep_their_register_budget():
         # budget does not apply to them
         if ("gemm_bf16_nt_kernelILi128ELi256E" in name or "gemm_bf16_nt_kernelILi256ELi128E" in name) and "ELb0E" in name:
             continue
-        # rings of 48 KB run three workgroups to a CU, three waves to a SIMD
-        three = "gemm_ring_kernel" in name and "gemm_ring_kernelILi128ELi128E" not in name
+        # rings of 48 KB run three workgroups to a CU, three waves to a SIMD; so do windows up to d = 64, a wave to a tile
+        three = ("gemm_ring_kernel" in name and "gemm_ring_kernelILi128ELi128E" not in name) or \
+                ("attn_window_kernel_wavesI" in name and "ILi80E" not in name and "ELb0E" in name)
         assert r["vgprs"] + r["agprs"] <= (168 if three else 256), (name, r)
 
 

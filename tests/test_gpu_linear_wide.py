@@ -24,7 +24,7 @@ CASES = [
     (2, True, 0, 651, 3072, 512), (2, True, 0, 714, 2816, 448), (2, True, 1, 651, 3072, 448), (2, True, 1, 777, 2560, 448),
     (2, True, 2, 769, 2560, 1280), (2, True, 3, 653, 3072, 448), (2, True, 3, 657, 3072, 448), (3, False, 0, 4978, 264, 576),
     (3, False, 1, 6388, 208, 1280), (3, False, 2, 6382, 200, 1280), (3, False, 3, 6198, 200, 576), (3, True, 0, 504, 2816, 1280),
-    (3, True, 1, 491, 2944, 1280), (3, True, 3, 518, 2816, 1280), (4, False, 0, 8319, 200, 320), (4, False, 0, 8325, 200, 384),
+    (3, True, 1, 491, 2944, 1280), (3, True, 2, 99, 8320, 960), (3, True, 3, 518, 2816, 1280), (4, False, 0, 8319, 200, 320), (4, False, 0, 8325, 200, 384),
     (4, False, 1, 8566, 200, 448), (4, False, 1, 8697, 200, 448), (4, False, 2, 8248, 200, 384), (4, False, 2, 8250, 200, 320),
     (4, False, 3, 8333, 200, 320), (4, False, 3, 8398, 200, 320), (4, True, 0, 712, 2816, 320), (4, True, 0, 782, 2560, 384),
     (4, True, 1, 1414, 2176, 512), (4, True, 2, 1154, 1792, 512), (4, True, 2, 1481, 1408, 512), (4, True, 3, 771, 2560, 320),
@@ -56,7 +56,7 @@ CASES = [
     (11, False, 3, 7688, 3120, 384), (11, False, 3, 8295, 1352, 512), (11, True, 0, 8200, 2944, 448), (11, True, 0, 8206, 2944, 384),
     (11, True, 2, 8241, 2944, 320), (11, True, 2, 8285, 2944, 320), (11, True, 3, 5016, 2432, 1280), (11, True, 1, 1567, 7552, 1792)]
 # (tile, M, N, K): qkv with LN1 folded in
-FOLDED = [(0, 128, 2304, 576), (1, 384, 2816, 512), (2, 640, 3328, 512), (4, 640, 3328, 320), (5, 1792, 3328, 384), (6, 5504, 768, 320),
+FOLDED = [(0, 128, 2304, 576), (1, 384, 2816, 512), (2, 640, 3328, 512), (3, 128, 8448, 768), (4, 640, 3328, 320), (5, 1792, 3328, 384), (6, 5504, 768, 320),
           (7, 1664, 3840, 448), (8, 5504, 1536, 320), (9, 6528, 1792, 448), (10, 8320, 1024, 320), (11, 1408, 8448, 1280)]
 # (tile, kept rows, hidden width, width): fc1 with gather and LN2 folded in
 MLP = [(0, 131, 1664, 640), (1, 270, 3328, 640), (2, 513, 3712, 512), (3, 385, 3456, 1280), (4, 781, 3840, 512),

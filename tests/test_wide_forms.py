@@ -19,7 +19,8 @@ def test_the_gpu_tests_reach_every_tile():
         assert wide(M, N, K, 3, True, folded=True) == tile, (tile, M, N, K)
     for tile, rows, Dm, D in MLP:
         assert wide(rows, Dm, D, 1, True) == tile, (tile, rows, Dm, D)
-    assert {c[:2] for c in CASES} == {(t, p) for t in range(12) for p in (False, True)}
+    assert {c[:3] for c in CASES} == {(t, p, e) for t in range(12) for p in (False, True) for e in range(4)}
+    assert {c[0] for c in FOLDED} == {c[0] for c in MLP} == set(range(12))
 
 
 def test_the_small_kernels_keep_the_shapes_they_are_tested_with():
