@@ -269,11 +269,13 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 // twice the bytes a flop of the large tiles: a slab takes 1.12 times as long for either operand and 1.36 for both in tiles below 128x128, 1.1 and 1.2
 // above.  Charged with more, since the others lose less there (a K-split 1.04 for both): of 639 row-major shapes with both operands torn 114 were
 // slower than without this kernel by more than 3 %, 84 % at most, with no such charge; 26, 13 % at most, with it, and 5 with one operand torn.
+// Few rows against a long K: with weights that no cache holds a slab of the 64x64 tile takes HBM's latency over the four slabs in flight, 0.22 us
+// where no other workgroup has fetched it (22 x 1088 x 3456 16.9 us, a K-split 14.1; 177 x 984 x 5120 26.4, 20.0).  With that charged from the 17th on, of 472 row-major
+// shapes of 8 to 300 rows 25 are slower than without this kernel by more than 3 % (18 % at most; 47 and 32 % without the charge), of 384 of any 9 (6 %; 22, 23 %).
 // Fitted to 1339 shapes (M 8 to 24576, N 128 to 5120, K 128 to 5376, all epilogues, both layouts, weights that no cache holds; those
 // cost the others 0.2 us a megabyte on top of their estimates, which is left out here: with warm weights 784 x 2304 x 768 takes the ring
 // 8.9 us and this kernel 9.5).  What is taken is 1 % on average from the fastest form, 10 % faster on average than
-// without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us); of 877 drawn later, down to
-// 8 rows, 15 % faster and slower on 21, the worst 60 x 2272 x 4416 row-major, 18.3 -> 23.8.  More than two rounds of packed problems
+// without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
 int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us)
@@ -289,7 +291,7 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
         const double slab = t.t_slab * (1.0 + torn * (t.bm * t.bn < 128 * 128 ? 0.3 : 0.15));
         const int rounds = ssam_div_up(ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 8), 32);      // (see the kernel's XCDs)
         if (rounds > (packed ? 2 : 4)) continue;
-        const double us = t.t0 + rounds * (t.t_round + nk * slab + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
+        const double us = t.t0 + rounds * (t.t_round + nk * slab + (i == 0 && nk > 16 ? 0.06 * (nk - 16) : 0.0) + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
                           + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
         if (us < best_us) { best_us = us; best = i; }
     }

@@ -57,9 +57,16 @@ def test_row_strides_reach_the_kernel():
     assert {t < 4 for t, *_ in STRIDED} == {True, False}
 
 
-@pytest.mark.parametrize("M,N,K,epi,us", [(30, 2488, 3648, 2, (18.1, 23.4)), (232, 368, 3776, 1, (16.5, 20.4)), (51, 272, 3648, 2, (14.5, 17.7)),
-                                          (136, 336, 3840, 1, (15.5, 20.4)), (327, 424, 3584, 1, (17.6, 19.5))])
+@pytest.mark.parametrize("M,N,K,epi,us", [(130, 864, 4096, 1, (18.4, 21.1)), (34, 3016, 3072, 0, (18.8, 21.1)), (439, 328, 4224, 1, (19.5, 22.6)),
+                                          (123, 2096, 3712, 1, (21.6, 29.3))])
 def test_rows_that_tear_lines_are_charged(M, N, K, epi, us):
     """us: measured with rows of A and W that do not begin on 128 bytes, the others and this kernel."""
     assert wide_ld(M, N, K, epi, False, K + 8, K + 8) == -1
     assert wide_ld(M, N, K, epi, False, K + 64, K + 64) == wide(M, N, K, epi) >= 0
+
+
+@pytest.mark.parametrize("M,N,K,epi,packed,us", [(22, 1088, 3456, 0, False, (14.1, 16.9)), (177, 984, 5120, 1, False, (20.0, 26.4)), (158, 272, 4224, 2, False, (16.0, 19.9)),
+                                                 (34, 2888, 4032, 1, False, (16.3, 20.6)), (57, 4224, 4800, 1, True, (21.6, 25.5))])
+def test_few_rows_and_a_long_k_keep_the_k_split(M, N, K, epi, packed, us):
+    """us: measured with weights from memory, K cut over many workgroups and this kernel."""
+    assert wide(M, N, K, epi, packed) == -1
