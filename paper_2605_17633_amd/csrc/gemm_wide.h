@@ -1,8 +1,9 @@
 // The contraction of gemm_kernel.h for problems of a few rounds of workgroups: one workgroup of eight waves to a CU, its tile as large
 // as still gives (almost) every CU one.  Same MFMA; K in one chain, or in two below 128x128.
 //
-// What bounds such a problem is what a CU can pull from the L2: 95 bytes a ns at best, 25 TB/s over the chip (measured with nothing else
-// going on), where a slab of a 64x64 tile is 16 KB for 0.05 us of matrix work and one of 256x192 56 KB for 0.64 us.  So
+// What bounds such a problem is one workgroup's chain on its CU: the first slabs from HBM, what a CU can pull from the L2 (95 bytes a ns at best, 25 TB/s over
+// the chip, measured with nothing else going on; a slab of a 64x64 tile is 16 KB for 0.05 us of matrix work and one of 256x192 56 KB for 0.64 us), and the epilogue.
+// Over whole launches of ViT layers the counters show 23 to 51 bytes a ns and CU and the matrix pipes 15 to 36 % busy.  So
 //   * tiles are as large as the problem allows, in many sizes (the dispatcher has their times): 4096 x 3072 x 1024 is 256 tiles of
 //     256x192; rings of 64x64 tiles pull 3.4 times its bytes;
 //   * the LDS of a CU, all of it, holds up to four slabs of A and W ahead of the MFMAs.  They come by 16-byte loads with an LDS destination
