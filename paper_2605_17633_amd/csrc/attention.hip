@@ -506,7 +506,7 @@ __device__ __forceinline__ void scale_queries(bf16x8 *qf, int e)
 // that the global stores are 16 bytes per lane and cover whole rows.  `stage` may overlay LDS that only
 // this wave used (its bias rows).  out_head: the output tensor at this head's columns; my_row: the output
 // row of this lane's query (l & 31), negative = not stored (past S, or dropped by the row map).
-template <int D, int STR = AttnCfg<D>::KSTR>
+template <int D, int STR = AttnCfg<D>::KSTR, bool ONES = AttnCfg<D>::ONES>
 __device__ __forceinline__ void finish_and_store(WaveState<D> &st, bf16 *stage, bf16 *out_head, long out_stride, long my_row)
 {
     using C = AttnCfg<D>;        // STR: row stride of the staging area in elements
@@ -517,7 +517,7 @@ __device__ __forceinline__ void finish_and_store(WaveState<D> &st, bf16 *stage, 
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     // ONES: row 16 + 4*half of the last tile of O^T is a ones column's output: the whole sum, in both half-waves
-    const float l = C::ONES ? st.o[C::DT - 1][8] : st.l + __shfl_xor(st.l, 32, 64);
+    const float l = ONES ? st.o[C::DT - 1][8] : st.l + __shfl_xor(st.l, 32, 64);
     const float inv = 1.0f / l;
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt)
@@ -884,47 +884,46 @@ size_t global_lds_bytes(int w)
 // vector and LDS pipes were all 35-50 % busy.  So
 //   * a wave works on three blocks at once: while the vector unit takes the exponentials of block b, one MFMA behind every
 //     few of those instructions forms the scores of block b + 1 and adds P V of block b - 1;
-//   * K and V blocks go from memory straight into two rings of three blocks in LDS, two blocks ahead (no registers, no LDS
-//     writes, one barrier per block).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
+//   * K and V blocks go from memory straight into two rings of four blocks in LDS, by twos, two blocks ahead (no registers, no LDS
+//     writes).  Such loads fill LDS in lane order, so rows are packed without padding and the 16-byte
 //     chunks of a row are swizzled on the memory side: the reads of K are conflict-free, as with padding;
-//     With d = 16 and 32 one block is little work between two barriers, so blocks come by twos there (UNIT): 2 images of 64 x 64,
-//     r = 1, d = 32 157 -> 136 us, d = 16 135 -> 130; a tile of 128 keys at a time takes 152 and 126;
+//   * one barrier for two blocks, no more: four waves that wait for each other were what bound a loop with a barrier a block, alone on their CU (1300
+//     cycles a block, now 920) as with another workgroup's.  Fewer instructions, operands read further ahead, wider spread requests or a deeper ring changed nothing
+//     there.  64 x 64, d = 80 | 64, us: 16 images of 16 heads, r = 0.4 802 | 660 -> 742 | 608; 1 image 53.7 | 44 -> 50 | 41; 8 heads of d = 80 39.5 -> 31.9;
+//     d = 32, 8 images 247 -> 225.  At large batches what is left is power: the clock falls to 1.8 GHz with the matrix pipes 45 % busy;
 //   * where the exponent reference moves in block b, the output is rescaled in front of block b + 1, behind P V of block b - 1, whose probabilities are still
 //     in units of the reference before.  (Moving it by whole powers of two would allow rescaling those probabilities instead,
 //     but then a query's largest probability is no longer exactly 1 and is rounded to bf16 like the others: up to 19 % more
 //     error where one key dominates.)
-constexpr int PATCH_RING = 3;
-
 template <int D>
 struct PatchPipe {
     using C = AttnCfg<D>;
     static constexpr int SLOT = 32 * D * 2;                       // bytes of a block of K or V
-    static constexpr int UNIT = D <= 32 ? 2 : 1;                  // blocks requested together, between two barriers
-    static constexpr int RING = PATCH_RING * UNIT * SLOT;         // bytes of a ring
+    static constexpr int RING = 4 * SLOT;                         // bytes of a ring
     static constexpr int NQ = 1 + C::KS, NP = 2 * C::DT;          // MFMAs of a block's scores (bias first) and of its P V
     static_assert(NQ == NP || NQ == NP + 1, "scores and P V alternate");
-    static constexpr int LOADS = UNIT * C::CH;                    // 1 KB requests of K and V of a unit, over four waves
-    static constexpr int LOADS_HI = (LOADS + 3) / 4;
+    static constexpr int LOADS = C::CH / 2;                       // 1 KB requests of a block of K or V
     static constexpr int AHEAD = 3, FR = 4;                       // operand fragments are read three MFMAs ahead
 
-    // chunk c of row `row` sits at chunk position c ^ swz(row): 16 rows at one chunk then touch 16 distinct 16-byte banks
-    static __device__ __forceinline__ int swz(int row)
+    // chunk c of row `row` sits at chunk position c ^ swz(row).  K: 16 rows at one chunk then touch 16 distinct 16-byte banks.  V: a transposing
+    // read takes 64 bytes of each of 8 rows, and of rows of 128 bytes every other pair has them in the other half
+    static __device__ __forceinline__ int swz(int row, bool v)
     {
-        return C::CH == 8 ? (row >> 1) & 7 : C::CH == 4 ? (row >> 2) & 3 : (row >> 3) & 1;
+        if (C::CH == 8) return v ? (row << 1) & 4 : (row >> 1) & 7;
+        return C::CH == 4 ? (row >> 2) & 3 : (row >> 3) & 1;
     }
 
     WaveState<D> &st;
     const bf16x8 *qf;
     const unsigned char *lds, *tq_lane;
     float scale_log2e;
-    int half;
-    bool ones_lane;                  // D = 16 mod 32: this lane's columns of the last O tile are the ones columns
     f16x8 efrag;
-    int ka[C::KS], va[2], ones_at;   // byte offsets: this lane's K chunks in a block, its V reads (rows +0 and +8), the ones
-    uint32_t bo;                     // table offsets of the first key of the block whose scores are formed next
+    int ka[C::KS], va[C::CH == 8 ? 2 : 1][2];   // byte offsets: this lane's K chunks in a block, its V reads (rows +0 and +8), by column tile where rows have 8 chunks
+    uint32_t bo;                     // table offsets of the block whose scores are formed next
     f32x16 s[2];
     bf16x8 p[2][2], frag[FR];
-    float alpha;                     // the reference moved by this factor in the block before (moved, wave-uniform)
+    float most;                      // the reference moves past this
+    float alpha;                     // it moved by this factor in the block before (moved, wave-uniform)
     bool moved;
 
     // operand I of the interleaved sequence of a step with scores (HQ) and / or P V (HP): even places scores, odd P V
@@ -942,17 +941,14 @@ struct PatchPipe {
                 bf16x4 v[2];
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    // column tile dt: four chunks on, under the swizzle of 8-chunk rows the other half of the row
-                    const int col = C::CH == 8 ? ((dt ^ u) - u) * 64 : dt * 64;
-                    int at = va[u] + v_slot + t * 16 * D * 2 + col;
-                    if (C::ONES && dt == C::DT - 1) at = ones_lane ? ones_at : at;
+                    const int at = va[C::CH == 8 ? dt : 0][u] + v_slot + t * 16 * D * 2 + (C::CH == 8 ? 0 : dt * 64);
                     v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(lds + at));
                 }
                 f = bf16x8{ v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3] };
             } else if constexpr (i == 0) {
                 // operand b of the bias product: f = 8*half + e; f 0..3 the block's rows, 4..11 its columns, 12..15 meet
-                // zeros of E (whatever finite values the second read of the upper half-wave returns)
-                const f16x4 t1 = *reinterpret_cast<const f16x4 *>(tq_lane + (half ? (bo >> 16) + 8 : (bo & 0xffffu)));
+                // zeros of E (finite values: the upper half-wave reads columns twice)
+                const f16x4 t1 = *reinterpret_cast<const f16x4 *>(tq_lane + (bo & 0xffffu));
                 const f16x4 t2 = *reinterpret_cast<const f16x4 *>(tq_lane + (bo >> 16));
                 f = __builtin_bit_cast(bf16x8, f16x8{ t1[0], t1[1], t1[2], t1[3], t2[0], t2[1], t2[2], t2[3] });
             } else {
@@ -988,7 +984,7 @@ struct PatchPipe {
             w[J % 4] = pair;
             // the sum of what P V multiplies, the rounded probabilities, as with the ones columns: one instruction, and the rounding of
             // a dominant one cancels
-            if constexpr (!C::ONES) st.l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), bf16x2{ (bf16)1.f, (bf16)1.f }, st.l, false);
+            st.l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), bf16x2{ (bf16)1.f, (bf16)1.f }, st.l, false);
             p[PAR][J / 4] = __builtin_bit_cast(bf16x8, w);
             exp_pairs<PAR, J + 1, J1>(mref);
         }
@@ -1030,19 +1026,19 @@ struct PatchPipe {
         float mx = fmaxf(s[PAR][0], s[PAR][1]);
 #pragma unroll
         for (int r = 2; r < 16; ++r) mx = fmaxf(mx, s[PAR][r]);
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
-        const bool move = mx > st.m + ATTN_LAG;         // see attn_softmax_pv
-        const bool any = __builtin_amdgcn_ballot_w64(move) != 0;
+        const bool any = __builtin_amdgcn_ballot_w64(mx * scale_log2e > most) != 0;        // over this half-wave's keys
         if (__builtin_expect(any || moved, 0)) {
             rescale();                                  // P V of the block before is in the output: what moved there
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
+            const bool move = mx > most;                // see attn_softmax_pv
             alpha = 1.f;
             moved = any;
             if (move) {
                 alpha = __builtin_amdgcn_exp2f(st.m - mx);
                 st.m = mx;
+                most = mx + ATTN_LAG;
             }
-            if constexpr (!C::ONES) st.l *= alpha;
+            st.l *= alpha;
         }
         __builtin_amdgcn_sched_barrier(0);
         // ahead of the other workgroup's requests, maxima and barriers (1 % at batch 16, 5 % when a launch is one round)
@@ -1053,8 +1049,8 @@ struct PatchPipe {
 };
 
 // LDS of the patch path: K ring, V ring (below 64 KB: the reach of M0 as LDS address), 32 bytes of ones, the waves' check
-// results, table offsets of every block, the waves' bias tables
-inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_blocks * 4 + 15) & ~15; }
+// results, table offsets of every block for either half-wave, the waves' bias tables
+inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_blocks * 8 + 15) & ~15; }
 template <int D>
 inline __host__ __device__ size_t patch_lds_bytes(int w, int n_blocks)
 {
@@ -1128,47 +1124,42 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
 {
     using C = AttnCfg<D>;
     using Pipe = PatchPipe<D>;
-    constexpr int SLOT = Pipe::SLOT, UNIT = Pipe::UNIT, V0 = Pipe::RING, ONES0 = 2 * Pipe::RING;
-    static_assert(ONES0 <= 64 * 1024, "the rings are filled through M0");
+    constexpr int SLOT = Pipe::SLOT, V0 = Pipe::RING, END = 2 * Pipe::RING;
+    static_assert(END <= 64 * 1024, "the rings are filled through M0");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
     const int lgw = 31 - __builtin_clz(P.w), nact = P.n_pre + (qt >= P.n_pre ? 1 : 0), nblk = nact * (GLB_TILE / 32);
-    int *ok_words = reinterpret_cast<int *>(smem + ONES0 + 32);
-    uint32_t *bo_tab = reinterpret_cast<uint32_t *>(smem + ONES0 + 64);
+    int *ok_words = reinterpret_cast<int *>(smem + END);
+    uint32_t *bo_tab = reinterpret_cast<uint32_t *>(smem + END + 16);
     const int tstr = glb_tstr(P.w);
-    unsigned char *Tb = smem + ONES0 + 64 + patch_blocks_bytes(nblk);
+    unsigned char *Tb = smem + END + 16 + patch_blocks_bytes(nblk);
     GlbTab *tq = reinterpret_cast<GlbTab *>(Tb + wave * wave_scratch_bytes<D>(tstr));
 
     const long base = (long)grp * P.S * P.row_stride + (long)head * D;
     const uint32_t rs2 = (uint32_t)P.row_stride * 2u;
     const unsigned char *kbase = reinterpret_cast<const unsigned char *>(P.k + base), *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
-    // request j of a unit (K: j < LOADS/2, then V) is wave j % 4's: lane l brings the chunk that belongs at 16-byte place
-    // 64*(j % (LOADS/2)) + l of the unit
-    uint32_t src_off[Pipe::LOADS_HI];
+    // waves 0 and 1 bring K, 2 and 3 V, a block each: lane l of request i the chunk that belongs at 16-byte place 64 * i + l
+    const bool is_v = wave >= 2;
+    uint32_t src_off[Pipe::LOADS];
+    int l64 = lane;
+    asm volatile("" : "+v"(l64));                 // (else rows and chunks are kept for finish_and_store, which has the same, through the loops)
 #pragma unroll
-    for (int i = 0; i < Pipe::LOADS_HI; ++i) {
-        const int j = wave + 4 * i, place = (j % (Pipe::LOADS / 2)) * 64 + lane, row = place / C::CH, pos = place % C::CH;
-        src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row)) * 16u;
+    for (int i = 0; i < Pipe::LOADS; ++i) {
+        const int place = i * 64 + l64, row = place / C::CH, pos = place % C::CH;
+        src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row, is_v)) * 16u;
     }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
-    auto key0_of = [&](int unit) {
-        const int blk = max(min(unit * UNIT, nblk - UNIT), 0), a = blk >> 2;   // past the end: the last unit again, so that every wait below can count
-        return (a < P.n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32;
-    };
-    auto request = [&](int kunit, int k_slot, int vunit, int v_slot) {     // slots in bytes; a negative unit: not requested
-        const unsigned char *kb = kbase + (size_t)key0_of(kunit) * rs2, *vb = vbase + (size_t)key0_of(vunit) * rs2;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem) + (is_v ? V0 : 0);
+    const unsigned char *kvbase = is_v ? vbase : kbase;
+    auto request = [&](int blk) {                 // this wave's operand of a block, into slot blk % 4 of its ring
+        if (blk >= nblk) return;
+        const int a = blk >> 2, key0 = (a < P.n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32;
+        const unsigned char *src = kvbase + (size_t)(uint32_t)__builtin_amdgcn_readfirstlane(key0) * rs2;
+        const uint32_t at = lds0 + __builtin_amdgcn_readfirstlane((blk & 3) * SLOT);
 #pragma unroll
-        for (int i = 0; i < Pipe::LOADS_HI; ++i) {
-            const int j = wave + 4 * i;                                    // wave-uniform
-            const bool is_k = j < Pipe::LOADS / 2;
-            if (j >= Pipe::LOADS || (is_k ? kunit : vunit) < 0) continue;
-            const uint32_t at = lds0 + (is_k ? k_slot + j * 1024 : V0 + v_slot + (j - Pipe::LOADS / 2) * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(at), "v"(src_off[i]), "s"(is_k ? kb : vb) : "m0", "memory");
-        }
+        for (int i = 0; i < Pipe::LOADS; ++i)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at + i * 1024), "v"(src_off[i]), "s"(src) : "m0", "memory");
     };
-    request(0, 0, -1, 0);
-    request(1, UNIT * SLOT, UNIT == 1 ? -1 : 0, 0);
-    if constexpr (UNIT == 1) request(2, 2 * SLOT, 0, 0);
+    if (wave != 3) request(wave & 1);             // K(0), K(1), V(0)
+    if (wave == 0) request(2);
 
     const int qpos = qt * GLB_TILE + wave * 32 + l32;
     bf16x8 qf[C::KS];
@@ -1197,15 +1188,16 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
             ok = ok && c0 >= 0 && r0 + 6 < P.w && cl0 + 14 < P.w && cell[j] == c0 + ((2 * patch_rr(k)) << lgw) + 2 * patch_cc(k);
             if (k == 0) {
                 const uint32_t hw = (uint32_t)P.w >> 1, esz = sizeof(GlbTab);
-                const uint32_t off = (esz * ((r0 & 1) * hw + (r0 >> 1))) | ((esz * (2 * hw + (cl0 & 1) * hw + (cl0 >> 1))) << 16);
-                ok = ok && (off & 7u) == 0 && ((off >> 16) & 15u) == 0;
-                bo_tab[a1 * (GLB_TILE / 32) + ((tid & 127) >> 5)] = off;
+                const uint32_t row = esz * ((r0 & 1) * hw + (r0 >> 1)), col = esz * (2 * hw + (cl0 & 1) * hw + (cl0 >> 1));
+                ok = ok && (row & 7u) == 0 && (col & 15u) == 0;
+                uint32_t *bo = bo_tab + 2 * (a1 * (GLB_TILE / 32) + ((tid & 127) >> 5));
+                bo[0] = row | col << 16;                                // of the lower half-wave and the upper one (see load)
+                bo[1] = (col + 8) | col << 16;
             }
         }
     }
     const bool wave_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
     if (lane == 0) ok_words[wave] = wave_ok;
-    if (C::ONES && tid < 8) reinterpret_cast<uint32_t *>(smem + ONES0)[tid] = 0x3f803f80u;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the first blocks have landed
     __syncthreads();
     if ((ok_words[0] & ok_words[1] & ok_words[2] & ok_words[3]) == 0) {
@@ -1221,10 +1213,10 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     init_state<D>(st);
 
     const int li = lane & 15, fblk = (lane >> 4) & 1;
-    Pipe pipe{ st, qf, smem, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e, half, C::ONES && fblk != 0 };
-    pipe.ones_at = ONES0;
+    Pipe pipe{ st, qf, smem, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e };
     pipe.moved = false;
     pipe.alpha = 1.f;
+    pipe.most = -INFINITY;
     // operand a of the bias product: lane (key l32, half) holds E[l32][8*half + e]
     const int rr = patch_rr(l32), cc = patch_cc(l32);
     const _Float16 one = __builtin_bit_cast(_Float16, (uint16_t)P.half_one);
@@ -1234,84 +1226,60 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
         pipe.efrag[e] = (f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? one : (_Float16)0.f;
     }
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) pipe.ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ Pipe::swz(l32)) * 16;
+    for (int ks = 0; ks < C::KS; ++ks) pipe.ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ Pipe::swz(l32, false)) * 16;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         // transposing read: lane li of a 16-lane group points at row (li >> 2) of its 4 keys, column chunk (li & 3) of 4
-        // features of its 16; feature columns past D are the ones columns (their lanes read elsewhere, see load)
+        // features of its 16; feature columns past D are whatever lies there in LDS, and their outputs are dropped
         const int row = 8 * u + 4 * half + (li >> 2), f0 = (C::ONES && D == 16 ? 0 : 16 * fblk) + 4 * (li & 3);
-        pipe.va[u] = V0 + row * D * 2 + (((f0 >> 3) ^ Pipe::swz(row)) << 4) + (f0 & 7) * 2;
+#pragma unroll
+        for (int dt = 0; dt < (C::CH == 8 ? 2 : 1); ++dt)
+            pipe.va[dt][u] = V0 + row * D * 2 + (((4 * dt + (f0 >> 3)) ^ Pipe::swz(row, true)) << 4) + (f0 & 7) * 2;
     }
 
-    int s0 = 0, s1 = UNIT * SLOT, s2 = 2 * UNIT * SLOT;      // slots of unit u, u + 1, u + 2 modulo the ring
-    auto rotate = [&]() { const int t = s0; s0 = s1; s1 = s2; s2 = t; };
-    pipe.bo = bo_tab[0];
-    pipe.template load<true, false, 0>(s0, 0);
-    pipe.template load<true, false, 1>(s0, 0);
-    pipe.template load<true, false, 2>(s0, 0);
-    pipe.template steps<true, false, 1, false, 0>(s0, 0, 0.f);       // scores of block 0
-    int last_v;                                  // where V of the last block is
-    if constexpr (UNIT == 1) {
-        // Block b: everything of block b - 1 has been read, so the scores of b (slot of K(b)) and V(b - 2) make room for K(b + 3) and
-        // V(b + 1); K(b + 1) and V(b - 1) were requested two blocks ago, and only the requests of one block are younger.
-        auto enter = [&](int b) {
-            if (Pipe::LOADS % 4 == 0 || wave < Pipe::LOADS % 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((Pipe::LOADS + 3) / 4) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(Pipe::LOADS / 4) : "memory");
-            LDS_BARRIER();
-            request(b + 3, s0, b + 1, s1);
-            pipe.bo = bo_tab[min(b + 1, nblk - 1)];
-        };
-        enter(0);
-        pipe.template block<true, false, 0>(s1, s2);
-        rotate();
-        for (int b = 1; b < nblk - 1; b += 2) {      // nblk is a multiple of four
-            enter(b);
-            pipe.template block<true, true, 1>(s1, s2);
-            rotate();
-            enter(b + 1);
-            pipe.template block<true, true, 0>(s1, s2);
-            rotate();
-        }
-        enter(nblk - 1);
-        pipe.template block<false, true, 1>(s1, s2);
-        // V of the last block was requested in front of the block before it
+    pipe.bo = bo_tab[half];
+    pipe.template load<true, false, 0>(0, 0);
+    pipe.template load<true, false, 1>(0, 0);
+    pipe.template load<true, false, 2>(0, 0);
+    pipe.template steps<true, false, 1, false, 0>(0, 0, 0.f);       // scores of block 0
+    // Blocks b and b + 1 (b even) form the scores of b + 1 and b + 2 and add P V of b - 1 and b: what they read was requested two blocks ago.  Every
+    // wave is done with K(b - 1) and K(b) and with V(b - 3) and V(b - 2): they make room for K(b + 3), K(b + 4), V(b + 1) and V(b + 2).
+    // nblk is a multiple of four: every slot read is a constant, in the instructions.
+    uint32_t bo1 = bo_tab[2 + half], bo2 = bo_tab[4 + half];
+    auto enter = [&](int b) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         LDS_BARRIER();
-        last_v = s0;
-    } else {
-        // Unit u = blocks 2u and 2u + 1, whose scores, like those of block 2u + 2, need K of units u and u + 1, and whose P V, of blocks
-        // 2u - 1 and 2u, needs V of units u - 1 and u.  So K(u - 1) and V(u - 2) make room for K(u + 2) and V(u + 1), and what was
-        // requested a unit ago has to be there.
-        auto enter = [&](int u) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            LDS_BARRIER();
-            const int units = nblk / 2;
-            request(u + 2 < units ? u + 2 : -1, s2, u + 1 < units ? u + 1 : -1, s1);
-            pipe.bo = bo_tab[2 * u + 1];
-        };
-        enter(0);
-        pipe.template block<true, false, 0>(s0 + SLOT, 0);
-        pipe.bo = bo_tab[2];
-        pipe.template block<true, true, 1>(s1, s0);
-        rotate();
-        for (int u = 1; u < nblk / 2 - 1; ++u) {
-            enter(u);
-            pipe.template block<true, true, 0>(s0 + SLOT, s2 + SLOT);
-            pipe.bo = bo_tab[2 * u + 2];
-            pipe.template block<true, true, 1>(s1, s0);
-            rotate();
-        }
-        enter(nblk / 2 - 1);
-        pipe.template block<true, true, 0>(s0 + SLOT, s2 + SLOT);
-        pipe.template block<false, true, 1>(0, s0);
-        last_v = s0 + SLOT;
+        request(b + (is_v ? 1 : 3) + (wave & 1));
+    };
+    auto pair = [&](auto odd_, auto first_, auto last_, int b) {
+        constexpr int K0 = decltype(odd_)::value ? 2 : 0;        // b % 4
+        constexpr bool FIRST = decltype(first_)::value, LAST = decltype(last_)::value;
+        enter(b);
+        pipe.bo = bo1;
+        const uint32_t next1 = bo_tab[2 * min(b + 3, nblk - 1) + half], next2 = bo_tab[2 * min(b + 4, nblk - 1) + half];
+        pipe.template block<true, !FIRST, 0>((K0 + 1) % 4 * SLOT, (K0 + 3) % 4 * SLOT);
+        pipe.bo = bo2;
+        pipe.template block<!LAST, true, 1>((K0 + 2) % 4 * SLOT, K0 * SLOT);
+        bo1 = next1;
+        bo2 = next2;
+    };
+    using std::true_type;
+    using std::false_type;
+    pair(false_type{}, true_type{}, false_type{}, 0);
+    for (int b = 2; b < nblk - 2; b += 4) {
+        pair(true_type{}, false_type{}, false_type{}, b);
+        pair(false_type{}, false_type{}, false_type{}, b + 2);
     }
+    pair(true_type{}, false_type{}, true_type{}, nblk - 2);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // V of the last block was requested in front of the block before it
+    LDS_BARRIER();
+    constexpr int last_v = 3 * SLOT;
     pipe.rescale();
     pipe.template load<false, true, 0>(0, last_v);
     pipe.template load<false, true, 1>(0, last_v);
     pipe.template load<false, true, 2>(0, last_v);
     pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
-    finish_and_store<D>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
+    finish_and_store<D, C::KSTR, false>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
     return true;
 }
 
