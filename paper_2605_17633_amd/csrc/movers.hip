@@ -284,6 +284,14 @@ channel_sum_kernel(const uint4 *__restrict__ x, float *__restrict__ csum, long t
     if (lane == 0) csum[t] = s;
 }
 
+// gradient magnitude of a cell from its eight neighbours
+__device__ __forceinline__ float sobel(float a00, float a01, float a02, float a10, float a12, float a20, float a21, float a22)
+{
+    const float gx = (a02 - a00) + 2.f * (a12 - a10) + (a22 - a20);
+    const float gy = (a20 - a00) + 2.f * (a21 - a01) + (a22 - a02);
+    return sqrtf(gx * gx + gy * gy);
+}
+
 // Sobel magnitude with zero padding on the channel-sum map
 __global__ void __launch_bounds__(256)
 sobel_kernel(const float *__restrict__ csum, float *__restrict__ scores, int B, int gh, int gw)
@@ -299,9 +307,70 @@ sobel_kernel(const float *__restrict__ csum, float *__restrict__ scores, int B, 
     float a00 = at(row - 1, col - 1), a01 = at(row - 1, col), a02 = at(row - 1, col + 1);
     float a10 = at(row, col - 1), a12 = at(row, col + 1);
     float a20 = at(row + 1, col - 1), a21 = at(row + 1, col), a22 = at(row + 1, col + 1);
-    float gx = (a02 - a00) + 2.f * (a12 - a10) + (a22 - a20);
-    float gy = (a20 - a00) + 2.f * (a21 - a01) + (a22 - a02);
-    scores[i] = sqrtf(gx * gx + gy * gy);
+    scores[i] = sobel(a00, a01, a02, a10, a12, a20, a21, a22);
+}
+
+// Both in one launch, for few tokens: a workgroup scores 4 x 4 cells from the channel sums of 6 x 6, three of them to a wave with all of their
+// loads in flight.  The sums are those of channel_sum_kernel, bit for bit; every row is read 2.25 times, most of that from the caches.
+constexpr int SCORE_TILE = 4, SCORE_HALO = SCORE_TILE + 2, SCORE_PER_WAVE = 3, SCORE_THREADS = SCORE_HALO * SCORE_HALO / SCORE_PER_WAVE * 64;
+template <int MAXC>
+__global__ void __launch_bounds__(SCORE_THREADS)
+score_kernel(const uint4 *__restrict__ x, float *__restrict__ scores, int gh, int gw, int chunks)
+{
+    __shared__ float cs[SCORE_HALO * SCORE_HALO];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r0 = (int)blockIdx.y * SCORE_TILE - 1, c0 = (int)blockIdx.x * SCORE_TILE - 1;
+    const long base = (long)blockIdx.z * gh * gw;
+    uint4 raw[SCORE_PER_WAVE][MAXC];
+#pragma unroll
+    for (int u = 0; u < SCORE_PER_WAVE; ++u) {
+        const int t = wave * SCORE_PER_WAVE + u, row = min(max(r0 + t / SCORE_HALO, 0), gh - 1), col = min(max(c0 + t % SCORE_HALO, 0), gw - 1);
+        const uint4 *src = x + (base + (long)row * gw + col) * chunks;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) raw[u][i] = src[min(lane + 64 * i, chunks - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < SCORE_PER_WAVE; ++u) {
+        const int t = wave * SCORE_PER_WAVE + u, row = r0 + t / SCORE_HALO, col = c0 + t % SCORE_HALO;
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            float f[8];
+            unpack_bf16x8(raw[u][i], f);
+            if (lane + 64 * i < chunks) s += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+        }
+        s = wave_sum(s);
+        if (lane == 0) cs[t] = row >= 0 && row < gh && col >= 0 && col < gw ? s : 0.f;
+    }
+    __syncthreads();
+    const int rr = threadIdx.x / SCORE_TILE, cc = threadIdx.x % SCORE_TILE;
+    if (rr >= SCORE_TILE || r0 + 1 + rr >= gh || c0 + 1 + cc >= gw) return;
+    const float *c = cs + rr * SCORE_HALO + cc;                     // the cell's upper left neighbour
+    constexpr int H = SCORE_HALO;
+    scores[base + (long)(r0 + 1 + rr) * gw + c0 + 1 + cc] = sobel(c[0], c[1], c[2], c[H], c[H + 2], c[2 * H], c[2 * H + 1], c[2 * H + 2]);
+}
+
+// Up to 28 MB of tokens: there the second launch costs more than the rows read twice (us, one launch | two, from a loop of calls: 4096 x 768
+// 6.6 | 9.3, the rate of the calls; 8192 x 1280, 21 MB, 7.4 | 9.2; 16384 x 768, 25 MB, 8.6 | 9.3; 16384 x 1024, 34 MB, 9.8 | 9.4; 65536 x 1280 39.8 | 32.4).
+bool score_in_one_launch(long tokens, int D) { return tokens * D * 2 <= 28000000 && D <= 2048; }
+
+// csum: where the channel sums of the form with two launches go
+int launch_score(const void *x, float *scores, int B, int gh, int gw, int D, float *csum, hipStream_t st)
+{
+    const long tokens = (long)B * gh * gw;
+    const int chunks = D / 8;
+    if (score_in_one_launch(tokens, D)) {
+        const dim3 grid(ssam_div_up(gw, SCORE_TILE), ssam_div_up(gh, SCORE_TILE), B);
+        auto kern = chunks <= 128 ? score_kernel<2> : chunks <= 192 ? score_kernel<3> : score_kernel<4>;
+        hipLaunchKernelGGL(kern, grid, dim3(SCORE_THREADS), 0, st, (const uint4 *)x, scores, gh, gw, chunks);
+        SSAM_CHECK_LAUNCH();
+        return SSAM_OK;
+    }
+    hipLaunchKernelGGL(channel_sum_kernel, dim3(ssam_div_up(tokens, 4)), dim3(256), 0, st, (const uint4 *)x, csum, tokens, chunks);
+    SSAM_CHECK_LAUNCH();
+    hipLaunchKernelGGL(sobel_kernel, dim3(ssam_div_up(tokens, 256)), dim3(256), 0, st, (const float *)csum, scores, B, gh, gw);
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
 }
 
 // ---------------------------------------------------------------- select
@@ -354,7 +423,7 @@ __device__ __forceinline__ T wave_inclusive_sum(T v)
 // then one scan over the workgroup places every index with a larger key and the lowest-index ties in ascending index
 // order.  One CU works alone here, so what counts is the length of the serial chain: the keys are read once and kept in
 // registers (ITEMS consecutive ones per thread; 16-byte loads), a pass is a histogram in LDS and a scan of its bins by
-// all threads (4096 scores: 32 -> 7.5 us; 16384: 45 -> 13; 65536: 151 -> 50; four 8-bit passes over memory with a serial
+// all threads (4096 scores: 32 -> 6.7 us, 0.4 of it by clearing the bins of all passes under the first load; 16384: 45 -> 13; 65536: 151 -> 50; four 8-bit passes over memory with a serial
 // walk of the bins and two barriers for every 1024 scores of the compaction before).  With ITEMS = 64 (more than 16384 scores) a
 // thread's 128 registers do not hold its keys and all the rest: 42 of them go through scratch (16400 scores: 34 us).
 constexpr int SEL_BINS = 2048;
@@ -362,7 +431,7 @@ template <int ITEMS>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int N, int K)
 {
-    __shared__ int hist[SEL_BINS];
+    __shared__ int hist[3][SEL_BINS];
     __shared__ unsigned long long scratch[SEL_THREADS / 64];
     __shared__ uint32_t sh_prefix;
     __shared__ int sh_remaining;
@@ -370,6 +439,7 @@ select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int 
     int32_t *out = keep + (long)blockIdx.x * K;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int first = tid * ITEMS;
+    for (int i = tid; i < 3 * SEL_BINS / 4; i += SEL_THREADS) reinterpret_cast<int4 *>(hist)[i] = make_int4(0, 0, 0, 0);      // under the latency of the scores
 
     uint32_t key[ITEMS];                        // past N: 0, below the key of every score
     if (first + ITEMS <= N && (reinterpret_cast<uintptr_t>(s) & 15) == 0) {
@@ -383,21 +453,20 @@ select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int 
         for (int i = 0; i < ITEMS; ++i) key[i] = first + i < N ? score_key(s[first + i]) : 0u;
     }
 
+    __syncthreads();
     uint32_t prefix = 0, prefix_mask = 0;
     int remaining = K;   // how many of the keys matching the prefix are still to be taken
     constexpr int SHIFT[3] = { 21, 10, 0 }, BITS[3] = { 11, 11, 10 };
 #pragma unroll
     for (int pass = 0; pass < 3; ++pass) {
         const uint32_t mask = (1u << BITS[pass]) - 1u;
-        for (int i = tid; i < SEL_BINS; i += SEL_THREADS) hist[i] = 0;
-        __syncthreads();
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
-            if (first + i < N && (key[i] & prefix_mask) == prefix) atomicAdd(&hist[(key[i] >> SHIFT[pass]) & mask], 1);
+            if (first + i < N && (key[i] & prefix_mask) == prefix) atomicAdd(&hist[pass][(key[i] >> SHIFT[pass]) & mask], 1);
         __syncthreads();
         // thread t holds bins 2t and 2t + 1 counted from the top: the bin in which the running count reaches `remaining`
         const int b0 = SEL_BINS - 1 - 2 * tid, b1 = b0 - 1;
-        const int c0 = hist[b0], c1 = hist[b1];
+        const int c0 = hist[pass][b0], c1 = hist[pass][b1];
         const int incl = wave_inclusive_sum(c0 + c1);
         if (lane == 63) scratch[wave] = (unsigned)incl;
         __syncthreads();
@@ -520,7 +589,7 @@ __device__ __forceinline__ void content_place(int cell, int rank, int g, int w, 
 // Rank by counting: a cell's rank is the number of cells of its group that come before it.  Quadratic in the group, but
 // every cell is independent of the others: RANK_LANES neighbouring lanes share one cell, each against its part of the keys
 // (all keys of the group in LDS, 32 bits each), and a group spreads over as many workgroups as it has runs of blockDim /
-// RANK_LANES cells; the sort below has one workgroup per group and a chain of log^2 barriers (64 x 64 grid: 40 -> 7.6 us).  Equal keys are told apart by their
+// RANK_LANES cells; the sort below has one workgroup per group and a chain of log^2 barriers (64 x 64 grid: 40 -> 7.0 us; 7.6 with the keys loaded one by one).  Equal keys are told apart by their
 // index: a key before the cell counts if it is <= the cell's, i.e. < mine + 1 (no key is the largest 32-bit number), a key
 // behind it if it is < mine.  The four cells of a wave lie in one aligned run of four keys, so which of the two holds is
 // the same for the whole wave except in the step that contains that run.
@@ -538,7 +607,21 @@ content_rank_kernel(const float *__restrict__ scores, int g, int w, int nws, int
     const int b = group / nW, win = group - b * nW, wr = win / nws, wc = win - wr * nws;
     const float *sc = scores + (long)b * g * g;
     const int padded = (S + RANK_STEP - 1) / RANK_STEP * RANK_STEP;      // past S: the largest number, counted by nobody
-    if (w == g) {
+    if (w == g && (S & 3) == 0 && (reinterpret_cast<uintptr_t>(sc) & 15) == 0) {
+        // four loads of 16 bytes in flight at a time
+        const float4 *s4 = reinterpret_cast<const float4 *>(sc);
+        for (int i0 = threadIdx.x; i0 < padded / 4; i0 += 4 * blockDim.x) {
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = s4[min(i0 + u * (int)blockDim.x, S / 4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * (int)blockDim.x;
+                const uint4 k = make_uint4(~score_key(v[u].x), ~score_key(v[u].y), ~score_key(v[u].z), ~score_key(v[u].w));
+                if (i < padded / 4) reinterpret_cast<uint4 *>(keys)[i] = i < S / 4 ? k : make_uint4(~0u, ~0u, ~0u, ~0u);
+            }
+        }
+    } else if (w == g) {
         for (int i = threadIdx.x; i < padded; i += blockDim.x) keys[i] = i < S ? ~score_key(sc[i]) : ~0u;
     } else {
         for (int i = threadIdx.x; i < padded; i += blockDim.x) keys[i] = i < S ? content_key(sc, g, w, wr, wc, i) : ~0u;
@@ -660,15 +743,7 @@ extern "C" int ssam_score_tokens(const void *x, float *scores, int B, int gh, in
     if (!x || !scores || !workspace || B <= 0 || gh <= 0 || gw <= 0 || D <= 0 || D % 8 != 0) return SSAM_EINVAL;
     if (!ssam_aligned16(x) || !ssam_aligned16(workspace)) return SSAM_EINVAL;
     if (workspace_bytes < ssam_score_tokens_workspace_bytes(B, gh, gw)) return SSAM_EWORKSPACE;
-    long tokens = (long)B * gh * gw;
-    float *csum = (float *)workspace;
-    hipLaunchKernelGGL(channel_sum_kernel, dim3(ssam_div_up(tokens, 4)), dim3(256), 0, (hipStream_t)stream,
-                       (const uint4 *)x, csum, tokens, D / 8);
-    SSAM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(sobel_kernel, dim3(ssam_div_up(tokens, 256)), dim3(256), 0, (hipStream_t)stream,
-                       (const float *)csum, scores, B, gh, gw);
-    SSAM_CHECK_LAUNCH();
-    return SSAM_OK;
+    return launch_score(x, scores, B, gh, gw, D, (float *)workspace, (hipStream_t)stream);
 }
 
 // ---- ssam_score_tokens for callers that cannot allocate: the channel-sum map lives in a file-scope device array.
@@ -706,13 +781,7 @@ extern "C" int ssam_score_tokens_static(const void *x, float *scores, int B, int
     if (rc != SSAM_OK) return rc;
     // channel_sum_kernel writes the sum of every token it is given and sobel_kernel reads only those, so nothing
     // in the array has to start at zero and what an earlier (larger) call left behind is never read
-    hipLaunchKernelGGL(channel_sum_kernel, dim3(ssam_div_up(tokens, 4)), dim3(256), 0, (hipStream_t)stream,
-                       (const uint4 *)x, csum, tokens, D / 8);
-    SSAM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(sobel_kernel, dim3(ssam_div_up(tokens, 256)), dim3(256), 0, (hipStream_t)stream,
-                       (const float *)csum, scores, B, gh, gw);
-    SSAM_CHECK_LAUNCH();
-    return SSAM_OK;
+    return launch_score(x, scores, B, gh, gw, D, csum, (hipStream_t)stream);
 }
 
 extern "C" int ssam_select_tokens(const float *scores, int32_t *keep_idx, int B, int N, int K, void *stream)

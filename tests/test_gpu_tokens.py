@@ -64,3 +64,22 @@ def test_content_tables_of_millions_of_windows():
     s = torch.randn(1, g * g, device=DEV)
     table, sigma = B.ssam_build_content_tables(s, g, 1, 1)
     assert torch.equal(table.reshape(-1), torch.arange(g * g, dtype=torch.int32, device=DEV)) and not sigma.any()
+
+
+@pytest.mark.parametrize("gh,gw,D", [(1, 1, 8), (4, 4, 768), (5, 3, 520), (3, 18, 1024), (17, 6, 1032), (13, 9, 1544), (2, 31, 2048), (4, 5, 2056)])
+def test_scores_in_one_launch(gh, gw, D):
+    """Edges of the 4 x 4 tiles, of a wave's loads of a row, and a row too wide for them: the bits of the form with two launches,
+    which a batch of more than 28 MB takes, and the sums of 64 bits up to the rounding of D additions in 32."""
+    announce("scores", gh, gw, D)
+    n = 28_000_000 // (gh * gw * D * 2) + 1
+    gen = torch.Generator(device=DEV).manual_seed(gh * gw + D)
+    x = torch.randn(1, gh, gw, D, generator=gen, device=DEV).bfloat16()
+    got = B.ssam_score_tokens(x)
+    two = B.ssam_score_tokens(x.expand(n, -1, -1, -1).contiguous())
+    assert torch.equal(got.expand(n, -1), two)
+    c = torch.nn.functional.pad(x[0].double().sum(-1), (1, 1, 1, 1))
+    at = lambda r, k: c[1 + r:1 + r + gh, 1 + k:1 + k + gw]
+    gx = at(-1, 1) - at(-1, -1) + 2 * (at(0, 1) - at(0, -1)) + at(1, 1) - at(1, -1)
+    gy = at(1, -1) - at(-1, -1) + 2 * (at(1, 0) - at(-1, 0)) + at(1, 1) - at(-1, 1)
+    bound = 12 * 2.0 ** -24 * D * float(x.float().abs().max())           # twelve sums of D terms weigh into a score
+    assert float((got[0].double() - torch.sqrt(gx * gx + gy * gy).reshape(-1)).abs().max()) <= bound
