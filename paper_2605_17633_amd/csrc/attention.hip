@@ -16,13 +16,13 @@
 // the transposing LDS read of gfx950 (ds_read_b64_tr_b16: a 16-lane group reads
 // 4 rows x 16 columns and every lane receives one column), so V is staged
 // exactly like K and never transposed in memory.
-// Key blocks (32 keys) are processed in chunks of one (window kernel, patch path) or as many as the register budget of
-// two waves per SIMD allows (two to four): all score MFMAs of the chunk first, one max and, where the reference moves,
-// one rescale of the running output per chunk, then all P V MFMAs; the patch path interleaves three blocks instead.
+// Key blocks (32 keys) are processed in chunks of one (window kernels) or as many as the register budget of
+// two waves per SIMD allows (two to four; above 64 x 64): all score MFMAs of the chunk first, one max and, where the reference moves,
+// one rescale of the running output per chunk, then all P V MFMAs; up to 64 x 64 the global kernel interleaves three blocks instead.
 // Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept in LDS as fp16, query-major.  A score gets
 // its two entries as a product with the table in the scores' accumulator: of one 16-entry operand on orders whose
-// blocks are patches (PatchPipe), of the whole row of up to 16 (windows) or 64 entries a table on others
-// (attn_chunk_step_onehot); above 64 x 64 by two look-ups.
+// blocks are patches, of the whole row of up to 64 entries a table on others (AttnPipe) or of 16 (windows,
+// attn_chunk_step_onehot); above 64 x 64 by two look-ups.
 // Memory requests are spread over a problem's / a tile's phases (see the prefetch
 // macros): a wave whose loads do not fit the CU's request queues waits instead of
 // computing, and a wait placed behind a branch or on a value that is used at once
@@ -37,9 +37,9 @@
 //                  and its Q straight into LDS, in three pieces, the rel-pos tables
 //                  resident in LDS;
 //   global kernel: one workgroup per (128-query mask tile, image, head), 4 waves, two or
-//                  more workgroups per CU; active key blocks go straight into rings in LDS (patch
-//                  path), or active 128-key tiles through registers into LDS (K and V requested
-//                  at different points).
+//                  more workgroups per CU; active key blocks go straight into rings in LDS, or, above
+//                  64 x 64 off the patch path, active 128-key tiles through registers into LDS (K and V
+//                  requested at different points).
 #include <type_traits>
 
 #include "common.h"
@@ -117,7 +117,7 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 // scale so that (score + row entry + column entry) * scale * log2e is the logit in log2 units.  General path:
 //   tq[q*tstr + p]                            = q . rel_h[row(q)-p+w-1] / scale      (p = key row)
 //   tq[q*tstr + wk + p]                       = q . rel_w[col(q)-p+w-1] / scale      (p = key column)
-// Up to w = 64 wk is w rounded up to whole 16-entry operands (32 or 64), the entries past w zero, and tstr = 2*wk + 8: the 16 bytes
+// Up to w = 64 wk is w rounded up to whole 32-entry operands (32 or 64), the entries past w zero, and tstr = 2*wk + 8: the 16 bytes
 // of padding put the operand reads of 16 lanes on distinct banks.  Above, where entries are looked up one by one, wk is w
 // rounded up to even and tstr = 2*wk + 4: 8 bytes of padding put the 32 lanes of a look-up (one entry, 32 queries) on
 // distinct banks.  Patch path (w a power of two):
@@ -127,7 +127,7 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 // and 8 column entries are then contiguous.  tstr = 4*hw + 4: the 8 bytes of padding put the 32 lanes of a look-up
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
 //
-// Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_chunk_step_onehot, PatchPipe) every entry
+// Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_chunk_step_onehot, AttnPipe) every entry
 // meets every key, most of them as a zero, and an infinity would make NaNs of the query's whole row.  So
 //   * entries past the range of fp16 become +-65504 (clamp_fp16), which as a logit is 65504 * scale, and
 //   * with a small scale the table is 2^shift times smaller and the ones of that matrix, or what a looked-up entry is multiplied
@@ -159,8 +159,9 @@ inline WindowScale window_scale(float scale)
 __device__ __forceinline__ void clamp_fp16() { __builtin_amdgcn_s_setreg(1 | 23 << 6 | (1 - 1) << 11, 1); }
 
 __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; }
-// Entries per table of the operand form, 0: look-ups.  Two images of 50 x 50, d = 80: 111 us by look-up, 88 by operand; of
-// 72 x 72, where the operand form takes 96 or 128 entries and its table a second workgroup's LDS: d = 64 264 against 434, d = 80 428 against 500.
+// Entries per table of the operand form (AttnPipe), 0: look-ups.  Two images of 50 x 50, d = 80: 111 us by look-up, 88 by dense operands (sparse
+// ones: see attn_onehot_body); of 72 x 72, where dense operands took 96 or 128 entries and their table a second workgroup's LDS: d = 64 264
+// against 434, d = 80 428 against 500.
 __host__ __device__ inline int glb_operand(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 0; }
 __host__ __device__ inline int glb_wk(int w) { return glb_operand(w) ? glb_operand(w) : (w + 1) & ~1; }
 __host__ __device__ inline int glb_general_tstr(int w) { return 2 * glb_wk(w) + (glb_operand(w) ? 8 : 4); }
@@ -218,6 +219,7 @@ __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *re
 typedef _Float16 WinTab;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
 // Bias operands of the window kernels (attn_chunk_step_onehot): entry p of the lane's query (p = key row, or 16 + key column) at
 // tq[(l & 31) * WIN_OSTR + p], divided by the softmax scale (AttnParams::table_inv); those past w are zero.  A window has 2w-1 <= 32
 // relative positions, so rel x Q^T is one MFMA tile per table.  It is stored the way it leaves the matrix core, query-major, and
@@ -871,15 +873,8 @@ constexpr int GLB_TILE = 128;
 // 78 KB of LDS, so two workgroups share a CU and one hides the other's LDS, MFMA and barrier latency.
 typedef _Float16 GlbTab;
 
-template <int D>
-size_t global_lds_bytes(int w)
-{
-    // K and V tile, the four waves' bias tables, per key (or per block) table offsets
-    return (size_t)2 * GLB_TILE * AttnCfg<D>::KSTR * 2 + (size_t)4 * wave_scratch_bytes<D>(glb_general_tstr(w)) + (size_t)GLB_TILE * 4;
-}
-
 // ---- patch path
-// One workgroup = one 128-query tile, four waves of 32 queries, as in the general path, but a pipeline of 32-key blocks.
+// One workgroup = one 128-query tile, four waves of 32 queries: a pipeline of 32-key blocks.
 // Scores, softmax and P V of a block depend on each other, and with a tile of 128 keys at a time between two barriers the matrix,
 // vector and LDS pipes were all 35-50 % busy.  So
 //   * a wave works on three blocks at once: while the vector unit takes the exponentials of block b, one MFMA behind every
@@ -895,13 +890,14 @@ size_t global_lds_bytes(int w)
 //     in units of the reference before.  (Moving it by whole powers of two would allow rescaling those probabilities instead,
 //     but then a query's largest probability is no longer exactly 1 and is rounded to bf16 like the others: up to 19 % more
 //     error where one key dominates.)
-template <int D>
-struct PatchPipe {
+// WK != 0: any order (attn_onehot_body), the bias by products with the whole table row of a query, WK entries each of rows and columns.
+template <int D, int WK>
+struct AttnPipe {
     using C = AttnCfg<D>;
     static constexpr int SLOT = 32 * D * 2;                       // bytes of a block of K or V
     static constexpr int RING = 4 * SLOT;                         // bytes of a ring
-    static constexpr int NQ = 1 + C::KS, NP = 2 * C::DT;          // MFMAs of a block's scores (bias first) and of its P V
-    static_assert(NQ == NP || NQ == NP + 1, "scores and P V alternate");
+    static constexpr int SEG = WK / 32;                           // sparse products of a block's bias and table
+    static constexpr int NQ = WK ? C::KS + 2 * SEG : 1 + C::KS, NP = 2 * C::DT;          // MFMAs of a block's scores and of its P V
     static constexpr int LOADS = C::CH / 2;                       // 1 KB requests of a block of K or V
     static constexpr int AHEAD = 3, FR = 4;                       // operand fragments are read three MFMAs ahead
 
@@ -919,16 +915,39 @@ struct PatchPipe {
     float scale_log2e;
     f16x8 efrag;
     int ka[C::KS], va[C::CH == 8 ? 2 : 1][2];   // byte offsets: this lane's K chunks in a block, its V reads (rows +0 and +8), by column tile where rows have 8 chunks
-    uint32_t bo;                     // table offsets of the block whose scores are formed next
+    uint32_t bo;                     // table offsets of the block whose scores are formed next (patches)
+    f16x16 t[2][WK ? SEG : 1];       // the lane's query's table entries: 32 * segment + 8 * half .. + 7 and 16 more on (any order)
+    int cell, w;                     // cell of this lane's key in the block whose scores are formed next, side of the grid
+    uint32_t per_w, half_one;        // 2^20 / w rounded up; the one of the bias products
+    int group[2];                    // that key's row and column: which four entries, less this half-wave's first four
+    uint32_t one[2], index[2];       //   the dword that holds the one, and which of the four it is
+    int limit;                       // keys of the block whose softmax is taken that exist
+    float start;                     // maximum of block 1's scores
     f32x16 s[2];
     bf16x8 p[2][2], frag[FR];
     float most;                      // the reference moves past this
     float alpha;                     // it moved by this factor in the block before (moved, wave-uniform)
     bool moved;
 
-    // operand I of the interleaved sequence of a step with scores (HQ) and / or P V (HP): even places scores, odd P V
-    template <bool HQ, bool HP> static constexpr bool is_q(int k) { return HQ && (!HP || k % 2 == 0); }
-    template <bool HQ, bool HP> static constexpr int idx(int k) { return HQ && HP ? k / 2 : k; }
+    // operand I of the interleaved sequence of a step with scores (HQ) and / or P V (HP): spread evenly, scores first
+    static constexpr int q_before(int k) { return NQ <= NP + 1 ? (k + 1) / 2 : (k * NQ + NQ + NP - 1) / (NQ + NP); }
+    template <bool HQ, bool HP> static constexpr bool is_q(int k) { return HQ && (!HP || q_before(k + 1) > q_before(k)); }
+    template <bool HQ, bool HP> static constexpr int idx(int k) { return !HQ || !HP ? k : is_q<HQ, HP>(k) ? q_before(k) : k - q_before(k); }
+
+    // Row and column of the next block's key for the bias products.  A table of 32 entries is one sparse product: the one is in the
+    // first of the two values kept of its four entries, or in the second where it is the last of them.
+    __device__ __forceinline__ void describe()
+    {
+        const int half = (threadIdx.x & 63) >> 5;
+        const uint32_t cl = min(max(cell, 0), w * w - 1), r = __umul24(cl, per_w) >> 20;
+#pragma unroll
+        for (int tab = 0; tab < 2; ++tab) {
+            const uint32_t at = tab ? cl - r * w : r, i = at & 3u;
+            group[tab] = (int)(at >> 2) - 4 * half;
+            one[tab] = i == 3 ? half_one << 16 : half_one;
+            index[tab] = (i == 3 ? 0xccccu : 0xccccu + i * 0x1111u);
+        }
+    }
 
     template <bool HQ, bool HP, int K>
     __device__ __forceinline__ void load(int k_slot, int v_slot)
@@ -945,6 +964,16 @@ struct PatchPipe {
                     v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)(lds + at));
                 }
                 f = bf16x8{ v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3] };
+            } else if constexpr (WK != 0) {
+                if constexpr (i < C::KS) {
+                    f = *reinterpret_cast<const bf16x8 *>(lds + k_slot + ka[i]);
+                } else {
+                    constexpr int tab = (i - C::KS) / SEG, seg = (i - C::KS) % SEG;
+                    u32x4 e;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) e[j] = group[tab] == 8 * seg + j ? one[tab] : 0u;
+                    f = __builtin_bit_cast(bf16x8, e);
+                }
             } else if constexpr (i == 0) {
                 // operand b of the bias product: f = 8*half + e; f 0..3 the block's rows, 4..11 its columns, 12..15 meet
                 // zeros of E (finite values: the upper half-wave reads columns twice)
@@ -965,6 +994,14 @@ struct PatchPipe {
         const bf16x8 &f = frag[K % FR];
         if constexpr (!is_q<HQ, HP>(K)) {
             st.o[i % C::DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, p[PAR ^ 1][i / C::DT], st.o[i % C::DT], 0, 0, 0);
+        } else if constexpr (WK != 0) {
+            const f32x16 zero = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
+            if constexpr (i < C::KS) {
+                s[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[i], i == 0 ? zero : s[PAR ^ 1], 0, 0, 0);
+            } else {
+                constexpr int tab = (i - C::KS) / SEG, seg = (i - C::KS) % SEG;
+                s[PAR ^ 1] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, f), t[tab][seg], s[PAR ^ 1], (int)index[tab], 0, 0);
+            }
         } else if constexpr (i == 0) {
             const f32x16 zero = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
             s[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(efrag, __builtin_bit_cast(f16x8, f), zero, 0, 0, 0);
@@ -995,11 +1032,41 @@ struct PatchPipe {
     {
         constexpr int n = (HQ ? NQ : 0) + (HP ? NP : 0);
         if constexpr (K < n) {
+            if constexpr (WK != 0 && HQ && K == 0 && C::KS >= 4) describe();
             load<HQ, HP, K + AHEAD>(k_slot, v_slot);
             mfma<HQ, HP, PAR, K>();
             if constexpr (SM) exp_pairs<PAR, 8 * K / n, 8 * (K + 1) / n>(mref);       // spread evenly behind the MFMAs
             __builtin_amdgcn_sched_barrier(0);
             steps<HQ, HP, PAR, SM, K + 1>(k_slot, v_slot, mref);
+        }
+    }
+
+    template <bool HQ, bool HP>
+    __device__ __forceinline__ void begin(int k_slot, int v_slot)
+    {
+        if constexpr (WK != 0 && HQ && C::KS < 4) describe();             // (else under the first products)
+        load<HQ, HP, 0>(k_slot, v_slot);
+        load<HQ, HP, 1>(k_slot, v_slot);
+        load<HQ, HP, 2>(k_slot, v_slot);
+    }
+
+    // addresses of this lane's operands, state of the softmax
+    __device__ __forceinline__ void addresses()
+    {
+        const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5, li = lane & 15, fblk = (lane >> 4) & 1;
+        moved = false;
+        alpha = 1.f;
+        most = -INFINITY;
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks) ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ swz(l32, false)) * 16;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            // transposing read: lane li of a 16-lane group points at row (li >> 2) of its 4 keys, column chunk (li & 3) of 4
+            // features of its 16; feature columns past D are whatever lies there in LDS, and their outputs are dropped
+            const int row = 8 * u + 4 * half + (li >> 2), f0 = (C::ONES && D == 16 ? 0 : 16 * fblk) + 4 * (li & 3);
+#pragma unroll
+            for (int dt = 0; dt < (C::CH == 8 ? 2 : 1); ++dt)
+                va[dt][u] = RING + row * D * 2 + (((4 * dt + (f0 >> 3)) ^ swz(row, true)) << 4) + (f0 & 7) * 2;
         }
     }
 
@@ -1020,12 +1087,19 @@ struct PatchPipe {
     template <bool HQ, bool HP, int PAR>
     __device__ __forceinline__ void block(int k_slot, int v_slot)
     {
-        load<HQ, HP, 0>(k_slot, v_slot);
-        load<HQ, HP, 1>(k_slot, v_slot);
-        load<HQ, HP, 2>(k_slot, v_slot);
+        begin<HQ, HP>(k_slot, v_slot);
+        if (WK != 0 && __builtin_expect(limit < 32, 0)) {          // keys past the end
+            const int half = (threadIdx.x & 63) >> 5;
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");      // the scores' MFMAs may be in flight
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[PAR][r] = 8 * (r >> 2) + 4 * half + (r & 3) < limit ? s[PAR][r] : -INFINITY;
+        }
         float mx = fmaxf(s[PAR][0], s[PAR][1]);
 #pragma unroll
         for (int r = 2; r < 16; ++r) mx = fmaxf(mx, s[PAR][r]);
+        if constexpr (WK != 0 && !HP) mx = fmaxf(mx, start);                               // the first block
         const bool any = __builtin_amdgcn_ballot_w64(mx * scale_log2e > most) != 0;        // over this half-wave's keys
         if (__builtin_expect(any || moved, 0)) {
             rescale();                                  // P V of the block before is in the output: what moved there
@@ -1048,13 +1122,115 @@ struct PatchPipe {
     }
 };
 
+// Requests of a wave for the rings of a workgroup: waves 0 and 1 bring K, 2 and 3 V, a block each: lane l of request i the chunk that
+// belongs at 16-byte place 64 * i + l.  RAGGED: rows past S repeat the last one (their scores are masked).
+template <int D, bool RAGGED>
+struct AttnRequests {
+    using Pipe = AttnPipe<D, 0>;
+    static constexpr int CH = AttnCfg<D>::CH, SLOT = Pipe::SLOT, LOADS = Pipe::LOADS;
+    static_assert(2 * Pipe::RING <= 64 * 1024, "the rings are filled through M0");
+    const unsigned char *kvbase;
+    uint32_t rs2, lds0, src_off[LOADS];
+    int S, n_pre, qt, nblk, wave;
+    bool is_v;
+
+    __device__ __forceinline__ AttnRequests(const AttnParams &P, int qt_, long base, unsigned char *smem)
+        : rs2((uint32_t)P.row_stride * 2u), S(P.S), n_pre(P.n_pre), qt(qt_), nblk((P.n_pre + (qt_ >= P.n_pre ? 1 : 0)) * (GLB_TILE / 32)),
+          wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))), is_v(wave >= 2)
+    {
+        kvbase = reinterpret_cast<const unsigned char *>((is_v ? P.v : P.k) + base);
+        lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem) + (is_v ? Pipe::RING : 0);
+        int l64 = threadIdx.x & 63;
+        asm volatile("" : "+v"(l64));             // (else rows and chunks are kept for finish_and_store, which has the same, through the loops)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int place = i * 64 + l64, row = place / CH, pos = place % CH;
+            src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row, is_v)) * 16u;
+        }
+    }
+    __device__ __forceinline__ int key0(int blk) const       // scan position of the first key of the workgroup's block blk
+    {
+        const int a = blk >> 2;
+        return __builtin_amdgcn_readfirstlane((a < n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32);
+    }
+    // this wave's operand of a block, into slot blk % 4 of its ring
+    __device__ __forceinline__ void operator()(int blk) const
+    {
+        if (blk >= nblk) return;
+        const int first = key0(blk);
+        const uint32_t at = lds0 + __builtin_amdgcn_readfirstlane((blk & 3) * SLOT);
+        if (RAGGED && first + 32 > S) {
+            int l64 = threadIdx.x & 63;
+            asm volatile("" : "+v"(l64));
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int place = i * 64 + l64, row = place / CH, pos = place % CH;
+                send(at + i * 1024, (uint32_t)min(first + row, S - 1) * rs2 + (uint32_t)(pos ^ Pipe::swz(row, is_v)) * 16u, kvbase);
+            }
+            return;
+        }
+        const unsigned char *src = kvbase + (size_t)(uint32_t)first * rs2;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) send(at + i * 1024, src_off[i], src);
+    }
+    __device__ __forceinline__ static void send(uint32_t at, uint32_t off, const unsigned char *src)
+    {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(src) : "m0", "memory");
+    }
+    __device__ __forceinline__ void first() const            // K(0), K(1), V(0), K(2)
+    {
+        if (wave != 3) (*this)(wave & 1);
+        if (wave == 0) (*this)(2);
+    }
+};
+
+// The blocks of a workgroup through its pipe; K(0), K(1), V(0) and K(2) have landed, or are waited for with what `arrived` waits for.
+// Blocks b and b + 1 (b even) form the scores of b + 1 and b + 2 and add P V of b - 1 and b: what they read was requested two blocks ago.  Every
+// wave is done with K(b - 1) and K(b) and with V(b - 3) and V(b - 2): they make room for K(b + 3), K(b + 4), V(b + 1) and V(b + 2).
+// nblk is a multiple of four: every slot read is a constant, in the instructions.
+// ahead(): in front of it all; arrived(): behind the wait for all that was requested; one(b), two(b): in front of blocks b and b + 1.
+template <class Pipe, class Request, class Ahead, class Arrived, class One, class Two>
+__device__ __forceinline__ void attn_pipe_run(Pipe &pipe, const Request &request, int nblk, Ahead ahead, Arrived arrived, One one, Two two)
+{
+    constexpr int SLOT = Pipe::SLOT;
+    ahead();
+    pipe.template begin<true, false>(0, 0);
+    pipe.template steps<true, false, 1, false, 0>(0, 0, 0.f);       // scores of block 0
+    auto pair = [&](auto odd_, auto first_, auto last_, int b) {
+        constexpr int K0 = decltype(odd_)::value ? 2 : 0;        // b % 4
+        constexpr bool FIRST = decltype(first_)::value, LAST = decltype(last_)::value;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        arrived();
+        LDS_BARRIER();
+        request(b + (request.is_v ? 1 : 3) + (request.wave & 1));
+        one(b);
+        pipe.template block<true, !FIRST, 0>((K0 + 1) % 4 * SLOT, (K0 + 3) % 4 * SLOT);
+        two(b);
+        pipe.template block<!LAST, true, 1>((K0 + 2) % 4 * SLOT, K0 * SLOT);
+    };
+    using std::true_type;
+    using std::false_type;
+    pair(false_type{}, true_type{}, false_type{}, 0);
+    for (int b = 2; b < nblk - 2; b += 4) {
+        pair(true_type{}, false_type{}, false_type{}, b);
+        pair(false_type{}, false_type{}, false_type{}, b + 2);
+    }
+    pair(true_type{}, false_type{}, true_type{}, nblk - 2);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // V of the last block was requested in front of the block before it
+    LDS_BARRIER();
+    constexpr int last_v = 3 * SLOT;
+    pipe.rescale();
+    pipe.template begin<false, true>(0, last_v);
+    pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
+}
+
 // LDS of the patch path: K ring, V ring (below 64 KB: the reach of M0 as LDS address), 32 bytes of ones, the waves' check
 // results, table offsets of every block for either half-wave, the waves' bias tables
 inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_blocks * 8 + 15) & ~15; }
 template <int D>
 inline __host__ __device__ size_t patch_lds_bytes(int w, int n_blocks)
 {
-    return (size_t)2 * PatchPipe<D>::RING + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
+    return (size_t)2 * AttnPipe<D, 0>::RING + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
 }
 
 // The bias table (layout of build_bias_rows) of a wave whose 32 queries are a patch: rows qr0 .. qr0 + 6 and columns
@@ -1123,9 +1299,8 @@ template <int D>
 __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
 {
     using C = AttnCfg<D>;
-    using Pipe = PatchPipe<D>;
-    constexpr int SLOT = Pipe::SLOT, V0 = Pipe::RING, END = 2 * Pipe::RING;
-    static_assert(END <= 64 * 1024, "the rings are filled through M0");
+    using Pipe = AttnPipe<D, 0>;
+    constexpr int END = 2 * Pipe::RING;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
     const int lgw = 31 - __builtin_clz(P.w), nact = P.n_pre + (qt >= P.n_pre ? 1 : 0), nblk = nact * (GLB_TILE / 32);
     int *ok_words = reinterpret_cast<int *>(smem + END);
@@ -1135,31 +1310,8 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     GlbTab *tq = reinterpret_cast<GlbTab *>(Tb + wave * wave_scratch_bytes<D>(tstr));
 
     const long base = (long)grp * P.S * P.row_stride + (long)head * D;
-    const uint32_t rs2 = (uint32_t)P.row_stride * 2u;
-    const unsigned char *kbase = reinterpret_cast<const unsigned char *>(P.k + base), *vbase = reinterpret_cast<const unsigned char *>(P.v + base);
-    // waves 0 and 1 bring K, 2 and 3 V, a block each: lane l of request i the chunk that belongs at 16-byte place 64 * i + l
-    const bool is_v = wave >= 2;
-    uint32_t src_off[Pipe::LOADS];
-    int l64 = lane;
-    asm volatile("" : "+v"(l64));                 // (else rows and chunks are kept for finish_and_store, which has the same, through the loops)
-#pragma unroll
-    for (int i = 0; i < Pipe::LOADS; ++i) {
-        const int place = i * 64 + l64, row = place / C::CH, pos = place % C::CH;
-        src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row, is_v)) * 16u;
-    }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem) + (is_v ? V0 : 0);
-    const unsigned char *kvbase = is_v ? vbase : kbase;
-    auto request = [&](int blk) {                 // this wave's operand of a block, into slot blk % 4 of its ring
-        if (blk >= nblk) return;
-        const int a = blk >> 2, key0 = (a < P.n_pre ? a : qt) * GLB_TILE + (blk & 3) * 32;
-        const unsigned char *src = kvbase + (size_t)(uint32_t)__builtin_amdgcn_readfirstlane(key0) * rs2;
-        const uint32_t at = lds0 + __builtin_amdgcn_readfirstlane((blk & 3) * SLOT);
-#pragma unroll
-        for (int i = 0; i < Pipe::LOADS; ++i)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at + i * 1024), "v"(src_off[i]), "s"(src) : "m0", "memory");
-    };
-    if (wave != 3) request(wave & 1);             // K(0), K(1), V(0)
-    if (wave == 0) request(2);
+    AttnRequests<D, false> request(P, qt, base, smem);
+    request.first();
 
     const int qpos = qt * GLB_TILE + wave * 32 + l32;
     bf16x8 qf[C::KS];
@@ -1212,11 +1364,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
     WaveState<D> st;
     init_state<D>(st);
 
-    const int li = lane & 15, fblk = (lane >> 4) & 1;
     Pipe pipe{ st, qf, smem, reinterpret_cast<const unsigned char *>(tq_lane), P.scale_log2e };
-    pipe.moved = false;
-    pipe.alpha = 1.f;
-    pipe.most = -INFINITY;
     // operand a of the bias product: lane (key l32, half) holds E[l32][8*half + e]
     const int rr = patch_rr(l32), cc = patch_cc(l32);
     const _Float16 one = __builtin_bit_cast(_Float16, (uint16_t)P.half_one);
@@ -1225,73 +1373,120 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
         const int f = 8 * half + e;
         pipe.efrag[e] = (f < 4 ? rr == f : (f < 12 ? cc == f - 4 : false)) ? one : (_Float16)0.f;
     }
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) pipe.ka[ks] = l32 * D * 2 + ((2 * ks + half) ^ Pipe::swz(l32, false)) * 16;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        // transposing read: lane li of a 16-lane group points at row (li >> 2) of its 4 keys, column chunk (li & 3) of 4
-        // features of its 16; feature columns past D are whatever lies there in LDS, and their outputs are dropped
-        const int row = 8 * u + 4 * half + (li >> 2), f0 = (C::ONES && D == 16 ? 0 : 16 * fblk) + 4 * (li & 3);
-#pragma unroll
-        for (int dt = 0; dt < (C::CH == 8 ? 2 : 1); ++dt)
-            pipe.va[dt][u] = V0 + row * D * 2 + (((4 * dt + (f0 >> 3)) ^ Pipe::swz(row, true)) << 4) + (f0 & 7) * 2;
-    }
+    pipe.addresses();
 
     pipe.bo = bo_tab[half];
-    pipe.template load<true, false, 0>(0, 0);
-    pipe.template load<true, false, 1>(0, 0);
-    pipe.template load<true, false, 2>(0, 0);
-    pipe.template steps<true, false, 1, false, 0>(0, 0, 0.f);       // scores of block 0
-    // Blocks b and b + 1 (b even) form the scores of b + 1 and b + 2 and add P V of b - 1 and b: what they read was requested two blocks ago.  Every
-    // wave is done with K(b - 1) and K(b) and with V(b - 3) and V(b - 2): they make room for K(b + 3), K(b + 4), V(b + 1) and V(b + 2).
-    // nblk is a multiple of four: every slot read is a constant, in the instructions.
-    uint32_t bo1 = bo_tab[2 + half], bo2 = bo_tab[4 + half];
-    auto enter = [&](int b) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        LDS_BARRIER();
-        request(b + (is_v ? 1 : 3) + (wave & 1));
-    };
-    auto pair = [&](auto odd_, auto first_, auto last_, int b) {
-        constexpr int K0 = decltype(odd_)::value ? 2 : 0;        // b % 4
-        constexpr bool FIRST = decltype(first_)::value, LAST = decltype(last_)::value;
-        enter(b);
-        pipe.bo = bo1;
-        const uint32_t next1 = bo_tab[2 * min(b + 3, nblk - 1) + half], next2 = bo_tab[2 * min(b + 4, nblk - 1) + half];
-        pipe.template block<true, !FIRST, 0>((K0 + 1) % 4 * SLOT, (K0 + 3) % 4 * SLOT);
-        pipe.bo = bo2;
-        pipe.template block<!LAST, true, 1>((K0 + 2) % 4 * SLOT, K0 * SLOT);
-        bo1 = next1;
-        bo2 = next2;
-    };
-    using std::true_type;
-    using std::false_type;
-    pair(false_type{}, true_type{}, false_type{}, 0);
-    for (int b = 2; b < nblk - 2; b += 4) {
-        pair(true_type{}, false_type{}, false_type{}, b);
-        pair(false_type{}, false_type{}, false_type{}, b + 2);
-    }
-    pair(true_type{}, false_type{}, true_type{}, nblk - 2);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // V of the last block was requested in front of the block before it
-    LDS_BARRIER();
-    constexpr int last_v = 3 * SLOT;
-    pipe.rescale();
-    pipe.template load<false, true, 0>(0, last_v);
-    pipe.template load<false, true, 1>(0, last_v);
-    pipe.template load<false, true, 2>(0, last_v);
-    pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
+    uint32_t bo1 = bo_tab[2 + half], bo2 = bo_tab[4 + half], next1, next2;
+    attn_pipe_run(pipe, request, nblk, [&]() {}, [&]() {},
+        [&](int b) {
+            pipe.bo = bo1;
+            next1 = bo_tab[2 * min(b + 3, nblk - 1) + half], next2 = bo_tab[2 * min(b + 4, nblk - 1) + half];
+        },
+        [&](int) { pipe.bo = bo2; bo1 = next1; bo2 = next2; });
     finish_and_store<D, C::KSTR, false>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
     return true;
 }
 
-// The general path of a workgroup: any order, any S (attn_chunk_step_onehot).  WK: see build_bias_rows' table; NB: key
-// blocks per softmax chunk, as many as the register budget of two waves per SIMD allows.
-template <int D, int WK, int NB>
+// Any order, any S, up to 64 x 64 (WK = 32 or 64 entries a table): the pipeline of the patch path, whose bias is one product of the patch's
+// entries, with the whole table row of a query instead, as in attn_chunk_step_onehot: B[k][q] = sum_p E[k][p] T[p][q], E a one at the key's row
+// and a one at its column.  Three quarters of E's groups of four are known zeros and no group has two ones, so it is a structured-sparse operand: a
+// 32x32x32 sparse product takes the time of a dense 32x32x16 one (15.6 ns against 15.4 on a SIMD, measured), four a block instead of eight at 64 entries, and a
+// lane makes 16 dwords of E for a block, two instructions each.  T stays in registers, as its operands b.
+// Tiles of 128 keys between two barriers with the dense products -> this, us: 2 images of 12 heads, 50 x 50, d = 64, r = 0.5 68.4 -> 54.3; content order of 64 x 64: 8 images
+// of 16 heads, d = 80, r = 0.4 583 -> 482, 4 of d = 64 dense 577 -> 448, 1 of 12 heads 74 -> 60; 8 images of 32 x 32 40.1 -> 33.3, 4 of 20 x 20 16.8 -> 15.2.  What bounds it
+// now: at large batches vector instructions issue in 61 % of the cycles (137 a block and wave), matrix pipes 39 % busy.
+template <int D, int WK>
+inline __host__ __device__ size_t onehot_lds_bytes()
+{
+    return (size_t)2 * AttnPipe<D, WK>::RING + (size_t)4 * wave_scratch_bytes<D>(2 * WK + 8);
+}
+
+template <int D, int WK>
+__device__ __forceinline__ void attn_onehot_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
+{
+    using C = AttnCfg<D>;
+    using Pipe = AttnPipe<D, WK>;
+    constexpr int TSTR = 2 * WK + 8;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), l32 = lane & 31, half = lane >> 5;
+    const int S = P.S;
+    GlbTab *tq = reinterpret_cast<GlbTab *>(smem + 2 * Pipe::RING + wave * wave_scratch_bytes<D>(TSTR));
+    const long base = (long)grp * S * P.row_stride + (long)head * D;
+    AttnRequests<D, true> request(P, qt, base, smem);
+    request.first();
+
+    const int qpos = qt * GLB_TILE + wave * 32 + l32, qclamp = min(qpos, S - 1);
+    bf16x8 qf[C::KS];
+    load_q_frags<D>(qf, P.q + base + (long)qclamp * P.row_stride);
+    const int32_t *sg = P.sigma + (long)grp * P.sigma_stride;
+    const uint32_t qrc = key_row_col(sg, qclamp, S, P.w);
+    const int nblk = request.nblk;
+    auto cell_of = [&](int b) { return sg[min(request.key0(min(b, nblk - 1)) + l32, S - 1)]; };
+    int cell0 = cell_of(0), cell1 = cell_of(1), cell2 = cell_of(2);
+    GlbTab *tq_lane = tq + l32 * TSTR;            // this lane's query row of the wave's bias table
+    build_bias_rows<D, GlbTab>(qf, P.rel_h, P.rel_w, D, P.w, (int)(qrc & 0xffffu), (int)(qrc >> 16), tq_lane, P.table_inv);
+    wave_lds_fence();
+    WaveState<D> st;
+    init_state<D>(st);
+    Pipe pipe{ st, qf, smem, nullptr, P.scale_log2e };
+    pipe.w = P.w;
+    pipe.per_w = ((1u << 20) + P.w - 1) / P.w;          // exact for cells below 4096: the error is below 4096 / 2^20 of a row
+    pipe.half_one = P.half_one;
+    pipe.addresses();
+#pragma unroll
+    for (int tab = 0; tab < 2; ++tab)
+#pragma unroll
+        for (int seg = 0; seg < Pipe::SEG; ++seg) {
+            // operand b of the sparse product: a half-wave holds entries 8 * half .. + 7 and 16 + 8 * half .. + 7
+            const f16x8 lo = *reinterpret_cast<const f16x8 *>(tq_lane + tab * WK + 32 * seg + 8 * half);
+            const f16x8 hi = *reinterpret_cast<const f16x8 *>(tq_lane + tab * WK + 32 * seg + 8 * half + 16);
+            pipe.t[tab][seg] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the first blocks have landed
+    asm volatile("" : "+v"(cell0), "+v"(cell1), "+v"(cell2));
+    LDS_BARRIER();
+    int next1 = cell1, next2 = cell2;
+    attn_pipe_run(pipe, request, nblk,
+        [&]() {
+            // The exponent reference begins as the maximum over two blocks (one more block's scores): the likelier a query's largest probability is
+            // exactly 1, the smaller the error.  With that of the first alone it is 1 to 6 % larger.  Keys past the end repeat the last one here.
+            pipe.cell = cell1;
+            pipe.template begin<true, false>(Pipe::SLOT, 0);
+            pipe.template steps<true, false, 0, false, 0>(Pipe::SLOT, 0, 0.f);
+            float mx = pipe.s[1][0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, pipe.s[1][r]);
+            pipe.start = mx;
+            pipe.cell = cell0;
+        },
+        [&]() { asm volatile("" : "+v"(next1), "+v"(next2)); },        // the compiler's own wait for them is here, where nothing else is out
+        [&](int b) {
+            pipe.cell = next1;
+            cell2 = next2;
+            next1 = cell_of(b + 3);
+            next2 = cell_of(b + 4);
+            pipe.limit = S - request.key0(b);
+        },
+        [&](int b) {
+            pipe.cell = cell2;
+            pipe.limit = S - request.key0(b + 1);
+        });
+    long my_row = -1;                             // output row of this lane's query (not looked up before: no registers)
+    if (qpos < S) {
+        my_row = (long)grp * S + qpos;
+        if (P.out_rows) my_row = P.out_rows[my_row];
+    }
+    finish_and_store<D, C::KSTR, false>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
+}
+
+// Above 64 x 64: tiles of 128 keys through registers into LDS, the bias by look-ups (attn_chunk_step).  NB: key blocks per
+// softmax chunk, as many as the register budget of two waves per SIMD allows.
+template <int D, int NB>
 __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
 {
     using C = AttnCfg<D>;
     constexpr int LOADS = GLB_TILE * C::CH / 256;       // 16-byte chunks per thread per operand
     static_assert(GLB_TILE * C::CH % 256 == 0, "tile chunks must divide over the workgroup");
-    const int wk = WK ? WK : glb_wk(P.w), tstr = 2 * wk + (WK ? 8 : 4);
+    const int wk = glb_wk(P.w), tstr = 2 * wk + 4;
     bf16 *Ks = reinterpret_cast<bf16 *>(smem);
     bf16 *Vs = Ks + GLB_TILE * C::KSTR;
     unsigned char *Tb = reinterpret_cast<unsigned char *>(Vs + GLB_TILE * C::KSTR);
@@ -1345,7 +1540,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
             *reinterpret_cast<u32x4 *>(Ks + key * C::KSTR + c * 8) = rk[i];                             \
             *reinterpret_cast<u32x4 *>(Vs + key * C::KSTR + c * 8) = rv[i];                             \
         }                                                                                               \
-        if (tid < GLB_TILE) krc[tid] = WK ? cell_row_col(rcell, P.w) : 2 * cell_row_col(rcell, P.w) + ((uint32_t)wk << 17); \
+        if (tid < GLB_TILE) krc[tid] = 2 * cell_row_col(rcell, P.w) + ((uint32_t)wk << 17); \
     }
 
     ATTN_LOAD_TILE(0 < P.n_pre ? 0 : qt, 3)       // in flight while the bias rows are formed
@@ -1371,14 +1566,9 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 #pragma unroll
             for (int b = 0; b < NB; ++b) { blk[b] = c0 + b; key0[b] = kt * GLB_TILE + 32 * (c0 + b); }
             const bool ragged = key0[NB - 1] + 32 > S;                          // ... but for one in a chunk with a block that is not: masked
-            if constexpr (WK != 0) {
-                if (ragged) attn_chunk_step_onehot<D, NB, true, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
-                else attn_chunk_step_onehot<D, NB, false, WK>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
-            } else {
-                const int nb = min(NB, nblk - c0);
-                if (ragged) attn_chunk_step<D, NB, true, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
-                else attn_chunk_step<D, NB, false, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
-            }
+            const int nb = min(NB, nblk - c0);
+            if (ragged) attn_chunk_step<D, NB, true, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
+            else attn_chunk_step<D, NB, false, GlbTab>(st, qf, Ks, Vs, krc, blk, key0, nb, S, P.scale_log2e, tq_lane, tq_lane, P.table_one);
             if (NB < GLB_TILE / 32 && c0 == 0 && a + 1 < nact) ATTN_LOAD_TILE(kt_next, 2)
         }
         __builtin_amdgcn_s_setprio(0);
@@ -1393,8 +1583,16 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
 #undef ATTN_STORE_TILE
 }
 
-// TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid (attn_patch_body, and the general
-// path where a block is not a patch).  !TRY_PATCH: the general path only.
+template <int D>
+size_t global_lds_bytes(int w)
+{
+    // K and V tile, the four waves' bias tables, per key (or per block) table offsets
+    if (glb_operand(w)) return glb_operand(w) == 32 ? onehot_lds_bytes<D, 32>() : onehot_lds_bytes<D, 64>();
+    return (size_t)2 * GLB_TILE * AttnCfg<D>::KSTR * 2 + (size_t)4 * wave_scratch_bytes<D>(glb_general_tstr(w)) + (size_t)GLB_TILE * 4;
+}
+
+// TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid (attn_patch_body, and one of the
+// others where a block is not a patch).  !TRY_PATCH: those only.
 template <int D, bool TRY_PATCH, int WK>
 __global__ void __launch_bounds__(256, 2)
 attn_global_kernel(AttnParams P, int T, int n_gh)
@@ -1411,7 +1609,8 @@ attn_global_kernel(AttnParams P, int T, int n_gh)
         if (attn_patch_body<D>(P, qt, grp, head, smem)) return;
         asm volatile("" : "+s"(qt));                            // nothing of what follows is computed in front of the patch path
     }
-    attn_global_body<D, WK, (WK == 0 && D <= 64 ? 4 : 2)>(P, qt, grp, head, smem);
+    if constexpr (WK != 0) attn_onehot_body<D, WK>(P, qt, grp, head, smem);
+    else attn_global_body<D, (D <= 64 ? 4 : 2)>(P, qt, grp, head, smem);
 }
 
 // CU count and LDS bytes per CU of the current device, asked once per device (host-side queries, no allocation)
@@ -1511,12 +1710,9 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_
             lds = need > lds ? need : lds;
         }
         if (lds > ds.lds) return SSAM_EUNSUPPORTED;
-        // beside the patch path the operand form has registers for one block at a time at d = 80, and is no better than look-ups up to
-        // 32 x 32 and worse at 64 x 64 (16 images row-major, r = 0.4: 1260 us against 1190; 2 images, dense: 370 against 350)
-        constexpr bool PATCH_OPERAND = D <= 64;
-        const int wk = patch && !PATCH_OPERAND ? 0 : glb_operand(P.w);
-        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, PATCH_OPERAND ? 32 : 0> : attn_global_kernel<D, false, 32>)
-                  : wk == 64 ? (patch ? attn_global_kernel<D, true, PATCH_OPERAND ? 64 : 0> : attn_global_kernel<D, false, 64>)
+        const int wk = glb_operand(P.w);
+        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, 32> : attn_global_kernel<D, false, 32>)
+                  : wk == 64 ? (patch ? attn_global_kernel<D, true, 64> : attn_global_kernel<D, false, 64>)
                              : (patch ? attn_global_kernel<D, true, 0> : attn_global_kernel<D, false, 0>);
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)

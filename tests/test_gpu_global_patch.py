@@ -79,6 +79,50 @@ def test_bias_past_fp16(w, d, order, scale):
     assert_close(got, p @ v / p.sum(1, keepdims=True), f"bias past fp16 w={w} d={d} {order} scale={scale}")
 
 
+def exact_global(qkv, rel, sigma, w, r):
+    """Attention of one group over tiles of 128, in 64 bits, for any table of cells."""
+    S, (_, _, nh, d) = w * w, qkv.shape
+    tile, row, col = np.arange(S) // 128, sigma // w, sigma % w
+    off = ~((tile[None, :] < int(r * (tile[-1] + 1) + 1e-6)) | (tile[None, :] == tile[:, None]))
+    want = np.empty((S, nh, d))
+    for h in range(nh):
+        q, k, v = (qkv[:, i, h].astype(np.float64) for i in range(3))
+        logit = d ** -0.5 * (q @ k.T)
+        for t, c in zip(rel, (row, col)):
+            logit += np.take_along_axis(q @ t.T.astype(np.float64), c[:, None] - c[None, :] + w - 1, axis=1)
+        logit[off] = -np.inf
+        p = np.exp(logit - logit.max(1, keepdims=True))
+        want[:, h] = p @ v / p.sum(1, keepdims=True)
+    return want
+
+
+@pytest.mark.parametrize("w,d,r,shared", [(1, 16, 1.0, True), (2, 80, 0.5, False), (3, 64, 0.4, False), (8, 80, 1.0, False), (11, 32, 0.4, False), (12, 64, 0.4, False),
+                                          (16, 80, 0.5, True), (23, 16, 1.0, False), (32, 64, 0.3, False), (32, 80, 1.0, True), (33, 32, 0.2, False),
+                                          (45, 80, 1.0, False), (64, 16, 0.1, True), (64, 64, 0.2, False), (64, 80, 0.1, True)])
+def test_any_order(w, d, r, shared):
+    """Two groups with tables of their own (or one table, which on a power-of-two grid goes through the check for patches first): a random order,
+    and entries that repeat and begin and end at the corners.  Less than a tile, ragged last blocks, blocks past the end, and sides where the
+    tables change from 32 to 64 entries.  The bound: a bf16 rounding is 2^-8 / sqrt(3) * sqrt(0.54) = 1.66e-3 of a value in the root mean square (over
+    mantissas spread evenly in their logarithm), the probabilities' and the output's together 2.34e-3 where no key dominates.  The tables' fp16 adds
+    2^-11 / sqrt(3) * b of a probability for a bias b, 0.1 * sqrt(80) = 0.9 and up to three times that where it gives a key its weight: both
+    tables' together up to 1.0e-3.  2.55e-3 in all."""
+    announce("global, any order", w, d, r, shared)
+    S, rng = w * w, np.random.default_rng(100 * w + d)
+    sigma = np.stack([rng.permutation(S) for _ in range(2)]).astype(np.int32)
+    sigma[0, :1], sigma[0, -1:] = S - 1, 0
+    if S > 8:
+        sigma[0, 3:6] = sigma[0, 2]
+    if shared:
+        sigma[1] = sigma[0]
+    qkv = inputs.bf16_round(rng.normal(size=(2, S, 3, 2, d)).astype(np.float32))
+    rel = [inputs.bf16_round(rng.normal(0, 0.1, size=(2 * w - 1, d)).astype(np.float32)) for _ in range(2)]
+    got = to_np(B.ssam_sparse_attention(dev_bf16(qkv), dev_bf16(rel[0]), dev_bf16(rel[1]), dev_i32(sigma[0] if shared else sigma), w, 128, r)).reshape(2, S, 2, d)
+    want = np.stack([exact_global(qkv[g], rel, sigma[g], w, r) for g in range(2)])
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print("error", err)
+    assert err < 2.6e-3
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 80])
 @pytest.mark.parametrize("w,r,order", [(32, 0.2, "position"), (64, 0.4, "position"), (28, 0.4, "position"), (50, 0.5, "row")])
 def test_error_where_one_key_dominates(w, r, order, d):
