@@ -22,7 +22,7 @@
 // Bias: per wave, U = Q R^T is formed once with the MFMA for both tables and kept in LDS as fp16, query-major.  A score gets
 // its two entries as a product with the table in the scores' accumulator: of one 16-entry operand on orders whose
 // blocks are patches, of the whole row of up to 64 entries a table on others (AttnPipe) or of 16 (windows,
-// attn_chunk_step_onehot); above 64 x 64 by two look-ups.
+// attn_window_step); above 64 x 64 by two look-ups.
 // Memory requests are spread over a problem's / a tile's phases (see the prefetch
 // macros): a wave whose loads do not fit the CU's request queues waits instead of
 // computing, and a wait placed behind a branch or on a value that is used at once
@@ -127,7 +127,7 @@ __device__ __forceinline__ void init_state(WaveState<D> &st)
 // and 8 column entries are then contiguous.  tstr = 4*hw + 4: the 8 bytes of padding put the 32 lanes of a look-up
 // (one entry, 32 queries) on distinct banks.  tq_lane: this lane's query row.  rel tables: rows of `rstr` elements.
 //
-// Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_chunk_step_onehot, AttnPipe) every entry
+// Range.  Where the bias is added as the product of a 0/1 matrix and the table (attn_window_step, AttnPipe) every entry
 // meets every key, most of them as a zero, and an infinity would make NaNs of the query's whole row.  So
 //   * entries past the range of fp16 become +-65504 (clamp_fp16), which as a logit is 65504 * scale, and
 //   * with a small scale the table is 2^shift times smaller and the ones of that matrix, or what a looked-up entry is multiplied
@@ -220,7 +220,7 @@ typedef _Float16 WinTab;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
-// Bias operands of the window kernels (attn_chunk_step_onehot): entry p of the lane's query (p = key row, or 16 + key column) at
+// Bias operands of the window kernels (attn_window_step): entry p of the lane's query (p = key row, or 16 + key column) at
 // tq[(l & 31) * WIN_OSTR + p], divided by the softmax scale (AttnParams::table_inv); those past w are zero.  A window has 2w-1 <= 32
 // relative positions, so rel x Q^T is one MFMA tile per table.  It is stored the way it leaves the matrix core, query-major, and
 // entry p read back as position q - p + w - 1: predicated stores of the entries to their places, as for larger grids, cost two to three times as much.
@@ -421,63 +421,46 @@ __device__ __forceinline__ void attn_chunk_step(WaveState<D> &st, const bf16x8 *
 __device__ __forceinline__ int patch_rr(int k) { return ((k >> 1) & 1) | ((k >> 2) & 2); }
 __device__ __forceinline__ int patch_cc(int k) { return (k & 1) | ((k >> 1) & 2) | ((k >> 2) & 4); }
 
-// Scores of a chunk in any order, with the decomposed bias as a product too: B[k][q] = sum_p E[k][p] T[p][q], where E has a one at
-// the key's row and a one at its column and T is the query's table row, WK entries each: 2 * WK / 16 more MFMAs per block
-// (fp16 operands, the same fp32 accumulator, issued first).  A lane makes its part of E from its key's row and column in
-// registers.  Two look-ups per score instead cost 32 LDS reads and 80 vector instructions per block.  One launch of 2
-// images, 50 x 50, 12 heads, d = 64, r = 0.5: 78 -> 67 us.
-template <int D, int NB, bool RAGGED, int WK>
-__device__ __forceinline__ void attn_chunk_step_onehot(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs,
-                                                       const uint32_t *krc, const int (&blk)[NB], const int (&key0)[NB],
-                                                       int S, float scale_log2e, const _Float16 *tq_lane, uint32_t half_one)
+// A block of 32 keys of a window, in any order, against the wave's 32 queries, with the decomposed bias as a product too: B[k][q] = sum_p E[k][p] T[p][q],
+// where E has a one at the key's row and a one at its column and T is the query's table row, 16 entries each.  One sparse product (fp16
+// operands, the same fp32 accumulator, issued last: its result cannot begin at a constant; see AttnPipe::describe): the lower half-wave makes the rows' part of E, the upper one the
+// columns'.  Two look-ups per score instead cost 32 LDS reads and 80 vector instructions per block.
+template <int D, bool RAGGED>
+__device__ __forceinline__ void attn_window_step(WaveState<D> &st, const bf16x8 *qf, const bf16 *Ks, const bf16 *Vs, const uint32_t *krc, int blk, int key0,
+                                                 int S, float scale_log2e, const _Float16 *tq_lane, uint32_t half_one)
 {
     using C = AttnCfg<D>;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    f32x16 s[NB];
+    const uint32_t rc = krc[blk * 32 + l32], at = half ? rc >> 16 : rc & 0xffffu, i = at & 3u;               // row | column << 16
+    const uint32_t one = i == 3 ? half_one << 16 : half_one, index = i == 3 ? 0xccccu : 0xccccu + i * 0x1111u;
+    u32x4 e;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        // the table operands are the same for every block: read again all the same (kept in registers they spill at d = 80)
-        uint32_t fresh = 0;
-        asm volatile("" : "+v"(fresh));
-        const uint32_t rc = krc[blk[b] * 32 + l32];               // row | column << 16
-        s[b] = f32x16{ 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
+    for (int j = 0; j < 4; ++j) e[j] = at >> 2 == (uint32_t)j ? one : 0u;
+    // operand b: entries 8 * half .. + 7 of the rows and of the columns; the same for every block, and read again all the same (kept in registers they spill)
+    uint32_t fresh = 0;
+    asm volatile("" : "+v"(fresh));
+    const f16x8 lo = *reinterpret_cast<const f16x8 *>(tq_lane + fresh + half * 8), hi = *reinterpret_cast<const f16x8 *>(tq_lane + fresh + 16 + half * 8);
+    const f16x16 t = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+    const f32x16 zero = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
+    f32x16 s[1];
+    const bf16 *kblk = Ks + blk * 32 * C::KSTR + l32 * C::KSTR + half * 8;
 #pragma unroll
-        for (int tab = 0; tab < 2; ++tab) {
-            // the one's place among 8 consecutive entries (two per register), and which such group it is in
-            const uint32_t at = tab ? rc >> 16 : rc & 0xffffu, one = half_one << ((at << 4) & 31u);
-            u32x4 e;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) e[j] = ((at >> 1) & 3u) == (uint32_t)j ? one : 0u;
-#pragma unroll
-            for (int ks = 0; ks < WK / 16; ++ks) {
-                const bool here = (at >> 3) == (uint32_t)(2 * ks + half);
-                u32x4 a;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = here ? e[j] : 0u;
-                const f16x8 t = *reinterpret_cast<const f16x8 *>(tq_lane + fresh + tab * WK + ks * 16 + half * 8);
-                s[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), t, s[b], 0, 0, 0);
-            }
-        }
-        const bf16 *kblk = Ks + blk[b] * 32 * C::KSTR + l32 * C::KSTR + half * 8;
-#pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            bf16x8 a = *reinterpret_cast<const bf16x8 *>(kblk + ks * 16);
-            s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[b], 0, 0, 0);
-        }
-        if constexpr (D > 64) __builtin_amdgcn_sched_barrier(0);       // one block's operands at a time: both at once spill
+    for (int ks = 0; ks < C::KS; ++ks) {
+        bf16x8 a = *reinterpret_cast<const bf16x8 *>(kblk + ks * 16);
+        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], ks == 0 ? zero : s[0], 0, 0, 0);
     }
+    s[0] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(f16x8, e), t, s[0], (int)index, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");          // MFMA passes done before the scores are read (as in attn_chunk_step)
     __builtin_amdgcn_sched_barrier(0);
     float mx = -INFINITY;
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            if (RAGGED) s[b][r] = key0[b] + 8 * (r >> 2) + 4 * half + (r & 3) < S ? s[b][r] : -INFINITY;
-            mx = fmaxf(mx, s[b][r]);
-        }
-    attn_softmax_pv<D, NB, true>(st, s, mx, Vs, blk, NB, scale_log2e);
+    for (int r = 0; r < 16; ++r) {
+        if (RAGGED) s[0][r] = key0 + 8 * (r >> 2) + 4 * half + (r & 3) < S ? s[0][r] : -INFINITY;
+        mx = fmaxf(mx, s[0][r]);
+    }
+    const int blks[1] = { blk };
+    attn_softmax_pv<D, 1, true>(st, s, mx, Vs, blks, 1, scale_log2e);
 }
 
 template <int D>
@@ -570,6 +553,7 @@ __host__ __device__ inline int wave_scratch_bytes(int tstr)
 // ------------------------------------------------------------------ window kernel, persistent
 // The bias as a product (two MFMAs a block, operands built once a tile) instead of 32 LDS look-ups and 80 vector instructions a block: 16 heads, d = 80,
 // 800 problems 34.2 -> 32.4 us at r = 0.4, 51.1 -> 45.7 dense; 3200: 99.6 -> 96.5 and 154.8 -> 137.3.
+// One sparse product instead of two dense ones: 3200 problems 98.4 -> 95.6 and 142.7 -> 138.6 on another box; a wave to a tile, d = 64, 1600 problems 38.3 -> 37.8.
 inline int window_rel_rows(int w) { return ((2 * w - 1 + 31) / 32) * 32; }
 
 // per-wave LDS landing area of the next problem's queries: the KS operand-b fragments of the wave's 32 queries
@@ -742,10 +726,10 @@ attn_window_kernel(AttnParams P, int n_groups)
         init_state<D>(st);
         // active key tiles of query tile `wave`: the dense prefix, then the diagonal
         for (int a = 0; a < nact; ++a) {
-            const int blk[1] = { a < P.n_pre ? a : wave }, key0[1] = { blk[0] * 32 };
+            const int blk = a < P.n_pre ? a : wave, key0 = blk * 32;
             // only the last 32-key tile of the window can cross S
-            if (key0[0] + 32 > S) attn_chunk_step_onehot<D, 1, true, 16>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
-            else attn_chunk_step_onehot<D, 1, false, 16>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            if (key0 + 32 > S) attn_window_step<D, true>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            else attn_window_step<D, false>(st, qf, Ks, Vs, krc, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
             // after the second tile (the only one, when there is one): early enough to cover the request's
             // latency with the last tile and the output stores on the tiles that have three, and not in the same
             // burst as the K or the V requests
@@ -857,9 +841,9 @@ attn_window_kernel_waves(AttnParams P, int prob0, int n_problems, int T)
             }
             wave_lds_fence();
             if (a + G::AHEAD < nact) load_block(rk[u], rv[u], a + G::AHEAD);
-            const int blk[1] = { 0 }, key0[1] = { block_at(a) * 32 };
-            if (key0[0] + 32 > S) attn_chunk_step_onehot<D, 1, true, 16>(st, qf, Ks, Vs, krc + 32 * a, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
-            else attn_chunk_step_onehot<D, 1, false, 16>(st, qf, Ks, Vs, krc + 32 * a, blk, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            const int key0 = block_at(a) * 32;
+            if (key0 + 32 > S) attn_window_step<D, true>(st, qf, Ks, Vs, krc + 32 * a, 0, key0, S, P.scale_log2e, tq_lane, P.half_one);
+            else attn_window_step<D, false>(st, qf, Ks, Vs, krc + 32 * a, 0, key0, S, P.scale_log2e, tq_lane, P.half_one);
         }
     }
     wave_lds_fence();
@@ -1388,7 +1372,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
 }
 
 // Any order, any S, up to 64 x 64 (WK = 32 or 64 entries a table): the pipeline of the patch path, whose bias is one product of the patch's
-// entries, with the whole table row of a query instead, as in attn_chunk_step_onehot: B[k][q] = sum_p E[k][p] T[p][q], E a one at the key's row
+// entries, with the whole table row of a query instead, as in attn_window_step: B[k][q] = sum_p E[k][p] T[p][q], E a one at the key's row
 // and a one at its column.  Three quarters of E's groups of four are known zeros and no group has two ones, so it is a structured-sparse operand: a
 // 32x32x32 sparse product takes the time of a dense 32x32x16 one (15.6 ns against 15.4 on a SIMD, measured), four a block instead of eight at 64 entries, and a
 // lane makes 16 dwords of E for a block, two instructions each.  T stays in registers, as its operands b.
