@@ -86,6 +86,22 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
+// Of 8 columns of a piece of a row's statistics (GemmParts): their sum, their squared deviations from the piece's mean.  In this order wherever pieces are written.
+__device__ __forceinline__ float gemm_piece_sum8(const float *v)
+{
+    float s = v[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) s += v[e];
+    return s;
+}
+__device__ __forceinline__ float gemm_piece_squares8(const float *v, float mean)
+{
+    float q = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { const float t = v[e] - mean; q = fmaf(t, t, q); }
+    return q;
+}
+
 // erf GELU, 0.5 t (1 + erf(t / sqrt 2)) = max(t, 0) - 0.5 |t| erfc(|t| / sqrt 2).  erfc by the rational approximation 7.1.26 of
 // Abramowitz & Stegun, erfc(x) = (a1 u + ... + a5 u^5) exp(-x^2), u = 1 / (1 + p x) for x >= 0; absolute error below
 // 1.5e-7, far under the bf16 rounding of the stored activation.  One reciprocal and one exp2 per element, eleven full-rate

@@ -9,6 +9,8 @@ int ssam_gemm_wide_add(int tile, bool packed, const GemmWideArgs &a);
 int ssam_gemm_wide_scatter(int tile, bool packed, const GemmWideArgs &a);
 int ssam_gemm_wide_ln_scatter(int tile, const GemmWideArgs &a);
 int ssam_gemm_wide_ln_gelu(int tile, const GemmWideArgs &a);
+int ssam_gemm_wide_parts_scatter(int tile, const GemmWideArgs &a);
+int ssam_gemm_wide_parts_gelu(int tile, const GemmWideArgs &a);
 
 namespace {
 
@@ -127,7 +129,7 @@ int launch_split(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M
     return launch_range<TM, TN, EPI, SUB_M, SUB_N, 2, 2, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, whole, fold, st);
 }
 
-const GemmFold no_fold = { nullptr, nullptr, nullptr };
+const GemmFold no_fold = {};
 
 template <int EPI, bool LNF = false>
 int launch_tile_packed(int tile, const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
@@ -278,7 +280,8 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 // without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
-int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us)
+// among: the tiles to choose from, by their indices.
+int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us, unsigned among = ~0u)
 {
     const int nk = K / GEMM_BK;
     if (K % GEMM_BK != 0 || nk < 5 || (packed && M <= 32)) return -1;
@@ -287,6 +290,7 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
     int best = -1;
     double best_us = 1e30;
     for (int i = 0; i < GEMM_WIDE_COUNT; ++i) {
+        if (!((among >> i) & 1)) continue;
         const WideTile &t = wide_tiles[i];
         const double slab = t.t_slab * (1.0 + torn * (t.bm * t.bn < 128 * 128 ? 0.3 : 0.15));
         const int rounds = ssam_div_up(ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 8), 32);      // (see the kernel's XCDs)
@@ -350,22 +354,80 @@ int launch_any(int tile, int ring, const bf16 *A, const bf16 *W, const float *bi
     else return launch_tile<EPI>(tile, A, W, bias, C, M, N, K, ld, rm, ws, st);
 }
 
+// The wide kernel's tile of a contraction (-1: another kernel); the kernel that takes it otherwise on return.
+int choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs &ws, bool packed, int &tile, int &ring, unsigned among = ~0u)
+{
+    double us;
+    tile = pick_tile(M, N, K, epilogue, ws, packed, us);
+    ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
+    return pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0), among);
+}
+
+// What reading a row's statistics in pieces saves (a launch of 4.6 us less what the reading takes): other kernels of a contraction that could
+// read them take that much longer.  fc1 of ViT-L at a density of 0.4 (1638 x 4096 x 1024) is 1 % faster on the large tiles by itself.
+constexpr double PARTS_US = 3.0;
+
+// The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics could come in pieces.
+int choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, int &tile, int &ring, bool parts)
+{
+    double us;
+    tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
+    ring = pick_ring(M, N, K, true, true, us);
+    if (parts) us += PARTS_US;
+    return pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us, parts ? GEMM_WIDE_READS_PARTS : ~0u);
+}
+
+double folded_ln_us(int tiles, int K);
+
+// And for qkv with a LayerNorm folded in.
+int choose_ln(int M, int N, int K, const GemmLd &ld, int &ring, bool parts)
+{
+    double us = folded_ln_us((M / 128) * (N / 256), K);
+    ring = pick_ring(M, N, K, true, true, us);
+    if (parts) us += PARTS_US;
+    return pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, us, us, parts ? GEMM_WIDE_READS_PARTS : ~0u);
+}
+
 }  // namespace
 
+// Row statistics in pieces (GemmParts) of the residual stream, [rows][D] of which `kept` go through the MLP: whether proj, fc1 and fc2 (packed
+// weights, LN2 folded into fc1) all take the wide kernel with tiles that write or read them.  None of them then uses its K-split scratch.
+bool ssam_parts_fit(int rows, int kept, int D, int Dm)
+{
+    alignas(16) static unsigned char some;
+    const SplitWs ws = { &some, GEMM_SPLIT_WS_BYTES };
+    int tile, ring;
+    return D % 128 == 0 && D / 64 <= GEMM_PARTS_MOST &&
+           choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, ws, true, tile, ring, GEMM_WIDE_WRITES_PARTS) >= 0 &&
+           choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, tile, ring, true) >= 0 &&
+           choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, tile, ring, GEMM_WIDE_WRITES_PARTS) >= 0;
+}
+
+// And whether qkv with LN1 folded in reads them.
+bool ssam_parts_fit_qkv(int rows, int D)
+{
+    int ring;
+    return choose_ln(rows, 3 * D, D, GemmLd{ D, D, 3 * D }, ring, true) >= 0;
+}
+
+// Both, for tests (1: ssam_parts_fit, 2: ssam_parts_fit_qkv).  Host only; not part of the interface.
+extern "C" int ssam_parts_form(int rows, int kept, int D, int Dm) { return (ssam_parts_fit(rows, kept, D, Dm) ? 1 : 0) + (ssam_parts_fit_qkv(rows, D) ? 2 : 0); }
+
+// parts (optional): row statistics that a scatter-add leaves; the caller has asked ssam_parts_fit.
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
-                     void *split_ws, size_t split_ws_bytes, hipStream_t st)
+                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts)
 {
     const SplitWs ws = { split_ws, split_ws_bytes };
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
     bf16 *c = (bf16 *)C;
     int ring = -1;
     if (tile == 0) {
-        double us;
-        tile = pick_tile(M, N, K, epilogue, ws, packed, us);
-        ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
-        if (const int wide = pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0)); wide >= 0) {
-            const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, no_fold, st };
+        if (const int wide = choose(M, N, K, epilogue, ld, ws, packed, tile, ring, parts.at ? GEMM_WIDE_WRITES_PARTS : ~0u); wide >= 0) {
+            GemmFold out;
+            out.parts = parts.at;
+            out.slots = parts.slots;
+            const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, out, st };
             switch (epilogue) {
             case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
             case SSAM_EPI_BIAS_GELU: return ssam_gemm_wide_gelu(wide, packed, args);
@@ -375,6 +437,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
             }
         }
     }
+    if (parts.at) return SSAM_EUNSUPPORTED;
     if (packed) {
         switch (epilogue) {
         case SSAM_EPI_BIAS: return launch_any<SSAM_EPI_BIAS, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
@@ -395,16 +458,20 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 
 // fc1 of the routed MLP with gather and LN2 folded in (see GemmFold): rows src[m] of A, packed folded weights,
 // GELU epilogue, any M; the kernel is picked as for the plain contraction of the same shape.  rows_a: rows of A.
+// With parts (see ssam_parts_fit) there are no stats, and src holds the rows of every batch of src_rows: row m / src_rows * src_stride + src[m] of A.
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
-                               void *split_ws, size_t split_ws_bytes, hipStream_t st)
+                               void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride)
 {
     const SplitWs ws = { split_ws, split_ws_bytes };
-    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src };
+    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src, parts.at, parts.slots, parts.eps, src_rows, src_stride };
     const GemmRowMap none = { nullptr, 1, 0, 1 };
-    double us;
-    const int tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us), ring = pick_ring(M, N, K, true, true, us);
-    if (const int wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us); wide >= 0)
+    int tile, ring;
+    const int wide = choose_fold_gelu(M, N, K, ld, rows_a, ws, tile, ring, parts.at != nullptr);
+    if (parts.at)
+        return wide < 0 ? SSAM_EUNSUPPORTED
+                        : ssam_gemm_wide_parts_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
+    if (wide >= 0)
         return ssam_gemm_wide_ln_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
     if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
@@ -413,25 +480,32 @@ int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, c
 }
 
 // Time of its large tiles: 512 workgroups a round, a last round of at most half of them at 0.62 of a round's time (as in pick_tile).
-static double folded_ln_us(int tiles, int K)
+namespace {
+
+double folded_ln_us(int tiles, int K)
 {
     const double round = (K / GEMM_BK) * 1.71 + 5.5;
     const int last = tiles % 512;
     return large_tile_us(4, (tiles / 512) * round + (last == 0 ? 0.0 : last <= 256 ? 0.62 * round : round), true);
 }
 
+}  // namespace
+
 // The contraction with the LayerNorm of its A rows folded in (see GemmFold): 128x256 tiles, packed weights,
 // mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
-                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st)
+                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts)
 {
     constexpr size_t lds = gemm_lds_bytes<128, 256, 1, 4, true>();
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
-    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr };
-    double us = folded_ln_us(tr.tile_count, K);
-    const int ring = pick_ring(M, N, K, true, true, us);
-    if (const int wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, us, us); wide >= 0)
+    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr, parts.at, parts.slots, parts.eps };
+    int ring;
+    const int wide = choose_ln(M, N, K, ld, ring, parts.at != nullptr);
+    if (parts.at)
+        return wide < 0 ? SSAM_EUNSUPPORTED
+                        : ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });
+    if (wide >= 0)
         return ssam_gemm_wide_ln_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });
     if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
@@ -454,7 +528,7 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     if (ldx < K || ldc < N || ldx % 8 || ldc % 8 || rows_per_batch <= 0 || map_batch_stride < 0 || dst_rows_per_batch <= 0) return SSAM_EINVAL;
     if (M % 128 != 0 || N % 256 != 0 || K % GEMM_BK != 0) return SSAM_EUNSUPPORTED;
     const GemmRowMap rm = { row_map, rows_per_batch, map_batch_stride, dst_rows_per_batch };
-    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream);
+    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{});
 }
 
 // Which kernel a contraction takes where the wide kernel does not (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
@@ -541,7 +615,7 @@ extern "C" int ssam_linear_ld(const void *A, int lda, const void *W, int ldw, in
     }
     GemmLd ld = { lda, ldw, ldc };
     return ssam_linear_impl(A, W, bias, C, M, N, K, ld, w_packed != 0, epilogue, rm, tile, workspace, workspace ? workspace_bytes : 0,
-                            (hipStream_t)stream);
+                            (hipStream_t)stream, GemmParts{});
 }
 
 extern "C" int ssam_linear_tiled(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,

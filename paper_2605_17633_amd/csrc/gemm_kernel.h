@@ -75,10 +75,26 @@ constexpr size_t GEMM_SPLIT_WS_BYTES = (size_t)32 << 20;   // workspace that let
 // with bias_n = b_n + sum_k beta_k W[n][k].  With `src` the rows are also gathered: row m of the product is row
 // src[m] of A (the routed MLP's kept tokens, read where they lie in the residual stream).
 struct GemmFold {
-    const float2 *stats;      // [M] per row of the product: { rstd, -rstd * mean } of the A row it reads
-    const float *colsum;      // [N] sum over k of the folded weight as stored (bf16 values, fp32 sum)
-    const int32_t *src;       // [M] row of A per row of the product (all inside A), or NULL: row m itself
+    const float2 *stats = nullptr;      // [M] per row of the product: { rstd, -rstd * mean } of the A row it reads
+    const float *colsum = nullptr;      // [N] sum over k of the folded weight as stored (bf16 values, fp32 sum)
+    const int32_t *src = nullptr;       // [M] row of A per row of the product (all inside A), or NULL: row m itself
+    float2 *parts = nullptr;  // row statistics in pieces (see GemmParts); with them src counts rows within batches:
+    int slots = 0;            //   row m of the product is row m / src_rows * src_stride + src[m] of A
+    float eps = 0.f;
+    int src_rows = 1, src_stride = 0;
 };
+
+// Statistics of the rows of the residual stream in pieces of 64 columns, [rows][GEMM_PARTS_MOST] { mean, sum of squared deviations from it }: the
+// epilogues that write the rows leave them, from the values as stored, and the contraction that wants a row's mean and variance puts
+// them together.  A statistics launch of its own takes 4.6 us however few rows there are; writing the pieces takes 0.3 to 0.6 (128x128 tiles of proj 11.3
+// -> 11.6, 96x64 of fc2 17.4 -> 18.0) and reading them 1 to 1.5 (256x192 of qkv 21.4 -> 22.6, 192x128 of fc1 16.0 -> 17.4; ViT-B, batch 1).  From two images of
+// 64 x 64 on qkv and fc1 of the larger models take the large tiles, which read statistics as before.  at = NULL: none.
+struct GemmParts {
+    float2 *at;
+    int slots;                // D / 64
+    float eps;
+};
+constexpr int GEMM_PARTS_MOST = 16;           // pieces of a row: 128 bytes, as long as a row of a slab of 64 bf16
 
 struct GemmSplit {
     float *partial;           // [tile_count*SUB_M*SUB_N][parts][BM][BN] fp32, NULL unless GEMM_EPI_PARTIAL
@@ -104,7 +120,7 @@ template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, in
 __device__ __forceinline__ void
 gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                   bf16 *C, int M, int N, int K, const GemmLd &ld, const GemmTileRange &tr, const GemmRowMap &rm,
-                  const GemmSplit &sp, int bid, const GemmFold &fold = GemmFold{ nullptr, nullptr, nullptr })
+                  const GemmSplit &sp, int bid, const GemmFold &fold = GemmFold{})
 {
     static_assert(!LNF || WPACK, "the folded forms exist for packed weights");
     // a K range of a folded product only gathers its rows: the normalisation is finished where the ranges are added

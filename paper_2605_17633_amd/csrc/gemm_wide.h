@@ -21,7 +21,8 @@
 //   4096 x 2304 x 768 22.9 -> 18.5 | 4096 x 3072 x 1024 31 -> 24 | 1638 x 3072 x 768 + GELU 17.8 -> 14.5 | 1638 x 768 x 3072 + scatter-add
 //   21 -> 16.5 | 4096 x 1024 x 1024 + scatter-add 16.9 -> 13 | 2456 x 1280 x 5120 57 -> 38 (its K-split launch and reduce) | 8192 x 1280 x 1280
 //   38 -> 28 | 8192 x 576 x 2304 row-major 36.5 -> 25.  Packed and row-major weights take the same time.
-// Encoders, batch 1: ViT-B 1360 -> 1258 us, ViT-L 3051 -> 2674.  Steady state 1.29 us a slab of 256x256 (1.66 PFLOP/s).  Not faster: eight or
+// Encoders, batch 1: ViT-B 1360 -> 1258 us, ViT-L 3051 -> 2674; with the row statistics left and read by these kernels instead of launches of their
+// own (GemmParts) 1181 -> 1149 and 2517 -> 2424 on another box.  Steady state 1.29 us a slab of 256x256 (1.66 PFLOP/s).  Not faster: eight or
 // six slabs ahead, requests in front of the k-step (10 % slower: they crowd out the fragment reads), wave priority, 128x192 tiles two to
 // a CU, a persistent form whose next tile's slabs are requested under the epilogue (its waits then are for the stores too).
 #pragma once
@@ -45,10 +46,11 @@ __device__ __forceinline__ void gemm_load_lds4(uint32_t lds, const int32_t *src)
 
 template <int N> __device__ __forceinline__ void gemm_wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-// WGK = 2: the workgroup's eight waves are 2 x 2 over the tile times two halves of every slab of K; 1: 2 x 4 or 4 x 2 over the tile.
+// WGK = 2: the workgroup's eight waves are 2 x 2 over the tile times two halves of every slab of K; 1: 2 x 4 or 4 x 2 over the tile (128x128: 4 x 2, as
+// many fragments read as 2 x 4, and waves with whole pieces of 64 columns).
 template <int BM, int BN, int WGK>
 struct GemmWide {
-    static constexpr int WGM = WGK == 1 && BM > BN ? 4 : 2, WGN = 8 / WGK / WGM, MT = BM / WGM / 16, NT = BN / WGN / 16;       // 16x16 MFMA tiles of a wave
+    static constexpr int WGM = WGK == 1 && BM > BN - (BN == 128) ? 4 : 2, WGN = 8 / WGK / WGM, MT = BM / WGM / 16, NT = BN / WGN / 16;       // 16x16 MFMA tiles of a wave
     static constexpr bool EARLY = MT * NT < 32;         // registers and LDS for what the epilogue reads before the last slabs
     static constexpr int AB = BM * GEMM_BK * 2, WB = BN * GEMM_BK * 2;                          // bytes of a slab
     static constexpr int MAP = EARLY ? 1024 : 0, LDS = 160 * 1024 - MAP;                        // of the tile's row map, of the ring
@@ -58,15 +60,29 @@ struct GemmWide {
     // 1 KB requests of a slab: A's, then W's; wave w takes w, w + 8, ...
     static constexpr int QA = BM / 8, QW = BN / 8, L = (QA + QW + 7) / 8, LREST = (QA + QW) % 8;
     static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0 && (WGK == 2 || (QA % 8 == 0 && QW % 8 == 0)), "whole MFMA tiles and requests");
+    static_assert(GEMM_BK * 2 == GEMM_PARTS_MOST * 8, "a row's pieces take the place of its part of a slab");
     static_assert(WGK == 1 || (size_t)BM * BN * 4 <= ring, "the halves are added in the ring's LDS");
 };
 
-template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF>
+// Sum over the four quads of a wave's lanes.
+__device__ __forceinline__ float gemm_quad_sum(float v)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// PARTS: the row statistics of the folded LayerNorm come in pieces (GemmParts).  The scatter-add epilogues leave such pieces where fold.parts is given.
+// The pieces of a tile's rows are as large as a slab of A and come as one more, into the stage that the last slab but SA - 1 has freed: no registers, and
+// under the products of the last slabs.  Loaded in front of the ring's first slabs they cost 4 us, as much as the launch they save.
+template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS = false>
 __global__ void __launch_bounds__(512, 1)
 gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                  bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
     using G = GemmWide<BM, BN, WGK>;
+    static_assert(!PARTS || (LNF && WGK == 1), "the forms that read pieces");
     constexpr int BK = GEMM_BK, WGN = G::WGN, MT = G::MT, NT = G::NT, NP = NT / 2, WM = MT * 16, WN = NT * 16;
     constexpr int SA = G::SA, SW = G::SW, L = G::L;
     constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER, ADD = EPI == SSAM_EPI_BIAS_SCATTER_ADD;
@@ -94,7 +110,13 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     // ---- requests
     uint32_t off[L], dst[L], inc[L];
     const unsigned char *base[L];
+    uint32_t poff[PARTS ? G::QA / 8 : 1];             // of the rows' pieces, which are requested as one more slab of A
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
+    auto a_row = [&](int m) {
+        if constexpr (!PARTS) return fold.src[m];
+        const int t = fold.src[m];
+        return m / fold.src_rows * fold.src_stride + ((unsigned)t < (unsigned)fold.src_stride ? t : 0);
+    };
     auto is_a = [&](int i) { return WGK == 1 ? i < G::QA / 8 : i * 8 + wave < G::QA; };
 #pragma unroll
     for (int i = 0; i < L; ++i) {
@@ -103,7 +125,9 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
         if (is_a(i)) {
             const int row = f * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7), m = min(m0 + row, M - 1);
             const bool gather = LNF && fold.src;
-            off[i] = ((uint32_t)(gather ? fold.src[m] : m - m0) * (uint32_t)ld.a + c * 8) * 2;
+            const int ar = gather ? a_row(m) : m - m0;
+            off[i] = ((uint32_t)ar * (uint32_t)ld.a + c * 8) * 2;
+            if constexpr (PARTS) poff[i] = (uint32_t)(gather ? ar : m) * (GEMM_PARTS_MOST * 8) + c * 16;
             base[i] = reinterpret_cast<const unsigned char *>(gather ? A : A + (long)m0 * ld.a);
             dst[i] = lds0 + f * 1024;
         } else {
@@ -140,6 +164,8 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             else if (G::LREST != 0 && !all) gemm_wait_vm<(L - 1) * s>();
             else gemm_wait_vm<L * s>();
         };
+        // (behind the last slab only the rows' pieces are out)
+        if (PARTS && rem < 1) { gemm_wait_vm<G::QA / 8>(); return; }
         if (rem >= MAX) out(integral_constant<int, MAX>{});
         else if (MAX > 2 && rem >= 2) out(integral_constant<int, 2>{});
         else if (MAX > 1 && rem >= 1) out(integral_constant<int, 1>{});
@@ -220,7 +246,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 #pragma unroll
             for (int k = 0; k < AHEAD; ++k) load_old(k);
         }
-        if constexpr (LNF) {
+        if constexpr (LNF && !PARTS) {
 #pragma unroll
             for (int k = 0; k < MTH; ++k) rst[k] = fold.stats[min(m0 + wm + 16 * (wk * MTH + k) + l16, M - 1)];
         }
@@ -235,6 +261,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 
     // ---- ring
     int sa = 0, sw = 0;                          // stages of slab t
+    int pieces = 0;                              // where in the ring the rows' pieces land
     if constexpr (WGK == 1) {
         // iteration t of the loop requests W of slab t + SW, then A of slab t + SA; here those of t = -SA .. -1
 #pragma unroll
@@ -279,6 +306,12 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
                 if (t + SW < n)
 #pragma unroll
                     for (int i = LA; i < L; ++i) request(i, sa, sw);
+                // into the first stage that takes no slab any more, behind every slab (what is waited for from here on counts on it)
+                if constexpr (PARTS) if (t == n - SA) {
+                    pieces = sa * STRIDE_A;
+#pragma unroll
+                    for (int i = 0; i < LA; ++i) gemm_load_lds16_s(dst[i] + pieces, poff[i], fold.parts);
+                }
                 if (t + 1 < n)
 #pragma unroll
                     for (int q = 0; q < NR; ++q) read(q, 0, 0, sa1, sw1);
@@ -350,6 +383,32 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     __builtin_amdgcn_sched_barrier(0);
 
     if (!EARLY) load_epilogue();
+    if constexpr (PARTS) {
+        // a row's pieces over the four quads, its mean, then the squares about it
+        gemm_wait_vm<0>();
+        LDS_BARRIER();
+#pragma unroll
+        for (int k = 0; k < MTH; ++k) {
+            const int row = wm + 16 * k + l16;
+            const unsigned char *at = as + pieces + row * 128;
+            float2 v[GEMM_PARTS_MOST / 4];
+            float mean = 0.f, sq = 0.f;
+#pragma unroll
+            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i) {
+                const int s = 4 * i + quad;
+                v[i] = *reinterpret_cast<const float2 *>(at + (((s >> 1) ^ ((row >> 1) & 7)) << 4) + (s & 1) * 8);
+                if (s < fold.slots) mean += v[i].x;
+            }
+            mean = gemm_quad_sum(mean) / (float)fold.slots;
+#pragma unroll
+            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i) {
+                const float d = v[i].x - mean;
+                if (4 * i + quad < fold.slots) sq += v[i].y + 64.f * d * d;
+            }
+            const float inv = rsqrtf(gemm_quad_sum(sq) / (float)K + fold.eps);          // K: the rows' length
+            rst[k] = make_float2(inv, -inv * mean);
+        }
+    }
 
     // ---- epilogue, straight from the accumulators: lane (l16, quad) holds row 16*i + l16, columns 8*quad .. + 7 of every pair of tiles
     f32x4 fin[MTH][NT];
@@ -385,6 +444,8 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             if constexpr (EPI == SSAM_EPI_BIAS_GELU) v[e] = gelu_erf(v[e]);
         }
     };
+    constexpr bool PIECES = ADD && WPACK && (WN == 32 || WN == 64);
+    uint4 kept[PIECES ? MTH : 1][PIECES ? NP : 1];
 #pragma unroll
     for (int k = 0; k < MTH; ++k) {
         bf16 *row = C + (long)drow[k] * ld.c;
@@ -400,7 +461,9 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] += o[e];
             }
-            if (drow[k] >= 0 && ncol + 32 * p < N) *reinterpret_cast<uint4 *>(row + ncol + 32 * p) = pack_bf16x8(v);      // N % 8 == 0
+            const uint4 packed = pack_bf16x8(v);
+            if (drow[k] >= 0 && ncol + 32 * p < N) *reinterpret_cast<uint4 *>(row + ncol + 32 * p) = packed;      // N % 8 == 0
+            if constexpr (PIECES) kept[k][p] = packed;
         }
         if constexpr (NT % 2) {
             float v[8];
@@ -414,5 +477,45 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             if (drow[k] >= 0 && ncol1 < N) *reinterpret_cast<uint2 *>(row + ncol1) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
         }
         if constexpr (ADD) if (k + AHEAD < MTH) load_old(k + AHEAD);
+    }
+    if constexpr (PIECES) if (fold.parts) {
+        // Pieces of the rows from the values as stored: sums of 8 columns, of columns 32 apart, over the quads (gemm_piece_sum8 and the same tree in
+        // whatever writes pieces: a row's are the same bits whichever kernel wrote it last).  Waves of 32 columns have the next wave's from LDS.
+        float *x = reinterpret_cast<float *>(smem) + lane;        // [2][wave][MTH][64]: the ring is done with
+        auto over_row = [&](float (&s8)[MTH][NP], int turn) {
+            if constexpr (WN == 32) {
+                if (turn == 0) LDS_BARRIER();
+#pragma unroll
+                for (int k = 0; k < MTH; ++k) x[((turn * 8 + wave) * MTH + k) * 64] = s8[k][0];
+                LDS_BARRIER();
+            }
+#pragma unroll
+            for (int k = 0; k < MTH; ++k)
+                s8[k][0] = gemm_quad_sum(s8[k][0] + (WN == 32 ? x[((turn * 8 + (wave ^ 1)) * MTH + k) * 64] : s8[k][NP - 1]));
+        };
+        float sum[MTH][NP], sq[MTH][NP];
+#pragma unroll
+        for (int k = 0; k < MTH; ++k)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                float v[8];
+                unpack_bf16x8(kept[k][p], v);
+                sum[k][p] = gemm_piece_sum8(v);
+            }
+        over_row(sum, 0);
+#pragma unroll
+        for (int k = 0; k < MTH; ++k)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                float v[8];
+                unpack_bf16x8(kept[k][p], v);
+                sq[k][p] = gemm_piece_squares8(v, sum[k][0] * (1.f / 64.f));
+            }
+        over_row(sq, 1);
+        const int col = n0 + (wn & ~63);
+        if (WN == 32 && (wt & 1)) return;
+#pragma unroll
+        for (int k = 0; k < MTH; ++k)
+            if (quad == 0 && drow[k] >= 0 && col < N) fold.parts[(long)drow[k] * GEMM_PARTS_MOST + (col >> 6)] = make_float2(sum[k][0] * (1.f / 64.f), sq[k][0]);
     }
 }

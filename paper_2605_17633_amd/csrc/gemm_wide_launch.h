@@ -20,11 +20,14 @@ struct GemmWideArgs {
     X(6, 192, 128, 1) X(7, 256, 128, 1) X(8, 192, 192, 1) X(9, 192, 256, 1) X(10, 256, 192, 1) X(11, 256, 256, 1)
 constexpr int GEMM_WIDE_COUNT = 12;
 
-template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF>
+// Tiles whose waves hold pieces of 64 columns or halves of them (what writes GemmParts), and tiles with a stage for A of its own (what reads them).
+constexpr unsigned GEMM_WIDE_WRITES_PARTS = 0xadb, GEMM_WIDE_READS_PARTS = 0xff0;
+
+template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS>
 int gemm_wide_launch_tile(const GemmWideArgs &a)
 {
     constexpr size_t lds = GemmWide<BM, BN, WGK>::lds_bytes;
-    auto kern = gemm_wide_kernel<BM, BN, WGK, EPI, WPACK, LNF>;
+    auto kern = gemm_wide_kernel<BM, BN, WGK, EPI, WPACK, LNF, PARTS>;
     // more than 64 KiB of LDS per workgroup needs the per-kernel opt-in (idempotent, host-side only)
     if (lds > 64 * 1024 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -36,11 +39,11 @@ int gemm_wide_launch_tile(const GemmWideArgs &a)
     return SSAM_OK;
 }
 
-template <int EPI, bool WPACK, bool LNF>
+template <int EPI, bool WPACK, bool LNF, bool PARTS = false>
 int gemm_wide_launch(int tile, const GemmWideArgs &a)
 {
     switch (tile) {
-#define X(id, bm, bn, wgk) case id: return gemm_wide_launch_tile<bm, bn, wgk, EPI, WPACK, LNF>(a);
+#define X(id, bm, bn, wgk) case id: if constexpr (!PARTS || ((GEMM_WIDE_READS_PARTS >> id) & 1)) return gemm_wide_launch_tile<bm, bn, wgk, EPI, WPACK, LNF, PARTS>(a); else return SSAM_EINVAL;
     GEMM_WIDE_TILES(X)
 #undef X
     default: return SSAM_EINVAL;

@@ -158,7 +158,7 @@ template <int MAXC>
 __global__ void __launch_bounds__(256)
 ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long rows, int chunks, float eps,
                 const int32_t *__restrict__ idx, int idx_batch_stride, int Nin, int Nout, int32_t *__restrict__ src,
-                PadFill fill, int ln_blocks)
+                PadFill fill, int ln_blocks, float2 *__restrict__ parts)
 {
     int lane = threadIdx.x & 63;
     long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -201,6 +201,21 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
     }
     float inv = rsqrtf(wave_sum(q) / (float)D + eps);
     if (lane == 0) stats[row] = make_float2(inv, -inv * mean);
+    if (parts) {                               // pieces of 64 columns, eight lanes each (GemmParts); sums of columns 32 apart first
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            float ps = gemm_piece_sum8(v[i]);
+            ps += __shfl_xor(ps, 4, 64);
+            ps += __shfl_xor(ps, 1, 64);
+            ps += __shfl_xor(ps, 2, 64);
+            const float pm = ps * (1.f / 64.f);
+            float pq = gemm_piece_squares8(v[i], pm);
+            pq += __shfl_xor(pq, 4, 64);
+            pq += __shfl_xor(pq, 1, 64);
+            pq += __shfl_xor(pq, 2, 64);
+            if ((lane & 7) == 0 && lane + 64 * i < chunks) parts[row * 16 + ((lane + 64 * i) >> 3)] = make_float2(pm, pq);
+        }
+    }
 }
 
 // Weight side of the fold: one wave per output channel n.
@@ -859,9 +874,9 @@ int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int 
     return SSAM_OK;
 }
 
-// statistics of rows idx[b][p] of image b (idx == NULL: of every row in order), see ln_stats_kernel
+// statistics of rows idx[b][p] of image b (idx == NULL: of every row in order), see ln_stats_kernel; parts (every row in order, D % 64 == 0): see GemmParts
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
-                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st)
+                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, float2 *parts)
 {
     if (!x || !stats || rows <= 0 || D <= 0 || D % 8 != 0) return SSAM_EINVAL;
     if (!ssam_aligned16(x) || ((uintptr_t)stats & 7)) return SSAM_EINVAL;
@@ -871,18 +886,18 @@ int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps,
     const int ln_blocks = ssam_div_up(rows, 4);
     dim3 grid((unsigned)(ln_blocks + ssam_div_up(fill.total_rows, 4))), block(256);
     if (chunks <= 128)
-        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
+        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
     else if (chunks <= 192)
-        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
+        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
     else
-        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks);
+        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
 
 extern "C" int ssam_ln_stats(const void *x, float *stats, long rows, int D, float eps, void *stream)
 {
-    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, PadFill{}, (hipStream_t)stream);
+    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, PadFill{}, (hipStream_t)stream, nullptr);
 }
 
 extern "C" int ssam_fold_ln_weight(const void *W, int ldw, const float *bias, const float *gamma, const float *beta,

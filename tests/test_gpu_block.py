@@ -358,6 +358,20 @@ def test_encoder_forward_small_stack(label, opts):
         check_stack(f"small stack, image {img}", shape, g, x, wts, 0.4, 0.4, [(label, opts)], img=img)
 
 
+@pytest.mark.parametrize("B_,g,density", [(1, 64, 0.4), (2, 48, 0.3)])
+def test_row_statistics_in_pieces(B_, g, density):
+    """Folded stacks whose projections leave the row statistics that fc1 and the next block's qkv read: the last block's windows meet pieces of
+    rows that fc2 wrote and of rows that only proj wrote.  (1, 64): tiles of 32 and 64 columns a wave; (2, 48): ragged tiles."""
+    import ctypes as C
+    rows = B_ * g * g
+    assert B.lib().ssam_parts_form(C.c_int(rows), C.c_int(B_ * B.ssam_keep_count(g * g, density)), C.c_int(768), C.c_int(3072)) == 3
+    shape = inputs.ModelShape("vit_b_3", 768, 3, 12, 3072, (1,), 14)
+    wts = inputs.encoder_weights(60, shape, g)
+    x = inputs.token_field(np.random.default_rng(61), B_, g, shape.D)
+    check_stack("row statistics in pieces", shape, g, x, wts, 0.4, density,
+                [("folded", dict(pack=True, fold_ln1=True, fold_kv_bias=True, fold_ln2=True))], img=B_ - 1)
+
+
 # ------------------------------------------------------------------ content-aware order (Sec. 4.1)
 @pytest.mark.parametrize("B_,g,ws", [(2, 28, 14), (3, 64, 14), (2, 64, 0), (1, 16, 0), (2, 9, 4), (1, 128, 0)])
 def test_content_tables(B_, g, ws):
