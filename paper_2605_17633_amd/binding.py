@@ -70,8 +70,14 @@ def _check(name, rc):
         raise SsamError(name, rc)
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object around the same handle, 3.0 of the
+# 8.5 us that a call took on the host (0.35 this way): four dependent calls on one image's scores were bound by it, 33 us for 22 of kernels.
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream():
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+else:
+    def _stream():
+        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _dev(t, dtype, name):

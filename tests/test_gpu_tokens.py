@@ -83,3 +83,12 @@ def test_scores_in_one_launch(gh, gw, D):
     gy = at(1, -1) - at(-1, -1) + 2 * (at(1, 0) - at(-1, 0)) + at(1, 1) - at(-1, 1)
     bound = 12 * 2.0 ** -24 * D * float(x.float().abs().max())           # twelve sums of D terms weigh into a score
     assert float((got[0].double() - torch.sqrt(gx * gx + gy * gy).reshape(-1)).abs().max()) <= bound
+
+
+def test_calls_go_to_the_current_stream():
+    """The binding asks for the raw handle of the current device's current stream: the one that torch.cuda.current_stream() wraps."""
+    side = torch.cuda.Stream()
+    assert (B._stream().value or 0) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream().value == side.cuda_stream
+    assert (B._stream().value or 0) == torch.cuda.current_stream().cuda_stream
