@@ -17,7 +17,7 @@ int ssam_ln_gather_impl(const void *x, const int32_t *idx, int idx_batch_stride,
                         int B, int Nin, int Nout, int D, const PadFill &fill, void *stream);
 int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int Nout, int N, int32_t *inv, hipStream_t st);
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
-                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts);
+                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill);
 
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
@@ -250,7 +250,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     }
     // The padding slots hold the qkv of a zero row: the bias, or, with the key and value biases taken out of the contraction,
     // zeros in the columns attention reads (k, v), which then need writing only when something else has used the memory
-    // since.  The LayerNorm's launch writes them.
+    // since.  The LayerNorm's launch writes them, or the contraction's where it needs none.
     PadFill fill = {};
     if (padded && !(kv_shift && pad_rows_zero && *pad_rows_zero))
         fill = { (bf16 *)qkv, 3L * D, kv_shift ? nullptr : w->bqkv, 3 * D, carve_pad_tables(tables, B, g).pad_slot, g.Nout - g.N, g.Nout, B * (g.Nout - g.N) };
@@ -261,13 +261,14 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
         // the tokens where they lie and stores every row to its scan-order slot
         float *stats = (float *)u;
         const bool use_parts = parts_fit && ssam_parts_fit_qkv(crows, D);          // (also from this launch: a stack's blocks are then the same bits as single ones)
-        if (!use_parts || !have_parts || fill.total_rows != 0) {
+        const bool launch = !use_parts || !have_parts;
+        if (launch) {
             rc = ssam_ln_stats_impl(x, stats, crows, D, cfg->eps, nullptr, 0, 0, 0, nullptr, fill, st, have_parts ? nullptr : parts.at);
             if (rc != SSAM_OK) return rc;
         }
         if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
         GemmRowMap to_slot = { slot_of_table(tables, B, g), g.N, per_image ? g.N : 0, g.Nout };
-        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, use_parts ? parts : GemmParts{});
+        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, use_parts ? parts : GemmParts{}, launch ? PadFill{} : fill);
         if (rc != SSAM_OK) return rc;
     }
 

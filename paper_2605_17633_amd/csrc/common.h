@@ -26,7 +26,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
     } while (0)
 
 // Rows of a windowed block's qkv tensor that hold no token (padding slots): rows_per_batch * b + pad_slot[b][i] of C, i < npad,
-// become bf16(bias) (NULL: zeros).  They are written by extra workgroups of the block's LayerNorm launch.
+// become bf16(bias) (NULL: zeros).  They are written by extra workgroups of the block's LayerNorm launch, or of its qkv contraction.
 struct PadFill {
     bf16 *C;
     long ldc;
@@ -84,6 +84,25 @@ __device__ __forceinline__ float wave_sum(float v)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// one padding row (see PadFill): a wave, 16 bytes per lane.  A launch of its own took 5 us of every unfolded block with padding
+// (ViT-B, 50 x 50 tokens, batch 2) and after every global block of a folded stack; behind the LayerNorm, or behind the qkv contraction's tiles, it is hidden.
+__device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
+{
+    if (r >= f.total_rows) return;
+    const int b = r / f.npad, i = r - b * f.npad, lane = threadIdx.x & 63;
+    bf16 *dst = f.C + ((long)b * f.rows_per_batch + f.pad_slot[(long)b * f.npad + i]) * f.ldc;
+    for (int c = lane * 8; c < f.n_cols; c += 64 * 8) {
+        if (f.bias == nullptr) {
+            *reinterpret_cast<uint4 *>(dst + c) = make_uint4(0, 0, 0, 0);
+            continue;
+        }
+        const float4 *b4 = reinterpret_cast<const float4 *>(f.bias + c);
+        float4 x0 = b4[0], x1 = b4[1];
+        float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
+        *reinterpret_cast<uint4 *>(dst + c) = pack_bf16x8(v);
+    }
 }
 
 // Of 8 columns of a piece of a row's statistics (GemmParts): their sum, their squared deviations from the piece's mean.  In this order wherever pieces are written.

@@ -494,12 +494,12 @@ double folded_ln_us(int tiles, int K)
 // The contraction with the LayerNorm of its A rows folded in (see GemmFold): 128x256 tiles, packed weights,
 // mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
-                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts)
+                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill)
 {
     constexpr size_t lds = gemm_lds_bytes<128, 256, 1, 4, true>();
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
-    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr, parts.at, parts.slots, parts.eps };
+    const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr, parts.at, parts.slots, parts.eps, 1, 0, fill };
     int ring;
     const int wide = choose_ln(M, N, K, ld, ring, parts.at != nullptr);
     if (parts.at)
@@ -528,7 +528,7 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     if (ldx < K || ldc < N || ldx % 8 || ldc % 8 || rows_per_batch <= 0 || map_batch_stride < 0 || dst_rows_per_batch <= 0) return SSAM_EINVAL;
     if (M % 128 != 0 || N % 256 != 0 || K % GEMM_BK != 0) return SSAM_EUNSUPPORTED;
     const GemmRowMap rm = { row_map, rows_per_batch, map_batch_stride, dst_rows_per_batch };
-    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{});
+    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{}, PadFill{});
 }
 
 // Which kernel a contraction takes where the wide kernel does not (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,

@@ -82,6 +82,7 @@ struct GemmFold {
     int slots = 0;            //   row m of the product is row m / src_rows * src_stride + src[m] of A
     float eps = 0.f;
     int src_rows = 1, src_stride = 0;
+    PadFill fill = {};        // with parts: padding rows that workgroups behind the tiles write
 };
 
 // Statistics of the rows of the residual stream in pieces of 64 columns, [rows][GEMM_PARTS_MOST] { mean, sum of squared deviations from it }: the

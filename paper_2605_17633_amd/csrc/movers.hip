@@ -51,25 +51,6 @@ unpermute_kernel(const uint4 *__restrict__ y, const int32_t *__restrict__ idx, u
     }
 }
 
-// one padding row (see PadFill): a wave, 16 bytes per lane.  A launch of its own took 5 us of every unfolded block with padding
-// (ViT-B, 50 x 50 tokens, batch 2) and after every global block of a folded stack; behind the LayerNorm it is hidden.
-__device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
-{
-    if (r >= f.total_rows) return;
-    const int b = r / f.npad, i = r - b * f.npad, lane = threadIdx.x & 63;
-    bf16 *dst = f.C + ((long)b * f.rows_per_batch + f.pad_slot[(long)b * f.npad + i]) * f.ldc;
-    for (int c = lane * 8; c < f.n_cols; c += 64 * 8) {
-        if (f.bias == nullptr) {
-            *reinterpret_cast<uint4 *>(dst + c) = make_uint4(0, 0, 0, 0);
-            continue;
-        }
-        const float4 *b4 = reinterpret_cast<const float4 *>(f.bias + c);
-        float4 x0 = b4[0], x1 = b4[1];
-        float v[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };
-        *reinterpret_cast<uint4 *>(dst + c) = pack_bf16x8(v);
-    }
-}
-
 // ---------------------------------------------------------------- LN + gather
 // One wave per output row; the row lives in registers (MAXC 16-byte chunks per
 // lane), two-pass statistics in fp32.
