@@ -348,14 +348,19 @@ score_kernel(const uint4 *__restrict__ x, float *__restrict__ scores, int gh, in
 
 // Up to 28 MB of tokens: there the second launch costs more than the rows read twice (us, one launch | two, from a loop of calls: 4096 x 768
 // 6.6 | 9.3, the rate of the calls; 8192 x 1280, 21 MB, 7.4 | 9.2; 16384 x 768, 25 MB, 8.6 | 9.3; 16384 x 1024, 34 MB, 9.8 | 9.4; 65536 x 1280 39.8 | 32.4).
-bool score_in_one_launch(long tokens, int D) { return tokens * D * 2 <= 28000000 && D <= 2048; }
+// Its images are the grid's z and its rows of tiles the grid's y, which the device states to reach 65536 at most: more of them are left to two launches, whose
+// grids have one dimension.
+bool score_in_one_launch(int B, int gh, int gw, int D)
+{
+    return (long)B * gh * gw * D * 2 <= 28000000 && D <= 2048 && B <= 65535 && ssam_div_up(gh, SCORE_TILE) <= 65535;
+}
 
 // csum: where the channel sums of the form with two launches go
 int launch_score(const void *x, float *scores, int B, int gh, int gw, int D, float *csum, hipStream_t st)
 {
     const long tokens = (long)B * gh * gw;
     const int chunks = D / 8;
-    if (score_in_one_launch(tokens, D)) {
+    if (score_in_one_launch(B, gh, gw, D)) {
         const dim3 grid(ssam_div_up(gw, SCORE_TILE), ssam_div_up(gh, SCORE_TILE), B);
         auto kern = chunks <= 128 ? score_kernel<2> : chunks <= 192 ? score_kernel<3> : score_kernel<4>;
         hipLaunchKernelGGL(kern, grid, dim3(SCORE_THREADS), 0, st, (const uint4 *)x, scores, gh, gw, chunks);
@@ -765,6 +770,9 @@ int scratch_on_current_device(float **out)
     return SSAM_OK;
 }
 }  // namespace
+
+// Launches that the scores of such an input take.  Host only, for tests; not part of the interface.
+extern "C" int ssam_score_form(int B, int gh, int gw, int D) { return score_in_one_launch(B, gh, gw, D) ? 1 : 2; }
 
 extern "C" int ssam_score_tokens_static(const void *x, float *scores, int B, int gh, int gw, int D, void *stream)
 {

@@ -85,6 +85,21 @@ def test_scores_in_one_launch(gh, gw, D):
     assert float((got[0].double() - torch.sqrt(gx * gx + gy * gy).reshape(-1)).abs().max()) <= bound
 
 
+@pytest.mark.parametrize("B_,gh,gw,D", [(70000, 1, 2, 8), (65536, 1, 1, 16), (65535, 2, 2, 8), (1, 262145, 1, 8), (1, 262140, 1, 8), (2, 300000, 1, 16), (3, 9, 6, 768)])
+def test_scores_of_many_images_and_tall_grids(B_, gh, gw, D):
+    """More images, or more rows of tiles, than a grid's second and third dimension hold, the most that they hold, and images that differ."""
+    announce("scores", B_, gh, gw, D)
+    gen = torch.Generator(device=DEV).manual_seed(B_ + gh)
+    x = torch.randn(B_, gh, gw, D, generator=gen, device=DEV).bfloat16()
+    got = B.ssam_score_tokens(x)
+    c = torch.nn.functional.pad(x.double().sum(-1), (1, 1, 1, 1))
+    at = lambda r, k: c[:, 1 + r:1 + r + gh, 1 + k:1 + k + gw]
+    gx = at(-1, 1) - at(-1, -1) + 2 * (at(0, 1) - at(0, -1)) + at(1, 1) - at(1, -1)
+    gy = at(1, -1) - at(-1, -1) + 2 * (at(1, 0) - at(-1, 0)) + at(1, 1) - at(-1, 1)
+    bound = 12 * 2.0 ** -24 * D * float(x.float().abs().max())           # as above
+    assert float((got.double() - torch.sqrt(gx * gx + gy * gy).reshape(B_, -1)).abs().max()) <= bound
+
+
 def test_calls_go_to_the_current_stream():
     """The binding asks for the raw handle of the current device's current stream: the one that torch.cuda.current_stream() wraps."""
     side = torch.cuda.Stream()

@@ -93,3 +93,10 @@ def test_error_codes():
     cfg = B.make_cfg(1, 28, 768, 12, 3072, 14, 32, 313, 0.4)
     assert B.ssam_encoder_block_workspace_bytes(cfg) > 0
     assert L.ssam_encoder_block(None, None, C.byref(cfg), None, None, None, None, C.c_size_t(0), None) == B.EINVAL
+
+
+@pytest.mark.parametrize("B_,gh,gw,D,launches", [(65535, 1, 2, 8, 1), (65536, 1, 2, 8, 2), (100000, 1, 1, 8, 2), (1, 262140, 1, 8, 1), (1, 262141, 1, 8, 2),
+                                                  (1, 64, 64, 768, 1), (1, 8, 8, 2056, 2), (16, 64, 64, 768, 2)])
+def test_scores_stay_within_the_grid(B_, gh, gw, D, launches):
+    """One launch has the images in the grid's z and tiles of four rows in its y: 65536 at most."""
+    assert B.lib().ssam_score_form(*(C.c_int(v) for v in (B_, gh, gw, D))) == launches
