@@ -105,6 +105,8 @@ __device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
     }
 }
 
+constexpr int GEMM_PARTS_MOST = 16;           // pieces of a row's statistics (GemmParts): 128 bytes, as long as a row of a slab of 64 bf16
+
 // Of 8 columns of a piece of a row's statistics (GemmParts): their sum, their squared deviations from the piece's mean.  In this order wherever pieces are written.
 __device__ __forceinline__ float gemm_piece_sum8(const float *v)
 {

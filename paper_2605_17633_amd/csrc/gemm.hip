@@ -284,7 +284,7 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us, unsigned among = ~0u)
 {
     const int nk = K / GEMM_BK;
-    if (K % GEMM_BK != 0 || nk < 5 || (packed && M <= 32)) return -1;
+    if (K % GEMM_BK != 0 || nk < GEMM_WIDE_SLABS || (packed && M <= 32)) return -1;
     if ((long)256 * ld.a * 2 >= 1L << 31 || (rows_a + 1) * ld.a * 2 >= 1L << 32 || (long)256 * (packed ? K : ld.w) * 2 >= 1L << 31) return -1;
     const int torn = (ld.a % GEMM_BK != 0) + (!packed && ld.w % GEMM_BK != 0);
     int best = -1;

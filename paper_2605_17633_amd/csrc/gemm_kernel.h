@@ -95,7 +95,6 @@ struct GemmParts {
     int slots;                // D / 64
     float eps;
 };
-constexpr int GEMM_PARTS_MOST = 16;           // pieces of a row: 128 bytes, as long as a row of a slab of 64 bf16
 
 struct GemmSplit {
     float *partial;           // [tile_count*SUB_M*SUB_N][parts][BM][BN] fp32, NULL unless GEMM_EPI_PARTIAL

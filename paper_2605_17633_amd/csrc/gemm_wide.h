@@ -46,6 +46,8 @@ __device__ __forceinline__ void gemm_load_lds4(uint32_t lds, const int32_t *src)
 
 template <int N> __device__ __forceinline__ void gemm_wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
+constexpr int GEMM_WIDE_SLABS = 5;           // the fewest slabs of K that are taken
+
 // WGK = 2: the workgroup's eight waves are 2 x 2 over the tile times two halves of every slab of K; 1: 2 x 4 or 4 x 2 over the tile (128x128: 4 x 2, as
 // many fragments read as 2 x 4, and waves with whole pieces of 64 columns).
 template <int BM, int BN, int WGK>
@@ -62,6 +64,11 @@ struct GemmWide {
     static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0 && (WGK == 2 || (QA % 8 == 0 && QW % 8 == 0)), "whole MFMA tiles and requests");
     static_assert(GEMM_BK * 2 == GEMM_PARTS_MOST * 8, "a row's pieces take the place of its part of a slab");
     static_assert(WGK == 1 || (size_t)BM * BN * 4 <= ring, "the halves are added in the ring's LDS");
+    // Row statistics in pieces (GemmParts).  Waves that hold whole pieces of 64 columns, or halves of which the next wave has the other, can write them.
+    static constexpr bool WRITES_PARTS = (NT * 16 == 32 && WGN % 2 == 0) || NT * 16 == 64;
+    // Where A has stages of its own its rows' pieces can come as one more slab.  They are requested in iteration n - SA of n: that has to be one (SA <= the fewest
+    // slabs), every slab of W has to be out by then (SA <= SW + 1), and the wait for the last slab has to come behind it (SA >= 3).
+    static constexpr bool READS_PARTS = WGK == 1 && SA >= 3 && SA <= SW + 1 && SA <= GEMM_WIDE_SLABS;
 };
 
 constexpr int GEMM_WIDE_FILL = 16;
@@ -84,7 +91,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
                  bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
     using G = GemmWide<BM, BN, WGK>;
-    static_assert(!PARTS || (LNF && WGK == 1), "the forms that read pieces");
+    static_assert(!PARTS || (LNF && G::READS_PARTS), "the forms that read pieces");
     constexpr int BK = GEMM_BK, WGN = G::WGN, MT = G::MT, NT = G::NT, NP = NT / 2, WM = MT * 16, WN = NT * 16;
     constexpr int SA = G::SA, SW = G::SW, L = G::L;
     constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER, ADD = EPI == SSAM_EPI_BIAS_SCATTER_ADD;
@@ -452,7 +459,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             if constexpr (EPI == SSAM_EPI_BIAS_GELU) v[e] = gelu_erf(v[e]);
         }
     };
-    constexpr bool PIECES = ADD && WPACK && (WN == 32 || WN == 64);
+    constexpr bool PIECES = ADD && WPACK && G::WRITES_PARTS;
     uint4 kept[PIECES ? MTH : 1][PIECES ? NP : 1];
 #pragma unroll
     for (int k = 0; k < MTH; ++k) {

@@ -20,8 +20,13 @@ struct GemmWideArgs {
     X(6, 192, 128, 1) X(7, 256, 128, 1) X(8, 192, 192, 1) X(9, 192, 256, 1) X(10, 256, 192, 1) X(11, 256, 256, 1)
 constexpr int GEMM_WIDE_COUNT = 12;
 
-// Tiles whose waves hold pieces of 64 columns or halves of them (what writes GemmParts), and tiles with a stage for A of its own (what reads them).
-constexpr unsigned GEMM_WIDE_WRITES_PARTS = 0xadb, GEMM_WIDE_READS_PARTS = 0xff0;
+// Tiles that can write GemmParts, and tiles that can read them, a bit each.
+#define X(id, bm, bn, wgk) | (unsigned)GemmWide<bm, bn, wgk>::WRITES_PARTS << id
+constexpr unsigned GEMM_WIDE_WRITES_PARTS = 0 GEMM_WIDE_TILES(X);
+#undef X
+#define X(id, bm, bn, wgk) | (unsigned)GemmWide<bm, bn, wgk>::READS_PARTS << id
+constexpr unsigned GEMM_WIDE_READS_PARTS = 0 GEMM_WIDE_TILES(X);
+#undef X
 
 template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS>
 int gemm_wide_launch_tile(const GemmWideArgs &a)

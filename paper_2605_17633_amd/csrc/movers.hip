@@ -194,7 +194,7 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
             pq += __shfl_xor(pq, 4, 64);
             pq += __shfl_xor(pq, 1, 64);
             pq += __shfl_xor(pq, 2, 64);
-            if ((lane & 7) == 0 && lane + 64 * i < chunks) parts[row * 16 + ((lane + 64 * i) >> 3)] = make_float2(pm, pq);
+            if ((lane & 7) == 0 && lane + 64 * i < chunks) parts[row * GEMM_PARTS_MOST + ((lane + 64 * i) >> 3)] = make_float2(pm, pq);
         }
     }
 }
