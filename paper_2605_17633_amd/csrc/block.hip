@@ -8,8 +8,7 @@
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
                      void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts = GemmParts{});
-bool ssam_parts_fit(int rows, int kept, int D, int Dm);
-bool ssam_parts_fit_qkv(int rows, int D);
+int ssam_parts_form_of(int rows, int kept, int D, int Dm);
 
 int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int Nout, int N,
                        int32_t *real_slot, int32_t *real_spatial, int32_t *slot_row, int32_t *pad_slot, hipStream_t st);
@@ -23,7 +22,7 @@ int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, c
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
                                void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride);
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
-                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, float2 *parts);
+                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, int slots);
 
 namespace {
 
@@ -110,11 +109,12 @@ extern "C" size_t ssam_routed_mlp_workspace_bytes(int B, int K, int D, int Dm)
 }
 
 // colsum1 != NULL: gather and LN2 folded into fc1 (w1 the packed folded weight, b1 the folded bias; ln_g, ln_b unused)
-// parts: row statistics of x in pieces, read by fc1 instead of a statistics launch and kept up to date by fc2
+// parts: row statistics of x in pieces, read by fc1 instead of a statistics launch; left: what fc2 does with them (see ssam_linear_impl)
 static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, const float *ln_b, float eps,
                            const void *w1, const float *b1, const void *w2, const float *b2, bool packed,
                            int B, int N, int D, int Dm, int K,
-                           void *workspace, size_t workspace_bytes, void *stream, const float *colsum1 = nullptr, const GemmParts &parts = GemmParts{})
+                           void *workspace, size_t workspace_bytes, void *stream, const float *colsum1 = nullptr, const GemmParts &parts = GemmParts{},
+                           const GemmParts &left = GemmParts{})
 {
     const bool fold = colsum1 != nullptr;
     if (!x || !keep_idx || (!fold && (!ln_g || !ln_b)) || !w1 || !b1 || !w2 || !b2 || !workspace) return SSAM_EINVAL;
@@ -136,7 +136,7 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
         // the region of the normalised rows holds only their statistics and the rows of x they are (8 + 4 bytes a row)
         float *stats = (float *)a2;
         int32_t *src = (int32_t *)(stats + 2 * (size_t)B * K);
-        rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st, nullptr);
+        rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st, 0);
         if (rc != SSAM_OK) return rc;
         rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, 1, 0);
     } else {
@@ -148,7 +148,7 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
     if (rc != SSAM_OK) return rc;
     GemmRowMap scatter = { keep_idx, K, K, N };
     return ssam_linear_impl(hid, w2, b2, x, B * K, D, Dm, GemmLd{ Dm, Dm, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, scatter, 0,
-                            split, GEMM_SPLIT_WS_BYTES, st, parts);
+                            split, GEMM_SPLIT_WS_BYTES, st, left);
 }
 
 extern "C" int ssam_routed_mlp(void *x, const int32_t *keep_idx, const float *ln_g, const float *ln_b, float eps,
@@ -199,9 +199,10 @@ extern "C" size_t ssam_encoder_block_workspace_bytes(const ssam_block_cfg *cfg)
 }
 
 // tables: this block's block_tables_bytes region; tables_ready: a stack has built it already
-// parts_ready: the row statistics of x in pieces (GemmParts) are up to date, on entry from the block before.  They lie at the end of the workspace's
-// bytes in front of the tables, the K-split scratch of the MLP, which is not used where they are (ssam_parts_fit); a stack's blocks all
-// have the same end.  Every row gets its pieces from a statistics launch once; from then on whatever writes a row writes them too.
+// parts_ready (a block of a stack): the row statistics of x in pieces (GemmParts) are up to date, on entry from the block before.  They lie at the end of the
+// workspace's bytes in front of the tables, the K-split scratch of the MLP; a stack's blocks all have the same end.  proj writes every row, and with it its
+// pieces, which fc1 reads; where the next block's qkv reads them too (ssam_parts_form_of: 3) fc2 keeps them up to date and nothing uses that scratch, else they
+// are done with when fc2, which may use it, begins.
 static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_block_cfg *cfg,
                               const int32_t *gather_table, const int32_t *sigma, const int32_t *keep_idx,
                               void *workspace, size_t workspace_bytes, void **qkv_events, unsigned char *tables,
@@ -240,10 +241,11 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     if (kv_shift && (!fold || !w->bproj_folded)) return SSAM_EINVAL;
     const float *bproj = kv_shift ? w->bproj_folded : w->bproj;
     const size_t parts_bytes = align256((size_t)crows * GEMM_PARTS_MOST * sizeof(float2));
-    const bool parts_fit = fold && w->fold_ln2 != 0 && parts_bytes <= GEMM_SPLIT_WS_BYTES - 256 && ssam_parts_fit(crows, B * cfg->K, D, cfg->Dm);
-    GemmParts parts = { parts_fit ? (float2 *)((unsigned char *)workspace + (workspace_bytes & ~(size_t)255) - parts_bytes) : nullptr, D / 64, cfg->eps };
-    const bool have_parts = parts_fit && parts_ready && *parts_ready;
-    if (parts_ready) *parts_ready = parts_fit;
+    const int form = fold && w->fold_ln2 != 0 && parts_bytes <= GEMM_SPLIT_WS_BYTES - 256 ? ssam_parts_form_of(crows, B * cfg->K, D, cfg->Dm) : 0;
+    const GemmParts parts = form ? GemmParts{ (float2 *)((unsigned char *)workspace + (workspace_bytes & ~(size_t)255) - parts_bytes), D / 64, cfg->eps } : GemmParts{};
+    const GemmParts whole = form == 3 ? parts : GemmParts{}, tile_only = { nullptr, whole.slots, cfg->eps };       // (in a single block: a stack's blocks are then the same bits)
+    const bool have_parts = whole.at && parts_ready && *parts_ready;
+    if (parts_ready) *parts_ready = whole.at != nullptr;
     if (!tables_ready) {
         rc = build_block_tables(cfg, g, gather_table, tables, fold, st);
         if (rc != SSAM_OK) return rc;
@@ -260,15 +262,13 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
         // start of u, which nothing else uses before attention writes its output there); the contraction reads
         // the tokens where they lie and stores every row to its scan-order slot
         float *stats = (float *)u;
-        const bool use_parts = parts_fit && ssam_parts_fit_qkv(crows, D);          // (also from this launch: a stack's blocks are then the same bits as single ones)
-        const bool launch = !use_parts || !have_parts;
-        if (launch) {
-            rc = ssam_ln_stats_impl(x, stats, crows, D, cfg->eps, nullptr, 0, 0, 0, nullptr, fill, st, have_parts ? nullptr : parts.at);
+        if (!have_parts) {
+            rc = ssam_ln_stats_impl(x, stats, crows, D, cfg->eps, nullptr, 0, 0, 0, nullptr, fill, st, whole.slots);
             if (rc != SSAM_OK) return rc;
         }
         if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
         GemmRowMap to_slot = { slot_of_table(tables, B, g), g.N, per_image ? g.N : 0, g.Nout };
-        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, use_parts ? parts : GemmParts{}, launch ? PadFill{} : fill);
+        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, have_parts ? whole : tile_only, have_parts ? fill : PadFill{});
         if (rc != SSAM_OK) return rc;
     }
 
@@ -316,7 +316,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     if (w->fold_ln2 != 0) {
         if (!packed || !w->fc1_colsum || !w->b1_folded) return SSAM_EINVAL;
         return routed_mlp_impl(x, keep_idx, nullptr, nullptr, cfg->eps, w->w1, w->b1_folded, w->w2, w->b2, true,
-                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts);
+                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts, parts_ready ? whole : tile_only);
     }
     return routed_mlp_impl(x, keep_idx, w->ln2_g, w->ln2_b, cfg->eps, w->w1, w->b1, w->w2, w->b2, packed,
                            B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream);

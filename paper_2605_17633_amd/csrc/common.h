@@ -123,6 +123,13 @@ __device__ __forceinline__ float gemm_piece_squares8(const float *v, float mean)
     return q;
 }
 
+// What a piece adds to the squared deviations from the row's mean.
+__device__ __forceinline__ float gemm_piece_term(float2 piece, float mean)
+{
+    const float d = piece.x - mean;
+    return fmaf(64.f * d, d, piece.y);
+}
+
 // erf GELU, 0.5 t (1 + erf(t / sqrt 2)) = max(t, 0) - 0.5 |t| erfc(|t| / sqrt 2).  erfc by the rational approximation 7.1.26 of
 // Abramowitz & Stegun, erfc(x) = (a1 u + ... + a5 u^5) exp(-x^2), u = 1 / (1 + p x) for x >= 0; absolute error below
 // 1.5e-7, far under the bf16 rounding of the stored activation.  One reciprocal and one exp2 per element, eleven full-rate

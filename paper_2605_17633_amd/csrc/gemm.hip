@@ -260,6 +260,7 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
     { 64, 128, 0, 4.27, 0.228, 0.614, 0.075, 0.354 },   { 128, 128, 1.14, 2.89, 0.382, 1.2, 0, 0.153 },   { 128, 192, 0.896, 4.09, 0.498, 1.31, 0, 0.205 },
     { 192, 128, 0.478, 3.86, 0.505, 1.71, 0, 0.183 },   { 256, 128, 0.243, 4.64, 0.623, 2.1, 0, 0.2 },    { 192, 192, 0.697, 5.38, 0.668, 1.56, 0, 0.22 },
     { 192, 256, 1.07, 4.83, 0.85, 3.16, 0, 0.197 },     { 256, 192, 0.964, 5, 0.838, 3.1, 0, 0.194 },     { 256, 256, 1.7, 4.96, 1.09, 4.28, 0, 0.207 } };
+enum PartsUse { PARTS_LEFT, PARTS_READ, PARTS_READ_GATHERED, PARTS_NONE };
 
 // Index of the wide kernel's tile that is faster than the others' launch_us, or -1.  rows_a: rows of A where its rows are
 // gathered.  The tiles below 128x128 add K in two chains instead of one, and are taken where that is faster than the others with either
@@ -280,9 +281,10 @@ constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
 // without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
-// among: the tiles to choose from, by their indices.
-int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double launch_us, double both_us, unsigned among = ~0u)
+// parts: what the kernel does with row statistics in pieces, of the tiles that can.  launch_us: what is taken, on return.
+int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double &launch_us, double both_us, PartsUse parts = PARTS_NONE)
 {
+    const unsigned among = parts == PARTS_NONE ? ~0u : parts == PARTS_LEFT ? GEMM_WIDE_WRITES_PARTS : GEMM_WIDE_READS_PARTS;
     const int nk = K / GEMM_BK;
     if (K % GEMM_BK != 0 || nk < GEMM_WIDE_SLABS || (packed && M <= 32)) return -1;
     if ((long)256 * ld.a * 2 >= 1L << 31 || (rows_a + 1) * ld.a * 2 >= 1L << 32 || (long)256 * (packed ? K : ld.w) * 2 >= 1L << 31) return -1;
@@ -299,8 +301,10 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
                           + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
         if (us < best_us) { best_us = us; best = i; }
     }
-    if (best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128) launch_us = both_us < launch_us ? both_us : launch_us;
-    return best_us < 0.99 * launch_us ? best : -1;
+    const double others_us = best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128 && both_us < launch_us ? both_us : launch_us;
+    if (best_us >= 0.99 * others_us) return -1;
+    launch_us = best_us;
+    return best;
 }
 
 // What the others take with the other layout of the weights (1e30: there is none).
@@ -354,66 +358,84 @@ int launch_any(int tile, int ring, const bf16 *A, const bf16 *W, const float *bi
     else return launch_tile<EPI>(tile, A, W, bias, C, M, N, K, ld, rm, ws, st);
 }
 
-// The wide kernel's tile of a contraction (-1: another kernel); the kernel that takes it otherwise on return.
-int choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs &ws, bool packed, int &tile, int &ring, unsigned among = ~0u)
+// The kernel of a contraction: the wide kernel's tile, or (wide = -1) the ring, or (ring = -1) the large tile; what it takes, in microseconds.
+struct Choice { int wide, tile, ring; double us; };
+
+Choice choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs &ws, bool packed, PartsUse parts = PARTS_NONE)
 {
-    double us;
-    tile = pick_tile(M, N, K, epilogue, ws, packed, us);
-    ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, us);
-    return pick_wide(M, N, K, epilogue, ld, packed, 0, us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0), among);
+    Choice c;
+    c.tile = pick_tile(M, N, K, epilogue, ws, packed, c.us);
+    c.ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, c.us);
+    c.wide = pick_wide(M, N, K, epilogue, ld, packed, 0, c.us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0), parts);
+    return c;
 }
 
 // What reading a row's statistics in pieces saves (a launch of 4.6 us less what the reading takes): other kernels of a contraction that could
 // read them take that much longer.  fc1 of ViT-L at a density of 0.4 (1638 x 4096 x 1024) is 1 % faster on the large tiles by itself.
 constexpr double PARTS_US = 3.0;
 
-// The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics could come in pieces.
-int choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, int &tile, int &ring, bool parts)
+// The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics come in pieces.
+Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, bool parts)
 {
-    double us;
-    tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, us);
-    ring = pick_ring(M, N, K, true, true, us);
-    if (parts) us += PARTS_US;
-    return pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us, parts ? GEMM_WIDE_READS_PARTS : ~0u);
+    Choice c;
+    c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us);
+    c.ring = pick_ring(M, N, K, true, true, c.us);
+    if (parts) c.us += PARTS_US;
+    c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, c.us, c.us, parts ? PARTS_READ_GATHERED : PARTS_NONE);
+    return c;
 }
 
 double folded_ln_us(int tiles, int K);
 
 // And for qkv with a LayerNorm folded in.
-int choose_ln(int M, int N, int K, const GemmLd &ld, int &ring, bool parts)
+Choice choose_ln(int M, int N, int K, const GemmLd &ld, bool parts)
 {
-    double us = folded_ln_us((M / 128) * (N / 256), K);
-    ring = pick_ring(M, N, K, true, true, us);
-    if (parts) us += PARTS_US;
-    return pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, us, us, parts ? GEMM_WIDE_READS_PARTS : ~0u);
+    Choice c = { -1, 4, -1, folded_ln_us((M / 128) * (N / 256), K) };
+    c.ring = pick_ring(M, N, K, true, true, c.us);
+    if (parts) c.us += PARTS_US;
+    c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, c.us, c.us, parts ? PARTS_READ : PARTS_NONE);
+    return c;
+}
+
+// The contractions of a block with both LayerNorms folded in that can read or leave pieces: qkv, proj, fc1, fc2.
+struct BlockChoices { Choice c[4]; };
+
+BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
+{
+    alignas(16) static unsigned char some;
+    const SplitWs ws = { &some, GEMM_SPLIT_WS_BYTES };
+    const PartsUse left = parts ? PARTS_LEFT : PARTS_NONE;
+    return { { choose_ln(rows, 3 * D, D, GemmLd{ D, D, 3 * D }, parts),
+               choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, ws, true, left),
+               choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, parts),
+               choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, left) } };
 }
 
 }  // namespace
 
-// Row statistics in pieces (GemmParts) of the residual stream, [rows][D] of which `kept` go through the MLP: whether proj, fc1 and fc2 (packed
-// weights, LN2 folded into fc1) all take the wide kernel with tiles that write or read them.  None of them then uses its K-split scratch.
-bool ssam_parts_fit(int rows, int kept, int D, int Dm)
+// Row statistics in pieces (GemmParts) of the residual stream, [rows][D] of which `kept` go through the MLP, in blocks with packed weights and both
+// LayerNorms folded in.  0: none; 1: proj leaves them and fc1 reads them; 3: fc2 leaves them too, and the next block's qkv reads those.  What leaves or reads
+// them is the wide kernel, by some of its tiles.  A block by itself has a launch for qkv's statistics all the same, reads and leaves nothing there and takes the
+// stack's tiles.
+int ssam_parts_form_of(int rows, int kept, int D, int Dm)
 {
-    alignas(16) static unsigned char some;
-    const SplitWs ws = { &some, GEMM_SPLIT_WS_BYTES };
-    int tile, ring;
-    return D % 128 == 0 && D / 64 <= GEMM_PARTS_MOST &&
-           choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, ws, true, tile, ring, GEMM_WIDE_WRITES_PARTS) >= 0 &&
-           choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, tile, ring, true) >= 0 &&
-           choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, tile, ring, GEMM_WIDE_WRITES_PARTS) >= 0;
+    if (D % 128 != 0 || D / 64 > GEMM_PARTS_MOST) return 0;
+    const BlockChoices with = block_choices(rows, kept, D, Dm, true);
+    if (with.c[1].wide < 0 || with.c[2].wide < 0) return 0;
+    return with.c[0].wide >= 0 && with.c[3].wide >= 0 ? 3 : 1;
 }
 
-// And whether qkv with LN1 folded in reads them.
-bool ssam_parts_fit_qkv(int rows, int D)
+// The form, for tests, and the wide kernel's tiles of qkv, proj, fc1 and fc2 with it (-1: another kernel).  Host only; not part of the interface.
+extern "C" int ssam_parts_form(int rows, int kept, int D, int Dm) { return ssam_parts_form_of(rows, kept, D, Dm); }
+
+extern "C" int ssam_parts_tiles(int rows, int kept, int D, int Dm, int *tiles)
 {
-    int ring;
-    return choose_ln(rows, 3 * D, D, GemmLd{ D, D, 3 * D }, ring, true) >= 0;
+    const int form = ssam_parts_form_of(rows, kept, D, Dm);
+    for (int i = 0; i < 4; ++i) tiles[i] = block_choices(rows, kept, D, Dm, form == 3 || (form == 1 && (i == 1 || i == 2))).c[i].wide;
+    return form;
 }
 
-// Both, for tests (1: ssam_parts_fit, 2: ssam_parts_fit_qkv).  Host only; not part of the interface.
-extern "C" int ssam_parts_form(int rows, int kept, int D, int Dm) { return (ssam_parts_fit(rows, kept, D, Dm) ? 1 : 0) + (ssam_parts_fit_qkv(rows, D) ? 2 : 0); }
-
-// parts (optional): row statistics that a scatter-add leaves; the caller has asked ssam_parts_fit.
+// parts (optional): row statistics that a scatter-add leaves; the caller has asked ssam_parts_form_of.  With no place for them (at = NULL) only its tile is taken.
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
                      void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts)
@@ -423,7 +445,10 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
     bf16 *c = (bf16 *)C;
     int ring = -1;
     if (tile == 0) {
-        if (const int wide = choose(M, N, K, epilogue, ld, ws, packed, tile, ring, parts.at ? GEMM_WIDE_WRITES_PARTS : ~0u); wide >= 0) {
+        const Choice pick = choose(M, N, K, epilogue, ld, ws, packed, parts.slots ? PARTS_LEFT : PARTS_NONE);
+        tile = pick.tile;
+        ring = pick.ring;
+        if (const int wide = pick.wide; wide >= 0) {
             GemmFold out;
             out.parts = parts.at;
             out.slots = parts.slots;
@@ -437,7 +462,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
             }
         }
     }
-    if (parts.at) return SSAM_EUNSUPPORTED;
+    if (parts.slots) return SSAM_EUNSUPPORTED;
     if (packed) {
         switch (epilogue) {
         case SSAM_EPI_BIAS: return launch_any<SSAM_EPI_BIAS, true>(tile, ring, a, w, bias, c, M, N, K, ld, rm, ws, st);
@@ -458,7 +483,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 
 // fc1 of the routed MLP with gather and LN2 folded in (see GemmFold): rows src[m] of A, packed folded weights,
 // GELU epilogue, any M; the kernel is picked as for the plain contraction of the same shape.  rows_a: rows of A.
-// With parts (see ssam_parts_fit) there are no stats, and src holds the rows of every batch of src_rows: row m / src_rows * src_stride + src[m] of A.
+// With parts (see ssam_parts_form_of) there are no stats, and src holds the rows of every batch of src_rows: row m / src_rows * src_stride + src[m] of A.
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
                                void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride)
@@ -466,8 +491,7 @@ int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, c
     const SplitWs ws = { split_ws, split_ws_bytes };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src, parts.at, parts.slots, parts.eps, src_rows, src_stride };
     const GemmRowMap none = { nullptr, 1, 0, 1 };
-    int tile, ring;
-    const int wide = choose_fold_gelu(M, N, K, ld, rows_a, ws, tile, ring, parts.at != nullptr);
+    const auto [wide, tile, ring, us] = choose_fold_gelu(M, N, K, ld, rows_a, ws, parts.at != nullptr);
     if (parts.at)
         return wide < 0 ? SSAM_EUNSUPPORTED
                         : ssam_gemm_wide_parts_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
@@ -492,7 +516,8 @@ double folded_ln_us(int tiles, int K)
 }  // namespace
 
 // The contraction with the LayerNorm of its A rows folded in (see GemmFold): 128x256 tiles, packed weights,
-// mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.
+// mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.  parts: instead of stats; with at = NULL the same kernel that would read
+// them with stats (of ssam_ln_stats_impl as from pieces: the same bits).
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
                         void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill)
 {
@@ -500,8 +525,7 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     static_assert(lds <= 64 * 1024, "default LDS limit");
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr, parts.at, parts.slots, parts.eps, 1, 0, fill };
-    int ring;
-    const int wide = choose_ln(M, N, K, ld, ring, parts.at != nullptr);
+    const auto [wide, tile, ring, us] = choose_ln(M, N, K, ld, parts.slots != 0);
     if (parts.at)
         return wide < 0 ? SSAM_EUNSUPPORTED
                         : ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });

@@ -399,7 +399,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 
     if (!EARLY) load_epilogue();
     if constexpr (PARTS) {
-        // a row's pieces over the four quads, its mean, then the squares about it
+        // a row's pieces over the four quads, its mean, then the squares about it (ln_stats_kernel's pieces in the same order)
         gemm_wait_vm<0>();
         LDS_BARRIER();
 #pragma unroll
@@ -416,10 +416,8 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             }
             mean = gemm_quad_sum(mean) / (float)fold.slots;
 #pragma unroll
-            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i) {
-                const float d = v[i].x - mean;
-                if (4 * i + quad < fold.slots) sq += v[i].y + 64.f * d * d;
-            }
+            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i)
+                if (4 * i + quad < fold.slots) sq += gemm_piece_term(v[i], mean);
             const float inv = rsqrtf(gemm_quad_sum(sq) / (float)K + fold.eps);          // K: the rows' length
             rst[k] = make_float2(inv, -inv * mean);
         }

@@ -135,11 +135,12 @@ ln_gather_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx, i
 // statistics are those of the gathered rows, Nout per image, and src[row] receives the row of x that was read, for
 // the contraction that gathers the same rows; an index outside [0, Nin) reads the image's first row (its result is
 // dropped by the scatter that follows).
+// slots != 0: the statistics are put together from the row's pieces of 64 columns, in the order of a contraction that reads pieces (GemmParts): the same bits.
 template <int MAXC>
 __global__ void __launch_bounds__(256)
 ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long rows, int chunks, float eps,
                 const int32_t *__restrict__ idx, int idx_batch_stride, int Nin, int Nout, int32_t *__restrict__ src,
-                PadFill fill, int ln_blocks, float2 *__restrict__ parts)
+                PadFill fill, int ln_blocks, int slots)
 {
     int lane = threadIdx.x & 63;
     long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -161,28 +162,12 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) raw[i] = xrow[min(lane + 64 * i, chunks - 1)];
     float v[MAXC][8];
-    float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < MAXC; ++i) {
-        unpack_bf16x8(raw[i], v[i]);
-        if (lane + 64 * i < chunks) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s += v[i][e];
-        }
-    }
+    for (int i = 0; i < MAXC; ++i) unpack_bf16x8(raw[i], v[i]);
     int D = chunks * 8;
-    float mean = wave_sum(s) / (float)D;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < MAXC; ++i) {
-        if (lane + 64 * i < chunks) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { float t = v[i][e] - mean; q += t * t; }
-        }
-    }
-    float inv = rsqrtf(wave_sum(q) / (float)D + eps);
-    if (lane == 0) stats[row] = make_float2(inv, -inv * mean);
-    if (parts) {                               // pieces of 64 columns, eight lanes each (GemmParts); sums of columns 32 apart first
+    if constexpr (MAXC * 8 == GEMM_PARTS_MOST) if (slots) {
+        // piece (lane >> 3) + 8 * i, in its eight lanes: sums of columns 32 apart first
+        float2 own[MAXC], other[MAXC];           // other: piece s ^ 4
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
             float ps = gemm_piece_sum8(v[i]);
@@ -194,9 +179,47 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
             pq += __shfl_xor(pq, 4, 64);
             pq += __shfl_xor(pq, 1, 64);
             pq += __shfl_xor(pq, 2, 64);
-            if ((lane & 7) == 0 && lane + 64 * i < chunks) parts[row * GEMM_PARTS_MOST + ((lane + 64 * i) >> 3)] = make_float2(pm, pq);
+            own[i] = make_float2(pm, pq);
+            other[i] = make_float2(__shfl_xor(pm, 32, 64), __shfl_xor(pq, 32, 64));
+        }
+        // pieces 4 * k + quad one after the other, then the four quads
+        const int quad = (lane >> 3) & 3;
+        const bool upper = lane >= 32;
+        float2 piece[GEMM_PARTS_MOST / 4];
+#pragma unroll
+        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k) piece[k] = upper == (k % 2 == 1) ? own[k / 2] : other[k / 2];
+        auto over_quads = [](float t) { t += __shfl_xor(t, 8, 64); return t + __shfl_xor(t, 16, 64); };
+        float mean = 0.f, sq = 0.f;
+#pragma unroll
+        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k)
+            if (4 * k + quad < slots) mean += piece[k].x;
+        mean = over_quads(mean) / (float)slots;
+#pragma unroll
+        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k)
+            if (4 * k + quad < slots) sq += gemm_piece_term(piece[k], mean);
+        const float inv = rsqrtf(over_quads(sq) / (float)D + eps);
+        if (lane == 0) stats[row] = make_float2(inv, -inv * mean);
+        return;
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        if (lane + 64 * i < chunks) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += v[i][e];
         }
     }
+    float mean = wave_sum(s) / (float)D;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        if (lane + 64 * i < chunks) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { float t = v[i][e] - mean; q += t * t; }
+        }
+    }
+    float inv = rsqrtf(wave_sum(q) / (float)D + eps);
+    if (lane == 0) stats[row] = make_float2(inv, -inv * mean);
 }
 
 // Weight side of the fold: one wave per output channel n.
@@ -863,9 +886,9 @@ int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int 
     return SSAM_OK;
 }
 
-// statistics of rows idx[b][p] of image b (idx == NULL: of every row in order), see ln_stats_kernel; parts (every row in order, D % 64 == 0): see GemmParts
+// statistics of rows idx[b][p] of image b (idx == NULL: of every row in order), slots (D / 64 of at most GEMM_PARTS_MOST, or 0): see ln_stats_kernel
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
-                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, float2 *parts)
+                       int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, int slots)
 {
     if (!x || !stats || rows <= 0 || D <= 0 || D % 8 != 0) return SSAM_EINVAL;
     if (!ssam_aligned16(x) || ((uintptr_t)stats & 7)) return SSAM_EINVAL;
@@ -875,18 +898,18 @@ int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps,
     const int ln_blocks = ssam_div_up(rows, 4);
     dim3 grid((unsigned)(ln_blocks + ssam_div_up(fill.total_rows, 4))), block(256);
     if (chunks <= 128)
-        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
+        hipLaunchKernelGGL(ln_stats_kernel<2>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, slots);
     else if (chunks <= 192)
-        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
+        hipLaunchKernelGGL(ln_stats_kernel<3>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, slots);
     else
-        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, parts);
+        hipLaunchKernelGGL(ln_stats_kernel<4>, grid, block, 0, st, (const uint4 *)x, (float2 *)stats, rows, chunks, eps, idx, idx_batch_stride, Nin, Nout, src, fill, ln_blocks, slots);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
 
 extern "C" int ssam_ln_stats(const void *x, float *stats, long rows, int D, float eps, void *stream)
 {
-    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, PadFill{}, (hipStream_t)stream, nullptr);
+    return ssam_ln_stats_impl(x, stats, rows, D, eps, nullptr, 0, 0, 0, nullptr, PadFill{}, (hipStream_t)stream, 0);
 }
 
 extern "C" int ssam_fold_ln_weight(const void *W, int ldw, const float *bias, const float *gamma, const float *beta,
