@@ -254,12 +254,22 @@ int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double &launch
 
 // The wide kernel's tiles (gemm_wide.h).  A launch of r rounds (one workgroup per CU at a time) takes
 // t0 + r * (t_round + t_slab per slab of 64, t_gelu and t_add behind those epilogues) + t_mb per megabyte of C.
-struct WideTile { int bm, bn; double t0, t_round, t_slab, t_gelu, t_add, t_mb; };
+// t_parts: what a round takes longer where it leaves row statistics in pieces (GemmParts), reads them, and reads them of gathered rows (measured with the tiles
+// that can: D = 768 and 1024, half a round and a whole one, within 0.2 of these).
+struct WideTile { int bm, bn; double t0, t_round, t_slab, t_gelu, t_add, t_mb, t_parts[3]; };
 constexpr WideTile wide_tiles[GEMM_WIDE_COUNT] = {
-    { 64, 64, 3.7, 0, 0.16, 0.262, 0, 0.326 },          { 96, 64, 0, 4.18, 0.207, 0.375, 0.03, 0.246 },   { 96, 96, 0, 4.66, 0.251, 0.336, 0.504, 0.223 },
-    { 64, 128, 0, 4.27, 0.228, 0.614, 0.075, 0.354 },   { 128, 128, 1.14, 2.89, 0.382, 1.2, 0, 0.153 },   { 128, 192, 0.896, 4.09, 0.498, 1.31, 0, 0.205 },
-    { 192, 128, 0.478, 3.86, 0.505, 1.71, 0, 0.183 },   { 256, 128, 0.243, 4.64, 0.623, 2.1, 0, 0.2 },    { 192, 192, 0.697, 5.38, 0.668, 1.56, 0, 0.22 },
-    { 192, 256, 1.07, 4.83, 0.85, 3.16, 0, 0.197 },     { 256, 192, 0.964, 5, 0.838, 3.1, 0, 0.194 },     { 256, 256, 1.7, 4.96, 1.09, 4.28, 0, 0.207 } };
+    { 64, 64, 3.7, 0, 0.16, 0.262, 0, 0.326, { 0.3 } },
+    { 96, 64, 0, 4.18, 0.207, 0.375, 0.03, 0.246, { 0.55 } },
+    { 96, 96, 0, 4.66, 0.251, 0.336, 0.504, 0.223, {} },
+    { 64, 128, 0, 4.27, 0.228, 0.614, 0.075, 0.354, { 0.25 } },
+    { 128, 128, 1.14, 2.89, 0.382, 1.2, 0, 0.153, { 0.35, 0.45, 1.15 } },
+    { 128, 192, 0.896, 4.09, 0.498, 1.31, 0, 0.205, { 0, 1.05, 1.75 } },
+    { 192, 128, 0.478, 3.86, 0.505, 1.71, 0, 0.183, { 0.65, 0.75, 1.5 } },
+    { 256, 128, 0.243, 4.64, 0.623, 2.1, 0, 0.2, { 0.95, 0.95, 2.25 } },
+    { 192, 192, 0.697, 5.38, 0.668, 1.56, 0, 0.22, { 0, 1.35, 2.4 } },
+    { 192, 256, 1.07, 4.83, 0.85, 3.16, 0, 0.197, { 1.8, 1.55, 2.55 } },
+    { 256, 192, 0.964, 5, 0.838, 3.1, 0, 0.194, { 0, 1.05, 2.5 } },
+    { 256, 256, 1.7, 4.96, 1.09, 4.28, 0, 0.207, { 2.1, 1.9, 3.4 } } };
 enum PartsUse { PARTS_LEFT, PARTS_READ, PARTS_READ_GATHERED, PARTS_NONE };
 
 // Index of the wide kernel's tile that is faster than the others' launch_us, or -1.  rows_a: rows of A where its rows are
@@ -281,7 +291,8 @@ enum PartsUse { PARTS_LEFT, PARTS_READ, PARTS_READ_GATHERED, PARTS_NONE };
 // without this kernel, and on 9 of the shapes slower than that by more than 3 %, 9 % at most (shapes of 5 to 8 us).  More than two rounds of packed problems
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
-// parts: what the kernel does with row statistics in pieces, of the tiles that can.  launch_us: what is taken, on return.
+// parts: what the kernel does with row statistics in pieces, of the tiles that can; what that takes is not held against the others, who would have to wait for a
+// launch.  launch_us: what is taken, on return.
 int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double &launch_us, double both_us, PartsUse parts = PARTS_NONE)
 {
     const unsigned among = parts == PARTS_NONE ? ~0u : parts == PARTS_LEFT ? GEMM_WIDE_WRITES_PARTS : GEMM_WIDE_READS_PARTS;
@@ -290,7 +301,7 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
     if ((long)256 * ld.a * 2 >= 1L << 31 || (rows_a + 1) * ld.a * 2 >= 1L << 32 || (long)256 * (packed ? K : ld.w) * 2 >= 1L << 31) return -1;
     const int torn = (ld.a % GEMM_BK != 0) + (!packed && ld.w % GEMM_BK != 0);
     int best = -1;
-    double best_us = 1e30;
+    double best_us = 1e30, best_parts = 0.0;
     for (int i = 0; i < GEMM_WIDE_COUNT; ++i) {
         if (!((among >> i) & 1)) continue;
         const WideTile &t = wide_tiles[i];
@@ -299,11 +310,12 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
         if (rounds > (packed ? 2 : 4)) continue;
         const double us = t.t0 + rounds * (t.t_round + nk * slab + (i == 0 && nk > 16 ? 0.06 * (nk - 16) : 0.0) + (epilogue == SSAM_EPI_BIAS_GELU ? t.t_gelu : epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? t.t_add : 0.0))
                           + t.t_mb * (epilogue == SSAM_EPI_BIAS_SCATTER_ADD ? 4e-6 : 2e-6) * M * N;
-        if (us < best_us) { best_us = us; best = i; }
+        const double parts_us = parts == PARTS_NONE ? 0.0 : rounds * t.t_parts[parts];
+        if (us + parts_us < best_us + best_parts) { best_us = us; best_parts = parts_us; best = i; }
     }
     const double others_us = best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128 && both_us < launch_us ? both_us : launch_us;
     if (best_us >= 0.99 * others_us) return -1;
-    launch_us = best_us;
+    launch_us = best_us + best_parts;
     return best;
 }
 
@@ -370,8 +382,8 @@ Choice choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs
     return c;
 }
 
-// What reading a row's statistics in pieces saves (a launch of 4.6 us less what the reading takes): other kernels of a contraction that could
-// read them take that much longer.  fc1 of ViT-L at a density of 0.4 (1638 x 4096 x 1024) is 1 % faster on the large tiles by itself.
+// How much faster the others may be than a tile that reads row statistics in pieces: fc1 of ViT-L at a density of 0.4 (1638 x 4096 x 1024) is 1 % faster on the
+// large tiles by itself.
 constexpr double PARTS_US = 3.0;
 
 // The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics come in pieces.
@@ -415,14 +427,21 @@ BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
 
 // Row statistics in pieces (GemmParts) of the residual stream, [rows][D] of which `kept` go through the MLP, in blocks with packed weights and both
 // LayerNorms folded in.  0: none; 1: proj leaves them and fc1 reads them; 3: fc2 leaves them too, and the next block's qkv reads those.  What leaves or reads
-// them is the wide kernel, by some of its tiles.  A block by itself has a launch for qkv's statistics all the same, reads and leaves nothing there and takes the
-// stack's tiles.
+// them is the wide kernel, where it is at least near the fastest by the tiles that can: what a contraction takes longer than without, leaving and reading included,
+// goes against the launch saved.  A block by itself has a launch for qkv's statistics all the same, reads and leaves nothing there and takes the stack's tiles.
+// LAUNCH_US: 90 folded stacks of widths 512, 768 and 1024 (512 to 10000 rows, densities 0.2 to 1) ran with each form.  With 4.6 to 5.5 all together are 231 us a
+// block faster than without pieces (235 with the best form of each, 230 with pieces wherever tiles fit) and two are slower, by 1.1 us at most; with 3.4 212.  Larger
+// ones lost without that charge: fc2 of ViT-B with 2760 kept rows (6 images of 48 x 48, density 0.2) went from 96x96 to 128x128, 25.2 -> 29.0 us, and dense or
+// large stacks were up to 5 % slower than without.
 int ssam_parts_form_of(int rows, int kept, int D, int Dm)
 {
     if (D % 128 != 0 || D / 64 > GEMM_PARTS_MOST) return 0;
-    const BlockChoices with = block_choices(rows, kept, D, Dm, true);
-    if (with.c[1].wide < 0 || with.c[2].wide < 0) return 0;
-    return with.c[0].wide >= 0 && with.c[3].wide >= 0 ? 3 : 1;
+    const BlockChoices with = block_choices(rows, kept, D, Dm, true), without = block_choices(rows, kept, D, Dm, false);
+    constexpr double LAUNCH_US = 5.0;
+    double gain[2] = { LAUNCH_US, LAUNCH_US };    // of the pieces between proj and fc1, and between fc2 and qkv
+    for (int i = 0; i < 4; ++i) gain[i == 0 || i == 3] -= with.c[i].wide < 0 ? 1e30 : with.c[i].us - without.c[i].us;
+    if (gain[1] > 0 && gain[0] + gain[1] > 0) return 3;
+    return gain[0] > 0 ? 1 : 0;
 }
 
 // The form, for tests, and the wide kernel's tiles of qkv, proj, fc1 and fc2 with it (-1: another kernel).  Host only; not part of the interface.

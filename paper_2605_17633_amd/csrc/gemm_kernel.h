@@ -87,8 +87,8 @@ struct GemmFold {
 
 // Statistics of the rows of the residual stream in pieces of 64 columns, [rows][GEMM_PARTS_MOST] { mean, sum of squared deviations from it }: the
 // epilogues that write the rows leave them, from the values as stored, and the contraction that wants a row's mean and variance puts
-// them together.  A statistics launch of its own takes 4.6 us however few rows there are; writing the pieces takes 0.3 to 0.6 (128x128 tiles of proj 11.3
-// -> 11.6, 96x64 of fc2 17.4 -> 18.0) and reading them 1 to 1.5 (256x192 of qkv 21.4 -> 22.6, 192x128 of fc1 16.0 -> 17.4; ViT-B, batch 1).  at = NULL: none.
+// them together.  A statistics launch takes 4.6 us however few rows there are, 3.4 of which a stack gets back; leaving the pieces takes 0.25 to 2.1 and reading
+// them 0.45 to 3.4, by tile (wide_tiles in gemm.hip), and ssam_parts_form_of says where that is worth it.  at = NULL: none.
 struct GemmParts {
     float2 *at;
     int slots;                // D / 64, 0: none

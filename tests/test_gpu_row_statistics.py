@@ -1,5 +1,5 @@
-"""Row statistics that the projections of a folded stack leave in pieces of 64 columns, instead of a launch for them: tiles of the wide contraction that
-leave or read them (which ones the library takes is checked without a GPU, in test_parts_forms.py)."""
+"""Row statistics that the projections of a folded stack leave in pieces of 64 columns, instead of a launch for them: every tile of the wide contraction that
+leaves or reads them (which ones the library takes is checked without a GPU, in test_parts_forms.py)."""
 import pytest
 import torch
 
@@ -17,6 +17,7 @@ CASES = [
     (1024, 6, 16, 0.75, 3, (6, 1, 6, 1), False),
     (768, 11, 16, 0.75, 3, (7, 4, 7, 3), True),
     (768, 8, 28, 0.6, 3, (11, 6, 10, 4), False),       # no padding
+    (768, 11, 16, 1.0, 1, (7, 4, 8, 2), False),
     (768, 1, 64, 0.5, 3, (10, 4, 5, 3), False),
     (1024, 3, 32, 1.0, 3, (8, 4, 9, 4), True),
     (1024, 2, 40, 1.0, 3, (10, 4, 11, 4), False),
