@@ -455,7 +455,7 @@ template <int ITEMS>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int N, int K)
 {
-    __shared__ int hist[3][SEL_BINS];
+    __shared__ alignas(16) int hist[3][SEL_BINS];         // cleared by 16-byte stores
     __shared__ unsigned long long scratch[SEL_THREADS / 64];
     __shared__ uint32_t sh_prefix;
     __shared__ int sh_remaining;
