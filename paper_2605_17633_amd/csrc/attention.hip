@@ -164,7 +164,7 @@ __host__ __device__ inline int glb_tstr(int w) { return 4 * ((w + 1) >> 1) + 4; 
 // against 434, d = 80 428 against 500.
 __host__ __device__ inline int glb_operand(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 0; }
 __host__ __device__ inline int glb_wk(int w) { return glb_operand(w) ? glb_operand(w) : (w + 1) & ~1; }
-__host__ __device__ inline int glb_general_tstr(int w) { return 2 * glb_wk(w) + (glb_operand(w) ? 8 : 4); }
+__host__ __device__ inline int glb_general_tstr(int w) { return 2 * glb_wk(w) + 4; }        // of the look-ups
 
 template <int D, typename TabT>
 __device__ __forceinline__ void build_bias_rows(const bf16x8 *qf, const bf16 *rel_h, const bf16 *rel_w, int rstr,
@@ -1208,13 +1208,13 @@ __device__ __forceinline__ void attn_pipe_run(Pipe &pipe, const Request &request
     pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
 }
 
-// LDS of the patch path: K ring, V ring (below 64 KB: the reach of M0 as LDS address), 32 bytes of ones, the waves' check
-// results, table offsets of every block for either half-wave, the waves' bias tables
+// LDS of the patch path: K ring, V ring (below 64 KB: the reach of M0 as LDS address), the waves' check results, table offsets
+// of every block for either half-wave, the waves' bias tables
 inline __host__ __device__ int patch_blocks_bytes(int n_blocks) { return (n_blocks * 8 + 15) & ~15; }
 template <int D>
 inline __host__ __device__ size_t patch_lds_bytes(int w, int n_blocks)
 {
-    return (size_t)2 * AttnPipe<D, 0>::RING + 64 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
+    return (size_t)2 * AttnPipe<D, 0>::RING + 16 + patch_blocks_bytes(n_blocks) + (size_t)4 * wave_scratch_bytes<D>(glb_tstr(w));
 }
 
 // The bias table (layout of build_bias_rows) of a wave whose 32 queries are a patch: rows qr0 .. qr0 + 6 and columns
@@ -1470,7 +1470,7 @@ __device__ __forceinline__ void attn_global_body(const AttnParams &P, int qt, in
     using C = AttnCfg<D>;
     constexpr int LOADS = GLB_TILE * C::CH / 256;       // 16-byte chunks per thread per operand
     static_assert(GLB_TILE * C::CH % 256 == 0, "tile chunks must divide over the workgroup");
-    const int wk = glb_wk(P.w), tstr = 2 * wk + 4;
+    const int wk = glb_wk(P.w), tstr = glb_general_tstr(P.w);
     bf16 *Ks = reinterpret_cast<bf16 *>(smem);
     bf16 *Vs = Ks + GLB_TILE * C::KSTR;
     unsigned char *Tb = reinterpret_cast<unsigned char *>(Vs + GLB_TILE * C::KSTR);
