@@ -65,7 +65,9 @@ def test_hot_kernels_keep_their_register_budget():
         # rings of 48 KB run three workgroups to a CU, three waves to a SIMD; so do windows up to d = 64, a wave to a tile
         three = ("gemm_ring_kernel" in name and "gemm_ring_kernelILi128ELi128E" not in name) or \
                 ("attn_window_kernel_wavesI" in name and "ILi80E" not in name and "ELb0E" in name)
-        assert r["vgprs"] + r["agprs"] <= (168 if three else 256), (name, r)
+        # global attention at d = 16 with tables of 32 runs four (but for its form for short last tiles)
+        four = "attn_global_kernelILi16E" in name and "ELi32E" in name and "ELb1EEE" not in name
+        assert r["vgprs"] + r["agprs"] <= (128 if four else 168 if three else 256), (name, r)
 
 
 def test_what_spills_elsewhere():
