@@ -1108,7 +1108,7 @@ struct AttnPipe {
 
 // Requests of a wave for the rings of a workgroup: waves 0 and 1 bring K, 2 and 3 V, a block each: lane l of request i the chunk that
 // belongs at 16-byte place 64 * i + l.  RAGGED: rows past S repeat the last one (their scores are masked).
-template <int D, bool RAGGED>
+template <int D, bool RAGGED, bool SHORT = false>
 struct AttnRequests {
     using Pipe = AttnPipe<D, 0>;
     static constexpr int CH = AttnCfg<D>::CH, SLOT = Pipe::SLOT, LOADS = Pipe::LOADS;
@@ -1119,7 +1119,7 @@ struct AttnRequests {
     bool is_v;
 
     __device__ __forceinline__ AttnRequests(const AttnParams &P, int qt_, long base, unsigned char *smem)
-        : rs2((uint32_t)P.row_stride * 2u), S(P.S), n_pre(P.n_pre), qt(qt_), nblk((P.n_pre + (qt_ >= P.n_pre ? 1 : 0)) * (GLB_TILE / 32)),
+        : rs2((uint32_t)P.row_stride * 2u), S(P.S), n_pre(P.n_pre), qt(qt_), nblk(blocks(P, qt_)),
           wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))), is_v(wave >= 2)
     {
         kvbase = reinterpret_cast<const unsigned char *>((is_v ? P.v : P.k) + base);
@@ -1131,6 +1131,16 @@ struct AttnRequests {
             const int place = i * 64 + l64, row = place / CH, pos = place % CH;
             src_off[i] = (uint32_t)row * rs2 + (uint32_t)(pos ^ Pipe::swz(row, is_v)) * 16u;
         }
+    }
+    // Blocks of the active tiles; with SHORT two of the last one, where no more than two have keys (sides that are 4 mod 8 have 16 keys in their last tile).  Its other
+    // two, masked, cost 12 x 12, 256 problems, r = 0.5 1.9 us at d = 64 (14.3 -> 12.4; tiles of 128 keys between two barriers took 13.0), 16 problems of
+    // 28 x 28, dense, 21.4 -> 20.1.
+    __device__ __forceinline__ static int blocks(const AttnParams &P, int qt)
+    {
+        const int n = (P.n_pre + (qt >= P.n_pre ? 1 : 0)) * (GLB_TILE / 32);
+        if (!SHORT) return n;
+        const int last = max(qt, P.n_pre - 1) * GLB_TILE;       // first key of the last active tile
+        return P.S - last <= 64 ? n - 2 : n;
     }
     __device__ __forceinline__ int key0(int blk) const       // scan position of the first key of the workgroup's block blk
     {
@@ -1171,9 +1181,9 @@ struct AttnRequests {
 // The blocks of a workgroup through its pipe; K(0), K(1), V(0) and K(2) have landed, or are waited for with what `arrived` waits for.
 // Blocks b and b + 1 (b even) form the scores of b + 1 and b + 2 and add P V of b - 1 and b: what they read was requested two blocks ago.  Every
 // wave is done with K(b - 1) and K(b) and with V(b - 3) and V(b - 2): they make room for K(b + 3), K(b + 4), V(b + 1) and V(b + 2).
-// nblk is a multiple of four: every slot read is a constant, in the instructions.
+// nblk is a multiple of four, with TWO_MORE two more: every slot read is a constant, in the instructions.
 // ahead(): in front of it all; arrived(): behind the wait for all that was requested; one(b), two(b): in front of blocks b and b + 1.
-template <class Pipe, class Request, class Ahead, class Arrived, class One, class Two>
+template <bool TWO_MORE, class Pipe, class Request, class Ahead, class Arrived, class One, class Two>
 __device__ __forceinline__ void attn_pipe_run(Pipe &pipe, const Request &request, int nblk, Ahead ahead, Arrived arrived, One one, Two two)
 {
     constexpr int SLOT = Pipe::SLOT;
@@ -1194,15 +1204,30 @@ __device__ __forceinline__ void attn_pipe_run(Pipe &pipe, const Request &request
     };
     using std::true_type;
     using std::false_type;
-    pair(false_type{}, true_type{}, false_type{}, 0);
-    for (int b = 2; b < nblk - 2; b += 4) {
-        pair(true_type{}, false_type{}, false_type{}, b);
-        pair(false_type{}, false_type{}, false_type{}, b + 2);
+    if constexpr (TWO_MORE) {
+        // the last pair is the other one
+        if (nblk == 2) {
+            pair(false_type{}, true_type{}, true_type{}, 0);
+        } else {
+            pair(false_type{}, true_type{}, false_type{}, 0);
+            for (int b = 2; b < nblk - 4; b += 4) {
+                pair(true_type{}, false_type{}, false_type{}, b);
+                pair(false_type{}, false_type{}, false_type{}, b + 2);
+            }
+            pair(true_type{}, false_type{}, false_type{}, nblk - 4);
+            pair(false_type{}, false_type{}, true_type{}, nblk - 2);
+        }
+    } else {
+        pair(false_type{}, true_type{}, false_type{}, 0);
+        for (int b = 2; b < nblk - 2; b += 4) {
+            pair(true_type{}, false_type{}, false_type{}, b);
+            pair(false_type{}, false_type{}, false_type{}, b + 2);
+        }
+        pair(true_type{}, false_type{}, true_type{}, nblk - 2);
     }
-    pair(true_type{}, false_type{}, true_type{}, nblk - 2);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // V of the last block was requested in front of the block before it
     LDS_BARRIER();
-    constexpr int last_v = 3 * SLOT;
+    constexpr int last_v = TWO_MORE ? SLOT : 3 * SLOT;
     pipe.rescale();
     pipe.template begin<false, true>(0, last_v);
     pipe.template steps<false, true, 0, false, 0>(0, last_v, 0.f);   // P V of the last block (parity 1)
@@ -1361,7 +1386,7 @@ __device__ __forceinline__ bool attn_patch_body(const AttnParams &P, int qt, int
 
     pipe.bo = bo_tab[half];
     uint32_t bo1 = bo_tab[2 + half], bo2 = bo_tab[4 + half], next1, next2;
-    attn_pipe_run(pipe, request, nblk, [&]() {}, [&]() {},
+    attn_pipe_run<false>(pipe, request, nblk, [&]() {}, [&]() {},
         [&](int b) {
             pipe.bo = bo1;
             next1 = bo_tab[2 * min(b + 3, nblk - 1) + half], next2 = bo_tab[2 * min(b + 4, nblk - 1) + half];
@@ -1385,7 +1410,7 @@ inline __host__ __device__ size_t onehot_lds_bytes()
     return (size_t)2 * AttnPipe<D, WK>::RING + (size_t)4 * wave_scratch_bytes<D>(2 * WK + 8);
 }
 
-template <int D, int WK>
+template <int D, int WK, bool SHORT>
 __device__ __forceinline__ void attn_onehot_body(const AttnParams &P, int qt, int grp, int head, unsigned char *smem)
 {
     using C = AttnCfg<D>;
@@ -1395,7 +1420,7 @@ __device__ __forceinline__ void attn_onehot_body(const AttnParams &P, int qt, in
     const int S = P.S;
     GlbTab *tq = reinterpret_cast<GlbTab *>(smem + 2 * Pipe::RING + wave * wave_scratch_bytes<D>(TSTR));
     const long base = (long)grp * S * P.row_stride + (long)head * D;
-    AttnRequests<D, true> request(P, qt, base, smem);
+    AttnRequests<D, true, SHORT> request(P, qt, base, smem);
     request.first();
 
     const int qpos = qt * GLB_TILE + wave * 32 + l32, qclamp = min(qpos, S - 1);
@@ -1429,37 +1454,41 @@ __device__ __forceinline__ void attn_onehot_body(const AttnParams &P, int qt, in
     asm volatile("" : "+v"(cell0), "+v"(cell1), "+v"(cell2));
     LDS_BARRIER();
     int next1 = cell1, next2 = cell2;
-    attn_pipe_run(pipe, request, nblk,
-        [&]() {
-            // The exponent reference begins as the maximum over two blocks (one more block's scores): the likelier a query's largest probability is
-            // exactly 1, the smaller the error.  With that of the first alone it is 1 to 6 % larger.  Keys past the end repeat the last one here.
-            pipe.cell = cell1;
-            pipe.template begin<true, false>(Pipe::SLOT, 0);
-            pipe.template steps<true, false, 0, false, 0>(Pipe::SLOT, 0, 0.f);
-            float mx = pipe.s[1][0];
+    auto run = [&](auto two_more) {
+        attn_pipe_run<decltype(two_more)::value>(pipe, request, nblk,
+            [&]() {
+                // The exponent reference begins as the maximum over two blocks (one more block's scores): the likelier a query's largest probability is
+                // exactly 1, the smaller the error.  With that of the first alone it is 1 to 6 % larger.  Keys past the end repeat the last one here.
+                pipe.cell = cell1;
+                pipe.template begin<true, false>(Pipe::SLOT, 0);
+                pipe.template steps<true, false, 0, false, 0>(Pipe::SLOT, 0, 0.f);
+                float mx = pipe.s[1][0];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, pipe.s[1][r]);
-            pipe.start = mx;
-            pipe.cell = cell0;
-        },
-        [&]() { asm volatile("" : "+v"(next1), "+v"(next2)); },        // the compiler's own wait for them is here, where nothing else is out
-        [&](int b) {
-            pipe.cell = next1;
-            cell2 = next2;
-            next1 = cell_of(b + 3);
-            next2 = cell_of(b + 4);
-            pipe.limit = S - request.key0(b);
-        },
-        [&](int b) {
-            pipe.cell = cell2;
-            pipe.limit = S - request.key0(b + 1);
-        });
-    long my_row = -1;                             // output row of this lane's query (not looked up before: no registers)
-    if (qpos < S) {
-        my_row = (long)grp * S + qpos;
-        if (P.out_rows) my_row = P.out_rows[my_row];
-    }
-    finish_and_store<D, C::KSTR, false>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
+                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, pipe.s[1][r]);
+                pipe.start = mx;
+                pipe.cell = cell0;
+            },
+            [&]() { asm volatile("" : "+v"(next1), "+v"(next2)); },        // the compiler's own wait for them is here, where nothing else is out
+            [&](int b) {
+                pipe.cell = next1;
+                cell2 = next2;
+                next1 = cell_of(b + 3);
+                next2 = cell_of(b + 4);
+                pipe.limit = S - request.key0(b);
+            },
+            [&](int b) {
+                pipe.cell = cell2;
+                pipe.limit = S - request.key0(b + 1);
+            });
+        long my_row = -1;                             // output row of this lane's query (not looked up before: no registers)
+        if (qpos < S) {
+            my_row = (long)grp * S + qpos;
+            if (P.out_rows) my_row = P.out_rows[my_row];
+        }
+        finish_and_store<D, C::KSTR, false>(st, reinterpret_cast<bf16 *>(tq), P.out + (long)head * D, (long)P.h * D, my_row);
+    };
+    if (SHORT && (nblk & 2)) run(std::bool_constant<SHORT>{});
+    else run(std::false_type{});
 }
 
 // Above 64 x 64: tiles of 128 keys through registers into LDS, the bias by look-ups (attn_chunk_step).  NB: key blocks per
@@ -1576,11 +1605,11 @@ size_t global_lds_bytes(int w)
 }
 
 // TRY_PATCH: the instantiation for a shared position-only order on a power-of-two grid (attn_patch_body, and one of the
-// others where a block is not a patch).  !TRY_PATCH: those only.
+// others where a block is not a patch).  !TRY_PATCH: those only.  SHORT: any order, of the last tile two blocks (see AttnRequests::blocks).
 // d = 16 with tables of 32: four workgroups to a CU, for which registers nearly suffice by themselves (135): with three 28 x 28, 8 images of 16 heads, r = 0.4
 // took 25.0 us instead of 21.0, 32 x 32 in position order 26.4 instead of 22.5, both longer than tiles of 128 keys between two barriers.
-template <int D, bool TRY_PATCH, int WK>
-__global__ void __launch_bounds__(256, D == 16 && WK == 32 ? 4 : 2)
+template <int D, bool TRY_PATCH, int WK, bool SHORT = false>
+__global__ void __launch_bounds__(256, D == 16 && WK == 32 && !SHORT ? 4 : 2)
 attn_global_kernel(AttnParams P, int T, int n_gh)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1595,7 +1624,7 @@ attn_global_kernel(AttnParams P, int T, int n_gh)
         if (attn_patch_body<D>(P, qt, grp, head, smem)) return;
         asm volatile("" : "+s"(qt));                            // nothing of what follows is computed in front of the patch path
     }
-    if constexpr (WK != 0) attn_onehot_body<D, WK>(P, qt, grp, head, smem);
+    if constexpr (WK != 0) attn_onehot_body<D, WK, SHORT>(P, qt, grp, head, smem);
     else attn_global_body<D, (D <= 64 ? 4 : 2)>(P, qt, grp, head, smem);
 }
 
@@ -1697,7 +1726,12 @@ int launch_attention(const AttnParams &P, int groups, int mask_block, hipStream_
         }
         if (lds > ds.lds) return SSAM_EUNSUPPORTED;
         const int wk = glb_operand(P.w);
-        auto kern = wk == 32 ? (patch ? attn_global_kernel<D, true, 32> : attn_global_kernel<D, false, 32>)
+        // SHORT takes registers: at d = 16 and 32 a CU holds fewer workgroups (36 x 36, 16 images, d = 32 108 | 124 us)
+        const int rest = P.S % GLB_TILE;          // keys of the last tile
+        const bool short_end = rest > 0 && rest <= 64 && (D >= 64 || (long)T * groups * P.h <= 2L * ds.cus);
+        auto kern = wk == 32 && short_end ? attn_global_kernel<D, false, 32, true>
+                  : wk == 64 && short_end ? attn_global_kernel<D, false, 64, true>
+                  : wk == 32 ? (patch ? attn_global_kernel<D, true, 32> : attn_global_kernel<D, false, 32>)
                   : wk == 64 ? (patch ? attn_global_kernel<D, true, 64> : attn_global_kernel<D, false, 64>)
                              : (patch ? attn_global_kernel<D, true, 0> : attn_global_kernel<D, false, 0>);
         if (lds > 64 * 1024 &&

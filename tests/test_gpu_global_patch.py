@@ -123,6 +123,14 @@ def test_any_order(w, d, r, shared):
     assert err < 2.6e-3
 
 
+@pytest.mark.parametrize("w,d,r,shared", [(4, 64, 1.0, True), (5, 16, 1.0, False), (7, 80, 1.0, False), (8, 32, 1.0, True), (12, 80, 1.0, False), (12, 64, 0.5, True), (20, 64, 1.0, True),
+                                          (20, 80, 0.3, False), (23, 32, 1.0, False), (28, 16, 1.0, True), (28, 80, 0.4, False), (36, 64, 0.2, False), (36, 80, 1.0, True), (60, 16, 0.1, False), (60, 32, 0.1, True),
+                                          (44, 80, 0.1, False)])
+def test_short_last_tile(w, d, r, shared):
+    """At most 64 keys in the last tile: its two blocks are the only ones, or come behind whole tiles, one or many."""
+    test_any_order(w, d, r, shared)
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 80])
 @pytest.mark.parametrize("w,r,order", [(32, 0.2, "position"), (64, 0.4, "position"), (28, 0.4, "position"), (50, 0.5, "row")])
 def test_error_where_one_key_dominates(w, r, order, d):
