@@ -371,11 +371,12 @@ score_kernel(const uint4 *__restrict__ x, float *__restrict__ scores, int gh, in
 
 // Up to 28 MB of tokens: there the second launch costs more than the rows read twice (us, one launch | two, from a loop of calls: 4096 x 768
 // 6.6 | 9.3, the rate of the calls; 8192 x 1280, 21 MB, 7.4 | 9.2; 16384 x 768, 25 MB, 8.6 | 9.3; 16384 x 1024, 34 MB, 9.8 | 9.4; 65536 x 1280 39.8 | 32.4).
-// Its images are the grid's z and its rows of tiles the grid's y, which the device states to reach 65536 at most: more of them are left to two launches, whose
-// grids have one dimension.
+// And up to 1024 workgroups, whose twelve waves each take 3.7 ns of the launch: small images and thin grids have many of few cells (64 images of 14 x 14 x 768, 1024 of
+// them, 8.3 | 7.5 to 9.4; 22 of 28 x 28 9.8 | the same; 3000 of 2 x 2 15.0 | 7.9; 256 x 256 x 144, 4096, 18.7 | 10.8; 20000 single tokens 74.8 | 7.6).  Far within the 65536 that the device
+// states for the grid's z (images) and y (rows of tiles).
 bool score_in_one_launch(int B, int gh, int gw, int D)
 {
-    return (long)B * gh * gw * D * 2 <= 28000000 && D <= 2048 && B <= 65535 && ssam_div_up(gh, SCORE_TILE) <= 65535;
+    return (long)B * gh * gw * D * 2 <= 28000000 && D <= 2048 && (long)B * ssam_div_up(gh, SCORE_TILE) * ssam_div_up(gw, SCORE_TILE) <= 1024;
 }
 
 // csum: where the channel sums of the form with two launches go

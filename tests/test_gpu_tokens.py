@@ -85,9 +85,9 @@ def test_scores_in_one_launch(gh, gw, D):
     assert float((got[0].double() - torch.sqrt(gx * gx + gy * gy).reshape(-1)).abs().max()) <= bound
 
 
-@pytest.mark.parametrize("B_,gh,gw,D", [(70000, 1, 2, 8), (65536, 1, 1, 16), (65535, 2, 2, 8), (1, 262145, 1, 8), (1, 262140, 1, 8), (2, 300000, 1, 16), (3, 9, 6, 768)])
+@pytest.mark.parametrize("B_,gh,gw,D", [(70000, 1, 2, 8), (65536, 1, 1, 16), (1024, 2, 2, 8), (1025, 2, 2, 8), (1, 262145, 1, 8), (1, 4096, 1, 8), (2, 300000, 1, 16), (3, 9, 6, 768)])
 def test_scores_of_many_images_and_tall_grids(B_, gh, gw, D):
-    """More images, or more rows of tiles, than a grid's second and third dimension hold, the most that they hold, and images that differ."""
+    """More images, or more rows of tiles, than a grid's second and third dimension hold, the most that one launch takes, and images that differ."""
     announce("scores", B_, gh, gw, D)
     gen = torch.Generator(device=DEV).manual_seed(B_ + gh)
     x = torch.randn(B_, gh, gw, D, generator=gen, device=DEV).bfloat16()

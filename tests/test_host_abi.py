@@ -95,8 +95,8 @@ def test_error_codes():
     assert L.ssam_encoder_block(None, None, C.byref(cfg), None, None, None, None, C.c_size_t(0), None) == B.EINVAL
 
 
-@pytest.mark.parametrize("B_,gh,gw,D,launches", [(65535, 1, 2, 8, 1), (65536, 1, 2, 8, 2), (100000, 1, 1, 8, 2), (1, 262140, 1, 8, 1), (1, 262141, 1, 8, 2),
-                                                  (1, 64, 64, 768, 1), (1, 8, 8, 2056, 2), (16, 64, 64, 768, 2)])
-def test_scores_stay_within_the_grid(B_, gh, gw, D, launches):
-    """One launch has the images in the grid's z and tiles of four rows in its y: 65536 at most."""
+@pytest.mark.parametrize("B_,gh,gw,D,launches", [(1, 64, 64, 768, 1), (64, 14, 14, 768, 1), (1, 128, 128, 288, 1), (1024, 1, 2, 8, 1), (1, 4096, 4, 8, 1), (1, 8, 8, 2056, 2),
+                                                  (16, 64, 64, 768, 2), (65, 14, 14, 768, 2), (3000, 2, 2, 768, 2), (1, 256, 256, 144, 2), (100000, 1, 1, 8, 2), (1, 262144, 1, 8, 2)])
+def test_scores_in_one_launch_or_two(B_, gh, gw, D, launches):
+    """One launch up to 28 MB of tokens and 1024 workgroups of 4 x 4 cells: the grid has the images in z and rows of tiles in y, 65536 at most."""
     assert B.lib().ssam_score_form(*(C.c_int(v) for v in (B_, gh, gw, D))) == launches
