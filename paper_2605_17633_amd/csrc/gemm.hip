@@ -11,6 +11,7 @@ int ssam_gemm_wide_ln_scatter(int tile, const GemmWideArgs &a);
 int ssam_gemm_wide_ln_gelu(int tile, const GemmWideArgs &a);
 int ssam_gemm_wide_parts_scatter(int tile, const GemmWideArgs &a);
 int ssam_gemm_wide_parts_gelu(int tile, const GemmWideArgs &a);
+int ssam_gemm_wide_parts_add(int tile, const GemmWideArgs &a);
 
 namespace {
 
@@ -470,12 +471,11 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
         if (const int wide = pick.wide; wide >= 0) {
             GemmFold out;
             out.parts = parts.at;
-            out.slots = parts.slots;
             const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, out, st };
             switch (epilogue) {
             case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
             case SSAM_EPI_BIAS_GELU: return ssam_gemm_wide_gelu(wide, packed, args);
-            case SSAM_EPI_BIAS_SCATTER_ADD: return ssam_gemm_wide_add(wide, packed, args);
+            case SSAM_EPI_BIAS_SCATTER_ADD: return parts.at ? ssam_gemm_wide_parts_add(wide, args) : ssam_gemm_wide_add(wide, packed, args);
             case SSAM_EPI_BIAS_SCATTER: return ssam_gemm_wide_scatter(wide, packed, args);
             default: return SSAM_EINVAL;
             }

@@ -83,7 +83,7 @@ __device__ __forceinline__ float gemm_quad_sum(float v)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// PARTS: the row statistics of the folded LayerNorm come in pieces (GemmParts).  The scatter-add epilogues leave such pieces where fold.parts is given.
+// PARTS: the row statistics of the folded LayerNorm come in pieces (GemmParts), or, of a scatter-add, it leaves such pieces.
 // The pieces of a tile's rows are as large as a slab of A and come as one more, into the stage that the last slab but SA - 1 has freed: no registers, and
 // under the products of the last slabs.  Loaded in front of the ring's first slabs they cost 4 us, as much as the launch they save.
 template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS = false>
@@ -92,7 +92,8 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
                  bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
     using G = GemmWide<BM, BN, WGK>;
-    static_assert(!PARTS || (LNF && G::READS_PARTS), "the forms that read pieces");
+    constexpr bool READS = PARTS && LNF, LEAVES = PARTS && !LNF;
+    static_assert((!READS || G::READS_PARTS) && (!LEAVES || (EPI == SSAM_EPI_BIAS_SCATTER_ADD && WPACK && G::WRITES_PARTS)), "the forms that read or leave pieces");
     constexpr int BK = GEMM_BK, WGN = G::WGN, MT = G::MT, NT = G::NT, NP = NT / 2, WM = MT * 16, WN = NT * 16;
     constexpr int SA = G::SA, SW = G::SW, L = G::L;
     constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER, ADD = EPI == SSAM_EPI_BIAS_SCATTER_ADD;
@@ -102,7 +103,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     unsigned char *as = smem, *ws = smem + W0;
 
     const int per_xcd = (tr.tile_count + 7) / 8, bid = blockIdx.x;
-    if constexpr (PARTS && EPI == SSAM_EPI_BIAS_SCATTER) if (bid >= 8 * per_xcd) {
+    if constexpr (READS && EPI == SSAM_EPI_BIAS_SCATTER) if (bid >= 8 * per_xcd) {
         // padding rows, GEMM_WIDE_FILL a workgroup, one after the other in a wave: on CUs that have no tile, or behind the first tiles that end.  After a
         // global block they are all that the statistics launch would be for (ViT-B, 64 x 64, batch 1: 192 tiles, 1110 -> 1093 us; ViT-L, 256 tiles: no change)
         for (int i = threadIdx.x >> 6; i < GEMM_WIDE_FILL; i += 8) fill_pad_row(fold.fill, (bid - 8 * per_xcd) * GEMM_WIDE_FILL + i);
@@ -126,10 +127,10 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     // ---- requests
     uint32_t off[L], dst[L], inc[L];
     const unsigned char *base[L];
-    uint32_t poff[PARTS ? G::QA / 8 : 1];             // of the rows' pieces, which are requested as one more slab of A
+    uint32_t poff[READS ? G::QA / 8 : 1];             // of the rows' pieces, which are requested as one more slab of A
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
     auto a_row = [&](int m) {
-        if constexpr (!PARTS) return fold.src[m];
+        if constexpr (!READS) return fold.src[m];
         const int t = fold.src[m];
         return m / fold.src_rows * fold.src_stride + ((unsigned)t < (unsigned)fold.src_stride ? t : 0);
     };
@@ -143,7 +144,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             const bool gather = LNF && fold.src;
             const int ar = gather ? a_row(m) : m - m0;
             off[i] = ((uint32_t)ar * (uint32_t)ld.a + c * 8) * 2;
-            if constexpr (PARTS) poff[i] = (uint32_t)(gather ? ar : m) * (GEMM_PARTS_MOST * 8) + c * 16;
+            if constexpr (READS) poff[i] = (uint32_t)(gather ? ar : m) * (GEMM_PARTS_MOST * 8) + c * 16;
             base[i] = reinterpret_cast<const unsigned char *>(gather ? A : A + (long)m0 * ld.a);
             dst[i] = lds0 + f * 1024;
         } else {
@@ -181,7 +182,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             else gemm_wait_vm<L * s>();
         };
         // (behind the last slab only the rows' pieces are out)
-        if (PARTS && rem < 1) { gemm_wait_vm<G::QA / 8>(); return; }
+        if (READS && rem < 1) { gemm_wait_vm<G::QA / 8>(); return; }
         if (rem >= MAX) out(integral_constant<int, MAX>{});
         else if (MAX > 2 && rem >= 2) out(integral_constant<int, 2>{});
         else if (MAX > 1 && rem >= 1) out(integral_constant<int, 1>{});
@@ -262,7 +263,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 #pragma unroll
             for (int k = 0; k < AHEAD; ++k) load_old(k);
         }
-        if constexpr (LNF && !PARTS) {
+        if constexpr (LNF && !READS) {
 #pragma unroll
             for (int k = 0; k < MTH; ++k) rst[k] = fold.stats[min(m0 + wm + 16 * (wk * MTH + k) + l16, M - 1)];
         }
@@ -323,7 +324,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 #pragma unroll
                     for (int i = LA; i < L; ++i) request(i, sa, sw);
                 // into the first stage that takes no slab any more, behind every slab (what is waited for from here on counts on it)
-                if constexpr (PARTS) if (t == n - SA) {
+                if constexpr (READS) if (t == n - SA) {
                     pieces = sa * STRIDE_A;
 #pragma unroll
                     for (int i = 0; i < LA; ++i) gemm_load_lds16_s(dst[i] + pieces, poff[i], fold.parts);
@@ -399,7 +400,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     __builtin_amdgcn_sched_barrier(0);
 
     if (!EARLY) load_epilogue();
-    if constexpr (PARTS) {
+    if constexpr (READS) {
         // a row's pieces over the four quads, its mean, then the squares about it (ln_stats_kernel's pieces in the same order)
         gemm_wait_vm<0>();
         LDS_BARRIER();
@@ -458,8 +459,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             if constexpr (EPI == SSAM_EPI_BIAS_GELU) v[e] = gelu_erf(v[e]);
         }
     };
-    constexpr bool PIECES = ADD && WPACK && G::WRITES_PARTS;
-    uint4 kept[PIECES ? MTH : 1][PIECES ? NP : 1];
+    uint4 kept[LEAVES ? MTH : 1][LEAVES ? NP : 1];
 #pragma unroll
     for (int k = 0; k < MTH; ++k) {
         bf16 *row = C + (long)drow[k] * ld.c;
@@ -477,7 +477,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             }
             const uint4 packed = pack_bf16x8(v);
             if (drow[k] >= 0 && ncol + 32 * p < N) *reinterpret_cast<uint4 *>(row + ncol + 32 * p) = packed;      // N % 8 == 0
-            if constexpr (PIECES) kept[k][p] = packed;
+            if constexpr (LEAVES) kept[k][p] = packed;
         }
         if constexpr (NT % 2) {
             float v[8];
@@ -492,7 +492,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
         }
         if constexpr (ADD) if (k + AHEAD < MTH) load_old(k + AHEAD);
     }
-    if constexpr (PIECES) if (fold.parts) {
+    if constexpr (LEAVES) {
         // Pieces of the rows from the values as stored: sums of 8 columns, of columns 32 apart, over the quads (gemm_piece_sum8 and the same tree in
         // whatever writes pieces: a row's are the same bits whichever kernel wrote it last).  Waves of 32 columns have the next wave's from LDS.
         float *x = reinterpret_cast<float *>(smem) + lane;        // [2][wave][MTH][64]: the ring is done with

@@ -39,7 +39,7 @@ int gemm_wide_launch_tile(const GemmWideArgs &a)
         return SSAM_EHIP;
     GemmTileRange tr = { ssam_div_up(a.M, BM), ssam_div_up(a.N, BN), 0, 0 };
     tr.tile_count = tr.tiles_m * tr.tiles_n;
-    hipLaunchKernelGGL(kern, dim3(ssam_div_up(tr.tile_count, 8) * 8 + (PARTS ? ssam_div_up(a.fold.fill.total_rows, GEMM_WIDE_FILL) : 0)), dim3(512), lds, a.st, a.A, a.W, a.bias, a.C, a.M, a.N, a.K, a.ld, tr, a.rm, a.fold);
+    hipLaunchKernelGGL(kern, dim3(ssam_div_up(tr.tile_count, 8) * 8 + (PARTS && LNF ? ssam_div_up(a.fold.fill.total_rows, GEMM_WIDE_FILL) : 0)), dim3(512), lds, a.st, a.A, a.W, a.bias, a.C, a.M, a.N, a.K, a.ld, tr, a.rm, a.fold);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
@@ -48,7 +48,7 @@ template <int EPI, bool WPACK, bool LNF, bool PARTS = false>
 int gemm_wide_launch(int tile, const GemmWideArgs &a)
 {
     switch (tile) {
-#define X(id, bm, bn, wgk) case id: if constexpr (!PARTS || ((GEMM_WIDE_READS_PARTS >> id) & 1)) return gemm_wide_launch_tile<bm, bn, wgk, EPI, WPACK, LNF, PARTS>(a); else return SSAM_EINVAL;
+#define X(id, bm, bn, wgk) case id: if constexpr (!PARTS || (((LNF ? GEMM_WIDE_READS_PARTS : GEMM_WIDE_WRITES_PARTS) >> id) & 1)) return gemm_wide_launch_tile<bm, bn, wgk, EPI, WPACK, LNF, PARTS>(a); else return SSAM_EINVAL;
     GEMM_WIDE_TILES(X)
 #undef X
     default: return SSAM_EINVAL;
