@@ -72,7 +72,7 @@ def _check(name, rc):
 
 # The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object around the same handle, 3.0 of the
 # 8.5 us that a call took on the host (0.35 this way): four dependent calls on one image's scores were bound by it, 33 us for 22 of kernels.
-if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):          # private names of torch
     def _stream():
         return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 else:
