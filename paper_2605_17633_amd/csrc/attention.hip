@@ -553,7 +553,7 @@ __host__ __device__ inline int wave_scratch_bytes(int tstr)
 // ------------------------------------------------------------------ window kernel, persistent
 // The bias as a product (two MFMAs a block, operands built once a tile) instead of 32 LDS look-ups and 80 vector instructions a block: 16 heads, d = 80,
 // 800 problems 34.2 -> 32.4 us at r = 0.4, 51.1 -> 45.7 dense; 3200: 99.6 -> 96.5 and 154.8 -> 137.3.
-// One sparse product instead of two dense ones: 3200 problems 98.4 -> 95.6 and 142.7 -> 138.6 on another box; a wave to a tile, d = 64, 1600 problems 38.3 -> 37.8.
+// One sparse product instead of two dense ones: 3200 problems 98.4 -> 95.6 and 142.7 -> 138.6 on another card; a wave to a tile, d = 64, 1600 problems 38.3 -> 37.8.
 inline int window_rel_rows(int w) { return ((2 * w - 1 + 31) / 32) * 32; }
 
 // per-wave LDS landing area of the next problem's queries: the KS operand-b fragments of the wave's 32 queries

@@ -22,7 +22,7 @@
 //   21 -> 16.5 | 4096 x 1024 x 1024 + scatter-add 16.9 -> 13 | 2456 x 1280 x 5120 57 -> 38 (its K-split launch and reduce) | 8192 x 1280 x 1280
 //   38 -> 28 | 8192 x 576 x 2304 row-major 36.5 -> 25.  Packed and row-major weights take the same time.
 // Encoders, batch 1: ViT-B 1360 -> 1258 us, ViT-L 3051 -> 2674; with the row statistics left and read by these kernels instead of launches of their
-// own (GemmParts) 1181 -> 1149 and 2517 -> 2424 on another box.  Steady state 1.29 us a slab of 256x256 (1.66 PFLOP/s).  Not faster: eight or
+// own (GemmParts) 1181 -> 1149 and 2517 -> 2424 on another card.  Steady state 1.29 us a slab of 256x256 (1.66 PFLOP/s).  Not faster: eight or
 // six slabs ahead, requests in front of the k-step (10 % slower: they crowd out the fragment reads), wave priority, 128x192 tiles two to
 // a CU, a persistent form whose next tile's slabs are requested under the epilogue (its waits then are for the stores too).
 #pragma once
