@@ -7,7 +7,7 @@
 
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
-                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts = GemmParts{});
+                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts = GemmParts{}, WarmAhead *warm = nullptr);
 int ssam_parts_form_of(int rows, int kept, int D, int Dm);
 
 int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int Nout, int N,
@@ -16,11 +16,11 @@ int ssam_ln_gather_impl(const void *x, const int32_t *idx, int idx_batch_stride,
                         int B, int Nin, int Nout, int D, const PadFill &fill, void *stream);
 int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int Nout, int N, int32_t *inv, hipStream_t st);
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
-                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill);
+                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill, WarmAhead *warm);
 
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
-                               void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride);
+                               void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride, WarmAhead *warm);
 int ssam_ln_stats_impl(const void *x, float *stats, long rows, int D, float eps, const int32_t *idx, int idx_batch_stride,
                        int Nin, int Nout, int32_t *src, const PadFill &fill, hipStream_t st, int slots);
 
@@ -114,7 +114,7 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
                            const void *w1, const float *b1, const void *w2, const float *b2, bool packed,
                            int B, int N, int D, int Dm, int K,
                            void *workspace, size_t workspace_bytes, void *stream, const float *colsum1 = nullptr, const GemmParts &parts = GemmParts{},
-                           const GemmParts &left = GemmParts{})
+                           const GemmParts &left = GemmParts{}, WarmAhead *warm = nullptr)
 {
     const bool fold = colsum1 != nullptr;
     if (!x || !keep_idx || (!fold && (!ln_g || !ln_b)) || !w1 || !b1 || !w2 || !b2 || !workspace) return SSAM_EINVAL;
@@ -130,25 +130,27 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
     void *split = ws + mlp_core_bytes(B, K, D, Dm);
     hipStream_t st = (hipStream_t)stream;
     int rc;
+    if (warm) warm->now += 1;
     if (fold && parts.at) {
-        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, keep_idx, nullptr, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, parts, K, N);
+        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, keep_idx, nullptr, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, parts, K, N, warm);
     } else if (fold) {
         // the region of the normalised rows holds only their statistics and the rows of x they are (8 + 4 bytes a row)
         float *stats = (float *)a2;
         int32_t *src = (int32_t *)(stats + 2 * (size_t)B * K);
         rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st, 0);
         if (rc != SSAM_OK) return rc;
-        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, 1, 0);
+        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, 1, 0, warm);
     } else {
         rc = ssam_ln_gather(x, keep_idx, K, ln_g, ln_b, eps, a2, B, N, K, D, stream);
         if (rc != SSAM_OK) return rc;
         GemmRowMap none = { nullptr, 1, 0, 1 };
-        rc = ssam_linear_impl(a2, w1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, packed, SSAM_EPI_BIAS_GELU, none, 0, split, GEMM_SPLIT_WS_BYTES, st);
+        rc = ssam_linear_impl(a2, w1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, packed, SSAM_EPI_BIAS_GELU, none, 0, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, warm);
     }
     if (rc != SSAM_OK) return rc;
     GemmRowMap scatter = { keep_idx, K, K, N };
+    if (warm) warm->now += 1;
     return ssam_linear_impl(hid, w2, b2, x, B * K, D, Dm, GemmLd{ Dm, Dm, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, scatter, 0,
-                            split, GEMM_SPLIT_WS_BYTES, st, left);
+                            split, GEMM_SPLIT_WS_BYTES, st, left, warm);
 }
 
 extern "C" int ssam_routed_mlp(void *x, const int32_t *keep_idx, const float *ln_g, const float *ln_b, float eps,
@@ -206,7 +208,7 @@ extern "C" size_t ssam_encoder_block_workspace_bytes(const ssam_block_cfg *cfg)
 static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_block_cfg *cfg,
                               const int32_t *gather_table, const int32_t *sigma, const int32_t *keep_idx,
                               void *workspace, size_t workspace_bytes, void **qkv_events, unsigned char *tables,
-                              bool tables_ready, bool *pad_rows_zero, bool *parts_ready, void *stream)
+                              bool tables_ready, bool *pad_rows_zero, bool *parts_ready, WarmAhead *warm, void *stream)
 {
     BlockGeom g;
     if (!x || !w || !gather_table || !sigma || !keep_idx || !workspace || !block_geom(cfg, g)) return SSAM_EINVAL;
@@ -268,7 +270,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
         }
         if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
         GemmRowMap to_slot = { slot_of_table(tables, B, g), g.N, per_image ? g.N : 0, g.Nout };
-        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, have_parts ? whole : tile_only, have_parts ? fill : PadFill{});
+        rc = ssam_linear_ln_impl(x, stats, w->wqkv, w->qkv_colsum, w->bqkv_folded, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, to_slot, st, have_parts ? whole : tile_only, have_parts ? fill : PadFill{}, warm);
         if (rc != SSAM_OK) return rc;
     }
 
@@ -277,7 +279,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
             rc = ssam_ln_gather(x, gather_table, per_image ? g.Nout : 0, w->ln1_g, w->ln1_b, cfg->eps, u, B, g.N, g.Nout, D, stream);
             if (rc != SSAM_OK) return rc;
             if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
-            rc = ssam_linear_impl(u, w->wqkv, w->bqkv, qkv, rows, 3 * D, D, GemmLd{ D, D, 3 * D }, packed, SSAM_EPI_BIAS, none, 0, split, GEMM_SPLIT_WS_BYTES, st);
+            rc = ssam_linear_impl(u, w->wqkv, w->bqkv, qkv, rows, 3 * D, D, GemmLd{ D, D, 3 * D }, packed, SSAM_EPI_BIAS, none, 0, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, warm);
             if (rc != SSAM_OK) return rc;
         }
         if (qkv_events && qkv_events[1] && hipEventRecord((hipEvent_t)qkv_events[1], st) != hipSuccess) return SSAM_EHIP;
@@ -285,8 +287,9 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
                                    B * g.nW, g.S, g.w, cfg->heads, g.d, cfg->mask_block, cfg->r,
                                    1.0f / sqrtf((float)g.d), stream);
         if (rc != SSAM_OK) return rc;
+        warm->now += 1;
         GemmRowMap back = { gather_table, g.Nout, per_image ? g.Nout : 0, g.N };
-        rc = ssam_linear_impl(u, w->wproj, bproj, x, rows, D, D, GemmLd{ D, D, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, back, 0, split, GEMM_SPLIT_WS_BYTES, st, parts);
+        rc = ssam_linear_impl(u, w->wproj, bproj, x, rows, D, D, GemmLd{ D, D, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, back, 0, split, GEMM_SPLIT_WS_BYTES, st, parts, warm);
         if (rc != SSAM_OK) return rc;
     } else {
         // Windows with padding: the padding slots are zero rows after LN1, so their qkv rows are the bias and
@@ -300,7 +303,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
             if (rc != SSAM_OK) return rc;
             if (qkv_events && qkv_events[0] && hipEventRecord((hipEvent_t)qkv_events[0], st) != hipSuccess) return SSAM_EHIP;
             GemmRowMap to_slot = { pt.real_slot, g.N, g.N, g.Nout };
-            rc = ssam_linear_impl(u, w->wqkv, w->bqkv, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, packed, SSAM_EPI_BIAS_SCATTER, to_slot, 0, split, GEMM_SPLIT_WS_BYTES, st);
+            rc = ssam_linear_impl(u, w->wqkv, w->bqkv, qkv, crows, 3 * D, D, GemmLd{ D, D, 3 * D }, packed, SSAM_EPI_BIAS_SCATTER, to_slot, 0, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, warm);
             if (rc != SSAM_OK) return rc;
         }
         if (qkv_events && qkv_events[1] && hipEventRecord((hipEvent_t)qkv_events[1], st) != hipSuccess) return SSAM_EHIP;
@@ -308,25 +311,27 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
                                    B * g.nW, g.S, g.w, cfg->heads, g.d, cfg->mask_block, cfg->r,
                                    1.0f / sqrtf((float)g.d), stream);
         if (rc != SSAM_OK) return rc;
+        warm->now += 1;
         GemmRowMap back = { pt.real_spatial, g.N, g.N, g.N };
-        rc = ssam_linear_impl(u, w->wproj, bproj, x, crows, D, D, GemmLd{ D, D, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, back, 0, split, GEMM_SPLIT_WS_BYTES, st, parts);
+        rc = ssam_linear_impl(u, w->wproj, bproj, x, crows, D, D, GemmLd{ D, D, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, back, 0, split, GEMM_SPLIT_WS_BYTES, st, parts, warm);
         if (rc != SSAM_OK) return rc;
     }
     const size_t attn_bytes = attn_half_bytes(cfg, g);
     if (w->fold_ln2 != 0) {
         if (!packed || !w->fc1_colsum || !w->b1_folded) return SSAM_EINVAL;
         return routed_mlp_impl(x, keep_idx, nullptr, nullptr, cfg->eps, w->w1, w->b1_folded, w->w2, w->b2, true,
-                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts, parts_ready ? whole : tile_only);
+                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts, parts_ready ? whole : tile_only, warm);
     }
     return routed_mlp_impl(x, keep_idx, w->ln2_g, w->ln2_b, cfg->eps, w->w1, w->b1, w->w2, w->b2, packed,
-                           B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream);
+                           B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, nullptr, GemmParts{}, GemmParts{}, warm);
 }
 
 extern "C" int ssam_encoder_block(void *x, const ssam_block_weights *w, const ssam_block_cfg *cfg,
                                   const int32_t *gather_table, const int32_t *sigma, const int32_t *keep_idx,
                                   void *workspace, size_t workspace_bytes, void *stream)
 {
-    return encoder_block_impl(x, w, cfg, gather_table, sigma, keep_idx, workspace, workspace_bytes, nullptr, nullptr, false, nullptr, nullptr, stream);
+    WarmAhead warm = { w, 1, cfg ? cfg->D : 0, cfg ? cfg->Dm : 0 };
+    return encoder_block_impl(x, w, cfg, gather_table, sigma, keep_idx, workspace, workspace_bytes, nullptr, nullptr, false, nullptr, nullptr, &warm, stream);
 }
 
 extern "C" size_t ssam_encoder_workspace_bytes(const ssam_block_cfg *cfg_local, const ssam_block_cfg *cfg_global)
@@ -409,11 +414,13 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
     }
     bool pad_rows_zero = false;                 // the padding slots of the windowed blocks' qkv tensor hold zeros
     bool parts_ready = false;                   // and the row statistics of x in pieces are up to date
+    WarmAhead warm = { weights, n_blocks, c0->D, c0->Dm };
     for (int i = 0; i < n_blocks; ++i) {
+        warm.now = 4 * i;
         void **ev = qkv_events ? qkv_events + 2 * i : nullptr;
         rc = is_global[i]
-                 ? encoder_block_impl(x, &weights[i], cfg_global, global_table, sigma_global, keep_idx, workspace, core, ev, tables_global, true, &pad_rows_zero, &parts_ready, stream)
-                 : encoder_block_impl(x, &weights[i], cfg_local, window_table, sigma_window, keep_idx, workspace, core, ev, tables_local, true, &pad_rows_zero, &parts_ready, stream);
+                 ? encoder_block_impl(x, &weights[i], cfg_global, global_table, sigma_global, keep_idx, workspace, core, ev, tables_global, true, &pad_rows_zero, &parts_ready, &warm, stream)
+                 : encoder_block_impl(x, &weights[i], cfg_local, window_table, sigma_window, keep_idx, workspace, core, ev, tables_local, true, &pad_rows_zero, &parts_ready, &warm, stream);
         if (rc != SSAM_OK) return rc;
     }
     return SSAM_OK;

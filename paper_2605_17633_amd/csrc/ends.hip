@@ -8,7 +8,7 @@
 
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
-                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts = GemmParts{});
+                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts = GemmParts{}, WarmAhead *warm = nullptr);
 
 namespace {
 

@@ -455,10 +455,50 @@ extern "C" int ssam_parts_tiles(int rows, int kept, int D, int Dm, int *tiles)
     return form;
 }
 
+// What a launch of `groups` workgroups without a tile reads: weights of the next contractions, no more than most_bytes, none twice.
+GemmWarm WarmAhead::take(int groups, double most_bytes)
+{
+    constexpr int AHEAD = 2;      // contractions; what lies further off is pushed out again by what is written before it is read (four ahead: 0.5 to 1 % slower)
+    GemmWarm out = {};
+    if (next <= now) { next = now + 1; done = 0; }
+    for (int s = 0; s < 3 && next <= now + AHEAD && next < 4 * blocks; ++s) {
+        const ssam_block_weights &b = w[next / 4];
+        const size_t sizes[4] = { (size_t)6 * D * D, (size_t)2 * D * D, (size_t)2 * D * Dm, (size_t)2 * D * Dm };
+        const void *at[4] = { b.wqkv, b.wproj, b.w1, b.w2 };
+        size_t bytes = sizes[next % 4] - done;
+        if ((double)bytes > most_bytes) bytes = (size_t)most_bytes & ~(size_t)8191;
+        if (bytes == 0 || !at[next % 4] || !ssam_aligned16(at[next % 4])) break;      // (the contraction itself refuses such weights)
+        out.at[s] = (const unsigned char *)at[next % 4] + done;
+        out.bytes[s] = (uint32_t)bytes;
+        out.groups = groups;
+        most_bytes -= (double)bytes;
+        done += bytes;
+        if (done < sizes[next % 4]) break;
+        ++next;
+        done = 0;
+    }
+    return out;
+}
+
+// The pieces that the launch of contraction `now` (four a block) reads ahead with `groups` workgroups, after those of every contraction before it: their
+// addresses and bytes.  Returns their number.  Host only, for tests; not part of the interface.
+extern "C" int ssam_warm_pieces(const ssam_block_weights *weights, int n_blocks, int D, int Dm, int now, int groups, double most_bytes, const void **at, uint32_t *bytes)
+{
+    WarmAhead ahead = { weights, n_blocks, D, Dm };
+    GemmWarm w = {};
+    for (int i = 0; i <= now; ++i) {
+        ahead.now = i;
+        w = ahead.take(groups, most_bytes);
+    }
+    int k = 0;
+    for (; k < 3 && w.bytes[k]; ++k) { at[k] = w.at[k]; bytes[k] = w.bytes[k]; }
+    return w.groups == groups || k == 0 ? k : SSAM_EINVAL;
+}
+
 // parts (optional): row statistics that a scatter-add leaves; the caller has asked ssam_parts_form_of.  With no place for them (at = NULL) only its tile is taken.
 int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,
                      const GemmLd &ld, bool packed, int epilogue, const GemmRowMap &rm, int tile,
-                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts)
+                     void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, WarmAhead *warm)
 {
     const SplitWs ws = { split_ws, split_ws_bytes };
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
@@ -471,7 +511,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
         if (const int wide = pick.wide; wide >= 0) {
             GemmFold out;
             out.parts = parts.at;
-            const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, out, st };
+            const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, out, st, warm, pick.us };
             switch (epilogue) {
             case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
             case SSAM_EPI_BIAS_GELU: return ssam_gemm_wide_gelu(wide, packed, args);
@@ -505,7 +545,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 // With parts (see ssam_parts_form_of) there are no stats, and src holds the rows of every batch of src_rows: row m / src_rows * src_stride + src[m] of A.
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
-                               void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride)
+                               void *split_ws, size_t split_ws_bytes, hipStream_t st, const GemmParts &parts, int src_rows, int src_stride, WarmAhead *warm)
 {
     const SplitWs ws = { split_ws, split_ws_bytes };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, src, parts.at, parts.slots, parts.eps, src_rows, src_stride };
@@ -513,9 +553,9 @@ int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, c
     const auto [wide, tile, ring, us] = choose_fold_gelu(M, N, K, ld, rows_a, ws, parts.at != nullptr);
     if (parts.at)
         return wide < 0 ? SSAM_EUNSUPPORTED
-                        : ssam_gemm_wide_parts_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
+                        : ssam_gemm_wide_parts_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st, warm, us });
     if (wide >= 0)
-        return ssam_gemm_wide_ln_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st });
+        return ssam_gemm_wide_ln_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st, warm, us });
     if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_GELU, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st);
     return launch_tile_packed<SSAM_EPI_BIAS_GELU, true>(tile, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld,
@@ -538,7 +578,7 @@ double folded_ln_us(int tiles, int K)
 // mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.  parts: instead of stats; with at = NULL the same kernel that would read
 // them with stats (of ssam_ln_stats_impl as from pieces: the same bits).
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
-                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill)
+                        void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill, WarmAhead *warm)
 {
     constexpr size_t lds = gemm_lds_bytes<128, 256, 1, 4, true>();
     static_assert(lds <= 64 * 1024, "default LDS limit");
@@ -547,9 +587,9 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     const auto [wide, tile, ring, us] = choose_ln(M, N, K, ld, parts.slots != 0);
     if (parts.at)
         return wide < 0 ? SSAM_EUNSUPPORTED
-                        : ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });
+                        : ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st, warm, us });
     if (wide >= 0)
-        return ssam_gemm_wide_ln_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st });
+        return ssam_gemm_wide_ln_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st, warm, us });
     if (ring >= 0)
         return launch_ring<SSAM_EPI_BIAS_SCATTER, true, true>(ring, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st);
     const int per_xcd = ssam_div_up(tr.tile_count, 8);
@@ -571,7 +611,7 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     if (ldx < K || ldc < N || ldx % 8 || ldc % 8 || rows_per_batch <= 0 || map_batch_stride < 0 || dst_rows_per_batch <= 0) return SSAM_EINVAL;
     if (M % 128 != 0 || N % 256 != 0 || K % GEMM_BK != 0) return SSAM_EUNSUPPORTED;
     const GemmRowMap rm = { row_map, rows_per_batch, map_batch_stride, dst_rows_per_batch };
-    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{}, PadFill{});
+    return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{}, PadFill{}, nullptr);
 }
 
 // Which kernel a contraction takes where the wide kernel does not (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
@@ -658,7 +698,7 @@ extern "C" int ssam_linear_ld(const void *A, int lda, const void *W, int ldw, in
     }
     GemmLd ld = { lda, ldw, ldc };
     return ssam_linear_impl(A, W, bias, C, M, N, K, ld, w_packed != 0, epilogue, rm, tile, workspace, workspace ? workspace_bytes : 0,
-                            (hipStream_t)stream, GemmParts{});
+                            (hipStream_t)stream, GemmParts{}, nullptr);
 }
 
 extern "C" int ssam_linear_tiled(const void *A, const void *W, const float *bias, void *C, int M, int N, int K,

@@ -95,6 +95,27 @@ struct GemmParts {
     float eps;
 };
 
+// Weights of contractions still to come that a launch reads with the CUs it has no tile for, so that they lie in the memory-side cache by then.  From HBM a
+// megabyte of weights costs the contraction that reads it 0.2 to 0.4 us (its first slabs wait, and a chain over K has four slabs in flight): 1228 x 1024 x 4096
+// 22.1 us, 18.4 from the cache; 8192 x 3840 x 1280 77.3, 72.2.  Encoders: ViT-B, one image 1138 -> 1076 us; ViT-L, one image 2405 -> 2315; ViT-B, 50 x 50, two
+// images 1469 -> 1369; ViT-H, content order, two images 7620 -> 7214.
+struct GemmWarm {
+    const unsigned char *at[3];
+    uint32_t bytes[3];        // multiples of 16
+    int groups;               // workgroups behind the tiles; 0: none
+};
+
+// The contractions of a stack of blocks in their order (four a block), and how far their weights have been read ahead.  Host side, for one call.
+struct WarmAhead {
+    const ssam_block_weights *w;
+    int blocks, D, Dm;
+    int now = 0;              // the contraction that is being launched
+    int next = 1;             // the first whose weights are not all read ahead
+    size_t done = 0;          //   and how much of them is
+
+    GemmWarm take(int groups, double most_bytes);
+};
+
 struct GemmSplit {
     float *partial;           // [tile_count*SUB_M*SUB_N][parts][BM][BN] fp32, NULL unless GEMM_EPI_PARTIAL
     int parts;                // K ranges per tile (1 otherwise); parts <= K/64

@@ -74,6 +74,24 @@ struct GemmWide {
 
 constexpr int GEMM_WIDE_FILL = 16;
 
+// Reads its share of the weights to come; nothing is kept.  Plain loads: with the non-temporal hint they do not stay in the memory-side cache (encoders 2 to 5 %
+// slower than without any).  More than 32 KB in flight a CU delays the tiles beside it (16 loads a thread: ViT-L 2538 -> 2550 us, ViT-H 7728 -> 7750).
+__device__ __forceinline__ void gemm_warm(const GemmWarm &warm, int group)
+{
+    constexpr uint32_t STEP = 512 * 16, U = 4;
+    const uint32_t stride = warm.groups * STEP;
+    for (int s = 0; s < 3; ++s) {
+        const uint32_t bytes = warm.bytes[s];
+        for (uint32_t at = group * STEP + threadIdx.x * 16; at < bytes; at += U * stride) {
+            u32x4 v[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) v[u] = *reinterpret_cast<const u32x4 *>(warm.at[s] + min(at + u * stride, bytes - 16));
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) asm volatile("" :: "v"(v[u]));
+        }
+    }
+}
+
 // Sum over the four quads of a wave's lanes.
 __device__ __forceinline__ float gemm_quad_sum(float v)
 {
@@ -89,7 +107,7 @@ __device__ __forceinline__ float gemm_quad_sum(float v)
 template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS = false>
 __global__ void __launch_bounds__(512, 1)
 gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
-                 bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
+                 bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold, GemmWarm warm)
 {
     using G = GemmWide<BM, BN, WGK>;
     constexpr bool READS = PARTS && LNF, LEAVES = PARTS && !LNF;
@@ -103,6 +121,11 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     unsigned char *as = smem, *ws = smem + W0;
 
     const int per_xcd = (tr.tile_count + 7) / 8, bid = blockIdx.x;
+    const int fills = READS && EPI == SSAM_EPI_BIAS_SCATTER ? (fold.fill.total_rows + GEMM_WIDE_FILL - 1) / GEMM_WIDE_FILL : 0;
+    if (bid >= 8 * per_xcd + fills) {
+        gemm_warm(warm, bid - 8 * per_xcd - fills);
+        return;
+    }
     if constexpr (READS && EPI == SSAM_EPI_BIAS_SCATTER) if (bid >= 8 * per_xcd) {
         // padding rows, GEMM_WIDE_FILL a workgroup, one after the other in a wave: on CUs that have no tile, or behind the first tiles that end.  After a
         // global block they are all that the statistics launch would be for (ViT-B, 64 x 64, batch 1: 192 tiles, 1110 -> 1093 us; ViT-L, 256 tiles: no change)

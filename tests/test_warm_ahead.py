@@ -1,0 +1,53 @@
+"""Which weights a launch with idle compute units reads ahead (host code: no GPU needed)."""
+import ctypes as C
+
+import pytest
+
+from paper_2605_17633_amd import binding as B
+
+NAMES = ("wqkv", "wproj", "w1", "w2")
+
+
+def pieces(ws, D, Dm, now, groups, most):
+    at, nbytes = (C.c_void_p * 3)(), (C.c_uint32 * 3)()
+    k = B.lib().ssam_warm_pieces(ws, C.c_int(len(ws)), C.c_int(D), C.c_int(Dm), C.c_int(now), C.c_int(groups), C.c_double(most), at, nbytes)
+    assert 0 <= k <= 3
+    return [(at[i], nbytes[i]) for i in range(k)]
+
+
+def stack(blocks, D, Dm, base=1 << 40):
+    """Blocks whose weights lie one behind the other, 4 KB between them."""
+    ws, spans = (B.BlockWeights * blocks)(), []
+    for i in range(blocks):
+        for name, size in zip(NAMES, (6 * D * D, 2 * D * D, 2 * D * Dm, 2 * D * Dm)):
+            setattr(ws[i], name, base)
+            spans.append((base, size))
+            base += size + 4096
+    return ws, spans
+
+
+@pytest.mark.parametrize("D,Dm,blocks,most", [(768, 3072, 3, 1e12), (128, 128, 2, 1e12), (1024, 4096, 2, 3e6), (1280, 5120, 2, 8191.0), (1280, 5120, 2, 0.0)])
+def test_pieces_lie_inside_the_next_weights_and_none_is_read_twice(D, Dm, blocks, most):
+    ws, spans = stack(blocks, D, Dm)
+    seen = {}
+    for now in range(4 * blocks):
+        total = 0
+        for at, n in pieces(ws, D, Dm, now, 32, most):
+            i = next(j for j, (b, size) in enumerate(spans) if b <= at < b + size)
+            assert now < i <= now + 2 and n > 0 and n % 16 == 0
+            assert at - spans[i][0] == seen.get(i, 0) and at + n <= spans[i][0] + spans[i][1]
+            seen[i] = seen.get(i, 0) + n
+            total += n
+        assert total <= most
+    if most == 1e12:
+        assert seen == {i: size for i, (_, size) in enumerate(spans) if i > 0}
+
+
+def test_missing_and_misaligned_weights_are_left_to_the_contraction():
+    ws, _ = stack(2, 256, 1024)
+    ws[0].w1 = None
+    ws[1].wproj = ws[1].wproj + 8
+    assert len(pieces(ws, 256, 1024, 0, 32, 1e12)) == 1      # wproj, not the missing w1
+    assert pieces(ws, 256, 1024, 1, 32, 1e12) == []
+    assert len(pieces(ws, 256, 1024, 2, 32, 1e12)) == 2      # w2 and the next wqkv
+    assert pieces(ws, 256, 1024, 3, 32, 1e12) == []          # not the misaligned wproj
