@@ -14,6 +14,7 @@ int ssam_compact_slots(const int32_t *table, int table_batch_stride, int B, int 
                        int32_t *real_slot, int32_t *real_spatial, int32_t *slot_row, int32_t *pad_slot, hipStream_t st);
 int ssam_ln_gather_impl(const void *x, const int32_t *idx, int idx_batch_stride, const float *gamma, const float *beta, float eps, void *y,
                         int B, int Nin, int Nout, int D, const PadFill &fill, void *stream);
+int ssam_select_and_tables(const float *scores, int32_t *keep_idx, int B, int N, int K, const BlockTables &local, const BlockTables &global, hipStream_t st);
 int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int Nout, int N, int32_t *inv, hipStream_t st);
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
                         void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill, WarmAhead *warm);
@@ -87,17 +88,31 @@ size_t block_tables_bytes(int B, const BlockGeom &g) { return pad_tables_bytes(B
 
 int32_t *slot_of_table(unsigned char *tables, int B, const BlockGeom &g) { return (int32_t *)(tables + pad_tables_bytes(B, g)); }
 
-// slots: some block folds its LayerNorm into the qkv contraction and reads slot_of (a launch of its own, 3 us of a small block)
-int build_block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int32_t *gather_table, unsigned char *tables, bool slots, hipStream_t st)
+// slots: some block folds its LayerNorm into the qkv contraction and reads slot_of
+BlockTables block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int32_t *gather_table, unsigned char *tables, bool slots)
 {
     const int per_image = cfg->content_order != 0;
+    BlockTables t = { gather_table, per_image ? g.Nout : 0, g.Nout, per_image ? cfg->B : 1 };
     if (g.Nout != g.N) {
         const PadTables pt = carve_pad_tables(tables, cfg->B, g);
-        int rc = ssam_compact_slots(gather_table, per_image ? g.Nout : 0, cfg->B, g.Nout, g.N, pt.real_slot, pt.real_spatial, pt.slot_row, pt.pad_slot, st);
+        t.real_slot = pt.real_slot;
+        t.real_spatial = pt.real_spatial;
+        t.slot_row = pt.slot_row;
+        t.pad_slot = pt.pad_slot;
+    }
+    if (slots) t.slot_of = slot_of_table(tables, cfg->B, g);
+    return t;
+}
+
+int build_block_tables(const ssam_block_cfg *cfg, const BlockGeom &g, const int32_t *gather_table, unsigned char *tables, bool slots, hipStream_t st)
+{
+    const BlockTables t = block_tables(cfg, g, gather_table, tables, slots);
+    if (t.real_slot) {
+        int rc = ssam_compact_slots(t.table, t.table_batch_stride, cfg->B, g.Nout, g.N, t.real_slot, t.real_spatial, t.slot_row, t.pad_slot, st);
         if (rc != SSAM_OK) return rc;
     }
-    if (!slots) return SSAM_OK;
-    return ssam_invert_table(gather_table, per_image ? g.Nout : 0, per_image ? cfg->B : 1, g.Nout, g.N, slot_of_table(tables, cfg->B, g), st);
+    if (!t.slot_of) return SSAM_OK;
+    return ssam_invert_table(t.table, t.table_batch_stride, t.slot_images, g.Nout, g.N, t.slot_of, st);
 }
 
 }  // namespace
@@ -386,8 +401,6 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
             if (rc != SSAM_OK) return rc;
         }
     }
-    rc = ssam_select_tokens(scores, keep_idx, c0->B, c0->g * c0->g, c0->K, stream);
-    if (rc != SSAM_OK) return rc;
     // the tables of either kind of block are the same for every block of that kind: built once, behind everything
     // the blocks write
     BlockGeom gl, gg;
@@ -404,14 +417,10 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
     }
     unsigned char *tables_local = (unsigned char *)workspace + core;
     unsigned char *tables_global = tables_local + (any_local ? block_tables_bytes(cfg_local->B, gl) : 0);
-    if (any_local) {
-        rc = build_block_tables(cfg_local, gl, window_table, tables_local, slots_local, (hipStream_t)stream);
-        if (rc != SSAM_OK) return rc;
-    }
-    if (any_global) {
-        rc = build_block_tables(cfg_global, gg, global_table, tables_global, slots_global, (hipStream_t)stream);
-        if (rc != SSAM_OK) return rc;
-    }
+    rc = ssam_select_and_tables(scores, keep_idx, c0->B, c0->g * c0->g, c0->K,
+                                any_local ? block_tables(cfg_local, gl, window_table, tables_local, slots_local) : BlockTables{},
+                                any_global ? block_tables(cfg_global, gg, global_table, tables_global, slots_global) : BlockTables{}, (hipStream_t)stream);
+    if (rc != SSAM_OK) return rc;
     bool pad_rows_zero = false;                 // the padding slots of the windowed blocks' qkv tensor hold zeros
     bool parts_ready = false;                   // and the row statistics of x in pieces are up to date
     WarmAhead warm = { weights, n_blocks, c0->D, c0->Dm };

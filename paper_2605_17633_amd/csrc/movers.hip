@@ -274,14 +274,18 @@ fold_kv_bias_kernel(const float *__restrict__ bias_in, const float *__restrict__
 }
 
 // inv[b][table[b][p]] = p for every slot p that holds a token (table entries < 0 are padding)
-__global__ void __launch_bounds__(256)
-invert_table_kernel(const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N, int32_t *__restrict__ inv, int total)
+__device__ __forceinline__ void invert_slot(int id, const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N, int32_t *__restrict__ inv, int total)
 {
-    int id = blockIdx.x * 256 + threadIdx.x;
     if (id >= total) return;
     int b = id / Nout, p = id - b * Nout;
     int s = table[(long)b * table_batch_stride + p];
     if (s >= 0 && s < N) inv[(long)b * N + s] = p;
+}
+
+__global__ void __launch_bounds__(256)
+invert_table_kernel(const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N, int32_t *__restrict__ inv, int total)
+{
+    invert_slot(blockIdx.x * 256 + threadIdx.x, table, table_batch_stride, Nout, N, inv, total);
 }
 
 // ---------------------------------------------------------------- scores
@@ -453,15 +457,12 @@ __device__ __forceinline__ T wave_inclusive_sum(T v)
 // thread's 128 registers do not hold its keys and all the rest: 42 of them go through scratch (16400 scores: 34 us).
 constexpr int SEL_BINS = 2048;
 template <int ITEMS>
-__global__ void __launch_bounds__(SEL_THREADS)
-select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int N, int K)
+__device__ __forceinline__ void select_image(const float *__restrict__ s, int32_t *__restrict__ out, int N, int K)
 {
     __shared__ alignas(16) int hist[3][SEL_BINS];         // cleared by 16-byte stores
     __shared__ unsigned long long scratch[SEL_THREADS / 64];
     __shared__ uint32_t sh_prefix;
     __shared__ int sh_remaining;
-    const float *s = scores + (long)blockIdx.x * N;
-    int32_t *out = keep + (long)blockIdx.x * K;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int first = tid * ITEMS;
     for (int i = tid; i < 3 * SEL_BINS / 4; i += SEL_THREADS) reinterpret_cast<int4 *>(hist)[i] = make_int4(0, 0, 0, 0);      // under the latency of the scores
@@ -537,6 +538,13 @@ select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int 
     }
 }
 
+template <int ITEMS>
+__global__ void __launch_bounds__(SEL_THREADS)
+select_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int N, int K)
+{
+    select_image<ITEMS>(scores + (long)blockIdx.x * N, keep + (long)blockIdx.x * K, N, K);
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- entry points
@@ -560,13 +568,12 @@ static int mover_grid(long total_chunks)
 //   slot_row[b][s]     b*N + c for a real slot (the compact row), -1 for padding
 //   pad_slot[b][i]     the i-th padding slot
 // so that the dense contractions run on the N real rows only.
-__global__ void __launch_bounds__(SEL_THREADS)
-compact_slots_kernel(const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N,
-                     int32_t *__restrict__ real_slot, int32_t *__restrict__ real_spatial,
-                     int32_t *__restrict__ slot_row, int32_t *__restrict__ pad_slot)
+__device__ __forceinline__ void compact_image(int b, const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N,
+                                              int32_t *__restrict__ real_slot, int32_t *__restrict__ real_spatial,
+                                              int32_t *__restrict__ slot_row, int32_t *__restrict__ pad_slot)
 {
     __shared__ int scratch[SEL_THREADS / 64];
-    const int b = blockIdx.x, npad = Nout - N;
+    const int npad = Nout - N;
     const int32_t *t = table + (long)b * table_batch_stride;
     int base = 0;
     for (int s0 = 0; s0 < Nout; s0 += SEL_THREADS) {
@@ -590,6 +597,36 @@ compact_slots_kernel(const int32_t *__restrict__ table, int table_batch_stride, 
         }
         base += total;
     }
+}
+
+__global__ void __launch_bounds__(SEL_THREADS)
+compact_slots_kernel(const int32_t *__restrict__ table, int table_batch_stride, int Nout, int N,
+                     int32_t *__restrict__ real_slot, int32_t *__restrict__ real_spatial,
+                     int32_t *__restrict__ slot_row, int32_t *__restrict__ pad_slot)
+{
+    compact_image(blockIdx.x, table, table_batch_stride, Nout, N, real_slot, real_spatial, slot_row, pad_slot);
+}
+
+// What a stack needs in front of its first block beside the scores, in one launch: the keep-set (a workgroup an image), then of either kind of block the
+// compaction of its slots (a workgroup an image) and the inverse of its gather table (a workgroup 1024 slots).  None waits for another, each leaves the chip all but
+// idle, and in a chain each took 4.6 to 7.4 us however small: ViT-B, 64 x 64, one image 23.1 us in four launches, 7.9 in one.
+template <int ITEMS>
+__global__ void __launch_bounds__(SEL_THREADS)
+select_and_tables_kernel(const float *__restrict__ scores, int32_t *__restrict__ keep, int B, int N, int K, BlockTables local, BlockTables global)
+{
+    int i = blockIdx.x;
+    if (i < B) {
+        select_image<ITEMS>(scores + (long)i * N, keep + (long)i * K, N, K);
+        return;
+    }
+    i -= B;
+    auto tables = [&](const BlockTables &t, int j) {
+        if (t.real_slot && j < B) compact_image(j, t.table, t.table_batch_stride, t.Nout, N, t.real_slot, t.real_spatial, t.slot_row, t.pad_slot);
+        else invert_slot((j - (t.real_slot ? B : 0)) * SEL_THREADS + threadIdx.x, t.table, t.table_batch_stride, t.Nout, N, t.slot_of, t.slot_images * t.Nout);
+    };
+    const int n = local.workgroups(B);
+    if (i < n) tables(local, i);
+    else tables(global, i - n);
 }
 
 // ---------------------------------------------------------------- content-aware order
@@ -820,6 +857,18 @@ extern "C" int ssam_select_tokens(const float *scores, int32_t *keep_idx, int B,
     if (N <= 4 * SEL_THREADS) hipLaunchKernelGGL(select_kernel<4>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
     else if (N <= 16 * SEL_THREADS) hipLaunchKernelGGL(select_kernel<16>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
     else hipLaunchKernelGGL(select_kernel<64>, dim3(B), dim3(SEL_THREADS), 0, st, scores, keep_idx, N, K);
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
+}
+
+// internal (stack composition): ssam_select_tokens and the tables of both kinds of block, in one launch
+int ssam_select_and_tables(const float *scores, int32_t *keep_idx, int B, int N, int K, const BlockTables &local, const BlockTables &global, hipStream_t st)
+{
+    if (!scores || !keep_idx || B <= 0 || N <= 0 || K <= 0 || K > N) return SSAM_EINVAL;
+    if (N > 65536) return SSAM_EUNSUPPORTED;
+    const dim3 grid(B + local.workgroups(B) + global.workgroups(B));
+    auto kern = N <= 4 * SEL_THREADS ? select_and_tables_kernel<4> : N <= 16 * SEL_THREADS ? select_and_tables_kernel<16> : select_and_tables_kernel<64>;
+    hipLaunchKernelGGL(kern, grid, dim3(SEL_THREADS), 0, st, scores, keep_idx, B, N, K, local, global);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
