@@ -861,18 +861,6 @@ extern "C" int ssam_select_tokens(const float *scores, int32_t *keep_idx, int B,
     return SSAM_OK;
 }
 
-// internal (stack composition): ssam_select_tokens and the tables of both kinds of block, in one launch
-int ssam_select_and_tables(const float *scores, int32_t *keep_idx, int B, int N, int K, const BlockTables &local, const BlockTables &global, hipStream_t st)
-{
-    if (!scores || !keep_idx || B <= 0 || N <= 0 || K <= 0 || K > N) return SSAM_EINVAL;
-    if (N > 65536) return SSAM_EUNSUPPORTED;
-    const dim3 grid(B + local.workgroups(B) + global.workgroups(B));
-    auto kern = N <= 4 * SEL_THREADS ? select_and_tables_kernel<4> : N <= 16 * SEL_THREADS ? select_and_tables_kernel<16> : select_and_tables_kernel<64>;
-    hipLaunchKernelGGL(kern, grid, dim3(SEL_THREADS), 0, st, scores, keep_idx, B, N, K, local, global);
-    SSAM_CHECK_LAUNCH();
-    return SSAM_OK;
-}
-
 // Threads of a counting workgroup: no more waves than the group has cells for.
 static int rank_threads(int S) { return S > 8192 ? 1024 : S >= 512 / RANK_LANES ? 512 : ssam_div_up(S, 64 / RANK_LANES) * 64; }
 
@@ -979,6 +967,27 @@ int ssam_invert_table(const int32_t *table, int table_batch_stride, int B, int N
 {
     const int total = B * Nout;
     hipLaunchKernelGGL(invert_table_kernel, dim3(ssam_div_up(total, 256)), dim3(256), 0, st, table, table_batch_stride, Nout, N, inv, total);
+    SSAM_CHECK_LAUNCH();
+    return SSAM_OK;
+}
+
+// internal (stack composition): ssam_select_tokens and the tables of both kinds of block, in one launch
+int ssam_select_and_tables(const float *scores, int32_t *keep_idx, int B, int N, int K, const BlockTables &local, const BlockTables &global, hipStream_t st)
+{
+    if (!scores || !keep_idx || B <= 0 || N <= 0 || K <= 0 || K > N) return SSAM_EINVAL;
+    if (N > 65536) return SSAM_EUNSUPPORTED;
+    // (a selection over more scores spills and takes 34 us: launches of their own)
+    if (N > 16 * SEL_THREADS) {
+        int rc = ssam_select_tokens(scores, keep_idx, B, N, K, st);
+        for (const BlockTables *t : { &local, &global }) {
+            if (rc == SSAM_OK && t->real_slot) rc = ssam_compact_slots(t->table, t->table_batch_stride, B, t->Nout, N, t->real_slot, t->real_spatial, t->slot_row, t->pad_slot, st);
+            if (rc == SSAM_OK && t->slot_of) rc = ssam_invert_table(t->table, t->table_batch_stride, t->slot_images, t->Nout, N, t->slot_of, st);
+        }
+        return rc;
+    }
+    const dim3 grid(B + local.workgroups(B) + global.workgroups(B));
+    auto kern = N <= 4 * SEL_THREADS ? select_and_tables_kernel<4> : select_and_tables_kernel<16>;
+    hipLaunchKernelGGL(kern, grid, dim3(SEL_THREADS), 0, st, scores, keep_idx, B, N, K, local, global);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }
