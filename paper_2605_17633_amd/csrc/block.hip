@@ -124,12 +124,13 @@ extern "C" size_t ssam_routed_mlp_workspace_bytes(int B, int K, int D, int Dm)
 }
 
 // colsum1 != NULL: gather and LN2 folded into fc1 (w1 the packed folded weight, b1 the folded bias; ln_g, ln_b unused)
-// parts: row statistics of x in pieces, read by fc1 instead of a statistics launch; left: what fc2 does with them (see ssam_linear_impl)
+// parts: row statistics of x in pieces, read by fc1 instead of a statistics launch; left: what fc2 does with them (see ssam_linear_impl); split_bytes: what is
+// left of the K-split scratch beside them
 static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, const float *ln_b, float eps,
                            const void *w1, const float *b1, const void *w2, const float *b2, bool packed,
                            int B, int N, int D, int Dm, int K,
                            void *workspace, size_t workspace_bytes, void *stream, const float *colsum1 = nullptr, const GemmParts &parts = GemmParts{},
-                           const GemmParts &left = GemmParts{}, WarmAhead *warm = nullptr)
+                           const GemmParts &left = GemmParts{}, WarmAhead *warm = nullptr, size_t split_bytes = GEMM_SPLIT_WS_BYTES)
 {
     const bool fold = colsum1 != nullptr;
     if (!x || !keep_idx || (!fold && (!ln_g || !ln_b)) || !w1 || !b1 || !w2 || !b2 || !workspace) return SSAM_EINVAL;
@@ -147,25 +148,25 @@ static int routed_mlp_impl(void *x, const int32_t *keep_idx, const float *ln_g, 
     int rc;
     if (warm) warm->now += 1;
     if (fold && parts.at) {
-        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, keep_idx, nullptr, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, parts, K, N, warm);
+        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, keep_idx, nullptr, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, split_bytes, st, parts, K, N, warm);
     } else if (fold) {
         // the region of the normalised rows holds only their statistics and the rows of x they are (8 + 4 bytes a row)
         float *stats = (float *)a2;
         int32_t *src = (int32_t *)(stats + 2 * (size_t)B * K);
         rc = ssam_ln_stats_impl(x, stats, (long)B * K, D, eps, keep_idx, K, N, K, src, PadFill{}, st, 0);
         if (rc != SSAM_OK) return rc;
-        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, 1, 0, warm);
+        rc = ssam_linear_fold_gelu_impl(x, (long)B * N, src, stats, w1, colsum1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, split, split_bytes, st, GemmParts{}, 1, 0, warm);
     } else {
         rc = ssam_ln_gather(x, keep_idx, K, ln_g, ln_b, eps, a2, B, N, K, D, stream);
         if (rc != SSAM_OK) return rc;
         GemmRowMap none = { nullptr, 1, 0, 1 };
-        rc = ssam_linear_impl(a2, w1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, packed, SSAM_EPI_BIAS_GELU, none, 0, split, GEMM_SPLIT_WS_BYTES, st, GemmParts{}, warm);
+        rc = ssam_linear_impl(a2, w1, b1, hid, B * K, Dm, D, GemmLd{ D, D, Dm }, packed, SSAM_EPI_BIAS_GELU, none, 0, split, split_bytes, st, GemmParts{}, warm);
     }
     if (rc != SSAM_OK) return rc;
     GemmRowMap scatter = { keep_idx, K, K, N };
     if (warm) warm->now += 1;
     return ssam_linear_impl(hid, w2, b2, x, B * K, D, Dm, GemmLd{ Dm, Dm, D }, packed, SSAM_EPI_BIAS_SCATTER_ADD, scatter, 0,
-                            split, GEMM_SPLIT_WS_BYTES, st, left, warm);
+                            split, split_bytes, st, left, warm);
 }
 
 extern "C" int ssam_routed_mlp(void *x, const int32_t *keep_idx, const float *ln_g, const float *ln_b, float eps,
@@ -219,7 +220,7 @@ extern "C" size_t ssam_encoder_block_workspace_bytes(const ssam_block_cfg *cfg)
 // parts_ready (a block of a stack): the row statistics of x in pieces (GemmParts) are up to date, on entry from the block before.  They lie at the end of the
 // workspace's bytes in front of the tables, the K-split scratch of the MLP; a stack's blocks all have the same end.  proj writes every row, and with it its
 // pieces, which fc1 reads; where the next block's qkv reads them too (ssam_parts_form_of: 3) fc2 keeps them up to date and nothing uses that scratch, else they
-// are done with when fc2, which may use it, begins.
+// are done with when fc2, which may use it, begins; where D > 1024 fc1 and fc2 use what is in front of them.
 static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_block_cfg *cfg,
                               const int32_t *gather_table, const int32_t *sigma, const int32_t *keep_idx,
                               void *workspace, size_t workspace_bytes, void **qkv_events, unsigned char *tables,
@@ -257,10 +258,12 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     }
     if (kv_shift && (!fold || !w->bproj_folded)) return SSAM_EINVAL;
     const float *bproj = kv_shift ? w->bproj_folded : w->bproj;
-    const size_t parts_bytes = align256((size_t)crows * GEMM_PARTS_MOST * sizeof(float2));
+    const size_t parts_bytes = align256((size_t)crows * gemm_parts_pitch(D / 64) * sizeof(float2));
     const int form = fold && w->fold_ln2 != 0 && parts_bytes <= GEMM_SPLIT_WS_BYTES - 256 ? ssam_parts_form_of(crows, B * cfg->K, D, cfg->Dm) : 0;
     const GemmParts parts = form ? GemmParts{ (float2 *)((unsigned char *)workspace + (workspace_bytes & ~(size_t)255) - parts_bytes), D / 64, cfg->eps } : GemmParts{};
     const GemmParts whole = form == 3 ? parts : GemmParts{}, tile_only = { nullptr, whole.slots, cfg->eps };       // (in a single block: a stack's blocks are then the same bits)
+    // the kernels of the longer rows cut K beside the pieces that lie in the same scratch (a single block likewise: the same cuts, the same bits)
+    const size_t split_bytes = form && D / 64 > GEMM_PARTS_LINE ? GEMM_SPLIT_WS_BYTES - 256 - parts_bytes : GEMM_SPLIT_WS_BYTES;
     const bool have_parts = whole.at && parts_ready && *parts_ready;
     if (parts_ready) *parts_ready = whole.at != nullptr;
     if (!tables_ready) {
@@ -335,7 +338,7 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     if (w->fold_ln2 != 0) {
         if (!packed || !w->fc1_colsum || !w->b1_folded) return SSAM_EINVAL;
         return routed_mlp_impl(x, keep_idx, nullptr, nullptr, cfg->eps, w->w1, w->b1_folded, w->w2, w->b2, true,
-                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts, parts_ready ? whole : tile_only, warm);
+                               B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, w->fc1_colsum, parts, parts_ready ? whole : tile_only, warm, split_bytes);
     }
     return routed_mlp_impl(x, keep_idx, w->ln2_g, w->ln2_b, cfg->eps, w->w1, w->b1, w->w2, w->b2, packed,
                            B, g.N, D, cfg->Dm, cfg->K, ws + attn_bytes, mlp_ws_bytes(B, cfg->K, D, cfg->Dm), stream, nullptr, GemmParts{}, GemmParts{}, warm);

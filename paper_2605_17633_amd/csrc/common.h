@@ -114,7 +114,10 @@ __device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
     }
 }
 
-constexpr int GEMM_PARTS_MOST = 16;           // pieces of a row's statistics (GemmParts): 128 bytes, as long as a row of a slab of 64 bf16
+constexpr int GEMM_PARTS_LINE = 16;           // pieces of a row's statistics (GemmParts) in 128 bytes, a row of a slab of 64 bf16
+constexpr int GEMM_PARTS_MOST = 20;           // the most: rows of 1280
+// pieces from one row to the next (their number is even: rows begin on 16 bytes)
+__host__ __device__ constexpr int gemm_parts_pitch(int slots) { return slots > GEMM_PARTS_LINE ? slots : GEMM_PARTS_LINE; }
 
 // Of 8 columns of a piece of a row's statistics (GemmParts): their sum, their squared deviations from the piece's mean.  In this order wherever pieces are written.
 __device__ __forceinline__ float gemm_piece_sum8(const float *v)
@@ -137,6 +140,26 @@ __device__ __forceinline__ float gemm_piece_term(float2 piece, float mean)
 {
     const float d = piece.x - mean;
     return fmaf(64.f * d, d, piece.y);
+}
+
+// { rstd, -rstd * mean } of a row of K from its pieces, by one thread: pieces 4 * k + quad one after the other, then the four quads, as in ln_stats_kernel.
+__device__ __forceinline__ float2 gemm_row_stats(const float2 *row, int slots, int K, float eps)
+{
+    float4 two[GEMM_PARTS_MOST / 2];
+#pragma unroll
+    for (int i = 0; i < GEMM_PARTS_MOST / 2; ++i) two[i] = reinterpret_cast<const float4 *>(row)[min(i, slots / 2 - 1)];
+    float s[4] = { 0.f, 0.f, 0.f, 0.f };
+#pragma unroll
+    for (int i = 0; i < GEMM_PARTS_MOST; ++i)
+        if (i < slots) s[i % 4] += i % 2 ? two[i / 2].z : two[i / 2].x;
+    const float mean = ((s[0] + s[1]) + (s[2] + s[3])) / (float)slots;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = 0.f;
+#pragma unroll
+    for (int i = 0; i < GEMM_PARTS_MOST; ++i)
+        if (i < slots) s[i % 4] += gemm_piece_term(i % 2 ? make_float2(two[i / 2].z, two[i / 2].w) : make_float2(two[i / 2].x, two[i / 2].y), mean);
+    const float inv = rsqrtf(((s[0] + s[1]) + (s[2] + s[3])) / (float)K + eps);
+    return make_float2(inv, -inv * mean);
 }
 
 // erf GELU, 0.5 t (1 + erf(t / sqrt 2)) = max(t, 0) - 0.5 |t| erfc(|t| / sqrt 2).  erfc by the rational approximation 7.1.26 of

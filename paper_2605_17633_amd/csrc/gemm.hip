@@ -1,4 +1,6 @@
 // Dispatcher of the bf16 NT GEMM (qkv / proj / fc1 / fc2 of the SAM block).
+#include <algorithm>
+
 #include "gemm_direct.h"
 #include "gemm_ring.h"
 #include "gemm_wide_launch.h"
@@ -53,14 +55,14 @@ TailPlan plan_tail(int total, int slots, int nk, int subs, size_t sub_tile_bytes
     return p;
 }
 
-template <int BM, int BN, int EPI, int SUB_M, int SUB_N, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
+template <int BM, int BN, int EPI, int SUB_M, int SUB_N, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false, bool PARTS = false>
 int launch_range(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
                  const GemmLd &ld, const GemmTileRange &tr, const GemmRowMap &rm, const GemmSplit &sp, const GemmFold &fold,
                  hipStream_t st)
 {
     if (tr.tile_count <= 0) return SSAM_OK;
     constexpr size_t lds = gemm_lds_bytes<BM, BN, WGM, WGN, WPACK>();
-    auto kern = gemm_bf16_nt_kernel<BM, BN, EPI, SUB_M, SUB_N, WGM, WGN, WPACK, LNF>;
+    auto kern = gemm_bf16_nt_kernel<BM, BN, EPI, SUB_M, SUB_N, WGM, WGN, WPACK, LNF, PARTS>;
     // more than 64 KiB of LDS per workgroup needs the per-kernel opt-in (idempotent, host-side only)
     if (lds > 64 * 1024 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -74,7 +76,7 @@ int launch_range(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M
 // Whole rounds of BM x BN tiles, then the left-over tiles (when they would fill less than half a round)
 // as TM x TN tiles, BM = SUB_M*TM, BN = SUB_N*TN.  slots = workgroups the chip runs at once with the large
 // tile.  With a workspace, a long K and few left-over tiles, the left-over launch also cuts K (see the kernel).
-template <int BM, int BN, int TM, int TN, int EPI, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
+template <int BM, int BN, int TM, int TN, int EPI, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false, bool PARTS = false>
 int launch_split(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M, int N, int K,
                  const GemmLd &ld, int slots, const GemmRowMap &rm, const SplitWs &ws, const GemmFold &fold, hipStream_t st)
 {
@@ -99,35 +101,35 @@ int launch_split(const bf16 *A, const bf16 *W, const float *bias, bf16 *C, int M
         static_assert(lds <= 64 * 1024, "the fused launch stays within the default LDS limit");
         if (parts > 1) {
             const GemmSplit sp = { (float *)ws.ptr, parts };
-            hipLaunchKernelGGL((gemm_bf16_nt_fused_kernel<BM, BN, EPI, WGM, WGN, TM, TN, GEMM_EPI_PARTIAL, SUB_M, SUB_N, WPACK, LNF>),
+            hipLaunchKernelGGL((gemm_bf16_nt_fused_kernel<BM, BN, EPI, WGM, WGN, TM, TN, GEMM_EPI_PARTIAL, SUB_M, SUB_N, WPACK, LNF, PARTS>),
                                dim3(n_tail + n_main), dim3(256), lds, st, A, W, bias, C, M, N, K, ld, tr, tt, rm, sp, n_tail, fold);
             SSAM_CHECK_LAUNCH();
             constexpr int RPB = 256 / (TN / 8);
-            hipLaunchKernelGGL((gemm_tail_reduce_kernel<TM, TN, EPI, SUB_M, SUB_N, LNF>), dim3(n_sub * (TM / RPB)), dim3(256), 0, st,
-                               (const float *)ws.ptr, parts, bias, C, M, N, ld, tt, rm, fold);
+            hipLaunchKernelGGL((gemm_tail_reduce_kernel<TM, TN, EPI, SUB_M, SUB_N, LNF, PARTS>), dim3(n_sub * (TM / RPB)), dim3(256), 0, st,
+                               (const float *)ws.ptr, parts, bias, C, M, N, K, ld, tt, rm, fold);
         } else {
-            hipLaunchKernelGGL((gemm_bf16_nt_fused_kernel<BM, BN, EPI, WGM, WGN, TM, TN, EPI, SUB_M, SUB_N, WPACK, LNF>),
+            hipLaunchKernelGGL((gemm_bf16_nt_fused_kernel<BM, BN, EPI, WGM, WGN, TM, TN, EPI, SUB_M, SUB_N, WPACK, LNF, PARTS>),
                                dim3(n_tail + n_main), dim3(256), lds, st, A, W, bias, C, M, N, K, ld, tr, tt, rm, whole, n_tail, fold);
         }
         SSAM_CHECK_LAUNCH();
         return SSAM_OK;
     }
-    int rc = launch_range<BM, BN, EPI, 1, 1, WGM, WGN, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, whole, fold, st);
+    int rc = launch_range<BM, BN, EPI, 1, 1, WGM, WGN, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr, rm, whole, fold, st);
     if (rc != SSAM_OK || rem == 0) return rc;
     tr.tile_begin = total - rem;
     tr.tile_count = rem;
     const int n_sub = rem * SUB_M * SUB_N;
     if (parts > 1) {
         const GemmSplit sp = { (float *)ws.ptr, parts };
-        rc = launch_range<TM, TN, GEMM_EPI_PARTIAL, SUB_M, SUB_N, 2, 2, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, sp, fold, st);
+        rc = launch_range<TM, TN, GEMM_EPI_PARTIAL, SUB_M, SUB_N, 2, 2, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr, rm, sp, fold, st);
         if (rc != SSAM_OK) return rc;
         constexpr int RPB = 256 / (TN / 8);
-        hipLaunchKernelGGL((gemm_tail_reduce_kernel<TM, TN, EPI, SUB_M, SUB_N, LNF>), dim3(n_sub * (TM / RPB)), dim3(256), 0, st,
-                           (const float *)ws.ptr, parts, bias, C, M, N, ld, tr, rm, fold);
+        hipLaunchKernelGGL((gemm_tail_reduce_kernel<TM, TN, EPI, SUB_M, SUB_N, LNF, PARTS>), dim3(n_sub * (TM / RPB)), dim3(256), 0, st,
+                           (const float *)ws.ptr, parts, bias, C, M, N, K, ld, tr, rm, fold);
         SSAM_CHECK_LAUNCH();
         return SSAM_OK;
     }
-    return launch_range<TM, TN, EPI, SUB_M, SUB_N, 2, 2, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, whole, fold, st);
+    return launch_range<TM, TN, EPI, SUB_M, SUB_N, 2, 2, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr, rm, whole, fold, st);
 }
 
 const GemmFold no_fold = {};
@@ -180,7 +182,7 @@ double all_split_us(int M, int N, int nk, int parts, int bn, int tm, int tn, boo
 // 5 us a round behind the GELU epilogue and 1-2.5 us behind the others.  The 128x128 tile (two per CU) moves
 // more data per flop and is for small problems.  The left-over launch costs a lone workgroup's walk over its
 // K range, latency bound, plus the reduce.
-int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed, double &launch_us)
+int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed, double &launch_us, int only = 0)
 {
     struct Cand { int id, bm, bn, tm, tn, slots; double t_slab, t_epi[4]; };   // t_epi: bias, +GELU, scatter-add, scatter
     const Cand cands[4] = { { 1, 256, 256, 128, 128, 256, 1.73, { 5.1, 13.6, 13.5, 6.0 } },
@@ -192,6 +194,7 @@ int pick_tile(int M, int N, int K, int epilogue, const SplitWs &ws, bool packed,
     double best_time = 1e30;
     for (const Cand &c : cands) {
         if (c.id == 2) continue;    // 256x128 is never the fastest on these shapes: kept as a forced choice only
+        if (only != 0 && c.id != only) continue;
         if (c.id == 4 && !packed) continue;   // with W in LDS a 128x256 workgroup needs 96 KB: one per CU, nothing overlaps
         const int subs = (c.bm / c.tm) * (c.bn / c.tn);
         const int total = ssam_div_up(M, c.bm) * ssam_div_up(N, c.bn);
@@ -374,6 +377,16 @@ int launch_any(int tile, int ring, const bf16 *A, const bf16 *W, const float *bi
 // The kernel of a contraction: the wide kernel's tile, or (wide = -1) the ring, or (ring = -1) the large tile; what it takes, in microseconds.
 struct Choice { int wide, tile, ring; double us; };
 
+// Row statistics in more pieces than a row of a slab holds (D = 1280) are read by the large 128x256 tile too, in front of its first slab: 0.5 us a round of it,
+// 1.2 of gathered rows (8192 x 3840 x 1280 69.0 -> 68.8 us, 32768 264.1 -> 268.7; 2456 x 5120 x 1280 40.0 -> 41.3).  It leaves none: 32768 x 1280 x 1280 103.9 -> 109.7,
+// and at such sizes, at the power limit, ViT-H of 8 images was 0.8 % slower with its launches saved.
+constexpr int LARGE_PARTS_TILE = 4;
+// By the estimates two rounds of 192x192 are 1 us faster for 3276 x 5120 x 1280; blocks of 8192 rows at a density of 0.4 took 262 us with them, 246 with the large tile
+// and 254 without pieces.
+constexpr double LARGE_PARTS_AHEAD_US = 3.0;
+bool large_reads_parts(int D) { return D / 64 > GEMM_PARTS_LINE; }
+double large_parts_us(int M, int N, bool gathered) { return ssam_div_up((long)ssam_div_up(M, 128) * ssam_div_up(N, 256), 512) * (gathered ? 1.2 : 0.5); }
+
 Choice choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs &ws, bool packed, PartsUse parts = PARTS_NONE)
 {
     Choice c;
@@ -391,6 +404,15 @@ constexpr double PARTS_US = 3.0;
 Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, bool parts)
 {
     Choice c;
+    if (parts && large_reads_parts(K)) {
+        c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us, LARGE_PARTS_TILE);
+        c.ring = -1;
+        c.us += large_parts_us(M, N, true);
+        double us = c.us - LARGE_PARTS_AHEAD_US;
+        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us, PARTS_READ_GATHERED);
+        if (c.wide >= 0) c.us = us;
+        return c;
+    }
     c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us);
     c.ring = pick_ring(M, N, K, true, true, c.us);
     if (parts) c.us += PARTS_US;
@@ -404,6 +426,11 @@ double folded_ln_us(int tiles, int K);
 Choice choose_ln(int M, int N, int K, const GemmLd &ld, bool parts)
 {
     Choice c = { -1, 4, -1, folded_ln_us((M / 128) * (N / 256), K) };
+    if (parts && large_reads_parts(K)) {
+        c.us += large_parts_us(M, N, false);
+        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, c.us, c.us, PARTS_READ);
+        return c;
+    }
     c.ring = pick_ring(M, N, K, true, true, c.us);
     if (parts) c.us += PARTS_US;
     c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, c.us, c.us, parts ? PARTS_READ : PARTS_NONE);
@@ -440,7 +467,15 @@ int ssam_parts_form_of(int rows, int kept, int D, int Dm)
     const BlockChoices with = block_choices(rows, kept, D, Dm, true), without = block_choices(rows, kept, D, Dm, false);
     constexpr double LAUNCH_US = 5.0;
     double gain[2] = { LAUNCH_US, LAUNCH_US };    // of the pieces between proj and fc1, and between fc2 and qkv
-    for (int i = 0; i < 4; ++i) gain[i == 0 || i == 3] -= with.c[i].wide < 0 ? 1e30 : with.c[i].us - without.c[i].us;
+    const bool large = large_reads_parts(D);
+    if (large) {
+        // A launch over 32768 rows of 1280 takes 14.9 us, 16384 9.8, 13104 9.1, 8192 5.6.  73 folded stacks of ViT-H's width (1024 to 9600 rows, densities 0.2 to 1) are
+        // 1.5 % faster than without pieces, -0.3 to 4.6 %; with 5 us for the smaller launches three more took pieces for fc1 alone, and lost 0.2 to 2 %.
+        const double row_us = 2.0 * D / 7.2e6;
+        gain[0] = std::max(4.0, 3.4 + kept * row_us);
+        gain[1] = std::max(4.0, 3.4 + rows * row_us);
+    }
+    for (int i = 0; i < 4; ++i) gain[i == 0 || i == 3] -= with.c[i].wide < 0 && !(large && i % 2 == 0) ? 1e30 : with.c[i].us - without.c[i].us;
     if (gain[1] > 0 && gain[0] + gain[1] > 0) return 3;
     return gain[0] > 0 ? 1 : 0;
 }
@@ -511,6 +546,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
         if (const int wide = pick.wide; wide >= 0) {
             GemmFold out;
             out.parts = parts.at;
+            out.slots = parts.slots;
             const GemmWideArgs args = { a, w, bias, c, M, N, K, ld, rm, out, st, warm, pick.us };
             switch (epilogue) {
             case SSAM_EPI_BIAS: return ssam_gemm_wide_bias(wide, packed, args);
@@ -552,7 +588,8 @@ int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, c
     const GemmRowMap none = { nullptr, 1, 0, 1 };
     const auto [wide, tile, ring, us] = choose_fold_gelu(M, N, K, ld, rows_a, ws, parts.at != nullptr);
     if (parts.at)
-        return wide < 0 ? SSAM_EUNSUPPORTED
+        return wide < 0 ? (!large_reads_parts(K) ? SSAM_EUNSUPPORTED
+                                                       : launch_split<128, 256, 128, 128, SSAM_EPI_BIAS_GELU, 1, 4, true, true, true>((const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, 512, none, ws, fold, st))
                         : ssam_gemm_wide_parts_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st, warm, us });
     if (wide >= 0)
         return ssam_gemm_wide_ln_gelu(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, none, fold, st, warm, us });
@@ -585,9 +622,15 @@ int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, cons
     GemmTileRange tr = { M / 128, N / 256, 0, (M / 128) * (N / 256) };
     const GemmFold fold = { reinterpret_cast<const float2 *>(stats), colsum, nullptr, parts.at, parts.slots, parts.eps, 1, 0, fill };
     const auto [wide, tile, ring, us] = choose_ln(M, N, K, ld, parts.slots != 0);
+    if (parts.at && wide < 0) {
+        if (!large_reads_parts(K)) return SSAM_EUNSUPPORTED;
+        hipLaunchKernelGGL((gemm_bf16_nt_lnf_kernel<128, 256, SSAM_EPI_BIAS_SCATTER, 1, 4, true>), dim3(ssam_div_up(tr.tile_count, 8) * 8 + ssam_div_up(fill.total_rows, GEMM_LNF_FILL)),
+                           dim3(256), lds, st, (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, tr, rm, fold);
+        SSAM_CHECK_LAUNCH();
+        return SSAM_OK;
+    }
     if (parts.at)
-        return wide < 0 ? SSAM_EUNSUPPORTED
-                        : ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st, warm, us });
+        return ssam_gemm_wide_parts_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st, warm, us });
     if (wide >= 0)
         return ssam_gemm_wide_ln_scatter(wide, GemmWideArgs{ (const bf16 *)A, (const bf16 *)Wfp, bias_f, (bf16 *)C, M, N, K, ld, rm, fold, st, warm, us });
     if (ring >= 0)

@@ -85,7 +85,7 @@ struct GemmFold {
     PadFill fill = {};        // with parts: padding rows that workgroups behind the tiles write
 };
 
-// Statistics of the rows of the residual stream in pieces of 64 columns, [rows][GEMM_PARTS_MOST] { mean, sum of squared deviations from it }: the
+// Statistics of the rows of the residual stream in pieces of 64 columns, [rows][gemm_parts_pitch] { mean, sum of squared deviations from it }: the
 // epilogues that write the rows leave them, from the values as stored, and the contraction that wants a row's mean and variance puts
 // them together.  A statistics launch takes 4.6 us however few rows there are, 3.4 of which a stack gets back; leaving the pieces takes 0.25 to 2.1 and reading
 // them 0.45 to 3.4, by tile (wide_tiles in gemm.hip), and ssam_parts_form_of says where that is worth it.  at = NULL: none.
@@ -134,15 +134,27 @@ __device__ __forceinline__ void gemm_tile_origin(const GemmTileRange &tr, int t,
     n0 = (tn * sub_n + sub % sub_n) * bn;
 }
 
+// Row of A of row m of a folded product (see GemmFold).
+template <bool LNF, bool PARTS>
+__device__ __forceinline__ long gemm_fold_row(const GemmFold &fold, int m)
+{
+    if (!LNF || !fold.src) return m;
+    const int t = fold.src[m];
+    if (!PARTS) return t;
+    return (long)(m / fold.src_rows) * fold.src_stride + ((unsigned)t < (unsigned)fold.src_stride ? t : 0);
+}
+
 // The workgroup's work, as a function of its index `bid` in the launch (the kernels below pass blockIdx.x, or
 // blockIdx.x less the workgroups of another kind that share the launch).
-template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
+// PARTS: the row statistics of the folded LayerNorm come in pieces (GemmParts).
+template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false, bool PARTS = false>
 __device__ __forceinline__ void
 gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                   bf16 *C, int M, int N, int K, const GemmLd &ld, const GemmTileRange &tr, const GemmRowMap &rm,
                   const GemmSplit &sp, int bid, const GemmFold &fold = GemmFold{})
 {
     static_assert(!LNF || WPACK, "the folded forms exist for packed weights");
+    static_assert(!PARTS || LNF, "pieces are read by the folded forms");
     // a K range of a folded product only gathers its rows: the normalisation is finished where the ranges are added
     constexpr bool FOLD_EPI = LNF && EPI != GEMM_EPI_PARTIAL;
     constexpr int THREADS = 64 * WGM * WGN, RSTEP = THREADS / 8;   // waves in a WGM x WGN grid; rows staged per pass
@@ -195,9 +207,8 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
     const bf16 *ga[A_LOADS];
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {        // rows past M repeat the last row; their results are never stored
-        long arow = min(m0 + r0 + RSTEP * i, M - 1);
-        if constexpr (LNF) if (fold.src) arow = fold.src[arow];
-        ga[i] = A + arow * ld.a + c0 * 8;
+        const int arow = min(m0 + r0 + RSTEP * i, M - 1);
+        ga[i] = A + gemm_fold_row<LNF, PARTS>(fold, arow) * ld.a + c0 * 8;
     }
     const bf16 *gb[B_LOADS];
 #pragma unroll
@@ -249,6 +260,12 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
                     af[slot_][i], bw[(p_) / HP][j], acc[((p_) % HP) * AF + i][j], 0, 0, 0);           \
     }
 
+    constexpr int EPS = WN + 4;                 // floats per staged row of the epilogue (16-byte multiple, odd in 16-byte units)
+    int *dst_row = reinterpret_cast<int *>(reinterpret_cast<float *>(smem) + WGM * WGN * 32 * EPS);   // [BM], -1 = skip
+    float2 *row_stats = reinterpret_cast<float2 *>(dst_row + BM);    // [BM] { rstd, -rstd*mean } (LNF), parked like dst_row
+    static_assert(!PARTS || BM <= THREADS, "a thread for a row's statistics");
+    static_assert(!PARTS || 2 * BM * GEMM_BK * sizeof(bf16) <= WGM * WGN * 32 * EPS * sizeof(float), "the row statistics lie behind the slabs");
+
     int buf = 0;
     if (WPACK) {
         // W arrives pre-shuffled into fragment order ([N/16][K/32][64 lanes][8]): every wave loads its own
@@ -283,6 +300,10 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
         // in the last phase with the slab after next.
         GEMM_LOAD_GLOBAL_A(kb)
         GEMM_LOAD_W(kb, 0) GEMM_LOAD_W(kb, 1)
+        if constexpr (PARTS && FOLD_EPI) {
+            // under the first slabs, before the accumulators are live
+            if (tid < BM) row_stats[tid] = gemm_row_stats(fold.parts + gemm_fold_row<LNF, PARTS>(fold, min(m0 + tid, M - 1)) * gemm_parts_pitch(fold.slots), fold.slots, K, fold.eps);
+        }
         GEMM_STORE_LDS_A(0)
         GEMM_LOAD_GLOBAL_A(min(kb + 1, ke - 1))
         LDS_BARRIER();
@@ -376,7 +397,6 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- epilogue: 32-row slices through a per-wave fp32 LDS region
-    constexpr int EPS = WN + 4;                 // floats per staged row (16-byte multiple, odd in 16-byte units)
     constexpr int LPR = WN / 8;                 // lanes per row when each lane owns 8 columns
     constexpr int RPP = 64 / LPR;               // rows per pass
     float *stage = reinterpret_cast<float *>(smem) + wave * 32 * EPS;
@@ -405,15 +425,13 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
     // are looked up once per tile (one row per thread, parked in LDS behind the staging regions) and the
     // old values of a whole 32-row slice are requested before the slice is staged, so that the slice pays
     // one memory round trip instead of one per pass.
-    int *dst_row = reinterpret_cast<int *>(reinterpret_cast<float *>(smem) + WGM * WGN * 32 * EPS);   // [BM], -1 = skip
     constexpr bool MAPPED = EPI == SSAM_EPI_BIAS_SCATTER_ADD || EPI == SSAM_EPI_BIAS_SCATTER;
-    float2 *row_stats = reinterpret_cast<float2 *>(dst_row + BM);    // [BM] { rstd, -rstd*mean } (LNF), parked like dst_row
-    if (MAPPED || FOLD_EPI) {
+    if (MAPPED || (FOLD_EPI && !PARTS)) {
         int mine = -1;
         float2 mine_stats = { 0.f, 0.f };
         if (tid < BM && m0 + tid < M) {
             int m = m0 + tid;
-            if constexpr (FOLD_EPI) mine_stats = fold.stats[m];
+            if constexpr (FOLD_EPI && !PARTS) mine_stats = fold.stats[m];
             if (MAPPED) {
                 int b = m / rm.rows_per_batch, p = m - b * rm.rows_per_batch;
                 int idx = rm.map[(long)b * rm.map_batch_stride + p];
@@ -423,7 +441,7 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
         __syncthreads();                        // every wave is done with the pipeline buffers
         if (tid < BM) {
             if (MAPPED) dst_row[tid] = mine;
-            if constexpr (FOLD_EPI) row_stats[tid] = mine_stats;
+            if constexpr (FOLD_EPI && !PARTS) row_stats[tid] = mine_stats;
         }
     }
     __syncthreads();                            // pipeline buffers free for staging; dst_row visible
@@ -523,22 +541,29 @@ gemm_bf16_nt_body(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const 
     }
 }
 
-template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false>
+template <int BM, int BN, int EPI, int SUB_M = 1, int SUB_N = 1, int WGM = 2, int WGN = 2, bool WPACK = false, bool LNF = false, bool PARTS = false>
 __global__ void __launch_bounds__(64 * WGM * WGN, (BN == 256 && WGM * WGN == 4 && WPACK) ? 2 : 1)
 gemm_bf16_nt_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                     bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmSplit sp, GemmFold fold)
 {
-    gemm_bf16_nt_body<BM, BN, EPI, SUB_M, SUB_N, WGM, WGN, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr, rm, sp, (int)blockIdx.x, fold);
+    gemm_bf16_nt_body<BM, BN, EPI, SUB_M, SUB_N, WGM, WGN, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr, rm, sp, (int)blockIdx.x, fold);
 }
 
-// The same workgroup with the LayerNorm of its A rows folded in (see GemmFold).
-template <int BM, int BN, int EPI, int WGM, int WGN>
+constexpr int GEMM_LNF_FILL = 16;
+
+// The same workgroup with the LayerNorm of its A rows folded in (see GemmFold).  PARTS: padding rows, GEMM_LNF_FILL a workgroup, are behind the tiles (there is no
+// statistics launch to write them).
+template <int BM, int BN, int EPI, int WGM, int WGN, bool PARTS = false>
 __global__ void __launch_bounds__(64 * WGM * WGN, (BN == 256 && WGM * WGN == 4) ? 2 : 1)
 gemm_bf16_nt_lnf_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                         bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
     const GemmSplit whole = { nullptr, 1 };
-    gemm_bf16_nt_body<BM, BN, EPI, 1, 1, WGM, WGN, true, true>(A, W, bias, C, M, N, K, ld, tr, rm, whole, (int)blockIdx.x, fold);
+    if constexpr (PARTS) if (const int behind = (int)blockIdx.x - (tr.tile_count + 7) / 8 * 8; behind >= 0) {
+        for (int i = threadIdx.x >> 6; i < GEMM_LNF_FILL; i += WGM * WGN) fill_pad_row(fold.fill, behind * GEMM_LNF_FILL + i);
+        return;
+    }
+    gemm_bf16_nt_body<BM, BN, EPI, 1, 1, WGM, WGN, true, true, PARTS>(A, W, bias, C, M, N, K, ld, tr, rm, whole, (int)blockIdx.x, fold);
 }
 
 // Whole rounds and left-over tiles in ONE launch (both kinds of workgroup have 256 threads): the first `n_tail`
@@ -546,7 +571,7 @@ gemm_bf16_nt_lnf_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, 
 // left-over sub-tiles (TEPI = the epilogue proper, or GEMM_EPI_PARTIAL with K ranges), the others the large
 // tiles.  The left-over workgroups are dispatched first and finish while the first round of large tiles runs,
 // instead of running as a launch of their own on a mostly idle chip.
-template <int BM, int BN, int EPI, int WGM, int WGN, int TM, int TN, int TEPI, int SUB_M, int SUB_N, bool WPACK, bool LNF = false>
+template <int BM, int BN, int EPI, int WGM, int WGN, int TM, int TN, int TEPI, int SUB_M, int SUB_N, bool WPACK, bool LNF = false, bool PARTS = false>
 __global__ void __launch_bounds__(256, 2)
 gemm_bf16_nt_fused_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
                           bf16 *C, int M, int N, int K, GemmLd ld, GemmTileRange tr_main, GemmTileRange tr_tail,
@@ -554,20 +579,20 @@ gemm_bf16_nt_fused_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W
 {
     static_assert(WGM * WGN == 4, "both kinds of workgroup are four waves");
     if ((int)blockIdx.x < n_tail) {
-        gemm_bf16_nt_body<TM, TN, TEPI, SUB_M, SUB_N, 2, 2, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr_tail, rm, sp_tail, (int)blockIdx.x, fold);
+        gemm_bf16_nt_body<TM, TN, TEPI, SUB_M, SUB_N, 2, 2, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr_tail, rm, sp_tail, (int)blockIdx.x, fold);
     } else {
         const GemmSplit whole = { nullptr, 1 };
-        gemm_bf16_nt_body<BM, BN, EPI, 1, 1, WGM, WGN, WPACK, LNF>(A, W, bias, C, M, N, K, ld, tr_main, rm, whole, (int)blockIdx.x - n_tail, fold);
+        gemm_bf16_nt_body<BM, BN, EPI, 1, 1, WGM, WGN, WPACK, LNF, PARTS>(A, W, bias, C, M, N, K, ld, tr_main, rm, whole, (int)blockIdx.x - n_tail, fold);
     }
 }
 
 // Second half of a K-split left-over launch: adds the `parts` fp32 slots of every sub-tile in slot
 // order, then bias (with a folded LayerNorm: its row and column terms, see GemmFold) and the epilogue proper.
 // One thread finishes 8 consecutive columns of a row.
-template <int BM, int BN, int EPI, int SUB_M, int SUB_N, bool LNF = false>
+template <int BM, int BN, int EPI, int SUB_M, int SUB_N, bool LNF = false, bool PARTS = false>
 __global__ void __launch_bounds__(256)
 gemm_tail_reduce_kernel(const float *__restrict__ partial, int parts, const float *__restrict__ bias, bf16 *C,
-                        int M, int N, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
+                        int M, int N, int K, GemmLd ld, GemmTileRange tr, GemmRowMap rm, GemmFold fold)
 {
     constexpr int LPR = BN / 8, RPB = 256 / LPR;                  // lanes per row, rows per workgroup
     constexpr int SUBS = SUB_M * SUB_N;
@@ -618,7 +643,7 @@ gemm_tail_reduce_kernel(const float *__restrict__ partial, int parts, const floa
         acc[4] += y1.x; acc[5] += y1.y; acc[6] += y1.z; acc[7] += y1.w;
     }
     if constexpr (LNF) {
-        const float2 t = fold.stats[m];
+        const float2 t = PARTS ? gemm_row_stats(fold.parts + gemm_fold_row<LNF, PARTS>(fold, m) * gemm_parts_pitch(fold.slots), fold.slots, K, fold.eps) : fold.stats[m];
         const float4 *c4 = reinterpret_cast<const float4 *>(fold.colsum + ncol);
         const float4 x0 = c4[0], x1 = c4[1];
         const float cs[8] = { x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w };

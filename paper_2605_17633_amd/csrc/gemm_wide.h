@@ -63,7 +63,7 @@ struct GemmWide {
     // 1 KB requests of a slab: A's, then W's; wave w takes w, w + 8, ...
     static constexpr int QA = BM / 8, QW = BN / 8, L = (QA + QW + 7) / 8, LREST = (QA + QW) % 8;
     static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0 && (WGK == 2 || (QA % 8 == 0 && QW % 8 == 0)), "whole MFMA tiles and requests");
-    static_assert(GEMM_BK * 2 == GEMM_PARTS_MOST * 8, "a row's pieces take the place of its part of a slab");
+    static_assert(GEMM_BK * 2 == GEMM_PARTS_LINE * 8 && GEMM_PARTS_MOST <= GEMM_PARTS_LINE + 4, "a row's pieces take the place of its part of a slab, the rest 32 bytes");
     static_assert(WGK == 1 || (size_t)BM * BN * 4 <= ring, "the halves are added in the ring's LDS");
     // Row statistics in pieces (GemmParts).  Waves that hold whole pieces of 64 columns, or halves of which the next wave has the other, can write them.
     static constexpr bool WRITES_PARTS = (NT * 16 == 32 && WGN % 2 == 0) || NT * 16 == 64;
@@ -150,7 +150,8 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
     // ---- requests
     uint32_t off[L], dst[L], inc[L];
     const unsigned char *base[L];
-    uint32_t poff[READS ? G::QA / 8 : 1];             // of the rows' pieces, which are requested as one more slab of A
+    uint32_t poff[READS ? G::QA / 8 : 1];             // of the rows' pieces, which are requested as one more slab of A,
+    uint32_t poff_rest = 0;                           // and of those past 128 bytes (rows of 1280), 32 bytes of 32 rows a request
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem);
     auto a_row = [&](int m) {
         if constexpr (!READS) return fold.src[m];
@@ -167,7 +168,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             const bool gather = LNF && fold.src;
             const int ar = gather ? a_row(m) : m - m0;
             off[i] = ((uint32_t)ar * (uint32_t)ld.a + c * 8) * 2;
-            if constexpr (READS) poff[i] = (uint32_t)(gather ? ar : m) * (GEMM_PARTS_MOST * 8) + c * 16;
+            if constexpr (READS) poff[i] = (uint32_t)(gather ? ar : m) * (gemm_parts_pitch(fold.slots) * 8) + c * 16;
             base[i] = reinterpret_cast<const unsigned char *>(gather ? A : A + (long)m0 * ld.a);
             dst[i] = lds0 + f * 1024;
         } else {
@@ -188,6 +189,10 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
             }
             dst[i] = lds0 + W0 + w * 1024;
         }
+    }
+    if constexpr (READS) if (fold.slots > GEMM_PARTS_LINE) {
+        const int m = min(m0 + wave * 32 + (lane >> 1), M - 1);
+        poff_rest = (uint32_t)(fold.src ? a_row(m) : m) * (gemm_parts_pitch(fold.slots) * 8) + GEMM_PARTS_LINE * 8 + (lane & 1) * 16;
     }
     const bool all = G::LREST == 0 || wave < G::LREST;              // this wave has an L-th request
     auto request = [&](int i, int sa, int sw) {
@@ -301,7 +306,7 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 
     // ---- ring
     int sa = 0, sw = 0;                          // stages of slab t
-    int pieces = 0;                              // where in the ring the rows' pieces land
+    int pieces = 0, pieces_rest = 0;             // where in the ring the rows' pieces land
     if constexpr (WGK == 1) {
         // iteration t of the loop requests W of slab t + SW, then A of slab t + SA; here those of t = -SA .. -1
 #pragma unroll
@@ -347,10 +352,15 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
 #pragma unroll
                     for (int i = LA; i < L; ++i) request(i, sa, sw);
                 // into the first stage that takes no slab any more, behind every slab (what is waited for from here on counts on it)
-                if constexpr (READS) if (t == n - SA) {
-                    pieces = sa * STRIDE_A;
+                if constexpr (READS) {
+                    if (t == n - SA) {
+                        pieces = sa * STRIDE_A;
 #pragma unroll
-                    for (int i = 0; i < LA; ++i) gemm_load_lds16_s(dst[i] + pieces, poff[i], fold.parts);
+                        for (int i = 0; i < LA; ++i) gemm_load_lds16_s(dst[i] + pieces, poff[i], fold.parts);
+                    } else if (t == n - SA + 1 && fold.slots > GEMM_PARTS_LINE) {       // (and the next; a request more than is counted on makes a wait longer, not shorter)
+                        pieces_rest = sa * STRIDE_A;
+                        if (wave < BM / 32) gemm_load_lds16_s(lds0 + pieces_rest + wave * 1024, poff_rest, fold.parts);
+                    }
                 }
                 if (t + 1 < n)
 #pragma unroll
@@ -431,18 +441,24 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
         for (int k = 0; k < MTH; ++k) {
             const int row = wm + 16 * k + l16;
             const unsigned char *at = as + pieces + row * 128;
-            float2 v[GEMM_PARTS_MOST / 4];
+            const bool rest = fold.slots > GEMM_PARTS_LINE;
+            float2 v[GEMM_PARTS_LINE / 4], v_rest = make_float2(0.f, 0.f);
             float mean = 0.f, sq = 0.f;
 #pragma unroll
-            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i) {
+            for (int i = 0; i < GEMM_PARTS_LINE / 4; ++i) {
                 const int s = 4 * i + quad;
                 v[i] = *reinterpret_cast<const float2 *>(at + (((s >> 1) ^ ((row >> 1) & 7)) << 4) + (s & 1) * 8);
                 if (s < fold.slots) mean += v[i].x;
             }
+            if (rest) {
+                v_rest = *reinterpret_cast<const float2 *>(as + pieces_rest + row * 32 + quad * 8);
+                if (GEMM_PARTS_LINE + quad < fold.slots) mean += v_rest.x;
+            }
             mean = gemm_quad_sum(mean) / (float)fold.slots;
 #pragma unroll
-            for (int i = 0; i < GEMM_PARTS_MOST / 4; ++i)
+            for (int i = 0; i < GEMM_PARTS_LINE / 4; ++i)
                 if (4 * i + quad < fold.slots) sq += gemm_piece_term(v[i], mean);
+            if (rest && GEMM_PARTS_LINE + quad < fold.slots) sq += gemm_piece_term(v_rest, mean);
             const float inv = rsqrtf(gemm_quad_sum(sq) / (float)K + fold.eps);          // K: the rows' length
             rst[k] = make_float2(inv, -inv * mean);
         }
@@ -549,10 +565,10 @@ gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const f
                 sq[k][p] = gemm_piece_squares8(v, sum[k][0] * (1.f / 64.f));
             }
         over_row(sq, 1);
-        const int col = n0 + (wn & ~63);
+        const int col = n0 + (wn & ~63), pitch = gemm_parts_pitch(fold.slots);
         if (WN == 32 && (wt & 1)) return;
 #pragma unroll
         for (int k = 0; k < MTH; ++k)
-            if (quad == 0 && drow[k] >= 0 && col < N) fold.parts[(long)drow[k] * GEMM_PARTS_MOST + (col >> 6)] = make_float2(sum[k][0] * (1.f / 64.f), sq[k][0]);
+            if (quad == 0 && drow[k] >= 0 && col < N) fold.parts[(long)drow[k] * pitch + (col >> 6)] = make_float2(sum[k][0] * (1.f / 64.f), sq[k][0]);
     }
 }

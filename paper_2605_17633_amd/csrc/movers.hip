@@ -165,7 +165,7 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) unpack_bf16x8(raw[i], v[i]);
     int D = chunks * 8;
-    if constexpr (MAXC * 8 == GEMM_PARTS_MOST) if (slots) {
+    if constexpr (MAXC * 8 <= (GEMM_PARTS_MOST + 7) / 8 * 8) if (slots) {
         // piece (lane >> 3) + 8 * i, in its eight lanes: sums of columns 32 apart first
         float2 own[MAXC], other[MAXC];           // other: piece s ^ 4
 #pragma unroll
@@ -185,17 +185,17 @@ ln_stats_kernel(const uint4 *__restrict__ x, float2 *__restrict__ stats, long ro
         // pieces 4 * k + quad one after the other, then the four quads
         const int quad = (lane >> 3) & 3;
         const bool upper = lane >= 32;
-        float2 piece[GEMM_PARTS_MOST / 4];
+        float2 piece[2 * MAXC];
 #pragma unroll
-        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k) piece[k] = upper == (k % 2 == 1) ? own[k / 2] : other[k / 2];
+        for (int k = 0; k < 2 * MAXC; ++k) piece[k] = upper == (k % 2 == 1) ? own[k / 2] : other[k / 2];
         auto over_quads = [](float t) { t += __shfl_xor(t, 8, 64); return t + __shfl_xor(t, 16, 64); };
         float mean = 0.f, sq = 0.f;
 #pragma unroll
-        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k)
+        for (int k = 0; k < 2 * MAXC; ++k)
             if (4 * k + quad < slots) mean += piece[k].x;
         mean = over_quads(mean) / (float)slots;
 #pragma unroll
-        for (int k = 0; k < GEMM_PARTS_MOST / 4; ++k)
+        for (int k = 0; k < 2 * MAXC; ++k)
             if (4 * k + quad < slots) sq += gemm_piece_term(piece[k], mean);
         const float inv = rsqrtf(over_quads(sq) / (float)D + eps);
         if (lane == 0) stats[row] = make_float2(inv, -inv * mean);
