@@ -256,6 +256,18 @@ int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double &launch
     return best;
 }
 
+// What the GELU epilogue adds to a ring's estimate, which is an average over the epilogues, by the columns x rows that its busiest CU finishes (two 128x128 tiles: 1.5 us).
+// Only against the wide kernel, whose estimate has it, and of the tiles of 128 rows: 94 routed MLPs of 900 to 3500 rows that it moves are 2.4 % faster (none slower), 64x64 rings
+// of 120 to 640 rows were 2 to 5 % faster than what it would move them to.  2500 x 3072 x 768 takes the ring 19.5 to 20.3 us, estimated as 16.9, and 256x128 17.8 with 56 CUs left to read weights ahead
+// (encoders of ViT-B, two images of 50 x 50: 1256 -> 1236 us packed, 1253 -> 1235 row-major).
+double ring_gelu_us(int ring, int M, int N, int epilogue)
+{
+    if (ring < 0 || ring >= RING_DIRECT || epilogue != SSAM_EPI_BIAS_GELU) return 0.0;
+    const RingTile &t = ring_tiles[ring];
+    if (t.bm < 128) return 0.0;
+    return 1.5 / (2 * 128 * 128) * t.bm * t.bn * ssam_div_up((long)ssam_div_up(M, t.bm) * ssam_div_up(N, t.bn), 256);
+}
+
 // The wide kernel's tiles (gemm_wide.h).  A launch of r rounds (one workgroup per CU at a time) takes
 // t0 + r * (t_round + t_slab per slab of 64, t_gelu and t_add behind those epilogues) + t_mb per megabyte of C.
 // t_parts: what a round takes longer where it leaves row statistics in pieces (GemmParts), reads them, and reads them of gathered rows (measured with the tiles
@@ -329,8 +341,8 @@ double other_layout_us(int M, int N, int K, int epilogue, const SplitWs &ws, boo
     if (!packed && N % 128 != 0) return 1e30;
     double us;
     pick_tile(M, N, K, epilogue, ws, !packed, us);
-    pick_ring(M, N, K, !packed, whole_lines, us);
-    return us;
+    const int ring = pick_ring(M, N, K, !packed, whole_lines, us);
+    return us + ring_gelu_us(ring, M, N, epilogue);
 }
 
 template <int BM, int BN, int STAGES, int EPI, bool WPACK, bool LNF>
@@ -392,6 +404,7 @@ Choice choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs
     Choice c;
     c.tile = pick_tile(M, N, K, epilogue, ws, packed, c.us);
     c.ring = pick_ring(M, N, K, packed, ld.a % GEMM_BK == 0 && ld.w % GEMM_BK == 0, c.us);
+    c.us += ring_gelu_us(c.ring, M, N, epilogue);
     c.wide = pick_wide(M, N, K, epilogue, ld, packed, 0, c.us, other_layout_us(M, N, K, epilogue, ws, packed, ld.a % GEMM_BK == 0), parts);
     return c;
 }
@@ -681,7 +694,8 @@ extern "C" int ssam_linear_wide_form_ld(int M, int N, int K, int epilogue, int p
     const SplitWs ws = { workspace_bytes ? &some : nullptr, workspace_bytes };
     const bool whole_lines = lda % GEMM_BK == 0 && ldw % GEMM_BK == 0;
     if (!folded) pick_tile(M, N, K, epilogue, ws, packed != 0, us);
-    pick_ring(M, N, K, packed != 0 || folded != 0, folded != 0 || whole_lines, us);
+    const int ring = pick_ring(M, N, K, packed != 0 || folded != 0, folded != 0 || whole_lines, us);
+    if (!folded) us += ring_gelu_us(ring, M, N, epilogue);
     return pick_wide(M, N, K, epilogue, GemmLd{ lda, ldw, N }, packed != 0 || folded != 0, 0, us,
                      folded ? us : other_layout_us(M, N, K, epilogue, ws, packed != 0, lda % GEMM_BK == 0));
 }
