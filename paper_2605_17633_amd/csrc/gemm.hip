@@ -468,7 +468,7 @@ BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
 
 // Row statistics in pieces (GemmParts) of the residual stream, [rows][D] of which `kept` go through the MLP, in blocks with packed weights and both
 // LayerNorms folded in.  0: none; 1: proj leaves them and fc1 reads them; 3: fc2 leaves them too, and the next block's qkv reads those.  What leaves or reads
-// them is the wide kernel, where it is at least near the fastest by the tiles that can: what a contraction takes longer than without, leaving and reading included,
+// them is the wide kernel (of rows of 1280 the large tile reads them too), where it is at least near the fastest by the tiles that can: what a contraction takes longer than without, leaving and reading included,
 // goes against the launch saved.  A block by itself has a launch for qkv's statistics all the same, reads and leaves nothing there and takes the stack's tiles.
 // LAUNCH_US: 90 folded stacks of widths 512, 768 and 1024 (512 to 10000 rows, densities 0.2 to 1) ran with each form.  With 4.6 to 5.5 all together are 231 us a
 // block faster than without pieces (235 with the best form of each, 230 with pieces wherever tiles fit) and two are slower, by 1.1 us at most; with 3.4 212.  Larger
@@ -626,7 +626,7 @@ double folded_ln_us(int tiles, int K)
 
 // The contraction with the LayerNorm of its A rows folded in (see GemmFold): 128x256 tiles, packed weights,
 // mapped store; M a multiple of 128 and N of 256, so there are no left-over tiles.  parts: instead of stats; with at = NULL the same kernel that would read
-// them with stats (of ssam_ln_stats_impl as from pieces: the same bits).
+// them with stats (of ssam_ln_stats_impl as from pieces: the same bits).  Padding rows of `fill` are written behind the tiles of whatever reads pieces.
 int ssam_linear_ln_impl(const void *A, const float *stats, const void *Wfp, const float *colsum, const float *bias_f,
                         void *C, int M, int N, int K, const GemmLd &ld, const GemmRowMap &rm, hipStream_t st, const GemmParts &parts, const PadFill &fill, WarmAhead *warm)
 {
