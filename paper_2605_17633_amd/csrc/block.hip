@@ -258,12 +258,12 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     }
     if (kv_shift && (!fold || !w->bproj_folded)) return SSAM_EINVAL;
     const float *bproj = kv_shift ? w->bproj_folded : w->bproj;
-    const size_t parts_bytes = align256((size_t)crows * gemm_parts_pitch(D / 64) * sizeof(float2));
-    const int form = fold && w->fold_ln2 != 0 && parts_bytes <= GEMM_SPLIT_WS_BYTES - 256 ? ssam_parts_form_of(crows, B * cfg->K, D, cfg->Dm) : 0;
+    const size_t parts_bytes = gemm_parts_bytes(crows, D);
+    const int form = fold && w->fold_ln2 != 0 && gemm_split_beside_parts(crows, D) != 0 ? ssam_parts_form_of(crows, B * cfg->K, D, cfg->Dm) : 0;
     const GemmParts parts = form ? GemmParts{ (float2 *)((unsigned char *)workspace + (workspace_bytes & ~(size_t)255) - parts_bytes), D / 64, cfg->eps } : GemmParts{};
     const GemmParts whole = form == 3 ? parts : GemmParts{}, tile_only = { nullptr, whole.slots, cfg->eps };       // (in a single block: a stack's blocks are then the same bits)
     // the kernels of the longer rows cut K beside the pieces that lie in the same scratch (a single block likewise: the same cuts, the same bits)
-    const size_t split_bytes = form && D / 64 > GEMM_PARTS_LINE ? GEMM_SPLIT_WS_BYTES - 256 - parts_bytes : GEMM_SPLIT_WS_BYTES;
+    const size_t split_bytes = form ? gemm_split_beside_parts(crows, D) : GEMM_SPLIT_WS_BYTES;
     const bool have_parts = whole.at && parts_ready && *parts_ready;
     if (parts_ready) *parts_ready = whole.at != nullptr;
     if (!tables_ready) {

@@ -456,10 +456,11 @@ struct BlockChoices { Choice c[4]; };
 BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
 {
     alignas(16) static unsigned char some;
-    const SplitWs ws = { &some, GEMM_SPLIT_WS_BYTES };
+    // fc1 and fc2 with what the launch will have: the kernel that is found here has to be the one that is taken there
+    const SplitWs whole = { &some, GEMM_SPLIT_WS_BYTES }, ws = { &some, parts ? gemm_split_beside_parts(rows, D) : GEMM_SPLIT_WS_BYTES };
     const PartsUse left = parts ? PARTS_LEFT : PARTS_NONE;
     return { { choose_ln(rows, 3 * D, D, GemmLd{ D, D, 3 * D }, parts),
-               choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, ws, true, left),
+               choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, whole, true, left),
                choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, parts),
                choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, left) } };
 }

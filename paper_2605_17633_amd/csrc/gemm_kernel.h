@@ -95,6 +95,15 @@ struct GemmParts {
     float eps;
 };
 
+// The pieces of a stack's rows lie at the end of the K-split scratch of its MLP; longer rows' fc1 and fc2 may cut K in what is in front of them (0: the pieces do not fit).
+inline size_t gemm_parts_bytes(long rows, int D) { return ((size_t)rows * gemm_parts_pitch(D / 64) * sizeof(float2) + 255) & ~(size_t)255; }
+inline size_t gemm_split_beside_parts(long rows, int D)
+{
+    const size_t taken = 256 + gemm_parts_bytes(rows, D);
+    if (taken > GEMM_SPLIT_WS_BYTES) return 0;
+    return D / 64 > GEMM_PARTS_LINE ? GEMM_SPLIT_WS_BYTES - taken : GEMM_SPLIT_WS_BYTES;
+}
+
 // Weights of contractions still to come that a launch reads with the CUs it has no tile for, so that they lie in the memory-side cache by then.  From HBM a
 // megabyte of weights costs the contraction that reads it 0.2 to 0.4 us (its first slabs wait, and a chain over K has four slabs in flight): 1228 x 1024 x 4096
 // 22.1 us, 18.4 from the cache; 8192 x 3840 x 1280 77.3, 72.2.  Encoders: ViT-B, one image 1138 -> 1076 us; ViT-L, one image 2405 -> 2315; ViT-B, 50 x 50, two
