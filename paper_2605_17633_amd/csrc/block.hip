@@ -348,7 +348,8 @@ extern "C" int ssam_encoder_block(void *x, const ssam_block_weights *w, const ss
                                   const int32_t *gather_table, const int32_t *sigma, const int32_t *keep_idx,
                                   void *workspace, size_t workspace_bytes, void *stream)
 {
-    WarmAhead warm = { w, 1, cfg ? cfg->D : 0, cfg ? cfg->Dm : 0 };
+    const int Dm = cfg ? cfg->Dm : 0;
+    WarmAhead warm = { w, nullptr, 1, cfg ? cfg->D : 0, { Dm, Dm } };
     return encoder_block_impl(x, w, cfg, gather_table, sigma, keep_idx, workspace, workspace_bytes, nullptr, nullptr, false, nullptr, nullptr, &warm, stream);
 }
 
@@ -364,6 +365,20 @@ extern "C" size_t ssam_encoder_workspace_bytes(const ssam_block_cfg *cfg_local, 
     const ssam_block_cfg *c = cfg_local ? cfg_local : cfg_global;
     size_t s = c ? align256(ssam_score_tokens_workspace_bytes(c->B, c->g, c->g)) : 0;
     return (core > s ? core : s) + tables;
+}
+
+// Either configuration may be missing where no block is of its kind.
+static WarmAhead warm_of_stack(const ssam_block_weights *weights, const uint8_t *is_global, int n_blocks, const ssam_block_cfg *cfg_local, const ssam_block_cfg *cfg_global)
+{
+    const ssam_block_cfg *c0 = cfg_local ? cfg_local : cfg_global;
+    return { weights, is_global, n_blocks, c0->D, { cfg_local ? cfg_local->Dm : 0, cfg_global ? cfg_global->Dm : 0 } };
+}
+
+// What the launch of contraction `now` of a stack reads ahead (WarmAhead::pieces).  Host only, for tests; not part of the interface.
+extern "C" int ssam_warm_pieces_of_stack(const ssam_block_weights *weights, const uint8_t *is_global, int n_blocks, const ssam_block_cfg *cfg_local, const ssam_block_cfg *cfg_global,
+                                         int now, int groups, double most_bytes, const void **at, uint32_t *bytes)
+{
+    return warm_of_stack(weights, is_global, n_blocks, cfg_local, cfg_global).pieces(now, groups, most_bytes, at, bytes);
 }
 
 extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, const uint8_t *is_global, int n_blocks,
@@ -426,7 +441,7 @@ extern "C" int ssam_encoder_forward(void *x, const ssam_block_weights *weights, 
     if (rc != SSAM_OK) return rc;
     bool pad_rows_zero = false;                 // the padding slots of the windowed blocks' qkv tensor hold zeros
     bool parts_ready = false;                   // and the row statistics of x in pieces are up to date
-    WarmAhead warm = { weights, n_blocks, c0->D, c0->Dm };
+    WarmAhead warm = warm_of_stack(weights, is_global, n_blocks, any_local ? cfg_local : nullptr, any_global ? cfg_global : nullptr);
     for (int i = 0; i < n_blocks; ++i) {
         warm.now = 4 * i;
         void **ev = qkv_events ? qkv_events + 2 * i : nullptr;

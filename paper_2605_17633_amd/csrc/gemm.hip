@@ -512,7 +512,7 @@ GemmWarm WarmAhead::take(int groups, double most_bytes)
     if (next <= now) { next = now + 1; done = 0; }
     for (int s = 0; s < 3 && next <= now + AHEAD && next < 4 * blocks; ++s) {
         const ssam_block_weights &b = w[next / 4];
-        const size_t sizes[4] = { (size_t)6 * D * D, (size_t)2 * D * D, (size_t)2 * D * Dm, (size_t)2 * D * Dm };
+        const size_t mlp = (size_t)2 * D * Dm[is_global && is_global[next / 4]], sizes[4] = { (size_t)6 * D * D, (size_t)2 * D * D, mlp, mlp };
         const void *at[4] = { b.wqkv, b.wproj, b.w1, b.w2 };
         size_t bytes = sizes[next % 4] - done;
         if ((double)bytes > most_bytes) bytes = (size_t)most_bytes & ~(size_t)8191;
@@ -529,19 +529,21 @@ GemmWarm WarmAhead::take(int groups, double most_bytes)
     return out;
 }
 
-// The pieces that the launch of contraction `now` (four a block) reads ahead with `groups` workgroups, after those of every contraction before it: their
-// addresses and bytes.  Returns their number.  Host only, for tests; not part of the interface.
+// The pieces that the launch of contraction `launch` reads ahead with `groups` workgroups, after those of every contraction before it: their addresses and
+// bytes.  Returns their number.  For tests.
+int WarmAhead::pieces(int launch, int groups, double most_bytes, const void **at, uint32_t *bytes)
+{
+    GemmWarm out = {};
+    for (now = 0; now <= launch; ++now) out = take(groups, most_bytes);
+    int k = 0;
+    for (; k < 3 && out.bytes[k]; ++k) { at[k] = out.at[k]; bytes[k] = out.bytes[k]; }
+    return out.groups == groups || k == 0 ? k : SSAM_EINVAL;
+}
+
+// The same of blocks of one kind.  Host only, for tests; not part of the interface.
 extern "C" int ssam_warm_pieces(const ssam_block_weights *weights, int n_blocks, int D, int Dm, int now, int groups, double most_bytes, const void **at, uint32_t *bytes)
 {
-    WarmAhead ahead = { weights, n_blocks, D, Dm };
-    GemmWarm w = {};
-    for (int i = 0; i <= now; ++i) {
-        ahead.now = i;
-        w = ahead.take(groups, most_bytes);
-    }
-    int k = 0;
-    for (; k < 3 && w.bytes[k]; ++k) { at[k] = w.at[k]; bytes[k] = w.bytes[k]; }
-    return w.groups == groups || k == 0 ? k : SSAM_EINVAL;
+    return WarmAhead{ weights, nullptr, n_blocks, D, { Dm, Dm } }.pieces(now, groups, most_bytes, at, bytes);
 }
 
 // parts (optional): row statistics that a scatter-add leaves; the caller has asked ssam_parts_form_of.  With no place for them (at = NULL) only its tile is taken.

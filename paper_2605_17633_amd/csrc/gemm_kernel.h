@@ -117,12 +117,14 @@ struct GemmWarm {
 // The contractions of a stack of blocks in their order (four a block), and how far their weights have been read ahead.  Host side, for one call.
 struct WarmAhead {
     const ssam_block_weights *w;
-    int blocks, D, Dm;
+    const uint8_t *is_global; // kind of every block (NULL: all windowed)
+    int blocks, D, Dm[2];     // width of the MLP of windowed and of global blocks, which need not agree
     int now = 0;              // the contraction that is being launched
     int next = 1;             // the first whose weights are not all read ahead
     size_t done = 0;          //   and how much of them is
 
     GemmWarm take(int groups, double most_bytes);
+    int pieces(int launch, int groups, double most_bytes, const void **at, uint32_t *bytes);
 };
 
 struct GemmSplit {

@@ -51,3 +51,34 @@ def test_missing_and_misaligned_weights_are_left_to_the_contraction():
     assert pieces(ws, 256, 1024, 1, 32, 1e12) == []
     assert len(pieces(ws, 256, 1024, 2, 32, 1e12)) == 2      # w2 and the next wqkv
     assert pieces(ws, 256, 1024, 3, 32, 1e12) == []          # not the misaligned wproj
+
+
+def stack_of_two_kinds(flags, D, Dm, base=1 << 40):
+    ws, spans = (B.BlockWeights * len(flags))(), []
+    for i, f in enumerate(flags):
+        for name, size in zip(NAMES, (6 * D * D, 2 * D * D, 2 * D * Dm[f], 2 * D * Dm[f])):
+            setattr(ws[i], name, base)
+            spans.append((base, size))
+            base += size + 4096
+    return ws, spans
+
+
+@pytest.mark.parametrize("Dm", [(4096, 1024), (1024, 4096), (2048, 2048)])
+@pytest.mark.parametrize("flags", [(0, 1, 0, 1), (1, 0, 0, 1, 1), (1, 1), (0, 0)])
+def test_a_block_of_either_kind_has_its_own_width(flags, Dm):
+    """Windowed blocks of one MLP width, global ones of another: every piece inside the weight that it is of, and all of them read."""
+    D = 512
+    ws, spans = stack_of_two_kinds(flags, D, Dm)
+    cfg = [B.make_cfg(1, 16, D, D // 64, Dm[f], 0 if f else 14, 128 if f else 32, 100, 0.4) if f in flags else None for f in (0, 1)]
+    seen = {}
+    for now in range(4 * len(flags)):
+        at, nbytes = (C.c_void_p * 3)(), (C.c_uint32 * 3)()
+        k = B.lib().ssam_warm_pieces_of_stack(ws, (C.c_uint8 * len(flags))(*flags), C.c_int(len(flags)), *(c and C.byref(c) for c in cfg),
+                                              C.c_int(now), C.c_int(32), C.c_double(1e12), at, nbytes)
+        assert 0 <= k <= 3
+        for j in range(k):
+            i = next(j2 for j2, (b, size) in enumerate(spans) if b <= at[j] < b + size)
+            assert at[j] - spans[i][0] == seen.get(i, 0)
+            seen[i] = seen.get(i, 0) + nbytes[j]
+            assert seen[i] <= spans[i][1], (now, i)
+    assert seen == {i: size for i, (_, size) in enumerate(spans) if i > 0}
