@@ -123,6 +123,8 @@ struct WarmAhead {
     int next = 1;             // the first whose weights are not all read ahead
     size_t done = 0;          //   and how much of them is
 
+    // what a launch of the wide kernel that takes `us` microseconds reads behind its `tiles` tiles (filled up to whole XCDs) and `fills` workgroups of padding rows
+    GemmWarm behind(int tiles, int fills, double us);
     GemmWarm take(int groups, double most_bytes);
     int pieces(int launch, int groups, double most_bytes, const void **at, uint32_t *bytes);
 };

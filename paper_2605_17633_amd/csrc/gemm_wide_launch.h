@@ -16,12 +16,6 @@ struct GemmWideArgs {
     double us = 0.0;          // what the launch takes
 };
 
-// Weights are read ahead by one workgroup for each CU without a tile, where there are a few; each gets what it can read in the launch's time (bytes a
-// microsecond; half of it leaves weights of ViT-B's 240 tiles unread: 2 % of an encoder).
-constexpr int GEMM_WARM_FEWEST = 8;
-constexpr double GEMM_WARM_RATE = 30e3;
-
-
 // Tiles, in the order of their index in the dispatcher's time model (gemm.hip).
 #define GEMM_WIDE_TILES(X)                                                                                     \
     X(0, 64, 64, 2) X(1, 96, 64, 2) X(2, 96, 96, 2) X(3, 64, 128, 2) X(4, 128, 128, 1) X(5, 128, 192, 1)         \
@@ -47,11 +41,9 @@ int gemm_wide_launch_tile(const GemmWideArgs &a)
         return SSAM_EHIP;
     GemmTileRange tr = { ssam_div_up(a.M, BM), ssam_div_up(a.N, BN), 0, 0 };
     tr.tile_count = tr.tiles_m * tr.tiles_n;
-    int groups = ssam_div_up(tr.tile_count, 8) * 8 + (PARTS && LNF && EPI == SSAM_EPI_BIAS_SCATTER ? ssam_div_up(a.fold.fill.total_rows, GEMM_WIDE_FILL) : 0);
-    GemmWarm warm = {};
-    if (const int idle = ssam_div_up(groups, 256) * 256 - groups; a.warm && idle >= GEMM_WARM_FEWEST) warm = a.warm->take(idle, idle * a.us * GEMM_WARM_RATE);
-    groups += warm.groups;
-    hipLaunchKernelGGL(kern, dim3(groups), dim3(512), lds, a.st, a.A, a.W, a.bias, a.C, a.M, a.N, a.K, a.ld, tr, a.rm, a.fold, warm);
+    const int tiles = ssam_div_up(tr.tile_count, 8) * 8, fills = PARTS && LNF && EPI == SSAM_EPI_BIAS_SCATTER ? ssam_div_up(a.fold.fill.total_rows, GEMM_WIDE_FILL) : 0;
+    const GemmWarm warm = a.warm ? a.warm->behind(tiles, fills, a.us) : GemmWarm{};
+    hipLaunchKernelGGL(kern, dim3(tiles + fills + warm.groups), dim3(512), lds, a.st, a.A, a.W, a.bias, a.C, a.M, a.N, a.K, a.ld, tr, a.rm, a.fold, warm);
     SSAM_CHECK_LAUNCH();
     return SSAM_OK;
 }

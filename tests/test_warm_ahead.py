@@ -82,3 +82,16 @@ def test_a_block_of_either_kind_has_its_own_width(flags, Dm):
             seen[i] = seen.get(i, 0) + nbytes[j]
             assert seen[i] <= spans[i][1], (now, i)
     assert seen == {i: size for i, (_, size) in enumerate(spans) if i > 0}
+
+
+def budget(tiles, fills, us):
+    most = C.c_double()
+    return B.lib().ssam_warm_budget(C.c_int(tiles), C.c_int(fills), C.c_double(us), C.byref(most)), most.value
+
+
+@pytest.mark.parametrize("tiles,us", [(240, 13.4), (504, 54.0), (760, 91.0), (1000, 130.0), (512 + 64, 80.0)])
+def test_a_launch_reads_in_its_last_round(tiles, us):
+    """A CU without a tile in the last of several rounds has tiles until then: no more than it can read from there on, at 30 KB a microsecond."""
+    groups, most = budget(tiles, 0, us)
+    assert 8 <= groups <= -tiles % 256
+    assert 0 < most <= groups * 30e3 * us / -(-tiles // 256) * (1 + 1e-12)
