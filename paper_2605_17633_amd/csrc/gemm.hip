@@ -512,13 +512,17 @@ struct WarmBudget { int groups; double bytes; };
 // that it has no tile in (bytes a microsecond; half of it leaves weights of ViT-B's 240 tiles unread: 2 % of an encoder).  With the whole launch's time the reading ended behind
 // the tiles of two rounds and more: eight blocks of ViT-H without reading, with that, now: row-major, five images of 60 x 60, density 0.4 4662 | 4820 | 4629 us, three of 44 x 44, 0.6
 // 2018 | 2067 | 1957, packed, four of 40 x 40, 0.5 1879 | 1959 | 1868; 70 stacks with such launches 0.9 % faster than with the whole launch's time.
+// Workgroups of padding rows, 16 rows of qkv at that rate, have the idle CUs first; counted as tiles they made qkv of ViT-L behind a global block, 256 tiles and 51 of those, a launch of two
+// rounds with 205 idle CUs: 31.3 -> 32.9 us.
 WarmBudget warm_budget(int tiles, int fills, double us)
 {
     constexpr int FEWEST = 8;
-    constexpr double RATE = 30e3;
-    const int rounds = ssam_div_up(tiles + fills, 256), idle = rounds * 256 - tiles - fills;
+    constexpr double RATE = 30e3, FILL_US = 3.0;
+    const int rounds = ssam_div_up(tiles, 256), idle = rounds * 256 - tiles;
     if (idle < FEWEST) return {};
-    return { idle, idle * RATE * us / rounds };
+    const double time = us / rounds - FILL_US * ssam_div_up(fills, idle);
+    if (time <= 0.0) return {};
+    return { idle, idle * RATE * time };
 }
 
 }  // namespace

@@ -95,3 +95,17 @@ def test_a_launch_reads_in_its_last_round(tiles, us):
     groups, most = budget(tiles, 0, us)
     assert 8 <= groups <= -tiles % 256
     assert 0 < most <= groups * 30e3 * us / -(-tiles // 256) * (1 + 1e-12)
+
+
+@pytest.mark.parametrize("us", [20.0, 31.3])
+@pytest.mark.parametrize("tiles,fills", [(256, 51), (512, 102), (250, 51), (192, 51), (192, 0), (192, 100), (64, 400)])
+def test_padding_rows_are_no_tiles(tiles, fills, us):
+    """Workgroups of padding rows behind the tiles: they open no round, and take some of the idle CUs' time."""
+    groups, most = budget(tiles, fills, us)
+    alone, most_alone = budget(tiles, 0, us)
+    assert groups in (0, alone) and most <= most_alone
+    assert (groups > 0) == (most > 0)
+    if alone:
+        assert most < most_alone or not fills
+    if (tiles, fills) == (192, 51):
+        assert most > 0.8 * most_alone
