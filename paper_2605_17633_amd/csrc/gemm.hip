@@ -514,15 +514,19 @@ struct WarmBudget { int groups; double bytes; };
 // 2018 | 2067 | 1957, packed, four of 40 x 40, 0.5 1879 | 1959 | 1868; 70 stacks with such launches 0.9 % faster than with the whole launch's time.
 // Workgroups of padding rows, 16 rows of qkv at that rate, have the idle CUs first; counted as tiles they made qkv of ViT-L behind a global block, 256 tiles and 51 of those, a launch of two
 // rounds with 205 idle CUs: 31.3 -> 32.9 us.
+// More than 64 workgroups bring weights from HBM no sooner, and where the cache has them they are in the tiles' way: of 129 stacks of up to 2048 rows the 43 of ViT-B, whose weights
+// stay there, were 0.5 % slower than without reading with as many as there are CUs (1.7 % at most), and are 0.1 % slower (1.2) with 64, all of them 0.4 % faster than with more; with 48 some
+// weights are left to their contraction (four of 45 stacks slower by 3 to 4 %), with 32 such stacks are 2.5 % slower.
 WarmBudget warm_budget(int tiles, int fills, double us)
 {
-    constexpr int FEWEST = 8;
+    constexpr int FEWEST = 8, MOST = 64;
     constexpr double RATE = 30e3, FILL_US = 3.0;
     const int rounds = ssam_div_up(tiles, 256), idle = rounds * 256 - tiles;
     if (idle < FEWEST) return {};
     const double time = us / rounds - FILL_US * ssam_div_up(fills, idle);
     if (time <= 0.0) return {};
-    return { idle, idle * RATE * time };
+    const int groups = std::min(idle, MOST);
+    return { groups, groups * RATE * time };
 }
 
 }  // namespace

@@ -109,3 +109,10 @@ def test_padding_rows_are_no_tiles(tiles, fills, us):
         assert most < most_alone or not fills
     if (tiles, fills) == (192, 51):
         assert most > 0.8 * most_alone
+
+
+@pytest.mark.parametrize("tiles", [8, 64, 184, 200, 248, 256, 300, 500])
+def test_few_workgroups_read(tiles):
+    """More than 64 stand in the way of the tiles; fewer than 8 CUs are not worth a launch's while."""
+    idle = -tiles % 256
+    assert budget(tiles, 0, 12.0)[0] == (min(idle, 64) if idle >= 8 else 0)
