@@ -517,12 +517,14 @@ struct WarmBudget { int groups; double bytes; };
 // More than 64 workgroups bring weights from HBM no sooner, and where the cache has them they are in the tiles' way: of 129 stacks of up to 2048 rows the 43 of ViT-B, whose weights
 // stay there, were 0.5 % slower than without reading with as many as there are CUs (1.7 % at most), and are 0.1 % slower (1.2) with 64, all of them 0.4 % faster than with more; with 48 some
 // weights are left to their contraction (four of 45 stacks slower by 3 to 4 %), with 32 such stacks are 2.5 % slower.
-WarmBudget warm_budget(int tiles, int fills, double us)
+// A block by itself reads nothing ahead: called again on other tokens it finds its weights in the cache, and reading them once more cost 50 such blocks of 60 to 9000 rows 1.2 % (4 % at most).
+// Only a stack knows of weights that no cache holds by their turn (stacks put together from calls of single blocks, 14 of ViT-B or ViT-L, would be 3.4 % faster with it).
+WarmBudget warm_budget(int blocks, int tiles, int fills, double us)
 {
     constexpr int FEWEST = 8, MOST = 64;
     constexpr double RATE = 30e3, FILL_US = 3.0;
     const int rounds = ssam_div_up(tiles, 256), idle = rounds * 256 - tiles;
-    if (idle < FEWEST) return {};
+    if (blocks < 2 || idle < FEWEST) return {};
     const double time = us / rounds - FILL_US * ssam_div_up(fills, idle);
     if (time <= 0.0) return {};
     const int groups = std::min(idle, MOST);
@@ -533,14 +535,14 @@ WarmBudget warm_budget(int tiles, int fills, double us)
 
 GemmWarm WarmAhead::behind(int tiles, int fills, double us)
 {
-    const WarmBudget b = warm_budget(tiles, fills, us);
+    const WarmBudget b = warm_budget(blocks, tiles, fills, us);
     return b.groups ? take(b.groups, b.bytes) : GemmWarm{};
 }
 
 // Its workgroups and the most bytes that they read, of any weights.  Host only, for tests; not part of the interface.
-extern "C" int ssam_warm_budget(int tiles, int fills, double us, double *bytes)
+extern "C" int ssam_warm_budget(int blocks, int tiles, int fills, double us, double *bytes)
 {
-    const WarmBudget b = warm_budget(tiles, fills, us);
+    const WarmBudget b = warm_budget(blocks, tiles, fills, us);
     *bytes = b.bytes;
     return b.groups;
 }

@@ -84,9 +84,9 @@ def test_a_block_of_either_kind_has_its_own_width(flags, Dm):
     assert seen == {i: size for i, (_, size) in enumerate(spans) if i > 0}
 
 
-def budget(tiles, fills, us):
+def budget(tiles, fills, us, blocks=12):
     most = C.c_double()
-    return B.lib().ssam_warm_budget(C.c_int(tiles), C.c_int(fills), C.c_double(us), C.byref(most)), most.value
+    return B.lib().ssam_warm_budget(C.c_int(blocks), C.c_int(tiles), C.c_int(fills), C.c_double(us), C.byref(most)), most.value
 
 
 @pytest.mark.parametrize("tiles,us", [(240, 13.4), (504, 54.0), (760, 91.0), (1000, 130.0), (512 + 64, 80.0)])
@@ -116,3 +116,9 @@ def test_few_workgroups_read(tiles):
     """More than 64 stand in the way of the tiles; fewer than 8 CUs are not worth a launch's while."""
     idle = -tiles % 256
     assert budget(tiles, 0, 12.0)[0] == (min(idle, 64) if idle >= 8 else 0)
+
+
+@pytest.mark.parametrize("tiles", [64, 192, 240, 504])
+def test_a_block_by_itself_reads_nothing(tiles):
+    """Its weights are where its last call left them."""
+    assert budget(tiles, 0, 12.0, blocks=1) == (0, 0.0) and budget(tiles, 0, 12.0, blocks=2)[0] >= 8
