@@ -550,14 +550,13 @@ extern "C" int ssam_warm_budget(int blocks, int tiles, int fills, double us, dou
 // What a launch of `groups` workgroups without a tile reads: weights of the next contractions, no more than most_bytes, none twice.
 GemmWarm WarmAhead::take(int groups, double most_bytes)
 {
-    constexpr int AHEAD = 2;      // contractions; what lies further off is pushed out again by what is written before it is read (four ahead: 0.5 to 1 % slower)
     GemmWarm out = {};
     if (next <= now) { next = now + 1; done = 0; }
-    for (int s = 0; s < 3 && next <= now + AHEAD && next < 4 * blocks; ++s) {
+    for (int s = 0; s < GEMM_WARM_AHEAD && next <= now + GEMM_WARM_AHEAD && next < 4 * blocks; ++s) {
         const ssam_block_weights &b = w[next / 4];
         const size_t mlp = (size_t)2 * D * Dm[is_global && is_global[next / 4]], sizes[4] = { (size_t)6 * D * D, (size_t)2 * D * D, mlp, mlp };
         const void *at[4] = { b.wqkv, b.wproj, b.w1, b.w2 };
-        size_t bytes = sizes[next % 4] - done;
+        size_t bytes = std::min(sizes[next % 4] - done, (size_t)GEMM_WARM_PIECE);
         if ((double)bytes > most_bytes) bytes = (size_t)most_bytes & ~(size_t)8191;
         if (bytes == 0 || !at[next % 4] || !ssam_aligned16(at[next % 4])) break;      // (the contraction itself refuses such weights)
         out.at[s] = (const unsigned char *)at[next % 4] + done;
@@ -579,7 +578,7 @@ int WarmAhead::pieces(int launch, int groups, double most_bytes, const void **at
     GemmWarm out = {};
     for (now = 0; now <= launch; ++now) out = take(groups, most_bytes);
     int k = 0;
-    for (; k < 3 && out.bytes[k]; ++k) { at[k] = out.at[k]; bytes[k] = out.bytes[k]; }
+    for (; k < GEMM_WARM_AHEAD && out.bytes[k]; ++k) { at[k] = out.at[k]; bytes[k] = out.bytes[k]; }
     return out.groups == groups || k == 0 ? k : SSAM_EINVAL;
 }
 

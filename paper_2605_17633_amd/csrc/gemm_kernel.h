@@ -108,9 +108,11 @@ inline size_t gemm_split_beside_parts(long rows, int D)
 // megabyte of weights costs the contraction that reads it 0.2 to 0.4 us (its first slabs wait, and a chain over K has four slabs in flight): 1228 x 1024 x 4096
 // 22.1 us, 18.4 from the cache; 8192 x 3840 x 1280 77.3, 72.2.  Encoders: ViT-B, one image 1138 -> 1076 us; ViT-L, one image 2405 -> 2315; ViT-B, 50 x 50, two
 // images 1469 -> 1369; ViT-H, content order, two images 7620 -> 7214.
+constexpr int GEMM_WARM_AHEAD = 2;            // contractions; what lies further off is pushed out again by what is written before it is read (four ahead: 0.5 to 1 % slower)
+constexpr uint32_t GEMM_WARM_PIECE = 1u << 30;  // the most bytes of a piece: offsets are 32 bits, past its end too
 struct GemmWarm {
-    const unsigned char *at[3];
-    uint32_t bytes[3];        // multiples of 16
+    const unsigned char *at[GEMM_WARM_AHEAD];
+    uint32_t bytes[GEMM_WARM_AHEAD];      // multiples of 16
     int groups;               // workgroups behind the tiles; 0: none
 };
 

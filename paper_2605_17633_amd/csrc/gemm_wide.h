@@ -79,8 +79,9 @@ constexpr int GEMM_WIDE_FILL = 16;
 __device__ __forceinline__ void gemm_warm(const GemmWarm &warm, int group)
 {
     constexpr uint32_t STEP = 512 * 16, U = 4;
+    static_assert(GEMM_WARM_PIECE + U * 256 * STEP < 1ull << 32, "32-bit offsets past the end of a piece");
     const uint32_t stride = warm.groups * STEP;
-    for (int s = 0; s < 3; ++s) {
+    for (int s = 0; s < GEMM_WARM_AHEAD; ++s) {
         const uint32_t bytes = warm.bytes[s];
         for (uint32_t at = group * STEP + threadIdx.x * 16; at < bytes; at += U * stride) {
             u32x4 v[U];

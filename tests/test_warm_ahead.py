@@ -122,3 +122,16 @@ def test_few_workgroups_read(tiles):
 def test_a_block_by_itself_reads_nothing(tiles):
     """Its weights are where its last call left them."""
     assert budget(tiles, 0, 12.0, blocks=1) == (0, 0.0) and budget(tiles, 0, 12.0, blocks=2)[0] >= 8
+
+
+@pytest.mark.parametrize("D,Dm", [(16384, 131072), (16384, 131072 - 128), (8192, 131072), (32768, 4096)])
+def test_a_piece_of_a_huge_weight_keeps_its_offsets_in_32_bits(D, Dm):
+    """A thread reads 16 bytes at offsets up to a piece's end and one stride of all workgroups (256 of 8 KB, four times) past it."""
+    ws, spans = stack(3, D, Dm)
+    seen = {}
+    for now in range(12):
+        for at, n in pieces(ws, D, Dm, now, 32, 1e13):
+            i = next(j for j, (b, size) in enumerate(spans) if b <= at < b + size)
+            assert 0 < n <= 2 ** 30 and n % 16 == 0
+            assert at - spans[i][0] >= seen.get(i, 0) and at + n <= spans[i][0] + spans[i][1]
+            seen[i] = at + n - spans[i][0]
