@@ -259,7 +259,8 @@ int pick_ring(int M, int N, int K, bool packed, bool whole_lines, double &launch
 // What the GELU epilogue adds to a ring's estimate, which is an average over the epilogues, by the columns x rows that its busiest CU finishes (two 128x128 tiles: 1.5 us).
 // Only against the wide kernel, whose estimate has it, and of the tiles of 128 rows: 94 routed MLPs of 900 to 3500 rows that it moves are 2.4 % faster (none slower), 64x64 rings
 // of 120 to 640 rows were 2 to 5 % faster than what it would move them to.  2500 x 3072 x 768 takes the ring 19.5 to 20.3 us, estimated as 16.9, and 256x128 17.8 with 56 CUs left to read weights ahead
-// (encoders of ViT-B, two images of 50 x 50: 1256 -> 1236 us packed, 1253 -> 1235 row-major).
+// (encoders of ViT-B, two images of 50 x 50: 1256 -> 1236 us packed, 1253 -> 1235 row-major).  With gather and LN2 folded in: 25 routed MLPs of 1580 to 3270 rows
+// (512 x 2048 to 1024 x 4096) 0.5 to 3.5 % faster, 26 stacks 1.1 % together (9 images of 30 x 30 of ViT-L's width, density 0.2 164.4 -> 158.0 us a block), none slower; same bits.
 double ring_gelu_us(int ring, int M, int N, int epilogue)
 {
     if (ring < 0 || ring >= RING_DIRECT || epilogue != SSAM_EPI_BIAS_GELU) return 0.0;
@@ -413,8 +414,8 @@ Choice choose(int M, int N, int K, int epilogue, const GemmLd &ld, const SplitWs
 // large tiles by itself.
 constexpr double PARTS_US = 3.0;
 
-// The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics come in pieces.
-Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, bool parts)
+// The same for fc1 with gather and LayerNorm folded in.  parts: its row statistics come in pieces.  ring_gelu: see ring_gelu_us.
+Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, const SplitWs &ws, bool parts, bool ring_gelu = true)
 {
     Choice c;
     if (parts && large_reads_parts(K)) {
@@ -428,7 +429,7 @@ Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, cons
     }
     c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us);
     c.ring = pick_ring(M, N, K, true, true, c.us);
-    if (parts) c.us += PARTS_US;
+    c.us += parts ? PARTS_US : ring_gelu ? ring_gelu_us(c.ring, M, N, SSAM_EPI_BIAS_GELU) : 0.0;
     c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, c.us, c.us, parts ? PARTS_READ_GATHERED : PARTS_NONE);
     return c;
 }
@@ -453,7 +454,7 @@ Choice choose_ln(int M, int N, int K, const GemmLd &ld, bool parts)
 // The contractions of a block with both LayerNorms folded in that can read or leave pieces: qkv, proj, fc1, fc2.
 struct BlockChoices { Choice c[4]; };
 
-BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
+BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts, bool ring_gelu = true)
 {
     alignas(16) static unsigned char some;
     // fc1 and fc2 with what the launch will have: the kernel that is found here has to be the one that is taken there
@@ -461,7 +462,7 @@ BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
     const PartsUse left = parts ? PARTS_LEFT : PARTS_NONE;
     return { { choose_ln(rows, 3 * D, D, GemmLd{ D, D, 3 * D }, parts),
                choose(rows, D, D, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ D, D, D }, whole, true, left),
-               choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, parts),
+               choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, parts, ring_gelu),
                choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, left) } };
 }
 
@@ -478,7 +479,9 @@ BlockChoices block_choices(int rows, int kept, int D, int Dm, bool parts)
 int ssam_parts_form_of(int rows, int kept, int D, int Dm)
 {
     if (D % 128 != 0 || D / 64 > GEMM_PARTS_MOST) return 0;
-    const BlockChoices with = block_choices(rows, kept, D, Dm, true), without = block_choices(rows, kept, D, Dm, false);
+    // (what fc1 takes without is as LAUNCH_US was fitted.  With a ring's GELU charged there nine more stacks would have pieces, at a density of 0.2: seven of them were 0.2 % faster than with
+    // the ring, less than the wide kernel without pieces is by itself)
+    const BlockChoices with = block_choices(rows, kept, D, Dm, true), without = block_choices(rows, kept, D, Dm, false, false);
     constexpr double LAUNCH_US = 5.0;
     double gain[2] = { LAUNCH_US, LAUNCH_US };    // of the pieces between proj and fc1, and between fc2 and qkv
     const bool large = large_reads_parts(D);
@@ -635,7 +638,7 @@ int ssam_linear_impl(const void *A, const void *W, const float *bias, void *C, i
 }
 
 // fc1 of the routed MLP with gather and LN2 folded in (see GemmFold): rows src[m] of A, packed folded weights,
-// GELU epilogue, any M; the kernel is picked as for the plain contraction of the same shape.  rows_a: rows of A.
+// GELU epilogue, any M; the kernel is picked as for the plain contraction of the same shape (choose_fold_gelu), but in one layout only.  rows_a: rows of A.
 // With parts (see ssam_parts_form_of) there are no stats, and src holds the rows of every batch of src_rows: row m / src_rows * src_stride + src[m] of A.
 int ssam_linear_fold_gelu_impl(const void *A, long rows_a, const int32_t *src, const float *stats, const void *Wfp, const float *colsum,
                                const float *bias_f, void *C, int M, int N, int K, const GemmLd &ld,
@@ -713,6 +716,13 @@ extern "C" int ssam_linear_ln(const void *x, int ldx, const float *stats, const 
     if (M % 128 != 0 || N % 256 != 0 || K % GEMM_BK != 0) return SSAM_EUNSUPPORTED;
     const GemmRowMap rm = { row_map, rows_per_batch, map_batch_stride, dst_rows_per_batch };
     return ssam_linear_ln_impl(x, stats, Wfp, colsum, bias_f, C, M, N, K, GemmLd{ ldx, K, ldc }, rm, (hipStream_t)stream, GemmParts{}, PadFill{}, nullptr);
+}
+
+// The wide kernel's tile of fc1 with gather and LN2 folded in, its row statistics from a launch, or -1: the ring or the large tiles.  Host only, for tests; not part of the interface.
+extern "C" int ssam_fold_gelu_wide_form(int rows, int kept, int D, int Dm)
+{
+    alignas(16) unsigned char some;
+    return choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, SplitWs{ &some, GEMM_SPLIT_WS_BYTES }, false).wide;
 }
 
 // Which kernel a contraction takes where the wide kernel does not (tile 0; `folded`: ssam_linear_ln): the large tile's id, or 16 + the ring's index (16: 128x128,
