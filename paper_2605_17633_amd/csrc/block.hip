@@ -216,6 +216,25 @@ extern "C" size_t ssam_encoder_block_workspace_bytes(const ssam_block_cfg *cfg)
     return block_core_bytes(cfg, g) + block_tables_bytes(cfg->B, g);
 }
 
+// Form of the row statistics (ssam_parts_form_of) and the scratch in which fc1 and fc2 may cut K: the kernels of the longer rows do so beside the pieces that lie in
+// the same scratch (a single block likewise: the same cuts, the same bits).
+struct PartsPlan { int form; size_t split_bytes; };
+
+static PartsPlan parts_plan(int rows, int kept, int D, int Dm)
+{
+    const size_t beside = gemm_split_beside_parts(rows, D);
+    const int form = beside ? ssam_parts_form_of(rows, kept, D, Dm) : 0;
+    return { form, form ? beside : GEMM_SPLIT_WS_BYTES };
+}
+
+// The same.  Host only, for tests; not part of the interface.
+extern "C" int ssam_parts_plan(int rows, int kept, int D, int Dm, size_t *split_bytes)
+{
+    const PartsPlan plan = parts_plan(rows, kept, D, Dm);
+    *split_bytes = plan.split_bytes;
+    return plan.form;
+}
+
 // tables: this block's block_tables_bytes region; tables_ready: a stack has built it already
 // parts_ready (a block of a stack): the row statistics of x in pieces (GemmParts) are up to date, on entry from the block before.  They lie at the end of the
 // workspace's bytes in front of the tables, the K-split scratch of the MLP; a stack's blocks all have the same end.  proj writes every row, and with it its
@@ -259,11 +278,9 @@ static int encoder_block_impl(void *x, const ssam_block_weights *w, const ssam_b
     if (kv_shift && (!fold || !w->bproj_folded)) return SSAM_EINVAL;
     const float *bproj = kv_shift ? w->bproj_folded : w->bproj;
     const size_t parts_bytes = gemm_parts_bytes(crows, D);
-    const int form = fold && w->fold_ln2 != 0 && gemm_split_beside_parts(crows, D) != 0 ? ssam_parts_form_of(crows, B * cfg->K, D, cfg->Dm) : 0;
+    const auto [form, split_bytes] = fold && w->fold_ln2 != 0 ? parts_plan(crows, B * cfg->K, D, cfg->Dm) : PartsPlan{ 0, GEMM_SPLIT_WS_BYTES };
     const GemmParts parts = form ? GemmParts{ (float2 *)((unsigned char *)workspace + (workspace_bytes & ~(size_t)255) - parts_bytes), D / 64, cfg->eps } : GemmParts{};
     const GemmParts whole = form == 3 ? parts : GemmParts{}, tile_only = { nullptr, whole.slots, cfg->eps };       // (in a single block: a stack's blocks are then the same bits)
-    // the kernels of the longer rows cut K beside the pieces that lie in the same scratch (a single block likewise: the same cuts, the same bits)
-    const size_t split_bytes = form ? gemm_split_beside_parts(crows, D) : GEMM_SPLIT_WS_BYTES;
     const bool have_parts = whole.at && parts_ready && *parts_ready;
     if (parts_ready) *parts_ready = whole.at != nullptr;
     if (!tables_ready) {

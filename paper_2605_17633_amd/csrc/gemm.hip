@@ -507,6 +507,15 @@ extern "C" int ssam_parts_tiles(int rows, int kept, int D, int Dm, int *tiles)
     return form;
 }
 
+// And what the launches of fc1 and fc2 take with split_bytes of scratch (fc1 reads pieces in form 1 and 3, fc2 leaves them in form 3).
+extern "C" void ssam_mlp_tiles(int rows, int kept, int D, int Dm, int form, size_t split_bytes, int *tiles)
+{
+    alignas(16) unsigned char some;
+    const SplitWs ws = { &some, split_bytes };
+    tiles[0] = choose_fold_gelu(kept, Dm, D, GemmLd{ D, D, Dm }, rows, ws, form != 0).wide;
+    tiles[1] = choose(kept, D, Dm, SSAM_EPI_BIAS_SCATTER_ADD, GemmLd{ Dm, Dm, D }, ws, true, form == 3 ? PARTS_LEFT : PARTS_NONE).wide;
+}
+
 namespace {
 
 struct WarmBudget { int groups; double bytes; };

@@ -26,13 +26,14 @@ CASES = [
 ]
 
 
-def device_weights(gen, D, w):
+def device_weights(gen, D, w, Dm=None):
+    Dm = Dm or 4 * D
     n = lambda *s, std=0.02, dtype=torch.float32: (torch.randn(*s, generator=gen, device=DEV) * std).to(dtype)
     bf = torch.bfloat16
     # a strong output projection: the rows that fc1 reads then have statistics of their own, not those of the block's input
     return {"ln1_g": 1 + n(D), "ln1_b": n(D), "wqkv": n(3 * D, D, dtype=bf), "bqkv": n(3 * D), "rel_h": n(2 * w - 1, 64, dtype=bf), "rel_w": n(2 * w - 1, 64, dtype=bf),
-            "wproj": n(D, D, std=0.1, dtype=bf), "bproj": n(D), "ln2_g": 1 + n(D), "ln2_b": n(D), "w1": n(4 * D, D, dtype=bf), "b1": n(4 * D),
-            "w2": n(D, 4 * D, dtype=bf), "b2": n(D)}
+            "wproj": n(D, D, std=0.1, dtype=bf), "bproj": n(D), "ln2_g": 1 + n(D), "ln2_b": n(D), "w1": n(Dm, D, dtype=bf), "b1": n(Dm),
+            "w2": n(D, Dm, dtype=bf), "b2": n(D)}
 
 
 def close(got, want, start, what):
@@ -46,17 +47,21 @@ def close(got, want, start, what):
 
 @pytest.mark.parametrize("D,images,g,density,form,tiles,kv", CASES)
 def test_row_statistics_in_pieces(D, images, g, density, form, tiles, kv):
-    announce("row statistics in pieces", D, images, g, density, form, tiles, kv)
+    check_row_statistics_in_pieces(D, images, g, density, form, tiles, kv, 4 * D)
+
+
+def check_row_statistics_in_pieces(D, images, g, density, form, tiles, kv, Dm):
+    announce("row statistics in pieces", D, images, g, density, form, tiles, kv, Dm)
     gen = torch.Generator(device=DEV).manual_seed(D + images * g)
     n, ws = g * g, 14
     K = B.ssam_keep_count(n, density)
     flags = [False, True, False]
-    base = [device_weights(gen, D, g if f else ws) for f in flags]
+    base = [device_weights(gen, D, g if f else ws, Dm) for f in flags]
     fold = dict(fold_ln1=True, fold_kv_bias=kv)
     wts = [B.pack_block_weights(w, fold_ln2=True, **fold) for w in base]
     structs = [B.block_weights_struct(w) for w in wts]
-    cfg_l = B.make_cfg(images, g, D, D // 64, 4 * D, ws, 32, K, 0.4)
-    cfg_g = B.make_cfg(images, g, D, D // 64, 4 * D, 0, 128, K, 0.4)
+    cfg_l = B.make_cfg(images, g, D, D // 64, Dm, ws, 32, K, 0.4)
+    cfg_g = B.make_cfg(images, g, D, D // 64, Dm, 0, 128, K, 0.4)
     dev = lambda a: torch.from_numpy(a).to(DEV)
     wtab, wsig, gtab = dev(B.ssam_build_window_table(g, ws, 4)), dev(B.ssam_build_perm(ws, ws, 4)[0]), dev(B.ssam_build_perm(g, g, 4)[0])
     x0 = torch.randn(images, n, D, generator=gen, device=DEV).bfloat16()

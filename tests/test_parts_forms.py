@@ -7,9 +7,9 @@ from paper_2605_17633_amd import binding as B
 from test_gpu_row_statistics import CASES
 
 
-def parts(D, images, g, density):
+def parts(D, images, g, density, Dm=None):
     tiles = (C.c_int * 4)()
-    form = B.lib().ssam_parts_tiles(C.c_int(images * g * g), C.c_int(images * B.ssam_keep_count(g * g, density)), C.c_int(D), C.c_int(4 * D), tiles)
+    form = B.lib().ssam_parts_tiles(C.c_int(images * g * g), C.c_int(images * B.ssam_keep_count(g * g, density)), C.c_int(D), C.c_int(Dm or 4 * D), tiles)
     return form, tuple(tiles)
 
 

@@ -1,7 +1,10 @@
 """Where the row statistics of folded stacks of width 1280 come in pieces, and by which tiles (host code: no GPU needed)."""
+import ctypes as C
+
 import pytest
 
-from test_gpu_row_statistics_long import CASES
+from paper_2605_17633_amd import binding as B
+from test_gpu_row_statistics_long import CASES, WIDTHS
 from test_parts_forms import parts, reached
 
 
@@ -28,3 +31,36 @@ def test_none_where_they_cost_more_than_a_launch(images, g, density, us):
 @pytest.mark.parametrize("images,g,density,us", [(2, 64, 0.3, (223.0, 218.8)), (3, 48, 0.4, (229.6, 219.6)), (2, 32, 0.2, (94.2, 90.8)), (1, 64, 0.2, (129.3, 126.7))])
 def test_both_launches_saved_where_that_pays(images, g, density, us):
     assert parts(1280, images, g, density)[0] == 3
+
+
+def test_the_gpu_tests_of_other_widths_take_what_they_name():
+    for D, images, g, density, form, tiles, kv, Dm in WIDTHS:
+        assert parts(D, images, g, density, Dm) == (form, tiles), (images, g, density, Dm)
+
+
+def mlp_tiles(rows, kept, D, Dm, form, split_bytes):
+    tiles = (C.c_int * 2)()
+    B.lib().ssam_mlp_tiles(*(C.c_int(v) for v in (rows, kept, D, Dm, form)), C.c_size_t(split_bytes), tiles)
+    return tuple(tiles)
+
+
+@pytest.mark.parametrize("D", [512, 768, 1024, 1280])
+def test_the_launches_take_what_the_form_was_decided_by(D):
+    """With the scratch that is left beside the pieces.  (fc2 leaves none in form 1, and takes what it likes.)"""
+    whole, other = 32 << 20, 0
+    for Dm in (256, 768, 1024, 1536, 2048, 2560, 3840, 4096, 5120, 6144, 8704, 10240, 16384):
+        for rows in (128, 640, 1024, 2176, 2304, 2816, 3456, 4096, 7168, 9216, 16384):
+            for kept in (rows // 10, rows * 3 // 10, rows // 2, rows * 3 // 4, rows):
+                if not kept:
+                    continue
+                split_bytes, tiles = C.c_size_t(), (C.c_int * 4)()
+                sizes = [C.c_int(v) for v in (rows, kept, D, Dm)]
+                form = B.lib().ssam_parts_tiles(*sizes, tiles)
+                assert B.lib().ssam_parts_plan(*sizes, C.byref(split_bytes)) == form
+                if not form:
+                    assert split_bytes.value == whole
+                    continue
+                got = mlp_tiles(rows, kept, D, Dm, form, split_bytes.value)
+                assert got[0] == tiles[2] and (form == 1 or got[1] == tiles[3] >= 0), (rows, kept, Dm, form)
+                other += form == 3 and got != mlp_tiles(rows, kept, D, Dm, form, whole)
+    assert (other > 0) == (D == 1280)        # (the shorter rows' kernels that read or leave pieces cut no K)
