@@ -493,7 +493,11 @@ int ssam_parts_form_of(int rows, int kept, int D, int Dm)
         gain[1] = std::max(4.0, 3.4 + rows * row_us);
     }
     for (int i = 0; i < 4; ++i) gain[i == 0 || i == 3] -= with.c[i].wide < 0 && !(large && i % 2 == 0) ? 1e30 : with.c[i].us - without.c[i].us;
-    if (gain[1] > 0 && gain[0] + gain[1] > 0) return 3;
+    // The estimates fall short where fc1 leaves the small tiles for one that reads twenty pieces, and of its largest launches.  With any gain at all, 97 shapes whose MLP is not four times as
+    // wide (200 to 3500 kept rows with Dm 512 to 3840, 7000 and more with 7680) were 1.6 % slower with pieces than without as stacks (4.6 % at most; 11 faster, by 1.7 % at most) and 3.4 % as blocks
+    // by themselves (7 % at most): 3 images of 16 x 16, dense, Dm = 1280 62.2 and 72.1 us a block without, 64.5 and 76.3 with.  At four times nothing changes.
+    const double least = large && with.c[2].us - without.c[2].us > 4.5 ? 1.5 : 0.0;
+    if (gain[1] > 0 && gain[0] + gain[1] > least) return 3;
     return gain[0] > 0 ? 1 : 0;
 }
 

@@ -32,9 +32,8 @@ def test_row_statistics_in_twenty_pieces(D, images, g, density, form, tiles, kv)
 
 # with MLPs that are not four times as wide: the large tile's forms that D * 4 does not reach, as kept rows x Dm here
 WIDTHS = [
-    (1280, 10, 8, 0.5, 3, (4, 0, -1, 0), True, 1024),       # 12 tiles, all of them left over: K cut in a launch of its own, and their sum
-    (1280, 3, 16, 0.3, 3, (4, 0, -1, 0), False, 768),       # the same, ragged rows
-    (1280, 16, 4, 0.1, 1, (0, 0, -1, -1), True, 10240),     # the same of 16 rows
+    (1280, 16, 4, 0.1, 1, (0, 0, -1, -1), True, 10240),     # 40 tiles, all of them left over: K cut in a launch of its own, and their sum; 16 rows
+    (1280, 3, 16, 0.02, 1, (4, 0, -1, -1), False, 10240),   # the same, ragged rows
     (1280, 1, 64, 0.4, 1, (-1, 6, -1, 2), False, 10240),    # a round and left-over tiles with K cut
     (1280, 2, 32, 0.9, 1, (7, 4, -1, -1), True, 10240),     # a round and left-over tiles in one piece
     (1280, 2, 64, 0.75, 1, (-1, 9, -1, -1), False, 1280),   # less than a round

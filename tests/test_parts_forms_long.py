@@ -64,3 +64,9 @@ def test_the_launches_take_what_the_form_was_decided_by(D):
                 assert got[0] == tiles[2] and (form == 1 or got[1] == tiles[3] >= 0), (rows, kept, Dm, form)
                 other += form == 3 and got != mlp_tiles(rows, kept, D, Dm, form, whole)
     assert (other > 0) == (D == 1280)        # (the shorter rows' kernels that read or leave pieces cut no K)
+
+
+# us a block of a stack, without and with pieces: 64.2, 66.7; 83.6, 85.7; 62.2, 64.5; 51.5, 53.8; 536.6, 553.8
+@pytest.mark.parametrize("images,g,density,Dm", [(1, 32, 0.3, 2560), (7, 16, 0.2, 2560), (3, 16, 1.0, 1280), (10, 8, 0.4, 768), (4, 48, 1.0, 7680)])
+def test_none_for_an_mlp_that_loses_more_than_the_launches(images, g, density, Dm):
+    assert parts(1280, images, g, density, Dm)[0] == 0
