@@ -309,8 +309,10 @@ enum PartsUse { PARTS_LEFT, PARTS_READ, PARTS_READ_GATHERED, PARTS_NONE };
 // are left to the large tiles, two workgroups to a CU, whose epilogues run under other workgroups' main loops (16384 x 1280 x 5120:
 // 180 us against 185, 32768 x 3840 x 1280: 264 against 269); with row-major weights those are alone on their CU too, and four are fitted.
 // parts: what the kernel does with row statistics in pieces, of the tiles that can; what that takes is not held against the others, who would have to wait for a
-// launch.  launch_us: what is taken, on return.
-int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double &launch_us, double both_us, PartsUse parts = PARTS_NONE)
+// launch, but where others_read: they read pieces too, and launch_us has it.  Left out there, fc1 of 1265 to 1536 rows (x 5120 x 1280) was left to the large tile for a margin that two rounds of
+// 192x192 wanted, 1 to 6 % of a block slower (2 images of 40 x 40, density 0.4 135.8 us, 125.9 with 256x128), and qkv of 3328 to 5120 rows taken from it, 1 to 2.5 % (5 of 32 x 32, 0.6 200.7,
+// 196.4).  launch_us: what is taken, on return.
+int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, long rows_a, double &launch_us, double both_us, PartsUse parts = PARTS_NONE, bool others_read = false)
 {
     const unsigned among = parts == PARTS_NONE ? ~0u : parts == PARTS_LEFT ? GEMM_WIDE_WRITES_PARTS : GEMM_WIDE_READS_PARTS;
     const int nk = K / GEMM_BK;
@@ -331,7 +333,7 @@ int pick_wide(int M, int N, int K, int epilogue, const GemmLd &ld, bool packed, 
         if (us + parts_us < best_us + best_parts) { best_us = us; best_parts = parts_us; best = i; }
     }
     const double others_us = best >= 0 && wide_tiles[best].bm * wide_tiles[best].bn < 128 * 128 && both_us < launch_us ? both_us : launch_us;
-    if (best_us >= 0.99 * others_us) return -1;
+    if (best_us + (others_read ? best_parts : 0.0) >= 0.99 * others_us) return -1;
     launch_us = best_us + best_parts;
     return best;
 }
@@ -394,9 +396,6 @@ struct Choice { int wide, tile, ring; double us; };
 // 1.2 of gathered rows (8192 x 3840 x 1280 69.0 -> 68.8 us, 32768 264.1 -> 268.7; 2456 x 5120 x 1280 40.0 -> 41.3).  It leaves none: 32768 x 1280 x 1280 103.9 -> 109.7,
 // and at such sizes, at the power limit, ViT-H of 8 images was 0.8 % slower with its launches saved.
 constexpr int LARGE_PARTS_TILE = 4;
-// By the estimates two rounds of 192x192 are 1 us faster for 3276 x 5120 x 1280; blocks of 8192 rows at a density of 0.4 took 262 us with them, 246 with the large tile
-// and 254 without pieces.
-constexpr double LARGE_PARTS_AHEAD_US = 3.0;
 bool large_reads_parts(int D) { return D / 64 > GEMM_PARTS_LINE; }
 double large_parts_us(int M, int N, bool gathered) { return ssam_div_up((long)ssam_div_up(M, 128) * ssam_div_up(N, 256), 512) * (gathered ? 1.2 : 0.5); }
 
@@ -422,9 +421,7 @@ Choice choose_fold_gelu(int M, int N, int K, const GemmLd &ld, long rows_a, cons
         c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us, LARGE_PARTS_TILE);
         c.ring = -1;
         c.us += large_parts_us(M, N, true);
-        double us = c.us - LARGE_PARTS_AHEAD_US;
-        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, us, us, PARTS_READ_GATHERED);
-        if (c.wide >= 0) c.us = us;
+        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_GELU, ld, true, rows_a, c.us, c.us, PARTS_READ_GATHERED, true);
         return c;
     }
     c.tile = pick_tile(M, N, K, SSAM_EPI_BIAS_GELU, ws, true, c.us);
@@ -442,7 +439,7 @@ Choice choose_ln(int M, int N, int K, const GemmLd &ld, bool parts)
     Choice c = { -1, 4, -1, folded_ln_us((M / 128) * (N / 256), K) };
     if (parts && large_reads_parts(K)) {
         c.us += large_parts_us(M, N, false);
-        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, c.us, c.us, PARTS_READ);
+        c.wide = pick_wide(M, N, K, SSAM_EPI_BIAS_SCATTER, ld, true, 0, c.us, c.us, PARTS_READ, true);
         return c;
     }
     c.ring = pick_ring(M, N, K, true, true, c.us);
@@ -493,10 +490,10 @@ int ssam_parts_form_of(int rows, int kept, int D, int Dm)
         gain[1] = std::max(4.0, 3.4 + rows * row_us);
     }
     for (int i = 0; i < 4; ++i) gain[i == 0 || i == 3] -= with.c[i].wide < 0 && !(large && i % 2 == 0) ? 1e30 : with.c[i].us - without.c[i].us;
-    // The estimates fall short where fc1 leaves the small tiles for one that reads twenty pieces, and of its largest launches.  With any gain at all, 97 shapes whose MLP is not four times as
-    // wide (200 to 3500 kept rows with Dm 512 to 3840, 7000 and more with 7680) were 1.6 % slower with pieces than without as stacks (4.6 % at most; 11 faster, by 1.7 % at most) and 3.4 % as blocks
-    // by themselves (7 % at most): 3 images of 16 x 16, dense, Dm = 1280 62.2 and 72.1 us a block without, 64.5 and 76.3 with.  At four times nothing changes.
-    const double least = large && with.c[2].us - without.c[2].us > 4.5 ? 1.5 : 0.0;
+    // The estimates fall short where fc1 leaves the small tiles for one that reads twenty pieces, and of its largest launches.  With any gain at all, 115 shapes, nearly all with an MLP that is not
+    // four times as wide (200 to 3500 kept rows with Dm 512 to 3840, 7000 and more with 7680), were 1.2 % slower with pieces than without as stacks (4.6 % at most; 23 faster, by 2.8 % at most) and
+    // 3.2 % as blocks by themselves (7 % at most): 3 images of 16 x 16, dense, Dm = 1280 62.2 and 72.1 us a block without, 64.5 and 76.3 with.
+    const double least = large && with.c[2].us - without.c[2].us > 4.5 ? 2.5 : 0.0;
     if (gain[1] > 0 && gain[0] + gain[1] > least) return 3;
     return gain[0] > 0 ? 1 : 0;
 }

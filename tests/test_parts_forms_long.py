@@ -70,3 +70,16 @@ def test_the_launches_take_what_the_form_was_decided_by(D):
 @pytest.mark.parametrize("images,g,density,Dm", [(1, 32, 0.3, 2560), (7, 16, 0.2, 2560), (3, 16, 1.0, 1280), (10, 8, 0.4, 768), (4, 48, 1.0, 7680)])
 def test_none_for_an_mlp_that_loses_more_than_the_launches(images, g, density, Dm):
     assert parts(1280, images, g, density, Dm)[0] == 0
+
+
+# kept rows 1280 to 1536 in one round of 256x128 (us a block of a stack with it, with the large tile: 143.4, 151.1; 125.9, 135.8; 132.6, 140.8), 3276 not in two of 192x192 (205.3, 198.9)
+@pytest.mark.parametrize("images,g,density,fc1", [(1, 64, 0.35, 7), (2, 40, 0.4, 7), (12, 16, 0.5, 7), (4, 32, 0.8, -1), (1, 64, 0.8, -1)])
+def test_fc1_reads_pieces_in_the_faster_tile(images, g, density, fc1):
+    assert parts(1280, images, g, density)[1][2] == fc1
+
+
+# 200.7 us by the wide kernel, 196.4 by the large tile; 160.3, 158.4
+@pytest.mark.parametrize("images,g,density", [(5, 32, 0.6), (6, 24, 0.75)])
+def test_qkv_reads_pieces_in_the_faster_tile(images, g, density):
+    form, tiles = parts(1280, images, g, density)
+    assert form == 3 and tiles[0] == -1
