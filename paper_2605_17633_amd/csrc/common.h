@@ -116,8 +116,8 @@ __device__ __forceinline__ void fill_pad_row(const PadFill &f, int r)
 
 constexpr int GEMM_PARTS_LINE = 16;           // pieces of a row's statistics (GemmParts) in 128 bytes, a row of a slab of 64 bf16
 constexpr int GEMM_PARTS_MOST = 20;           // the most: rows of 1280
-// pieces from one row to the next (their number is even: rows begin on 16 bytes)
-__host__ __device__ constexpr int gemm_parts_pitch(int slots) { return slots > GEMM_PARTS_LINE ? slots : GEMM_PARTS_LINE; }
+// pieces from one row to the next: what a reader requests of a row, whatever their number, lies inside it (128 bytes, and above 16 pieces 32 more)
+__host__ __device__ constexpr int gemm_parts_pitch(int slots) { return slots > GEMM_PARTS_LINE ? GEMM_PARTS_MOST : GEMM_PARTS_LINE; }
 
 // Of 8 columns of a piece of a row's statistics (GemmParts): their sum, their squared deviations from the piece's mean.  In this order wherever pieces are written.
 __device__ __forceinline__ float gemm_piece_sum8(const float *v)

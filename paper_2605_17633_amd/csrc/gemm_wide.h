@@ -64,6 +64,7 @@ struct GemmWide {
     static constexpr int QA = BM / 8, QW = BN / 8, L = (QA + QW + 7) / 8, LREST = (QA + QW) % 8;
     static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0 && (WGK == 2 || (QA % 8 == 0 && QW % 8 == 0)), "whole MFMA tiles and requests");
     static_assert(GEMM_BK * 2 == GEMM_PARTS_LINE * 8 && GEMM_PARTS_MOST <= GEMM_PARTS_LINE + 4, "a row's pieces take the place of its part of a slab, the rest 32 bytes");
+    static_assert(gemm_parts_pitch(GEMM_PARTS_LINE) >= GEMM_PARTS_LINE && gemm_parts_pitch(GEMM_PARTS_LINE + 1) >= GEMM_PARTS_LINE + 4, "and of no other row");
     static_assert(WGK == 1 || (size_t)BM * BN * 4 <= ring, "the halves are added in the ring's LDS");
     // Row statistics in pieces (GemmParts).  Waves that hold whole pieces of 64 columns, or halves of which the next wave has the other, can write them.
     static constexpr bool WRITES_PARTS = (NT * 16 == 32 && WGN % 2 == 0) || NT * 16 == 64;

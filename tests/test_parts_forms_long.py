@@ -83,3 +83,11 @@ def test_fc1_reads_pieces_in_the_faster_tile(images, g, density, fc1):
 def test_qkv_reads_pieces_in_the_faster_tile(images, g, density):
     form, tiles = parts(1280, images, g, density)
     assert form == 3 and tiles[0] == -1
+
+
+@pytest.mark.parametrize("D", [1152, 1280])
+def test_every_row_of_pieces_has_what_its_readers_request(D):
+    """128 bytes and, above 16 pieces, 32 more: the last row's lie inside the workspace.  (Blocks whose qkv folds its LayerNorm have no width between 1024 and 1280.)"""
+    rows, split_bytes = 2048, C.c_size_t()
+    assert B.lib().ssam_parts_plan(*(C.c_int(v) for v in (rows, rows // 2, D, 4 * D)), C.byref(split_bytes)) == 3
+    assert split_bytes.value == (32 << 20) - 256 - 160 * rows
