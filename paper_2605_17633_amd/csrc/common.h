@@ -36,13 +36,15 @@ struct PadFill {
     int npad, rows_per_batch, total_rows;      // total_rows = B * npad; 0: none
 };
 
+constexpr int SEL_THREADS = 1024;             // threads of a workgroup that selects, compacts or inverts, and slots of a table that it inverts
+
 // Tables of one kind of block that depend only on its gather table [image][Nout]: see compact_slots_kernel (real_slot = NULL: no padding) and
 // invert_table_kernel (slot_of = NULL: not wanted; slot_images: 1 if all images share the table).
 struct BlockTables {
     const int32_t *table;
     int table_batch_stride, Nout, slot_images;
     int32_t *real_slot, *real_spatial, *slot_row, *pad_slot, *slot_of;
-    __host__ __device__ int workgroups(int B) const { return (real_slot ? B : 0) + (slot_of ? (slot_images * Nout + 1023) / 1024 : 0); }
+    __host__ __device__ int workgroups(int B) const { return (real_slot ? B : 0) + (slot_of ? (slot_images * Nout + SEL_THREADS - 1) / SEL_THREADS : 0); }
 };
 
 #define SSAM_CHECK_LAUNCH()                                   \

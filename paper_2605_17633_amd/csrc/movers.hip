@@ -412,8 +412,6 @@ __device__ __forceinline__ uint32_t score_key(float s)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int SEL_THREADS = 1024;
-
 // exclusive prefix sum of one flag per thread over the block; returns the
 // thread's offset and (through total) the block total.  scratch: 16 ints.
 __device__ __forceinline__ int block_exclusive_count(bool flag, int *scratch, int &total)
