@@ -532,6 +532,10 @@ struct WarmBudget { int groups; double bytes; };
 // weights are left to their contraction (four of 45 stacks slower by 3 to 4 %), with 32 such stacks are 2.5 % slower.
 // A block by itself reads nothing ahead: called again on other tokens it finds its weights in the cache, and reading them once more cost 50 such blocks of 60 to 9000 rows 1.2 % (4 % at most).
 // Only a stack knows of weights that no cache holds by their turn (stacks put together from calls of single blocks, 14 of ViT-B or ViT-L, would be 3.4 % faster with it).
+// A stack reads whatever its size, since it does not know whether its last call's weights are still there: 40 stacks of 34 to 157 MB of weights are 5.0 % faster with it where they are not
+// (0.4 % slower at most), 61 such stacks called again and again, and nothing else in between, 0.4 % slower (2.8 % at most: three blocks of ViT-H, 3 images of 28 x 28); ViT-B's 170 MB 0.5 %
+// faster, more 1.9 %.  The launch that reads is itself slower by up to 0.8 us (fc1 of ViT-L), which is in all of these.  Its reading workgroups hold up to 64 CUs, each with a tile's LDS, for as
+// long as a last round takes: a second stream's kernels find these taken.
 WarmBudget warm_budget(int blocks, int tiles, int fills, double us)
 {
     constexpr int FEWEST = 8, MOST = 64;

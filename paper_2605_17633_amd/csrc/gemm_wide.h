@@ -106,7 +106,8 @@ __device__ __forceinline__ float gemm_quad_sum(float v)
 // PARTS: the row statistics of the folded LayerNorm come in pieces (GemmParts), or, of a scatter-add, it leaves such pieces.
 // The pieces of a tile's rows are as large as a slab of A and come as one more, into the stage that the last slab but SA - 1 has freed: no registers, and
 // under the products of the last slabs.  Loaded in front of the ring's first slabs they cost 4 us, as much as the launch they save.
-// Of rows of 1280 (20 pieces) the last four come with the next slab's place: 4608 rows, density 0.2, 149.7 us a block with statistics launches, 147.8.
+// Of rows of 1280 (20 pieces) the last four come with the next slab's place: 4608 rows, density 0.2, 149.7 us a block with statistics launches, 147.8.  (No other width has more than 16
+// pieces: a block that folds LN1 has 3 D in multiples of 256.)
 template <int BM, int BN, int WGK, int EPI, bool WPACK, bool LNF, bool PARTS = false>
 __global__ void __launch_bounds__(512, 1)
 gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ W, const float *__restrict__ bias,
