@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libssam.so")
-SOURCES = ["gemm.hip", "gemm_wide_folded.hip", "gemm_wide_parts.hip", "gemm_wide_add.hip", "gemm_wide_scatter.hip", "gemm_wide_gelu.hip", "gemm_wide_bias.hip",
+SOURCES = ["gemm.hip", "gemm_wide_folded.hip", "gemm_wide_parts.hip", "gemm_large_parts.hip", "gemm_wide_add.hip", "gemm_wide_scatter.hip", "gemm_wide_gelu.hip", "gemm_wide_bias.hip",
            "attention.hip", "movers.hip", "tables.hip", "block.hip", "ends.hip", "probe.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
