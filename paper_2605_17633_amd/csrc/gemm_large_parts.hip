@@ -1,6 +1,6 @@
 // The large tiles with a LayerNorm folded in whose row statistics come in pieces (GemmParts; rows of 1280): GELU with a gather (fc1), mapped store (qkv).  A source of their
 // own: in the dispatcher's code object these seven kernels moved the small ones, and a block of ViT-B, 28 x 28, whose kernels were the same instruction for instruction, took 46.6 -> 46.9 to
-// 47.1 us (fc1's ring and the LayerNorms 0.1 us slower each); apart 46.75, 46.8 before there were any.
+// 47.1 us (of it fc1's ring 0.1); apart 46.75, 46.8 before there were any.
 #include "gemm_large.h"
 #include "gemm_wide_launch.h"
 
