@@ -106,8 +106,8 @@ inline size_t gemm_split_beside_parts(long rows, int D)
 
 // Weights of contractions still to come that a launch reads with the CUs it has no tile for, so that they lie in the memory-side cache by then.  From HBM a
 // megabyte of weights costs the contraction that reads it 0.2 to 0.4 us (its first slabs wait, and a chain over K has four slabs in flight): 1228 x 1024 x 4096
-// 22.1 us, 18.4 from the cache; 8192 x 3840 x 1280 77.3, 72.2.  Encoders: ViT-B, one image 1138 -> 1076 us; ViT-L, one image 2405 -> 2315; ViT-B, 50 x 50, two
-// images 1469 -> 1369; ViT-H, content order, two images 7620 -> 7214.
+// 22.1 us, 18.4 from the cache; 8192 x 3840 x 1280 77.3, 72.2.  Encoders without and with reading, weights in
+// no cache: ViT-B, one image 1160 -> 1112 us; ViT-L, one image 2524 -> 2479; ViT-B, 50 x 50, two images, pixels in 1490 -> 1445; ViT-H, content order, two images 7826 -> 7500.
 constexpr int GEMM_WARM_AHEAD = 2;            // contractions; what lies further off is pushed out again by what is written before it is read (four ahead: 0.5 to 1 % slower)
 constexpr uint32_t GEMM_WARM_PIECE = 1u << 30;  // the most bytes of a piece: offsets are 32 bits, past its end too
 struct GemmWarm {
